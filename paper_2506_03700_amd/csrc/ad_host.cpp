@@ -277,6 +277,7 @@ ad_status ad_model_create(const ad_config *cfg, const ad_layer_weights *layers, 
     m->final_logits = (float *)take((size_t)AD_M_MAX * L.V * 4);
     m->pin = (int32_t *)pinned_alloc(4096);
     if (!m->pin) { delete m; return (ad_status)fail(AD_ENOMEM, "ad_model_create: pinned allocation failed"); }
+    memset(m->pin, 0, 4096);      // recycled memory may hold an earlier model's done word, which would end the first wait at once
     m->pin_conf = (float *)(m->pin + 32);
     m->bar_abort = (unsigned *)(m->pin + 64);
     *m->bar_abort = 0;
