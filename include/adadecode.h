@@ -91,7 +91,9 @@ ad_status ad_model_destroy(ad_model *);
  * stride = max_pos rounded up to a multiple of 64 and elements of cfg.dtype:
  *   per layer: K [kv head][position 0..stride)[head_dim]   (keys after rotary embedding)
  *        then  V [kv head][head_dim][position 0..stride)   (transposed: positions are contiguous)
- * Entries at positions >= the layer's length are dead, not zeroed. */
+ * Entries at positions >= the layer's length are dead, not zeroed.  Behind the entries the storage holds the library's
+ * scratch, of which the last part (16-bit models) lets ad_generate run up to 1024 prompt tokens through a layer at once;
+ * ad_kv_create accepts storage without that part, and prompts then go through the layers 8 rows at a time. */
 size_t    ad_kv_bytes(const ad_config *, int32_t max_pos);
 /* Also fills the cache's rotary table on `stream` and synchronises it. */
 ad_status ad_kv_create(const ad_model *, void *kv_storage /*dev*/, size_t kv_storage_bytes, int32_t max_pos, void *stream,

@@ -14,6 +14,7 @@
 
 #include "../../include/adadecode.h"
 #include "ad_internal.h"
+#include "ad_prompt.h"
 #include "ad_sched.h"
 
 using namespace ad;
@@ -177,6 +178,14 @@ struct ad_kv {
     float *part;
     int32_t max_pos;
     std::vector<int32_t> len;
+    // scratch of the prompt pass, behind the rest of the storage (pr.rows == 0: none): up to pr.rows tokens at once; rows
+<<<<<<< Updated upstream
+    // [rows][d], activation tiles of d, dq (queries, attention output) and f inputs, fp32 pieces of the projections
+    struct Prompt { int32_t rows; float *x, *pieces; char *Bd, *Q, *Bo, *Bg; } pr;
+=======
+    // [rows][d] and their 1 / rms, activation tiles of d, dq (queries, attention output) and f inputs, fp32 pieces of the projections
+    struct Prompt { int32_t rows; float *x, *scale, *pieces; char *Bd, *Q, *Bo, *Bg; } pr;
+>>>>>>> Stashed changes
 };
 
 extern "C" {
@@ -315,19 +324,49 @@ static size_t attn_part_bytes(const ad_config &c, int32_t max_pos) {
     return align_up((size_t)c.n_q_heads * 8 * S * (c.head_dim + 2) * 4);
 }
 
+// What a cache cannot do without: the entries, the attention partials, the rotary table.
+static size_t kv_core_bytes(const ad_config &c, int32_t max_pos) {
+    const size_t elem = c.dtype == AD_F32 ? 4 : 2;
+    const size_t stride = ((size_t)max_pos + 63) / 64 * 64;
+    const size_t cache = (size_t)c.n_layers * 2 * c.n_kv_heads * stride * c.head_dim * elem;
+    return align_up(cache) + attn_part_bytes(c, max_pos) + rope_table_bytes(c, max_pos);
+}
+
+// Lays the prompt pass's scratch out from `base` (null: sizes only); returns its size.  16-bit models only.
+static size_t prompt_layout(const ad_config &c, int32_t max_pos, char *base, ad_kv::Prompt *pr) {
+    ad_kv::Prompt p;
+    memset(&p, 0, sizeof p);
+    size_t off = 0;
+    if (c.dtype != AD_F32 && max_pos > kPromptMin) {
+        p.rows = max_pos < kPromptRows ? (max_pos + kPromptAlign - 1) / kPromptAlign * kPromptAlign : kPromptRows;
+        Layout L;
+        make_layout(c, L);
+        auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += align_up(bytes); return q; };
+        p.x = (float *)take((size_t)p.rows * L.d * 4);
+<<<<<<< Updated upstream
+=======
+        p.scale = (float *)take((size_t)p.rows * 4);
+>>>>>>> Stashed changes
+        p.Bd = take(prompt_act_bytes(p.rows, L.d));
+        p.pieces = (float *)take(prompt_part_floats(p.rows, L.nqkv, L.d) * 4);
+        p.Q = take(prompt_act_bytes(p.rows, L.dq));
+        p.Bo = take(prompt_act_bytes(p.rows, L.dq));
+        p.Bg = take(prompt_act_bytes(p.rows, L.f));
+    }
+    if (pr) *pr = p;
+    return off;
+}
+
 size_t ad_kv_bytes(const ad_config *cfg, int32_t max_pos) {
     const char *why;
     if (!config_ok(cfg, &why) || max_pos < 1) { fail(AD_EINVAL, "ad_kv_bytes: %s", max_pos < 1 ? "max_pos < 1" : why); return 0; }
-    const size_t elem = cfg->dtype == AD_F32 ? 4 : 2;
-    const size_t stride = ((size_t)max_pos + 63) / 64 * 64;
-    const size_t cache = (size_t)cfg->n_layers * 2 * cfg->n_kv_heads * stride * cfg->head_dim * elem;
-    return align_up(cache) + attn_part_bytes(*cfg, max_pos) + rope_table_bytes(*cfg, max_pos);
+    return kv_core_bytes(*cfg, max_pos) + prompt_layout(*cfg, max_pos, nullptr, nullptr);
 }
 
 ad_status ad_kv_create(const ad_model *model, void *kv_storage, size_t kv_storage_bytes, int32_t max_pos, void *stream, ad_kv **out) {
     if (!model || !kv_storage || !out || max_pos < 1) return (ad_status)fail(AD_EINVAL, "ad_kv_create: bad argument");
     if (((uintptr_t)kv_storage & 255u) != 0) return (ad_status)fail(AD_EINVAL, "ad_kv_create: storage must be 256-byte aligned");
-    const size_t need = ad_kv_bytes(&model->cfg, max_pos);
+    const size_t need = kv_core_bytes(model->cfg, max_pos);
     if (kv_storage_bytes < need) return (ad_status)fail(AD_ENOMEM, "ad_kv_create: storage has %zu bytes, %zu needed", kv_storage_bytes, need);
     ad_kv *kv = new (std::nothrow) ad_kv();
     if (!kv) return (ad_status)fail(AD_ENOMEM, "ad_kv_create: out of host memory");
@@ -347,6 +386,14 @@ ad_status ad_kv_create(const ad_model *model, void *kv_storage, size_t kv_storag
     ra.table = kv->rope; ra.n_pos = kv->stride; ra.half = c.head_dim / 2;
     for (int i = 0; i < ra.half; ++i) ra.inv_freq[i] = pow((double)c.rope_base, -2.0 * (double)i / (double)c.head_dim);
     int rc = launch_rope_table(ra, stream);
+    // storage without room for the prompt pass's scratch is a cache all the same: prompts then go through in layer steps
+    memset(&kv->pr, 0, sizeof kv->pr);
+    const size_t prompt_bytes = prompt_layout(c, max_pos, nullptr, nullptr);
+    if (!rc && prompt_bytes && kv_storage_bytes >= need + prompt_bytes) {
+        prompt_layout(c, max_pos, kv->storage + need, &kv->pr);
+        // (zeroed: the padding of the activation tiles is read and multiplied by the weights' zero padding)
+        rc = launch_zero(kv->storage + need, prompt_bytes, stream);
+    }
     if (!rc) rc = stream_sync(stream);
     if (rc) { delete kv; return (ad_status)hip_fail(rc, "ad_kv_create: rotary table"); }
     *out = kv;
@@ -590,6 +637,78 @@ ad_status ad_layer_step(const ad_model *m, ad_kv *kv, int32_t layer, void *hidde
 ad_status ad_layer_steps(const ad_model *m, ad_kv *kv, int32_t first_layer, int32_t n_layers, void *hidden, const int32_t *pos, int32_t n,
                          void *stream) {
     return (ad_status)layer_steps(m, kv, first_layer, n_layers, hidden, pos, n, stream, "ad_layer_steps");
+}
+
+// The prompt pass over n <= kv->pr.rows tokens at positions pos0 .. (pos0 a multiple of 64): fills every layer's cache.  The
+// rows' hidden states after the last layer are needed by nobody (the prompt's last token is not part of the pass), so
+// the last layer ends with its K and V.
+static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int32_t n, int32_t pos0, void *stream) {
+    const ad_config &c = m->cfg;
+    const Layout &L = m->lay;
+    const int ek = elem_kind(c), f16 = ek == kElemF16;
+    int rc;
+    PromptEmbed e;
+    e.table = m->embed; e.elem = ek; e.d = L.d;
+    for (int32_t s = 0; s < n; s += kPromptEmbedRows) {
+        e.n = n - s < kPromptEmbedRows ? n - s : kPromptEmbedRows;
+        e.out = kv->pr.x + (size_t)s * L.d;
+        memcpy(e.tok, tokens + s, sizeof(int32_t) * (size_t)e.n);
+        if ((rc = launch_prompt_embed(e, stream))) return hip_fail(rc, "prompt pass: embedding");
+    }
+    PromptRows rows;
+    memset(&rows, 0, sizeof rows);
+    rows.x = kv->pr.x; rows.part = kv->pr.pieces; rows.M = n; rows.d = L.d; rows.KT = L.kt_d; rows.elem = ek;
+<<<<<<< Updated upstream
+    rows.inv_dim = 1.0f / (float)L.d; rows.eps = c.rms_eps; rows.B = kv->pr.Bd;
+=======
+    rows.inv_dim = 1.0f / (float)L.d; rows.eps = c.rms_eps; rows.B = kv->pr.Bd; rows.scale = kv->pr.scale;
+>>>>>>> Stashed changes
+    rows.norm_w = m->layers[0].attn_norm;
+    if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
+    auto project = [&](const void *W, const void *B, int kt, int out_rows, int *n_split) {
+        PromptGemm g;
+        memset(&g, 0, sizeof g);
+        g.W = W; g.B = B; g.NT = out_rows / 16; g.KT = kt; g.N = out_rows; g.M = n; g.f16 = f16;
+<<<<<<< Updated upstream
+        g.part = kv->pr.pieces; g.part_floats = prompt_part_floats(kv->pr.rows, L.nqkv, L.d); g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
+=======
+        g.part = kv->pr.pieces; g.part_floats = prompt_part_floats(kv->pr.rows, L.nqkv, L.d); g.scale = kv->pr.scale; g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
+>>>>>>> Stashed changes
+        return launch_prompt_gemm(g, n_split == nullptr, m->n_wg, n_split, stream);
+    };
+    for (int32_t l = 0; l < c.n_layers; ++l) {
+        const LayerPacked &lp = m->layers[l];
+        PromptQkv q;
+        memset(&q, 0, sizeof q);
+        if ((rc = project(lp.wqkv, kv->pr.Bd, L.kt_d, L.nqkv, &q.n_split))) return hip_fail(rc, "prompt pass: qkv");
+<<<<<<< Updated upstream
+        q.part = kv->pr.pieces; q.M = n; q.nqkv = L.nqkv; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
+        q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
+        q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
+        q.stride = kv->stride; q.pos0 = pos0; q.q_rows = kv->pr.rows * q.G; q.Q = kv->pr.Q; q.scale = 1.0f / sqrtf((float)L.dh); q.f16 = f16;
+=======
+        q.part = kv->pr.pieces; q.scale = kv->pr.scale; q.M = n; q.nqkv = L.nqkv; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
+        q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
+        q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
+        q.stride = kv->stride; q.pos0 = pos0; q.q_rows = kv->pr.rows * q.G; q.Q = kv->pr.Q; q.q_scale = 1.0f / sqrtf((float)L.dh); q.f16 = f16;
+>>>>>>> Stashed changes
+        if ((rc = launch_prompt_qkv(q, stream))) return hip_fail(rc, "prompt pass: rotation");
+        if (l + 1 == c.n_layers) break;
+        PromptAttn a;
+        memset(&a, 0, sizeof a);
+        a.Q = kv->pr.Q; a.Kc = q.Kc; a.Vc = q.Vc; a.stride = kv->stride; a.pos0 = pos0; a.M = n; a.Hq = q.Hq; a.Hkv = q.Hkv; a.dh = L.dh; a.G = q.G;
+        a.q_rows = q.q_rows; a.Bo = kv->pr.Bo; a.Bo_KT = L.kt_q; a.f16 = f16;
+        if ((rc = launch_prompt_attn(a, stream))) return hip_fail(rc, "prompt pass: attention");
+        if ((rc = project(lp.wo, kv->pr.Bo, L.kt_q, L.d, &rows.n_split))) return hip_fail(rc, "prompt pass: wo");
+        rows.norm_w = lp.ffn_norm;
+        if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
+        if ((rc = project(lp.wgu, kv->pr.Bd, L.kt_d, 2 * L.f, nullptr))) return hip_fail(rc, "prompt pass: gate/up");
+        if ((rc = project(lp.wd, kv->pr.Bg, L.kt_f, L.d, &rows.n_split))) return hip_fail(rc, "prompt pass: down");
+        rows.norm_w = m->layers[l + 1].attn_norm;
+        if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
+    }
+    for (auto &len : kv->len) len = pos0 + n;
+    return AD_OK;
 }
 
 // Head at `layer` over n rows; shared by ad_exit_head, ad_verify, ad_verify_static and ad_head_logits.
@@ -869,8 +988,13 @@ struct GpuBackend : Backend {
         const int32_t chunk = m->cfg.m_max;
         in_prefill = true;
         int rc = AD_OK;
-        for (int32_t s = 0; s < n && rc == AD_OK; s += chunk) {
-            const int32_t k = (n - s < chunk) ? n - s : chunk;
+        for (int32_t s = 0, k; s < n && rc == AD_OK; s += k) {
+            if (kv->pr.rows && n - s >= kPromptMin) {
+                k = (n - s < kv->pr.rows) ? n - s : kv->pr.rows;
+                rc = prompt_pass(m, kv, tokens + s, k, s, stream);
+                continue;
+            }
+            k = (n - s < chunk) ? n - s : chunk;
             rc = ad_embed(m, tokens + s, k, row(0), stream);
             if (rc == AD_OK) rc = layer_steps(1, m->cfg.n_layers, 0, k, s);
         }

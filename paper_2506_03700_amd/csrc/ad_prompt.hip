@@ -1,0 +1,691 @@
+// The prompt pass: up to kPromptRows tokens through a decoder layer at once (16-bit models).  A layer step takes at most 8
+// rows and reads the layer's weights for them; here a weight tile that has reached the chip is multiplied by all the
+// tokens of a workgroup, and the pass is bound by the matrix cores instead of by memory.
+//
+// The arithmetic is the layer step's: activations are split into 16-bit hi and lo parts, both are multiplied, sums are
+// fp32; K and V are rounded to the cache type when they are stored and attention reads the stored values.
+//
+// Per layer: k_prompt_gemm (q, k, v) -> k_prompt_qkv (rotation, KV append, query tiles) -> k_prompt_attn ->
+// k_prompt_gemm (Wo) -> k_prompt_rows (residual, RMSNorm, tiles) -> k_prompt_gemm (gate/up, SwiGLU) ->
+// k_prompt_gemm (down) -> k_prompt_rows.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "ad_device.h"
+#include "ad_internal.h"
+#include "ad_prompt.h"
+
+namespace ad {
+
+namespace {
+
+typedef __attribute__((__vector_size__(4 * sizeof(uint16_t)))) uint16_t u16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(uint16_t)))) uint16_t u16x8;
+
+template <bool F16>
+__device__ __forceinline__ uint16_t to16(float v) {
+    if constexpr (F16) return __builtin_bit_cast(uint16_t, (_Float16)v);
+    else return __builtin_bit_cast(uint16_t, (__bf16)v);       // rounds to nearest even in hardware
+}
+template <bool F16>
+__device__ __forceinline__ float from16(uint16_t b) { return F16 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b); }
+<<<<<<< Updated upstream
+template <bool F16>
+__device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
+=======
+// v is rounded to fp32 before it is split: as a product it could otherwise be fused into one of the two uses of hi (a
+// multiplication that rounds to fp16 at once) and not into the other, and at a tie the two would differ
+template <bool F16>
+__device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
+    if constexpr (F16) asm("" : "+v"(v));
+>>>>>>> Stashed changes
+    hi = to16<F16>(v);
+    lo = to16<F16>(v - from16<F16>(hi));
+}
+
+// 16-byte unit of token t, inputs k .. k + 7 (k a multiple of 8), in activation tiles with KT k-steps (plane 0 = hi)
+__device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
+    return (((size_t)(t >> 4) * KT + (k >> 5)) * 2 + plane) * 64 + (t & 15) + 16 * ((k & 31) >> 3);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// projections
+// ---------------------------------------------------------------------------------------------------
+// A workgroup of NWR x NWT wavefronts computes BR = NWR * WR row tiles x BT = NWT * WT token tiles; a wavefront holds
+// WR x WT accumulators.  Weights and activations of KS k-steps are staged in LDS, two stages: while one is multiplied the
+// next is on its way in registers (loaded one whole stage ahead).  Both operands lie in memory in MFMA operand order, so
+// a stage is copied as it is and every LDS access is 64 consecutive 16-byte units: no bank conflicts, no address maths.
+<<<<<<< Updated upstream
+=======
+//
+// The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
+// the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
+// 512 inputs each and then each other, is as good).  A tile of 8 x 4 accumulators per wavefront has no registers left for
+// the second set; 8 wavefronts of 4 x 4 are as fast.  Measured, executed TFLOP/s (hi and lo products counted) at 1024 tokens,
+// 28672 x 4096 / 4096 x 14336: 4 x 4 by 8 wavefronts 1019 / 1105, 8 x 4 by 4 wavefronts without the second set 1048 / 1076,
+// 4 x 4 by 4 wavefronts 973 / 1001, 8 x 4 with the second set (one wavefront per SIMD) 766 / 853; two k-steps per stage lose 1 to
+// 25 % in all of them.
+constexpr int kFlush = 8;
+>>>>>>> Stashed changes
+enum { PG_PART = 0, PG_SWIGLU = 1 };
+
+template <int WR, int WT, int NWR, int NWT, int KS, bool F16, int EPI>
+__global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
+    constexpr int NTH = 64 * NWR * NWT, BR = WR * NWR, BT = WT * NWT;
+    constexpr int WU = BR * KS * 64, AU = BT * KS * 128;        // 16-byte units per stage
+    constexpr int NW_ = WU / NTH, NA = AU / NTH;                // loads per thread
+    static_assert(WU % NTH == 0 && AU % NTH == 0, "a stage is a whole number of loads per thread");
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    bf16x8 *lds = (bf16x8 *)lds_raw;                            // [2][WU + AU]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wr = wave % NWR, wt = wave / NWR;
+
+    // workgroups are dealt to the 8 XCDs in turn: give each XCD a contiguous run of (piece, row block, token block), so
+    // that the workgroups that share weights share an L2
+    const int total = g.n_rb * g.n_tb * g.n_split, q8 = total >> 3, r8 = total & 7;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+    const int tb = id % g.n_tb, rest = id / g.n_tb, rb = rest % g.n_rb, piece = rest / g.n_rb;
+    const int k0 = piece * g.k_per, k1 = (k0 + g.k_per < g.KT) ? k0 + g.k_per : g.KT;
+
+    unsigned woff[NW_], aoff[NA];
+    int wks[NW_], aks[NA];
+#pragma unroll
+    for (int i = 0; i < NW_; ++i) {
+        const int u = tid + i * NTH, in = u % (KS * 64);
+        int rt = rb * BR + u / (KS * 64);
+        if (rt > g.NT - 1) rt = g.NT - 1;                       // past the last row tile: its products are not stored
+        wks[i] = in >> 6;
+        woff[i] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)(in & 63)) << 4;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int u = tid + i * NTH, in = u % (KS * 128);
+        aks[i] = in >> 7;
+        aoff[i] = ((unsigned)(tb * BT + u / (KS * 128)) * (unsigned)g.KT * 128u + (unsigned)(in & 127)) << 4;
+    }
+    const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
+    bf16x8 wreg[NW_], areg[NA];
+    auto load = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < NW_; ++i) {
+            int kk = k + wks[i];
+            if (KS > 1 && kk > g.KT - 1) kk = g.KT - 1;
+            wreg[i] = *(const bf16x8 *)(Wb + (woff[i] + ((unsigned)kk << 10)));
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            int kk = k + aks[i];
+            if (KS > 1 && kk > g.KT - 1) kk = g.KT - 1;
+            areg[i] = *(const bf16x8 *)(Ab + (aoff[i] + ((unsigned)kk << 11)));
+        }
+    };
+    auto store = [&](bf16x8 *s) {
+#pragma unroll
+        for (int i = 0; i < NW_; ++i) s[tid + i * NTH] = wreg[i];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) s[WU + tid + i * NTH] = areg[i];
+    };
+
+<<<<<<< Updated upstream
+    f32x4 acc[WR][WT];
+#pragma unroll
+    for (int i = 0; i < WR; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+=======
+    f32x4 acc[WR][WT], sum[WR][WT];
+#pragma unroll
+    for (int i = 0; i < WR; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) acc[i][j] = sum[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto flush = [&]() {
+#pragma unroll
+        for (int i = 0; i < WR; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                sum[i][j] += acc[i][j];
+                acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+    };
+>>>>>>> Stashed changes
+
+    const int n_stage = (k1 - k0 + KS - 1) / KS;
+    load(k0);
+    store(lds);
+    if (n_stage > 1) load(k0 + KS);
+    __syncthreads();
+    for (int s = 0; s < n_stage; ++s) {
+        const bf16x8 *cur = lds + (s & 1) * (WU + AU);
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            if (KS == 1 || k0 + s * KS + j < k1) {
+                bf16x8 bh[WT], bl[WT];
+#pragma unroll
+                for (int t = 0; t < WT; ++t) {
+                    const bf16x8 *p = cur + WU + ((wt * WT + t) * KS + j) * 128 + lane;
+                    bh[t] = p[0];
+                    bl[t] = p[64];
+                }
+#pragma unroll
+                for (int r = 0; r < WR; ++r) {
+                    const bf16x8 a = cur[((wr * WR + r) * KS + j) * 64 + lane];
+#pragma unroll
+                    for (int t = 0; t < WT; ++t) acc[r][t] = mma16<F16>(a, bh[t], acc[r][t]);
+#pragma unroll
+                    for (int t = 0; t < WT; ++t) acc[r][t] = mma16<F16>(a, bl[t], acc[r][t]);
+                }
+            }
+        }
+<<<<<<< Updated upstream
+=======
+        if ((s + 1) % (kFlush / KS) == 0) flush();
+>>>>>>> Stashed changes
+        if (s + 1 < n_stage) {
+            store(lds + ((s + 1) & 1) * (WU + AU));
+            if (s + 2 < n_stage) load(k0 + (s + 2) * KS);
+        }
+        __syncthreads();
+    }
+<<<<<<< Updated upstream
+
+    // accumulator of a tile: lane (n, gq) holds token n, rows gq*4 .. +3
+=======
+    flush();
+
+    // sum of a tile: lane (n, gq) holds token n, rows gq*4 .. +3
+>>>>>>> Stashed changes
+    const int n = lane & 15, gq = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < WT; ++t) {
+        const int tok = (tb * BT + wt * WT + t) * 16 + n;
+<<<<<<< Updated upstream
+=======
+        const float scale = (EPI == PG_SWIGLU && tok < g.M) ? g.scale[tok] : 0.f;
+>>>>>>> Stashed changes
+#pragma unroll
+        for (int r = 0; r < WR; ++r) {
+            const int rt = rb * BR + wr * WR + r;
+            if (EPI == PG_PART) {
+                const int row = rt * 16 + gq * 4;
+<<<<<<< Updated upstream
+                if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = acc[r][t];
+=======
+                if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = sum[r][t];
+>>>>>>> Stashed changes
+            } else {
+                // rows 0..7 of a tile are gate, 8..15 up of the same 8 features: the other half sits 32 lanes away.  Both
+                // halves then hold the products of 4 features; the lower one stores their hi parts, the upper the lo parts.
+                u16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+<<<<<<< Updated upstream
+                    const float mine = acc[r][t][e], other = __shfl_xor(mine, 32);
+=======
+                    const float mine = scale * sum[r][t][e], other = __shfl_xor(mine, 32);
+>>>>>>> Stashed changes
+                    const float gate = gq < 2 ? mine : other, up = gq < 2 ? other : mine;
+                    uint16_t hi, lo;
+                    split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
+                    v[e] = gq < 2 ? hi : lo;
+                }
+                if (tok < g.M && rt < g.NT) {
+                    uint16_t *u = (uint16_t *)((bf16x8 *)g.Bnext + act_unit(tok, rt * 8, g.Bnext_KT, gq >> 1));
+                    *(u16x4 *)(u + 4 * (gq & 1)) = v;
+                }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// residual, RMSNorm and operand tiles: one workgroup per token
+// ---------------------------------------------------------------------------------------------------
+constexpr int kRowsThreads = 256;
+constexpr int kRowsUnits = 4;          // units of 8 inputs per thread: d_model <= 8192
+
+template <bool F16>
+__global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
+    __shared__ float wsum[kRowsThreads / 64];
+    const int t = blockIdx.x, tid = threadIdx.x;
+    float *x = a.x + (size_t)t * a.d;
+    const int nu = a.d / 8;
+    f32x4 v[kRowsUnits][2];
+    float ssq = 0.f;
+#pragma unroll
+    for (int i = 0; i < kRowsUnits; ++i) {
+        const int u = tid + i * kRowsThreads;
+        if (u < nu) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 s = {0.f, 0.f, 0.f, 0.f};
+                for (int p = 0; p < a.n_split; ++p) s += *(const f32x4 *)(a.part + ((size_t)p * a.M + t) * a.d + u * 8 + h * 4);
+                v[i][h] = *(const f32x4 *)(x + u * 8 + h * 4);
+                if (a.n_split) {
+                    v[i][h] += s;
+                    *(f32x4 *)(x + u * 8 + h * 4) = v[i][h];
+                }
+                ssq += v[i][h][0] * v[i][h][0] + v[i][h][1] * v[i][h][1] + v[i][h][2] * v[i][h][2] + v[i][h][3] * v[i][h][3];
+            }
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) ssq += __shfl_xor(ssq, off);
+    if ((tid & 63) == 0) wsum[tid >> 6] = ssq;
+    __syncthreads();
+    const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+<<<<<<< Updated upstream
+    const float scale = 1.0f / sqrtf(total * a.inv_dim + a.eps);
+=======
+    if (tid == 0) a.scale[t] = 1.0f / sqrtf(total * a.inv_dim + a.eps);
+>>>>>>> Stashed changes
+#pragma unroll
+    for (int i = 0; i < kRowsUnits; ++i) {
+        const int u = tid + i * kRowsThreads;
+        if (u < nu) {
+            float w[8];
+            load_w8(a.norm_w, a.elem, (size_t)u * 8, w);
+            u16x8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint16_t h, l;
+<<<<<<< Updated upstream
+                split16<F16>(v[i][e >> 2][e & 3] * scale * w[e], h, l);
+=======
+                split16<F16>(v[i][e >> 2][e & 3] * w[e], h, l);
+>>>>>>> Stashed changes
+                hi[e] = h;
+                lo[e] = l;
+            }
+            *((u16x8 *)a.B + act_unit(t, u * 8, a.KT, 0)) = hi;
+            *((u16x8 *)a.B + act_unit(t, u * 8, a.KT, 1)) = lo;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256) k_prompt_embed(PromptEmbed a) {
+    const int t = a.tok[blockIdx.x];
+    for (int c = threadIdx.x * 8; c < a.d; c += 256 * 8) {
+        float w[8];
+        load_w8(a.table, a.elem, (size_t)t * a.d + c, w);
+        float *o = a.out + (size_t)blockIdx.x * a.d + c;
+        *(f32x4 *)o = (f32x4){w[0], w[1], w[2], w[3]};
+        *(f32x4 *)(o + 4) = (f32x4){w[4], w[5], w[6], w[7]};
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// rotation, KV append, query tiles: one workgroup per 64 tokens and head (q heads, then k heads, then v heads)
+// ---------------------------------------------------------------------------------------------------
+constexpr int kQkvTokens = 64;
+
+template <int DH, bool F16>
+__global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
+    constexpr int half = DH / 2, NC = half / 8;         // groups of 8 dimensions in the lower half
+    const int t0 = blockIdx.x * kQkvTokens, head = blockIdx.y, tid = threadIdx.x;
+    auto load8 = [&](int t, int col, float (&o)[8]) {
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        for (int p = 0; p < a.n_split; ++p) {
+            const float *src = a.part + ((size_t)p * a.M + t) * a.nqkv + col;
+            s0 += *(const f32x4 *)src;
+            s1 += *(const f32x4 *)(src + 4);
+        }
+<<<<<<< Updated upstream
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o[e] = s0[e];
+            o[4 + e] = s1[e];
+=======
+        const float scale = a.scale[t];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o[e] = scale * s0[e];
+            o[4 + e] = scale * s1[e];
+>>>>>>> Stashed changes
+        }
+    };
+    if (head < a.Hq + a.Hkv) {
+        const bool is_q = head < a.Hq;
+        for (int idx = tid; idx < kQkvTokens * NC; idx += 256) {
+            const int tl = idx / NC, c = idx % NC, t = t0 + tl;
+            if (t >= a.M) break;
+            float x[8], y[8], r0[8], r1[8];
+            load8(t, head * DH + c * 8, x);
+            load8(t, head * DH + half + c * 8, y);
+            const float *rp = a.rope + ((size_t)t * half + c * 8) * 2;
+<<<<<<< Updated upstream
+            const float mul = is_q ? a.scale : 1.0f;
+=======
+            const float mul = is_q ? a.q_scale : 1.0f;
+>>>>>>> Stashed changes
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float cs = rp[2 * e], sn = rp[2 * e + 1];
+                r0[e] = x[e] * cs - y[e] * sn;
+                r1[e] = x[e] * sn + y[e] * cs;
+                if (is_q) {
+                    r0[e] *= mul;
+                    r1[e] *= mul;
+                }
+            }
+            if (is_q) {
+                // query row t * G + (head in group) of its kv head; tiles of 16 rows over DH inputs
+                const int kvh = head / a.G, r = t * a.G + (head - kvh * a.G);
+                u16x8 *Q = (u16x8 *)a.Q + (size_t)kvh * (size_t)(a.q_rows / 16) * (DH / 32) * 128;
+                u16x8 h0, l0, h1, l1;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    uint16_t hi, lo;
+                    split16<F16>(r0[e], hi, lo);
+                    h0[e] = hi;
+                    l0[e] = lo;
+                    split16<F16>(r1[e], hi, lo);
+                    h1[e] = hi;
+                    l1[e] = lo;
+                }
+                Q[act_unit(r, c * 8, DH / 32, 0)] = h0;
+                Q[act_unit(r, c * 8, DH / 32, 1)] = l0;
+                Q[act_unit(r, half + c * 8, DH / 32, 0)] = h1;
+                Q[act_unit(r, half + c * 8, DH / 32, 1)] = l1;
+            } else {
+                uint16_t *K = (uint16_t *)a.Kc + ((size_t)(head - a.Hq) * a.stride + a.pos0 + t) * DH;
+                u16x8 k0, k1;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    k0[e] = to16<F16>(r0[e]);
+                    k1[e] = to16<F16>(r1[e]);
+                }
+                *(u16x8 *)(K + c * 8) = k0;
+                *(u16x8 *)(K + half + c * 8) = k1;
+            }
+        }
+    } else {
+        // V is kept transposed: through LDS, then 8 positions of a dimension per store.  Positions past the prompt, up to the
+        // next multiple of 64 (within the cache row), are dead; they get zeros, which the attention kernel may multiply by 0.
+        __shared__ uint16_t vt[DH][kQkvTokens + 8];
+        const int h = head - a.Hq - a.Hkv;
+        for (int idx = tid; idx < kQkvTokens * (DH / 8); idx += 256) {
+            const int tl = idx / (DH / 8), c = idx % (DH / 8), t = t0 + tl;
+            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (t < a.M) load8(t, head * DH + c * 8, x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vt[c * 8 + e][tl] = to16<F16>(x[e]);
+        }
+        __syncthreads();
+        uint16_t *V = (uint16_t *)a.Vc + (size_t)h * DH * a.stride + a.pos0 + t0;
+        for (int idx = tid; idx < DH * (kQkvTokens / 8); idx += 256) {
+            const int e = idx / (kQkvTokens / 8), p = idx % (kQkvTokens / 8);
+            *(u16x8 *)(V + (size_t)e * a.stride + p * 8) = *(const u16x8 *)&vt[e][p * 8];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// attention: one workgroup per kv head and 128 query rows (row r = token r / G, head r % G of the group)
+// ---------------------------------------------------------------------------------------------------
+// The products are those of the decode kernel (ad_attention_device.h): S^T = K q^T with the rows of the two score tiles
+// assigned to keys so that a lane ends up with 8 consecutive keys of its query row, which is the B operand layout of
+// O^T = V^T P^T; queries and probabilities are split hi/lo.  A wavefront holds 32 query rows; the workgroup's four
+// wavefronts share the K and V tiles of 32 positions, staged in LDS one block ahead, and run the softmax online.
+constexpr int kPromptAttnRows = 128;
+
+template <int DH, bool F16>
+__global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
+    constexpr int KS = DH / 32, DT = DH / 16, RT = 2;
+    constexpr int KU = 2 * KS * 64, VU = DT * 64, NL = (KU + VU) / 256;
+    __shared__ bf16x8 lds[2][KU + VU];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, gq = lane >> 4;
+    const int kvh = blockIdx.x % a.Hkv, n_blk = (a.M * a.G + kPromptAttnRows - 1) / kPromptAttnRows;
+    const int blk = n_blk - 1 - blockIdx.x / a.Hkv;              // the blocks with the most keys first
+    const int R = a.M * a.G, r_blk = blk * kPromptAttnRows;
+    const int r_last = (r_blk + kPromptAttnRows < R ? r_blk + kPromptAttnRows : R) - 1;
+    const int n_key = a.pos0 + r_last / a.G + 1;                 // keys the block's last row sees
+    const int n_kb = (n_key + 31) / 32;
+
+    const int row0 = r_blk + wave * 16 * RT;
+    const bf16x8 *Q = (const bf16x8 *)a.Q + ((size_t)kvh * (a.q_rows / 16) + row0 / 16) * KS * 128;
+    bf16x8 q[RT][KS][2];
+    int t_row[RT], see[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int r = row0 + i * 16 + n;
+        t_row[i] = (r < R ? r : R - 1) / a.G;
+        see[i] = a.pos0 + t_row[i];                              // last visible position
+#pragma unroll
+        for (int j = 0; j < KS; ++j)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) q[i][j][p] = Q[((i * KS + j) * 2 + p) * 64 + lane];
+    }
+    const int w_last = (row0 + 16 * RT < R ? row0 + 16 * RT : R) - 1;
+    const int w_key = row0 < R ? a.pos0 + w_last / a.G + 1 : 0;  // keys this wavefront's last row sees
+    const int w_full = row0 < R ? a.pos0 + row0 / a.G + 1 : 0;   // keys all its rows see
+
+    const uint16_t *Kg = (const uint16_t *)a.Kc + (size_t)kvh * a.stride * DH;
+    const uint16_t *Vg = (const uint16_t *)a.Vc + (size_t)kvh * DH * a.stride;
+    bf16x8 st[NL];
+    // unit u of a block: K tiles [aa][j][lane], then V tiles [dt][lane].  A block lies inside the cache row (stride is a
+    // multiple of 64); positions at or past the row's end of keys are masked.
+    auto load = [&](int kb) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int u = tid + i * 256, l = u & 63, ln = l & 15, lg = l >> 4;
+            if (i * 256 < KU) {
+                const int aa = u / (KS * 64), j = (u >> 6) % KS;
+                const int key = kb * 32 + 8 * (ln >> 2) + 4 * aa + (ln & 3);
+                st[i] = *(const bf16x8 *)(Kg + (size_t)key * DH + j * 32 + lg * 8);
+            } else {
+                const int dt = (u - KU) >> 6;
+                st[i] = *(const bf16x8 *)(Vg + (size_t)(dt * 16 + ln) * a.stride + kb * 32 + lg * 8);
+            }
+        }
+    };
+    auto store = [&](bf16x8 *s) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) s[tid + i * 256] = st[i];
+    };
+
+    constexpr float kPScale = F16 ? 1024.0f : 1.0f;              // keeps small probabilities out of fp16's subnormals
+    f32x4 o[RT][DT];
+    float mx[RT], sum[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        mx[i] = -INFINITY;
+        sum[i] = 0.f;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) o[i][d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    load(0);
+    store(lds[0]);
+    if (n_kb > 1) load(1);
+    __syncthreads();
+    for (int kb = 0; kb < n_kb; ++kb) {
+        const bf16x8 *cur = lds[kb & 1];
+        if (kb * 32 < w_key) {
+            f32x4 s[RT][2];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) s[i][0] = s[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                const bf16x8 k0 = cur[j * 64 + lane], k1 = cur[(KS + j) * 64 + lane];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) {
+                        s[i][0] = mma16<F16>(k0, q[i][j][p], s[i][0]);
+                        s[i][1] = mma16<F16>(k1, q[i][j][p], s[i][1]);
+                    }
+            }
+            const bool masked = kb * 32 + 32 > w_full;           // some row of this wavefront does not see the whole block
+            bf16x8 ph[RT], pl[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                float sc[8], bm = -INFINITY;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    sc[c] = s[i][c >> 2][c & 3];
+                    if (masked && kb * 32 + gq * 8 + c > see[i]) sc[c] = -INFINITY;
+                    bm = fmaxf(bm, sc[c]);
+                }
+                bm = fmaxf(bm, __shfl_xor(bm, 16));
+                bm = fmaxf(bm, __shfl_xor(bm, 32));
+                const float nm = fmaxf(mx[i], bm);               // finite: every row sees position 0, which is in block 0
+                const float alpha = __expf(mx[i] - nm);
+                mx[i] = nm;
+                float add = 0.f;
+                u16x8 h8, l8;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float p = __expf(sc[c] - nm);
+                    add += p;
+                    uint16_t hi, lo;
+                    split16<F16>(p * kPScale, hi, lo);
+                    h8[c] = hi;
+                    l8[c] = lo;
+                }
+                ph[i] = __builtin_bit_cast(bf16x8, h8);
+                pl[i] = __builtin_bit_cast(bf16x8, l8);
+                sum[i] = sum[i] * alpha + add;
+                if (!__all(alpha == 1.0f)) {
+#pragma unroll
+                    for (int d = 0; d < DT; ++d) o[i][d] *= alpha;
+                }
+            }
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+                const bf16x8 v = cur[KU + d * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    o[i][d] = mma16<F16>(v, ph[i], o[i][d]);
+                    o[i][d] = mma16<F16>(v, pl[i], o[i][d]);
+                }
+            }
+        }
+        if (kb + 1 < n_kb) {
+            store(lds[(kb + 1) & 1]);
+            if (kb + 2 < n_kb) load(kb + 2);
+        }
+        __syncthreads();
+    }
+    // lane (n, gq): query row n of the tile, dims d*16 + gq*4 .. +3
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        float den = sum[i];
+        den += __shfl_xor(den, 16);
+        den += __shfl_xor(den, 32);
+        const float inv = 1.0f / (den * kPScale);
+        const int r = row0 + i * 16 + n;
+        if (r < R) {
+            const int hq = kvh * a.G + (r - t_row[i] * a.G);
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+                u16x4 h4, l4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint16_t hi, lo;
+                    split16<F16>(o[i][d][e] * inv, hi, lo);
+                    h4[e] = hi;
+                    l4[e] = lo;
+                }
+                const int k = hq * DH + d * 16 + (gq >> 1) * 8;
+                *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row[i], k, a.Bo_KT, 0)) + (gq & 1) * 4) = h4;
+                *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row[i], k, a.Bo_KT, 1)) + (gq & 1) * 4) = l4;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------------------------------
+template <int WR, int WT, int NWR, int NWT, int KS, bool F16, int EPI>
+int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
+    constexpr int BR = WR * NWR, BT = WT * NWT;
+    constexpr size_t lds = 2 * (size_t)(BR * KS * 64 + BT * KS * 128) * 16;
+    g.n_rb = (g.NT + BR - 1) / BR;
+    g.n_tb = ((g.M + 15) / 16 + BT - 1) / BT;
+<<<<<<< Updated upstream
+    // pieces along K: as many as bring the workgroups near two per compute unit, within the room for partial rows
+=======
+    // pieces along K: up to two workgroups per compute unit, within the room for partial rows
+>>>>>>> Stashed changes
+    int split = 1;
+    if (EPI == PG_PART) {
+        const int blocks = g.n_rb * g.n_tb;
+        while (split < kPromptMaxSplit && blocks * split * 2 <= 2 * n_wg && g.KT / (split * 2) >= 8 &&
+               (size_t)(split * 2) * g.M * g.N <= g.part_floats)
+            split *= 2;
+        if ((size_t)g.M * g.N > g.part_floats) return (int)hipErrorInvalidValue;
+    }
+    g.k_per = (g.KT + split - 1) / split;
+    g.n_split = (g.KT + g.k_per - 1) / g.k_per;
+    if (n_split) *n_split = g.n_split;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, KS, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return (int)e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, KS, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(64 * NWR * NWT), lds, s, g);
+    return (int)hipGetLastError();
+}
+
+template <bool F16, int EPI>
+int launch_gemm_sized(const PromptGemm &g, int n_wg, int *n_split, hipStream_t s) {
+    if (g.M <= 32) return launch_gemm_as<2, 2, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 rows x 32 tokens
+    if (g.M <= 64) return launch_gemm_as<2, 4, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 x 64
+    if (g.M <= 256) return launch_gemm_as<4, 4, 2, 2, 1, F16, EPI>(g, n_wg, n_split, s);       // 128 x 128
+<<<<<<< Updated upstream
+    return launch_gemm_as<8, 4, 2, 2, 1, F16, EPI>(g, n_wg, n_split, s);                       // 256 x 128
+=======
+    return launch_gemm_as<4, 4, 4, 2, 1, F16, EPI>(g, n_wg, n_split, s);                       // 256 x 128
+>>>>>>> Stashed changes
+}
+
+}  // namespace
+
+int launch_prompt_gemm(PromptGemm g, bool swiglu, int n_wg, int *n_split, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    if (g.M < 1 || g.M > kPromptRows || g.NT < 1 || g.KT < 1) return (int)hipErrorInvalidValue;
+    if (swiglu) return g.f16 ? launch_gemm_sized<true, PG_SWIGLU>(g, n_wg, n_split, s) : launch_gemm_sized<false, PG_SWIGLU>(g, n_wg, n_split, s);
+    return g.f16 ? launch_gemm_sized<true, PG_PART>(g, n_wg, n_split, s) : launch_gemm_sized<false, PG_PART>(g, n_wg, n_split, s);
+}
+
+int launch_prompt_embed(const PromptEmbed &a, void *stream) {
+    if (a.n < 1 || a.n > kPromptEmbedRows) return (int)hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_prompt_embed, dim3(a.n), dim3(256), 0, (hipStream_t)stream, a);
+    return (int)hipGetLastError();
+}
+
+int launch_prompt_rows(const PromptRows &a, void *stream) {
+    if (a.M < 1 || a.d > kRowsThreads * kRowsUnits * 8 || a.elem == kElemF32) return (int)hipErrorInvalidValue;
+    if (a.elem == kElemF16) hipLaunchKernelGGL((k_prompt_rows<true>), dim3(a.M), dim3(kRowsThreads), 0, (hipStream_t)stream, a);
+    else hipLaunchKernelGGL((k_prompt_rows<false>), dim3(a.M), dim3(kRowsThreads), 0, (hipStream_t)stream, a);
+    return (int)hipGetLastError();
+}
+
+template <int DH, bool F16>
+static int launch_qkv_as(const PromptQkv &a, hipStream_t s) {
+    hipLaunchKernelGGL((k_prompt_qkv<DH, F16>), dim3((a.M + kQkvTokens - 1) / kQkvTokens, a.Hq + 2 * a.Hkv), dim3(256), 0, s, a);
+    return (int)hipGetLastError();
+}
+int launch_prompt_qkv(const PromptQkv &a, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    if (a.pos0 % kQkvTokens) return (int)hipErrorInvalidValue;
+    if (a.dh == 128) return a.f16 ? launch_qkv_as<128, true>(a, s) : launch_qkv_as<128, false>(a, s);
+    if (a.dh == 64) return a.f16 ? launch_qkv_as<64, true>(a, s) : launch_qkv_as<64, false>(a, s);
+    return (int)hipErrorInvalidValue;
+}
+
+template <int DH, bool F16>
+static int launch_attn_as(const PromptAttn &a, hipStream_t s) {
+    const int n_blk = (a.M * a.G + kPromptAttnRows - 1) / kPromptAttnRows;
+    hipLaunchKernelGGL((k_prompt_attn<DH, F16>), dim3(n_blk * a.Hkv), dim3(256), 0, s, a);
+    return (int)hipGetLastError();
+}
+int launch_prompt_attn(const PromptAttn &a, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    if (a.dh == 128) return a.f16 ? launch_attn_as<128, true>(a, s) : launch_attn_as<128, false>(a, s);
+    if (a.dh == 64) return a.f16 ? launch_attn_as<64, true>(a, s) : launch_attn_as<64, false>(a, s);
+    return (int)hipErrorInvalidValue;
+}
+
+}  // namespace ad

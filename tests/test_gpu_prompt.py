@@ -1,0 +1,100 @@
+"""GPU parity of the prompt pass (many prompt tokens through a layer at once) against the CPU oracle: caches and the
+logits that follow, at the edges of its tiles, over several passes, with grouped and ungrouped heads and odd widths."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2506_03700_amd import synth
+from tolerances import check_kv, check_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ad():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2506_03700_amd import binding
+    binding.lib()
+    return binding
+
+
+# d_model 208 and d_ffn 200 are no multiples of an operand tile's 32 inputs; 3 query heads per kv head
+ODD = synth.TINY.with_(name="odd-bf16", dtype=synth.BF16, tied_head=False, n_q_heads=6, n_kv_heads=2, head_dim=64, d_model=208, d_ffn=200,
+                       vocab=301, n_layers=3, exit_layers=(1,), rope_base=500000.0)
+DH128 = ODD.with_(name="dh128-bf16", n_q_heads=4, n_kv_heads=1, head_dim=128, d_model=256, d_ffn=688)
+MHA = ODD.with_(name="mha-f16", dtype=synth.F16, n_q_heads=3, n_kv_heads=3, head_dim=128, n_layers=2)
+
+
+def follow_up(shape, g, o, prompt):
+    """Both sides take the prompt, then one token more; caches of all layers and that token's logits are compared."""
+    n = len(prompt)
+    g.ad_generate(prompt, 1, 2.0, 0)
+    o.generate_greedy(prompt, 1)
+    assert g.kv_lens() == o.kv_lens() == [n] * shape.n_layers
+    for l in range(1, shape.n_layers + 1):
+        ko, vo = o.kv_read(l, 0, n)
+        kg, vg = g.kv_read(l, n)
+        check_kv(shape.dtype, kg, ko, f"K of layer {l}, {n} tokens")
+        check_kv(shape.dtype, vg, vo, f"V of layer {l}, {n} tokens")
+    h, ho = g.ad_embed([7]), o.embed([7])
+    for l in range(1, shape.n_layers + 1):
+        g.ad_layer_step(l, h, [n])
+        ho = o.layer_step(l, ho, np.array([n]))
+    check_rows(shape.dtype, h.cpu().numpy(), ho, f"row after {n} tokens")
+
+
+# the prompt pass takes all but the last token of the prompt: 8 is the most that is left to a layer step; 16, 32, 64, 128
+# and 256 tokens are where tiles and workgroups of tokens end and the variants change
+@pytest.mark.parametrize("shape", [ODD, ODD.with_(name="odd-f16", dtype=synth.F16), DH128, MHA], ids=lambda s: s.name)
+def test_prompt_lengths_at_tile_edges(ad, shape):
+    w = synth.make_weights(shape, seed=4, norm_jitter=0.2)
+    max_pos = 320
+    g, o = ad.Model(shape, w, max_pos=max_pos), orc.Oracle(shape, w, max_pos=max_pos)
+    for n in (8, 9, 15, 17, 31, 32, 33, 64, 65, 127, 128, 129, 256, 257, 300):
+        print(f"case {shape.name} {n} tokens", flush=True)
+        follow_up(shape, g, o, synth.make_prompt(shape, n, n + 1))
+    g.close()
+
+
+# beyond 1024 tokens: a second pass at position 1024, of more and of fewer tokens than a layer step takes
+@pytest.mark.parametrize("shape,n", [(DH128, 1024), (DH128, 1031), (ODD, 1100)], ids=["one-pass", "pass-and-step", "two-passes"])
+def test_prompts_longer_than_a_pass(ad, shape, n):
+    w = synth.make_weights(shape, seed=5, norm_jitter=0.2)
+    g, o = ad.Model(shape, w, max_pos=1152), orc.Oracle(shape, w, max_pos=1152)
+    follow_up(shape, g, o, synth.make_prompt(shape, n, n + 1))
+    g.close()
+
+
+def test_storage_without_the_scratch_is_a_cache_too(ad):
+    """ad_kv_create takes storage that ends before the prompt pass's scratch: the same caches, by layer steps."""
+    import torch
+    shape = DH128
+    w = synth.make_weights(shape, seed=6, norm_jitter=0.2)
+    g, o = ad.Model(shape, w, max_pos=200), orc.Oracle(shape, w, max_pos=200)
+    L, full = g.L, g.L.ad_kv_bytes(C.byref(g.cfg), 200)
+    kv, stream = C.c_void_p(), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.ad_kv_create(g.model, C.c_void_p(g.kv_storage.data_ptr()), 4096, 200, stream, C.byref(kv)) == ad.AD_ENOMEM
+    L.ad_kv_destroy(g.kv)
+    assert L.ad_kv_create(g.model, C.c_void_p(g.kv_storage.data_ptr()), full - 256, 200, stream, C.byref(kv)) == ad.AD_OK
+    g.kv = kv
+    follow_up(shape, g, o, synth.make_prompt(shape, 1, 71))
+    g.close()
+<<<<<<< Updated upstream
+
+
+def test_a_new_model_does_not_see_an_earlier_ones_results(ad):
+    """Models made one after the other get the same pinned words: the first evaluation of each waits for its own result."""
+    shape = synth.TINY.with_(name="tiny-untied", tied_head=False, vocab=512)
+    w = synth.make_weights(shape, seed=1)
+    first = None
+    for i in range(4):
+        g = ad.Model(shape, w, max_pos=64)
+        out, _, _ = g.ad_generate(synth.make_prompt(shape, 1, 20), 1, 2.0, 0)
+        first = out[0] if first is None else first
+        assert out[0] == first, i
+        g.close()
+=======
+>>>>>>> Stashed changes
