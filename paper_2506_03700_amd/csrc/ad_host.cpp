@@ -179,13 +179,8 @@ struct ad_kv {
     int32_t max_pos;
     std::vector<int32_t> len;
     // scratch of the prompt pass, behind the rest of the storage (pr.rows == 0: none): up to pr.rows tokens at once; rows
-<<<<<<< Updated upstream
-    // [rows][d], activation tiles of d, dq (queries, attention output) and f inputs, fp32 pieces of the projections
-    struct Prompt { int32_t rows; float *x, *pieces; char *Bd, *Q, *Bo, *Bg; } pr;
-=======
     // [rows][d] and their 1 / rms, activation tiles of d, dq (queries, attention output) and f inputs, fp32 pieces of the projections
     struct Prompt { int32_t rows; float *x, *scale, *pieces; char *Bd, *Q, *Bo, *Bg; } pr;
->>>>>>> Stashed changes
 };
 
 extern "C" {
@@ -343,10 +338,7 @@ static size_t prompt_layout(const ad_config &c, int32_t max_pos, char *base, ad_
         make_layout(c, L);
         auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += align_up(bytes); return q; };
         p.x = (float *)take((size_t)p.rows * L.d * 4);
-<<<<<<< Updated upstream
-=======
         p.scale = (float *)take((size_t)p.rows * 4);
->>>>>>> Stashed changes
         p.Bd = take(prompt_act_bytes(p.rows, L.d));
         p.pieces = (float *)take(prompt_part_floats(p.rows, L.nqkv, L.d) * 4);
         p.Q = take(prompt_act_bytes(p.rows, L.dq));
@@ -658,22 +650,14 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
     PromptRows rows;
     memset(&rows, 0, sizeof rows);
     rows.x = kv->pr.x; rows.part = kv->pr.pieces; rows.M = n; rows.d = L.d; rows.KT = L.kt_d; rows.elem = ek;
-<<<<<<< Updated upstream
-    rows.inv_dim = 1.0f / (float)L.d; rows.eps = c.rms_eps; rows.B = kv->pr.Bd;
-=======
     rows.inv_dim = 1.0f / (float)L.d; rows.eps = c.rms_eps; rows.B = kv->pr.Bd; rows.scale = kv->pr.scale;
->>>>>>> Stashed changes
     rows.norm_w = m->layers[0].attn_norm;
     if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
     auto project = [&](const void *W, const void *B, int kt, int out_rows, int *n_split) {
         PromptGemm g;
         memset(&g, 0, sizeof g);
         g.W = W; g.B = B; g.NT = out_rows / 16; g.KT = kt; g.N = out_rows; g.M = n; g.f16 = f16;
-<<<<<<< Updated upstream
-        g.part = kv->pr.pieces; g.part_floats = prompt_part_floats(kv->pr.rows, L.nqkv, L.d); g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
-=======
         g.part = kv->pr.pieces; g.part_floats = prompt_part_floats(kv->pr.rows, L.nqkv, L.d); g.scale = kv->pr.scale; g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
->>>>>>> Stashed changes
         return launch_prompt_gemm(g, n_split == nullptr, m->n_wg, n_split, stream);
     };
     for (int32_t l = 0; l < c.n_layers; ++l) {
@@ -681,17 +665,10 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
         PromptQkv q;
         memset(&q, 0, sizeof q);
         if ((rc = project(lp.wqkv, kv->pr.Bd, L.kt_d, L.nqkv, &q.n_split))) return hip_fail(rc, "prompt pass: qkv");
-<<<<<<< Updated upstream
-        q.part = kv->pr.pieces; q.M = n; q.nqkv = L.nqkv; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
-        q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
-        q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
-        q.stride = kv->stride; q.pos0 = pos0; q.q_rows = kv->pr.rows * q.G; q.Q = kv->pr.Q; q.scale = 1.0f / sqrtf((float)L.dh); q.f16 = f16;
-=======
         q.part = kv->pr.pieces; q.scale = kv->pr.scale; q.M = n; q.nqkv = L.nqkv; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
         q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
         q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
         q.stride = kv->stride; q.pos0 = pos0; q.q_rows = kv->pr.rows * q.G; q.Q = kv->pr.Q; q.q_scale = 1.0f / sqrtf((float)L.dh); q.f16 = f16;
->>>>>>> Stashed changes
         if ((rc = launch_prompt_qkv(q, stream))) return hip_fail(rc, "prompt pass: rotation");
         if (l + 1 == c.n_layers) break;
         PromptAttn a;

@@ -27,10 +27,7 @@ struct PromptGemm {
     int NT, KT, N, M;         // row tiles, k-steps, valid output rows, tokens
     float *part;              // [pieces][M][N] fp32 (swiglu: unused)
     size_t part_floats;       // room there
-<<<<<<< Updated upstream
-=======
     const float *scale;       // swiglu: 1 / rms of each token's input row
->>>>>>> Stashed changes
     void *Bnext;              // swiglu: activation tiles of the next projection, Bnext_KT k-steps
     int Bnext_KT;
     int f16;                  // fp16 operands (else bf16)
@@ -38,13 +35,9 @@ struct PromptGemm {
     int n_rb, n_tb, n_split, k_per;
 };
 
-<<<<<<< Updated upstream
-// x[t] (+)= sum of the pieces; activation tiles of RMSNorm(x[t]) * w
-=======
 // x[t] (+)= sum of the pieces; activation tiles of x[t] * w, and the factor 1 / rms(x[t]) that makes RMSNorm of it, which
 // the projection's consumer applies (the embedding rows and norm weights of a 16-bit model have products that the split
 // keeps exactly; multiplied by the factor first, they lose that)
->>>>>>> Stashed changes
 struct PromptRows {
     float *x;                 // [M][d], updated in place if there are pieces
     const float *part;        // [n_split][M][d]
@@ -53,30 +46,20 @@ struct PromptRows {
     int elem;
     float inv_dim, eps;
     void *B;
-<<<<<<< Updated upstream
-=======
     float *scale;             // [M]
->>>>>>> Stashed changes
 };
 
 // q, k, v of M tokens from the pieces: rotated and scaled queries in operand tiles, K and V into the cache
 struct PromptQkv {
     const float *part;        // [n_split][M][nqkv]
-<<<<<<< Updated upstream
-=======
     const float *scale;       // [M], see PromptRows
->>>>>>> Stashed changes
     int n_split, M, nqkv, Hq, Hkv, dh, G;
     const float *rope;        // rows pos0 ..
     void *Kc, *Vc;            // the layer's cache (see AttnArgs)
     int stride, pos0;         // pos0: a multiple of 64
     int q_rows;               // query rows of a kv head that Q has room for
     void *Q;                  // per kv head, query rows r = t * G + head in group: tiles of 16 rows, [tile][ks][plane][lane][8]
-<<<<<<< Updated upstream
-    float scale;
-=======
     float q_scale;            // 1 / sqrt(dh)
->>>>>>> Stashed changes
     int f16;
 };
 

@@ -29,16 +29,11 @@ __device__ __forceinline__ uint16_t to16(float v) {
 }
 template <bool F16>
 __device__ __forceinline__ float from16(uint16_t b) { return F16 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b); }
-<<<<<<< Updated upstream
-template <bool F16>
-__device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
-=======
 // v is rounded to fp32 before it is split: as a product it could otherwise be fused into one of the two uses of hi (a
 // multiplication that rounds to fp16 at once) and not into the other, and at a tie the two would differ
 template <bool F16>
 __device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
     if constexpr (F16) asm("" : "+v"(v));
->>>>>>> Stashed changes
     hi = to16<F16>(v);
     lo = to16<F16>(v - from16<F16>(hi));
 }
@@ -55,8 +50,6 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // WR x WT accumulators.  Weights and activations of KS k-steps are staged in LDS, two stages: while one is multiplied the
 // next is on its way in registers (loaded one whole stage ahead).  Both operands lie in memory in MFMA operand order, so
 // a stage is copied as it is and every LDS access is 64 consecutive 16-byte units: no bank conflicts, no address maths.
-<<<<<<< Updated upstream
-=======
 //
 // The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
 // the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
@@ -66,7 +59,6 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // 4 x 4 by 4 wavefronts 973 / 1001, 8 x 4 with the second set (one wavefront per SIMD) 766 / 853; two k-steps per stage lose 1 to
 // 25 % in all of them.
 constexpr int kFlush = 8;
->>>>>>> Stashed changes
 enum { PG_PART = 0, PG_SWIGLU = 1 };
 
 template <int WR, int WT, int NWR, int NWT, int KS, bool F16, int EPI>
@@ -127,13 +119,6 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
         for (int i = 0; i < NA; ++i) s[WU + tid + i * NTH] = areg[i];
     };
 
-<<<<<<< Updated upstream
-    f32x4 acc[WR][WT];
-#pragma unroll
-    for (int i = 0; i < WR; ++i)
-#pragma unroll
-        for (int j = 0; j < WT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-=======
     f32x4 acc[WR][WT], sum[WR][WT];
 #pragma unroll
     for (int i = 0; i < WR; ++i)
@@ -148,7 +133,6 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
                 acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
     };
->>>>>>> Stashed changes
 
     const int n_stage = (k1 - k0 + KS - 1) / KS;
     load(k0);
@@ -177,53 +161,34 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
                 }
             }
         }
-<<<<<<< Updated upstream
-=======
         if ((s + 1) % (kFlush / KS) == 0) flush();
->>>>>>> Stashed changes
         if (s + 1 < n_stage) {
             store(lds + ((s + 1) & 1) * (WU + AU));
             if (s + 2 < n_stage) load(k0 + (s + 2) * KS);
         }
         __syncthreads();
     }
-<<<<<<< Updated upstream
-
-    // accumulator of a tile: lane (n, gq) holds token n, rows gq*4 .. +3
-=======
     flush();
 
     // sum of a tile: lane (n, gq) holds token n, rows gq*4 .. +3
->>>>>>> Stashed changes
     const int n = lane & 15, gq = lane >> 4;
 #pragma unroll
     for (int t = 0; t < WT; ++t) {
         const int tok = (tb * BT + wt * WT + t) * 16 + n;
-<<<<<<< Updated upstream
-=======
         const float scale = (EPI == PG_SWIGLU && tok < g.M) ? g.scale[tok] : 0.f;
->>>>>>> Stashed changes
 #pragma unroll
         for (int r = 0; r < WR; ++r) {
             const int rt = rb * BR + wr * WR + r;
             if (EPI == PG_PART) {
                 const int row = rt * 16 + gq * 4;
-<<<<<<< Updated upstream
-                if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = acc[r][t];
-=======
                 if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = sum[r][t];
->>>>>>> Stashed changes
             } else {
                 // rows 0..7 of a tile are gate, 8..15 up of the same 8 features: the other half sits 32 lanes away.  Both
                 // halves then hold the products of 4 features; the lower one stores their hi parts, the upper the lo parts.
                 u16x4 v;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-<<<<<<< Updated upstream
-                    const float mine = acc[r][t][e], other = __shfl_xor(mine, 32);
-=======
                     const float mine = scale * sum[r][t][e], other = __shfl_xor(mine, 32);
->>>>>>> Stashed changes
                     const float gate = gq < 2 ? mine : other, up = gq < 2 ? other : mine;
                     uint16_t hi, lo;
                     split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
@@ -273,11 +238,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
     if ((tid & 63) == 0) wsum[tid >> 6] = ssq;
     __syncthreads();
     const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-<<<<<<< Updated upstream
-    const float scale = 1.0f / sqrtf(total * a.inv_dim + a.eps);
-=======
     if (tid == 0) a.scale[t] = 1.0f / sqrtf(total * a.inv_dim + a.eps);
->>>>>>> Stashed changes
 #pragma unroll
     for (int i = 0; i < kRowsUnits; ++i) {
         const int u = tid + i * kRowsThreads;
@@ -288,11 +249,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 uint16_t h, l;
-<<<<<<< Updated upstream
-                split16<F16>(v[i][e >> 2][e & 3] * scale * w[e], h, l);
-=======
                 split16<F16>(v[i][e >> 2][e & 3] * w[e], h, l);
->>>>>>> Stashed changes
                 hi[e] = h;
                 lo[e] = l;
             }
@@ -329,18 +286,11 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
             s0 += *(const f32x4 *)src;
             s1 += *(const f32x4 *)(src + 4);
         }
-<<<<<<< Updated upstream
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            o[e] = s0[e];
-            o[4 + e] = s1[e];
-=======
         const float scale = a.scale[t];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             o[e] = scale * s0[e];
             o[4 + e] = scale * s1[e];
->>>>>>> Stashed changes
         }
     };
     if (head < a.Hq + a.Hkv) {
@@ -352,11 +302,7 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
             load8(t, head * DH + c * 8, x);
             load8(t, head * DH + half + c * 8, y);
             const float *rp = a.rope + ((size_t)t * half + c * 8) * 2;
-<<<<<<< Updated upstream
-            const float mul = is_q ? a.scale : 1.0f;
-=======
             const float mul = is_q ? a.q_scale : 1.0f;
->>>>>>> Stashed changes
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float cs = rp[2 * e], sn = rp[2 * e + 1];
@@ -602,11 +548,7 @@ int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
     constexpr size_t lds = 2 * (size_t)(BR * KS * 64 + BT * KS * 128) * 16;
     g.n_rb = (g.NT + BR - 1) / BR;
     g.n_tb = ((g.M + 15) / 16 + BT - 1) / BT;
-<<<<<<< Updated upstream
-    // pieces along K: as many as bring the workgroups near two per compute unit, within the room for partial rows
-=======
     // pieces along K: up to two workgroups per compute unit, within the room for partial rows
->>>>>>> Stashed changes
     int split = 1;
     if (EPI == PG_PART) {
         const int blocks = g.n_rb * g.n_tb;
@@ -633,11 +575,7 @@ int launch_gemm_sized(const PromptGemm &g, int n_wg, int *n_split, hipStream_t s
     if (g.M <= 32) return launch_gemm_as<2, 2, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 rows x 32 tokens
     if (g.M <= 64) return launch_gemm_as<2, 4, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 x 64
     if (g.M <= 256) return launch_gemm_as<4, 4, 2, 2, 1, F16, EPI>(g, n_wg, n_split, s);       // 128 x 128
-<<<<<<< Updated upstream
-    return launch_gemm_as<8, 4, 2, 2, 1, F16, EPI>(g, n_wg, n_split, s);                       // 256 x 128
-=======
     return launch_gemm_as<4, 4, 4, 2, 1, F16, EPI>(g, n_wg, n_split, s);                       // 256 x 128
->>>>>>> Stashed changes
 }
 
 }  // namespace
