@@ -47,45 +47,191 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // projections
 // ---------------------------------------------------------------------------------------------------
 // A workgroup of NWR x NWT wavefronts computes BR = NWR * WR row tiles x BT = NWT * WT token tiles; a wavefront holds
-// WR x WT accumulators.  Weights and activations of KS k-steps are staged in LDS, two stages: while one is multiplied the
-// next is on its way in registers (loaded one whole stage ahead).  Both operands lie in memory in MFMA operand order, so
-// a stage is copied as it is and every LDS access is 64 consecutive 16-byte units: no bank conflicts, no address maths.
+// WR x WT accumulators.  Both operands lie in memory in MFMA operand order, so tiles are copied as they are and every LDS
+// access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.  Activations are staged in LDS (two
+// stages: while one is multiplied the next is on its way in registers, loaded a whole stage ahead).
 //
 // The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
 // the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
-// 512 inputs each and then each other, is as good).  A tile of 8 x 4 accumulators per wavefront has no registers left for
-// the second set; 8 wavefronts of 4 x 4 are as fast.  Measured, executed TFLOP/s (hi and lo products counted) at 1024 tokens,
-// 28672 x 4096 / 4096 x 14336: 4 x 4 by 8 wavefronts 1019 / 1105, 8 x 4 by 4 wavefronts without the second set 1048 / 1076,
-// 4 x 4 by 4 wavefronts 973 / 1001, 8 x 4 with the second set (one wavefront per SIMD) 766 / 853; two k-steps per stage lose 1 to
-// 25 % in all of them.
+// 512 inputs each and then each other, is as good).
 constexpr int kFlush = 8;
 enum { PG_PART = 0, PG_SWIGLU = 1 };
 
-template <int WR, int WT, int NWR, int NWT, int KS, bool F16, int EPI>
+// Which tiles and k-steps this workgroup has.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets a contiguous run
+// of (piece, row block, token block), so that the workgroups that share weights share an L2.
+struct PromptTile { int rb, tb, piece, k0, k1; };
+__device__ __forceinline__ PromptTile prompt_tile(const PromptGemm &g) {
+    const int total = g.n_rb * g.n_tb * g.n_split, q8 = total >> 3, r8 = total & 7;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+    PromptTile t;
+    t.tb = id % g.n_tb;
+    const int rest = id / g.n_tb;
+    t.rb = rest % g.n_rb;
+    t.piece = rest / g.n_rb;
+    t.k0 = t.piece * g.k_per;
+    t.k1 = (t.k0 + g.k_per < g.KT) ? t.k0 + g.k_per : g.KT;
+    return t;
+}
+
+template <int WR, int WT>
+struct PromptAcc {
+    f32x4 acc[WR][WT], sum[WR][WT];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int i = 0; i < WR; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) acc[i][j] = sum[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void flush() {
+#pragma unroll
+        for (int i = 0; i < WR; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                sum[i][j] += acc[i][j];
+                acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+    }
+    // stores the sums of the tiles rt0 .., tt0 ..; a tile's lane (n, gq) holds token n, rows gq*4 .. +3
+    template <bool F16, int EPI>
+    __device__ __forceinline__ void store(const PromptGemm &g, int rt0, int tt0, int piece, int lane) const {
+        const int n = lane & 15, gq = lane >> 4;
+#pragma unroll
+        for (int t = 0; t < WT; ++t) {
+            const int tok = (tt0 + t) * 16 + n;
+            const float scale = (EPI == PG_SWIGLU && tok < g.M) ? g.scale[tok] : 0.f;
+#pragma unroll
+            for (int r = 0; r < WR; ++r) {
+                const int rt = rt0 + r;
+                if (EPI == PG_PART) {
+                    const int row = rt * 16 + gq * 4;
+                    if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = sum[r][t];
+                } else {
+                    // rows 0..7 of a tile are gate, 8..15 up of the same 8 features: the other half sits 32 lanes away.  Both
+                    // halves then hold the products of 4 features; the lower one stores their hi parts, the upper the lo parts.
+                    u16x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float mine = scale * sum[r][t][e], other = __shfl_xor(mine, 32);
+                        const float gate = gq < 2 ? mine : other, up = gq < 2 ? other : mine;
+                        uint16_t hi, lo;
+                        split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
+                        v[e] = gq < 2 ? hi : lo;
+                    }
+                    if (tok < g.M && rt < g.NT) {
+                        uint16_t *u = (uint16_t *)((bf16x8 *)g.Bnext + act_unit(tok, rt * 8, g.Bnext_KT, gq >> 1));
+                        *(u16x4 *)(u + 4 * (gq & 1)) = v;
+                    }
+                }
+            }
+        }
+    }
+};
+
+// More than 64 tokens: bound by the matrix cores, and next to them by what moves through LDS.  A wavefront therefore loads
+// its weight tiles from memory straight into registers, one k-step ahead (the NWT wavefronts that share them find them in
+// the compute unit's cache); only the activations, which NWR wavefronts share, go through LDS.  Measured at 1024 tokens,
+// executed TFLOP/s (hi and lo products both counted), 28672 x 4096 / 4096 x 14336, each pair of figures from one run:
+// weights in registers 1057 / 1223, staged in LDS 985 / 1015 (both 4 x 4 tiles by 4 x 2 wavefronts).  2 x 4 tiles by 4 x 2
+// wavefronts (two workgroups per compute unit) are as fast as 4 x 4 (one) from 512 tokens on and faster below (128 tokens,
+// 28672 x 4096: 79 against 102 us), and leave half the pieces to add up; two k-steps per stage lose 6 to 25 %.
+template <int WR, int WT, int NWR, int NWT, bool F16, int EPI>
 __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
     constexpr int NTH = 64 * NWR * NWT, BR = WR * NWR, BT = WT * NWT;
+    constexpr int AU = BT * 128, NA = AU / NTH;                 // 16-byte units of activations per stage, loads per thread
+    static_assert(AU % NTH == 0, "a stage is a whole number of loads per thread");
+    __shared__ bf16x8 lds[2][AU];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wr = wave % NWR, wt = wave / NWR;
+    const PromptTile T = prompt_tile(g);
+
+    unsigned woff[WR], aoff[NA];
+#pragma unroll
+    for (int r = 0; r < WR; ++r) {
+        int rt = T.rb * BR + wr * WR + r;
+        if (rt > g.NT - 1) rt = g.NT - 1;                       // past the last row tile: its products are not stored
+        woff[r] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)lane) << 4;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int u = tid + i * NTH;
+        aoff[i] = ((unsigned)(T.tb * BT + (u >> 7)) * (unsigned)g.KT * 128u + (unsigned)(u & 127)) << 4;
+    }
+    const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
+    bf16x8 w0[WR], w1[WR], areg[NA];
+    auto load_w = [&](bf16x8 (&w)[WR], int k) {
+#pragma unroll
+        for (int r = 0; r < WR; ++r) w[r] = *(const bf16x8 *)(Wb + (woff[r] + ((unsigned)k << 10)));
+    };
+    auto load_a = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) areg[i] = *(const bf16x8 *)(Ab + (aoff[i] + ((unsigned)k << 11)));
+    };
+    auto store_a = [&](bf16x8 *s) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) s[tid + i * NTH] = areg[i];
+    };
+    PromptAcc<WR, WT> C;
+    C.clear();
+    const int n_step = T.k1 - T.k0;
+    // k-step s: multiply w with stage s & 1 while wn and the stage after it are filled for the k-step that follows
+    auto step = [&](const bf16x8 (&w)[WR], bf16x8 (&wn)[WR], int s) {
+        load_w(wn, s + 1 < n_step ? T.k0 + s + 1 : T.k0 + s);
+        const bf16x8 *cur = lds[s & 1] + wt * WT * 128 + lane;
+        bf16x8 bh[WT], bl[WT];
+#pragma unroll
+        for (int t = 0; t < WT; ++t) {
+            bh[t] = cur[t * 128];
+            bl[t] = cur[t * 128 + 64];
+        }
+#pragma unroll
+        for (int r = 0; r < WR; ++r) {
+#pragma unroll
+            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bh[t], C.acc[r][t]);
+#pragma unroll
+            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bl[t], C.acc[r][t]);
+        }
+        if ((s + 1) % kFlush == 0) C.flush();
+        if (s + 1 < n_step) {
+            store_a(lds[(s + 1) & 1]);
+            if (s + 2 < n_step) load_a(T.k0 + s + 2);
+        }
+        __syncthreads();
+    };
+    load_a(T.k0);
+    load_w(w0, T.k0);
+    store_a(lds[0]);
+    if (n_step > 1) load_a(T.k0 + 1);
+    __syncthreads();
+    for (int s = 0; s < n_step; s += 2) {
+        step(w0, w1, s);
+        if (s + 1 < n_step) step(w1, w0, s + 1);
+    }
+    C.flush();
+    C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
+}
+
+// Up to 64 tokens: bound by the weights' way from memory (28672 x 4096 for 32 tokens: 38.6 us, 6.1 TB/s), which is best
+// when all of a workgroup's threads have whole stages of them in flight: weights and activations of KS = 2 k-steps are
+// staged in LDS together (weights in registers as above, 32 tokens: 50.7 us).
+template <int WR, int WT, int NWR, int NWT, bool F16, int EPI>
+__global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm_few(PromptGemm g) {
+    constexpr int KS = 2, NTH = 64 * NWR * NWT, BR = WR * NWR, BT = WT * NWT;
     constexpr int WU = BR * KS * 64, AU = BT * KS * 128;        // 16-byte units per stage
     constexpr int NW_ = WU / NTH, NA = AU / NTH;                // loads per thread
-    static_assert(WU % NTH == 0 && AU % NTH == 0, "a stage is a whole number of loads per thread");
+    static_assert(WU % NTH == 0 && AU % NTH == 0 && kFlush % KS == 0, "a stage is a whole number of loads per thread");
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     bf16x8 *lds = (bf16x8 *)lds_raw;                            // [2][WU + AU]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave % NWR, wt = wave / NWR;
-
-    // workgroups are dealt to the 8 XCDs in turn: give each XCD a contiguous run of (piece, row block, token block), so
-    // that the workgroups that share weights share an L2
-    const int total = g.n_rb * g.n_tb * g.n_split, q8 = total >> 3, r8 = total & 7;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int tb = id % g.n_tb, rest = id / g.n_tb, rb = rest % g.n_rb, piece = rest / g.n_rb;
-    const int k0 = piece * g.k_per, k1 = (k0 + g.k_per < g.KT) ? k0 + g.k_per : g.KT;
+    const PromptTile T = prompt_tile(g);
 
     unsigned woff[NW_], aoff[NA];
     int wks[NW_], aks[NA];
 #pragma unroll
     for (int i = 0; i < NW_; ++i) {
         const int u = tid + i * NTH, in = u % (KS * 64);
-        int rt = rb * BR + u / (KS * 64);
+        int rt = T.rb * BR + u / (KS * 64);
         if (rt > g.NT - 1) rt = g.NT - 1;                       // past the last row tile: its products are not stored
         wks[i] = in >> 6;
         woff[i] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)(in & 63)) << 4;
@@ -94,21 +240,19 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
     for (int i = 0; i < NA; ++i) {
         const int u = tid + i * NTH, in = u % (KS * 128);
         aks[i] = in >> 7;
-        aoff[i] = ((unsigned)(tb * BT + u / (KS * 128)) * (unsigned)g.KT * 128u + (unsigned)(in & 127)) << 4;
+        aoff[i] = ((unsigned)(T.tb * BT + u / (KS * 128)) * (unsigned)g.KT * 128u + (unsigned)(in & 127)) << 4;
     }
     const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
     bf16x8 wreg[NW_], areg[NA];
-    auto load = [&](int k) {
+    auto load = [&](int k) {                                    // k-steps past the matrix repeat its last one
 #pragma unroll
         for (int i = 0; i < NW_; ++i) {
-            int kk = k + wks[i];
-            if (KS > 1 && kk > g.KT - 1) kk = g.KT - 1;
+            const int kk = k + wks[i] < g.KT - 1 ? k + wks[i] : g.KT - 1;
             wreg[i] = *(const bf16x8 *)(Wb + (woff[i] + ((unsigned)kk << 10)));
         }
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            int kk = k + aks[i];
-            if (KS > 1 && kk > g.KT - 1) kk = g.KT - 1;
+            const int kk = k + aks[i] < g.KT - 1 ? k + aks[i] : g.KT - 1;
             areg[i] = *(const bf16x8 *)(Ab + (aoff[i] + ((unsigned)kk << 11)));
         }
     };
@@ -118,32 +262,18 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
 #pragma unroll
         for (int i = 0; i < NA; ++i) s[WU + tid + i * NTH] = areg[i];
     };
-
-    f32x4 acc[WR][WT], sum[WR][WT];
-#pragma unroll
-    for (int i = 0; i < WR; ++i)
-#pragma unroll
-        for (int j = 0; j < WT; ++j) acc[i][j] = sum[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto flush = [&]() {
-#pragma unroll
-        for (int i = 0; i < WR; ++i)
-#pragma unroll
-            for (int j = 0; j < WT; ++j) {
-                sum[i][j] += acc[i][j];
-                acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
-    };
-
-    const int n_stage = (k1 - k0 + KS - 1) / KS;
-    load(k0);
+    PromptAcc<WR, WT> C;
+    C.clear();
+    const int n_stage = (T.k1 - T.k0 + KS - 1) / KS;
+    load(T.k0);
     store(lds);
-    if (n_stage > 1) load(k0 + KS);
+    if (n_stage > 1) load(T.k0 + KS);
     __syncthreads();
     for (int s = 0; s < n_stage; ++s) {
         const bf16x8 *cur = lds + (s & 1) * (WU + AU);
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
-            if (KS == 1 || k0 + s * KS + j < k1) {
+            if (T.k0 + s * KS + j < T.k1) {
                 bf16x8 bh[WT], bl[WT];
 #pragma unroll
                 for (int t = 0; t < WT; ++t) {
@@ -155,52 +285,21 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
                 for (int r = 0; r < WR; ++r) {
                     const bf16x8 a = cur[((wr * WR + r) * KS + j) * 64 + lane];
 #pragma unroll
-                    for (int t = 0; t < WT; ++t) acc[r][t] = mma16<F16>(a, bh[t], acc[r][t]);
+                    for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a, bh[t], C.acc[r][t]);
 #pragma unroll
-                    for (int t = 0; t < WT; ++t) acc[r][t] = mma16<F16>(a, bl[t], acc[r][t]);
+                    for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a, bl[t], C.acc[r][t]);
                 }
             }
         }
-        if ((s + 1) % (kFlush / KS) == 0) flush();
+        if ((s + 1) % (kFlush / KS) == 0) C.flush();
         if (s + 1 < n_stage) {
             store(lds + ((s + 1) & 1) * (WU + AU));
-            if (s + 2 < n_stage) load(k0 + (s + 2) * KS);
+            if (s + 2 < n_stage) load(T.k0 + (s + 2) * KS);
         }
         __syncthreads();
     }
-    flush();
-
-    // sum of a tile: lane (n, gq) holds token n, rows gq*4 .. +3
-    const int n = lane & 15, gq = lane >> 4;
-#pragma unroll
-    for (int t = 0; t < WT; ++t) {
-        const int tok = (tb * BT + wt * WT + t) * 16 + n;
-        const float scale = (EPI == PG_SWIGLU && tok < g.M) ? g.scale[tok] : 0.f;
-#pragma unroll
-        for (int r = 0; r < WR; ++r) {
-            const int rt = rb * BR + wr * WR + r;
-            if (EPI == PG_PART) {
-                const int row = rt * 16 + gq * 4;
-                if (tok < g.M && row < g.N) *(f32x4 *)(g.part + ((size_t)piece * g.M + tok) * g.N + row) = sum[r][t];
-            } else {
-                // rows 0..7 of a tile are gate, 8..15 up of the same 8 features: the other half sits 32 lanes away.  Both
-                // halves then hold the products of 4 features; the lower one stores their hi parts, the upper the lo parts.
-                u16x4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float mine = scale * sum[r][t][e], other = __shfl_xor(mine, 32);
-                    const float gate = gq < 2 ? mine : other, up = gq < 2 ? other : mine;
-                    uint16_t hi, lo;
-                    split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
-                    v[e] = gq < 2 ? hi : lo;
-                }
-                if (tok < g.M && rt < g.NT) {
-                    uint16_t *u = (uint16_t *)((bf16x8 *)g.Bnext + act_unit(tok, rt * 8, g.Bnext_KT, gq >> 1));
-                    *(u16x4 *)(u + 4 * (gq & 1)) = v;
-                }
-            }
-        }
-    }
+    C.flush();
+    C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -542,13 +641,12 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-template <int WR, int WT, int NWR, int NWT, int KS, bool F16, int EPI>
-int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
-    constexpr int BR = WR * NWR, BT = WT * NWT;
-    constexpr size_t lds = 2 * (size_t)(BR * KS * 64 + BT * KS * 128) * 16;
+// Workgroups of BR row tiles x BT token tiles; with PG_PART also the pieces along K: up to two workgroups per compute unit,
+// within the room for partial rows.  Returns a hipError_t.
+template <int EPI>
+int plan_gemm(PromptGemm &g, int BR, int BT, int n_wg, int *n_split) {
     g.n_rb = (g.NT + BR - 1) / BR;
     g.n_tb = ((g.M + 15) / 16 + BT - 1) / BT;
-    // pieces along K: up to two workgroups per compute unit, within the room for partial rows
     int split = 1;
     if (EPI == PG_PART) {
         const int blocks = g.n_rb * g.n_tb;
@@ -560,22 +658,30 @@ int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
     g.k_per = (g.KT + split - 1) / split;
     g.n_split = (g.KT + g.k_per - 1) / g.k_per;
     if (n_split) *n_split = g.n_split;
+    return 0;
+}
+
+template <int WT, bool F16, int EPI>
+int launch_gemm_few(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
+    constexpr size_t lds = 2 * (size_t)(8 * 2 * 64 + WT * 2 * 128) * 16;
+    if (int rc = plan_gemm<EPI>(g, 8, WT, n_wg, n_split)) return rc;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, KS, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm_few<2, WT, 4, 1, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, KS, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(64 * NWR * NWT), lds, s, g);
+    hipLaunchKernelGGL((k_prompt_gemm_few<2, WT, 4, 1, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(256), lds, s, g);
     return (int)hipGetLastError();
 }
 
 template <bool F16, int EPI>
-int launch_gemm_sized(const PromptGemm &g, int n_wg, int *n_split, hipStream_t s) {
-    if (g.M <= 32) return launch_gemm_as<2, 2, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 rows x 32 tokens
-    if (g.M <= 64) return launch_gemm_as<2, 4, 4, 1, 2, F16, EPI>(g, n_wg, n_split, s);        // 128 x 64
-    if (g.M <= 256) return launch_gemm_as<4, 4, 2, 2, 1, F16, EPI>(g, n_wg, n_split, s);       // 128 x 128
-    return launch_gemm_as<4, 4, 4, 2, 1, F16, EPI>(g, n_wg, n_split, s);                       // 256 x 128
+int launch_gemm_sized(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
+    if (g.M <= 32) return launch_gemm_few<2, F16, EPI>(g, n_wg, n_split, s);       // 128 rows x 32 tokens
+    if (g.M <= 64) return launch_gemm_few<4, F16, EPI>(g, n_wg, n_split, s);       // 128 x 64
+    if (int rc = plan_gemm<EPI>(g, 8, 8, n_wg, n_split)) return rc;                // 128 x 128
+    hipLaunchKernelGGL((k_prompt_gemm<2, 4, 4, 2, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(512), 0, s, g);
+    return (int)hipGetLastError();
 }
 
 }  // namespace
