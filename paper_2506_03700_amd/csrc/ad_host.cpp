@@ -127,7 +127,6 @@ void make_layout(const ad_config &c, Layout &L) {
     s += 2 * align_up((size_t)8 * L.d * 4);                    // x1, rows
     s += align_up((size_t)4096 * 8 * 4 * 4);                   // head partials (up to 4096 workgroups)
     s += align_up((size_t)kBarrierWords * 4);                  // grid-barrier counters of the fused layer step
-    s += align_up((size_t)64 * 4);                             // sampled verification: (max, sum) per row
     s += 2 * align_up((size_t)AD_M_MAX * L.V * 4);             // sampled decoding: draft and final logits of the open rows
     L.scratch_bytes = s;
     L.total = off + s;
@@ -156,7 +155,7 @@ struct ad_model {
     char *B1, *Bo, *Bg, *Bx, *Bq;
     float *ssq, *ssq_q;
     float *qkv, *x1, *rows, *head_part;
-    float *samp_stats, *draft_logits, *final_logits;   // sampled decoding
+    float *draft_logits, *final_logits;   // sampled decoding
     // pinned host results for ad_generate
     int32_t *pin;         // [0..8) tok, [8] n_accept, [9] next, [16..24) row argmax, [28] the head's done word
     mutable int32_t done_seq = 0;   // last value asked for in the done word (unique per head evaluation of this model)
@@ -276,7 +275,6 @@ ad_status ad_model_create(const ad_config *cfg, const ad_layer_weights *layers, 
     m->head_part = (float *)take((size_t)4096 * 8 * 4 * 4);
     m->bar_ctr = (unsigned *)take((size_t)kBarrierWords * 4);     // zeroed with the rest of the scratch above
     m->bar_round = 0;
-    m->samp_stats = (float *)take((size_t)64 * 4);
     m->draft_logits = (float *)take((size_t)AD_M_MAX * L.V * 4);
     m->final_logits = (float *)take((size_t)AD_M_MAX * L.V * 4);
     m->pin = (int32_t *)pinned_alloc(4096);
@@ -791,7 +789,7 @@ ad_status ad_sample_logits(const ad_model *m, const void *logits, float temperat
     if (!m || !logits || !token || !prob) return (ad_status)fail(AD_EINVAL, "ad_sample_logits: null argument");
     if (!(temperature > 0.f) || !(u >= 0.f && u < 1.f)) return (ad_status)fail(AD_ERANGE, "ad_sample_logits: temperature must be > 0 and u in [0, 1)");
     SampleArgs a;
-    a.z = (const float *)logits; a.V = m->cfg.vocab; a.inv_t = 1.0f / temperature; a.u = u; a.tok_out = token; a.prob_out = prob;
+    a.z = (const float *)logits; a.V = m->cfg.vocab; a.inv_t = 1.0f / temperature; a.u = u; a.tok_out = token; a.prob_out = prob; a.scratch = m->head_part;
     const int rc = launch_sample_row(a, stream);
     return rc ? (ad_status)hip_fail(rc, "ad_sample_logits") : AD_OK;
 }
@@ -812,7 +810,7 @@ ad_status ad_verify_sampled(const ad_model *m, const void *final_logits, const v
             return (ad_status)fail(AD_ERANGE, "ad_verify_sampled: draws must be in [0, 1)");
         a.draft[i] = draft[i]; a.u_accept[i] = u_accept[i]; a.u_resample[i] = u_resample[i];
     }
-    a.u_final = u_final; a.stats = m->samp_stats; a.n_accept_out = n_accept; a.next_out = next_token; a.ratio_out = ratio;
+    a.u_final = u_final; a.scratch = m->head_part; a.n_accept_out = n_accept; a.next_out = next_token; a.ratio_out = ratio;
     const int rc = launch_verify_sampled(a, stream);
     return rc ? (ad_status)hip_fail(rc, "ad_verify_sampled") : AD_OK;
 }

@@ -158,6 +158,10 @@ struct EmbedArgs {
     const int32_t *tok_src; int vocab;
 };
 
+// Scratch of a draw or a sampled verification: per-segment statistics of its rows.  The model's vocabulary partials serve (free
+// between head evaluations).
+constexpr size_t kSampleScratchBytes = 32768;
+
 // Sampled decoding (Sec. 2.2).  inv_t = 1 / temperature; u, u_accept, u_resample, u_final are uniform draws in [0, 1).
 struct SampleArgs {
     const float *z;         // dev [V] logits
@@ -165,6 +169,7 @@ struct SampleArgs {
     float inv_t, u;
     int32_t *tok_out;       // pinned host or dev
     float *prob_out;        // pinned host or dev: probability of the drawn token
+    void *scratch;          // dev, kSampleScratchBytes
 };
 struct VerifySampledArgs {
     const float *zf;        // dev [m][V]: final-layer logits of the m rows
@@ -173,7 +178,7 @@ struct VerifySampledArgs {
     float inv_t;
     int32_t draft[8];
     float u_accept[8], u_resample[8], u_final;
-    float *stats;           // dev scratch [2 * (2m - 1)]: (max, sum of exp) per row
+    void *scratch;          // dev, kSampleScratchBytes
     int32_t *n_accept_out, *next_out;   // pinned host or dev
     float *ratio_out;       // null, or pinned host or dev [m - 1]: p*(t) / p_draft(t) of the drafts that were checked, else 0
 };

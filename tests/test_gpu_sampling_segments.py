@@ -1,0 +1,59 @@
+"""GPU: draws and sampled verification at the edges of the segments a logits row is cut into (2048 ids each; longer ones beyond
+256 of them), with masked ids and masked segments, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2506_03700_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SMALL = synth.TINY.with_(name="small", tied_head=False, n_layers=1, exit_layers=(), d_model=16, n_q_heads=1, n_kv_heads=1, d_ffn=8, dtype=synth.BF16)
+
+
+@pytest.fixture(scope="module")
+def ad():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2506_03700_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("V", [1, 2047, 2048, 2049, 4097, 600001])
+def test_draws_and_verification_at_segment_edges(ad, V):
+    import torch
+    seg = 2048 if V <= 2048 * 256 else -(-V // 256)
+    g = ad.Model(SMALL.with_(vocab=V), synth.make_weights(SMALL.with_(vocab=V), seed=0), max_pos=8)
+    rng = np.random.default_rng(V)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    edges = sorted({t for t in (0, 1, seg - 1, seg, seg + 1, V - 2, V - 1) if 0 <= t < V})
+    for t in edges:
+        print(f"case V={V} token {t}", flush=True)
+        z = (rng.standard_normal(V) * 0.5).astype(np.float32)
+        z[t] = 16.0
+        p = orc.softmax_t(z.astype(np.float64), 1.0)
+        u = float(np.float32(p[:t].sum() + p[t] / 2))
+        tok, prob = g.ad_sample_logits(dev(z), 1.0, u)
+        assert tok == t == orc.sample_cdf(p, u)[0] and abs(prob - p[t]) <= 1e-5 * p[t]
+        # only t and the edges have any weight, whatever the draw; masked ids are never drawn
+        z = np.full(V, -np.inf, dtype=np.float32)
+        z[edges] = rng.standard_normal(len(edges)).astype(np.float32)
+        p = orc.softmax_t(z.astype(np.float64), 1.0)
+        for u in (0.0, float(np.float32(rng.random())), float(np.float32(1 - 2.0 ** -24))):
+            tok, prob = g.ad_sample_logits(dev(z), 1.0, u)
+            want, margin = orc.sample_cdf(p, u)
+            assert tok in edges and abs(prob - p[tok]) <= 1e-5 * p[tok]
+            assert tok == want or margin < 1e-6
+        # a rejected draft whose residual is one token at a segment's edge: p* and p_draft differ at t and at the draft only
+        if V > 1:
+            zf = (rng.standard_normal((2, V)) * 0.5).astype(np.float32)
+            zq = zf[:1].copy()
+            d = edges[0] if t != edges[0] else edges[-1]
+            zf[0, t] = zq[0, d] = 14.0
+            n, nxt, ratio = g.ad_verify_sampled(dev(zf), dev(zq), [d], 1.0, [0.5], [float(np.float32(rng.random()))], 0.5)
+            p, q = orc.softmax_t(zf[0].astype(np.float64), 1.0), orc.softmax_t(zq[0].astype(np.float64), 1.0)
+            assert n == 0 and abs(ratio[0] - p[d] / q[d]) <= 1e-4 * p[d] / q[d]
+            r = np.maximum(p - q, 0.0)
+            assert nxt == t or r[nxt] > 0 and r[t] / r.sum() < 0.9999
+    g.close()
