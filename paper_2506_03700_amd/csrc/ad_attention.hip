@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ad_attention_device.h"
 #include "ad_device.h"
 #include "ad_internal.h"
@@ -23,22 +25,277 @@
 namespace ad {
 
 // ---------------------------------------------------------------------------------------------------
-// bf16 cache: MFMA kernel (device code in ad_attention_device.h), 8 wavefronts per work item: two per block of
-// 32 cached positions, which share the blocks of 8 query rows between them
+// 16-bit cache: MFMA kernel, one wavefront per block of 32 cached positions
 // ---------------------------------------------------------------------------------------------------
-constexpr int kAttnThreads = 512;
+// The products are those of the fused kernel's attention phase (ad_attention_device.h): S^T = K q^T with the rows of the
+// two score tiles assigned to keys so that a lane ends up with 8 consecutive keys of its query row, which is the B operand
+// layout of O^T = V^T P^T, K and V^T loaded from the cache straight into operand registers.  Query rows fill all 16
+// columns of a tile and their hi and lo parts are two operands (not two halves of the columns), so no score, exponential
+// or output is computed twice.  Wavefront w takes blocks w, w + 4, ... of the item under an online softmax (its next K is
+// requested as soon as the scores are formed, its next V after the second product); the last wavefront of the item that
+// holds the end of the cache then takes the call's own rows as one more block.  The four wavefronts' results meet in LDS.
+//
+// An item is a chain of dependent steps, whatever its size, so what counts is its length and how many run at once (a layer's
+// cache at context 9203 is read in 6 us).  Layer step of the 8B shape against the kernel this replaces (hi and lo parts in the
+// two halves of a tile's columns, two wavefronts per block, every item 128 positions): context 9203, 8 rows 142.8 -> 119 us, 1
+// row 106.8 -> 100.7; 4096, 4 rows 105.4 -> 102.2; 13B shape, 4096, 8 rows 179.9 -> 171.5.  RT row
+// tiles per wavefront, NRH wavefronts per block of keys (each with RT tiles of its own), up to 16 * RT * NRH query rows per pass.
+template <int DH, int RT, int NRH>
+struct AttnDecLds {
+    static constexpr int RP = RT * NRH * 16;
+    static constexpr int PD = DH / RT;                     // dimensions folded at a time
+    bf16x8 qb[RT * NRH * (DH / 32) * 2 * 64];              // [row tile][k-step][hi, lo][lane]
+    uint16_t knew[8 * DH];                                 // the call's own K rows, cache type: [row][dim]
+    uint16_t vnewT[DH * 8];                                // the call's own V rows, transposed: [dim][row]
+    float mx[4][RP], sum[4][RP];
+    float part[4][RP][PD + 4];                             // rows padded to 16 bytes for 128-bit LDS stores
+};
 
-// NT, RP: 512 threads and 32 query rows per pass; or, for calls with at most 16 query rows per kv head and more work
-// items than compute units, 256 threads (one wavefront per block of 32 positions) and 8 rows per pass, whose
-// registers and 30 KB of LDS let workgroups share a compute unit, so that one item's loads overlap another's
-// arithmetic (an item is a chain of dependent steps; with one workgroup per compute unit, items run one after the
-// other).  Measured on the 8B shape at context 6000 (376 items): faster up to 16 rows, slower from 24 rows on.
-template <int DH, bool F16, int NT, int RP>
-__global__ void __launch_bounds__(NT, NT == 256 ? 2 : 1) k_attn_mfma(AttnArgs a) {
+template <int DH, bool F16, int RT, int NRH>
+__global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
     warm_kernel_args<sizeof(AttnArgs)>();
+    constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, RP = RT * NRH * 16, NTH = 256 * NRH;
+    constexpr float kPScale = F16 ? 1024.0f : 1.0f;        // keeps small probabilities out of fp16's subnormals
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    AttnKv<DH> kv;
-    attn_mfma_items<DH, NT, IoPlain, F16, RP>(a, *reinterpret_cast<AttnMfmaLds<DH, RP> *>(lds_raw), blockIdx.x, gridDim.x, kv, false);
+    AttnDecLds<DH, RT, NRH> &L = *reinterpret_cast<AttnDecLds<DH, RT, NRH> *>(lds_raw);
+    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, n = lane & 15, gq = lane >> 4;
+    const int row_w = (tid >> 8) * RT * 16;                // this wavefront's first row of a pass
+    const int G = a.G, R = a.R;
+    const int item = blockIdx.x, g = div_small(item, a.mul_S), s = item - g * a.S;
+    const int c0 = s * a.C, c1 = (c0 + a.C < a.pos0) ? c0 + a.C : a.pos0;
+    const int nc = (c1 > c0) ? c1 - c0 : 0, nbc = (nc + 31) / 32;
+    const bool last = (s == a.S - 1);
+    uint16_t *Kg = (uint16_t *)a.Kc + (size_t)g * a.stride * DH;
+    uint16_t *Vg = (uint16_t *)a.Vc + (size_t)g * DH * a.stride;
+    const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+
+    // (addressed as a uniform pointer plus a 32-bit byte offset per lane: one register per load instead of two)
+    bf16x8 k[2][KS], v[DT];
+    auto load_k = [&](int b) {
+#pragma unroll
+        for (int aa = 0; aa < 2; ++aa) {
+            int key = c0 + b * 32 + 8 * (n >> 2) + 4 * aa + (n & 3);
+            if (key > a.pos0 - 1) key = a.pos0 - 1;         // dead positions are masked at use; stay in live memory
+            const unsigned off = (unsigned)key * (DH * 2u) + gq * 16u;
+#pragma unroll
+            for (int j = 0; j < KS; ++j) k[aa][j] = *(const bf16x8 *)((const char *)(Kg + j * 32) + off);
+        }
+    };
+    auto load_v = [&](int b) {
+        const unsigned off = ((unsigned)n * (unsigned)a.stride + (unsigned)(c0 + b * 32 + gq * 8)) * 2u;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) v[dt] = *(const bf16x8 *)((const char *)(Vg + (size_t)dt * 16 * a.stride) + off);
+    };
+
+    for (int r0 = 0; r0 < R; r0 += RP) {
+        const int nr = (R - r0 < RP) ? R - r0 : RP;
+        // this wavefront's first cached block goes in flight first: it does not depend on the queries
+        if (wave < nbc && row_w < nr) {
+            load_k(wave);
+            load_v(wave);
+        }
+        if (last && r0 == 0) {
+            // the call's own rows: rotate k, round to the cache type, append to the cache, keep a copy in LDS
+            for (int idx = tid; idx < a.m * half; idx += NTH) {
+                const int t = idx / half, i = idx % half;
+                const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
+                const float *vp = kp + (size_t)a.Hkv * DH;
+                const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
+                const float x = kp[i], y = kp[i + half];
+                const uint16_t k0 = f32_to_16<F16>(x * c - y * sn), k1 = f32_to_16<F16>(x * sn + y * c);
+                const uint16_t v0 = f32_to_16<F16>(vp[i]), v1 = f32_to_16<F16>(vp[i + half]);
+                L.knew[t * DH + i] = k0;
+                L.knew[t * DH + i + half] = k1;
+                L.vnewT[i * 8 + t] = v0;
+                L.vnewT[(i + half) * 8 + t] = v1;
+                const size_t p = (size_t)(a.pos0 + t);
+                Kg[p * DH + i] = k0;
+                Kg[p * DH + i + half] = k1;
+                Vg[(size_t)i * a.stride + p] = v0;
+                Vg[(size_t)(i + half) * a.stride + p] = v1;
+            }
+        }
+        // queries: rotate, scale, split hi/lo, store in operand order; a thread takes 4 dimensions of each half of a row
+        for (int idx = tid; idx < nr * (half / 4); idx += NTH) {
+            const int rr = idx / (half / 4), i = (idx % (half / 4)) * 4, r = r0 + rr;
+            const int t = div_small(r, a.mul_G), hq = g * G + (r - t * G);
+            const float *qp = a.qkv + (size_t)t * a.ld + (size_t)hq * DH + i;
+            const float *rp = a.rope + ((size_t)t * half + i) * 2;
+            const f32x4 x = *(const f32x4 *)qp, y = *(const f32x4 *)(qp + half);
+            const f32x4 ra = *(const f32x4 *)rp, rb = *(const f32x4 *)(rp + 4);
+            u16x4 h0, l0, h1, l1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float c = e < 2 ? ra[2 * e] : rb[2 * e - 4], sn = e < 2 ? ra[2 * e + 1] : rb[2 * e - 3];
+                uint16_t hi, lo;
+                split16<F16>((x[e] * c - y[e] * sn) * a.scale, hi, lo);
+                h0[e] = hi;
+                l0[e] = lo;
+                split16<F16>((x[e] * sn + y[e] * c) * a.scale, hi, lo);
+                h1[e] = hi;
+                l1[e] = lo;
+            }
+            auto put = [&](int d, int plane, u16x4 w) {
+                *(u16x4 *)((uint16_t *)&L.qb[(((rr >> 4) * KS + (d >> 5)) * 2 + plane) * 64 + (rr & 15) + 16 * ((d & 31) >> 3)] + (d & 7)) = w;
+            };
+            put(i, 0, h0);
+            put(i, 1, l0);
+            put(i + half, 0, h1);
+            put(i + half, 1, l1);
+        }
+        __syncthreads();
+
+        f32x4 o[RT][DT];
+        float mx[RT], sum[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            mx[i] = -INFINITY;
+            sum[i] = 0.f;
+#pragma unroll
+            for (int d = 0; d < DT; ++d) o[i][d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        // one block of 32 keys, in k and v: `live` of them from the block's start (IS_NEW: the call's own rows, causal)
+        auto block = [&](auto is_new, int live, auto after_scores) {
+            constexpr bool IS_NEW = decltype(is_new)::value;
+            f32x4 sc[RT][2];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                sc[i][0] = sc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                if (row_w + i * 16 < nr) {
+#pragma unroll
+                    for (int j = 0; j < KS; ++j)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) {
+                            const bf16x8 q = L.qb[(((row_w / 16 + i) * KS + j) * 2 + p) * 64 + lane];
+                            sc[i][0] = mma16<F16>(k[0][j], q, sc[i][0]);
+                            sc[i][1] = mma16<F16>(k[1][j], q, sc[i][1]);
+                        }
+                }
+            }
+            after_scores();
+            bf16x8 ph[RT], pl[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if (row_w + i * 16 >= nr) continue;
+                const int t_row = IS_NEW ? div_small(r0 + row_w + i * 16 + n, a.mul_G) : 0;
+                float w[8], bm = -INFINITY;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    w[c] = sc[i][c >> 2][c & 3];
+                    const int key = gq * 8 + c;
+                    if (IS_NEW ? (key >= a.m || key > t_row) : key >= live) w[c] = -INFINITY;
+                    bm = fmaxf(bm, w[c]);
+                }
+                bm = fmaxf(bm, __shfl_xor(bm, 16));
+                bm = fmaxf(bm, __shfl_xor(bm, 32));
+                const float nm = fmaxf(mx[i], bm);          // finite: every row sees the first key of every block it is given
+                const float alpha = __expf(mx[i] - nm);
+                mx[i] = nm;
+                float add = 0.f;
+                u16x8 h8, l8;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float p = __expf(w[c] - nm);
+                    add += p;
+                    uint16_t hi, lo;
+                    split16<F16>(p * kPScale, hi, lo);
+                    h8[c] = hi;
+                    l8[c] = lo;
+                }
+                ph[i] = __builtin_bit_cast(bf16x8, h8);
+                pl[i] = __builtin_bit_cast(bf16x8, l8);
+                sum[i] = sum[i] * alpha + add;
+                if (!__all(alpha == 1.0f)) {
+#pragma unroll
+                    for (int d = 0; d < DT; ++d) o[i][d] *= alpha;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if (row_w + i * 16 >= nr) continue;
+#pragma unroll
+                for (int d = 0; d < DT; ++d) {
+                    o[i][d] = mma16<F16>(v[d], ph[i], o[i][d]);
+                    o[i][d] = mma16<F16>(v[d], pl[i], o[i][d]);
+                }
+            }
+        };
+        for (int b = wave; b < nbc && row_w < nr; b += 4) {
+            const int live = nc - b * 32;
+            if (live < 32) {                                // ragged end of the cache: dead positions contribute nothing
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (gq * 8 + e >= live) v[dt][e] = 0;
+            }
+            block(std::false_type{}, live, [&]() { if (b + 4 < nbc) load_k(b + 4); });
+            if (b + 4 < nbc) load_v(b + 4);
+        }
+        if (last && wave == 3 && row_w < nr) {
+#pragma unroll
+            for (int aa = 0; aa < 2; ++aa) {
+                const int key = 8 * (n >> 2) + 4 * aa + (n & 3);
+#pragma unroll
+                for (int j = 0; j < KS; ++j) k[aa][j] = (key < a.m) ? *(const bf16x8 *)(L.knew + key * DH + j * 32 + gq * 8) : zero;
+            }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                // keys gq * 8 .. + 7 of dimension dt * 16 + n: only the first lane group has live keys
+                bf16x8 cv = (gq == 0) ? *(const bf16x8 *)(L.vnewT + (dt * 16 + n) * 8) : zero;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (e >= a.m) cv[e] = 0;
+                v[dt] = cv;
+            }
+            block(std::true_type{}, 0, []() {});
+        }
+        // lane (n, gq): row n of a tile, dimensions d*16 + gq*4 .. +3.  The wavefronts' results are folded in wavefront order, PD
+        // dimensions at a time: a thread takes two neighbouring dimensions of a row and derives the wavefronts' weights itself.
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            float den = sum[i];
+            den += __shfl_xor(den, 16);
+            den += __shfl_xor(den, 32);
+            if (gq == 0) {
+                L.mx[wave][row_w + i * 16 + n] = mx[i];
+                L.sum[wave][row_w + i * 16 + n] = den;
+            }
+        }
+        constexpr int PD = AttnDecLds<DH, RT, NRH>::PD;
+#pragma unroll
+        for (int h = 0; h < RT; ++h) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int d = 0; d < PD / 16; ++d)
+                    if (row_w + i * 16 + n < nr) *(f32x4 *)&L.part[wave][row_w + i * 16 + n][d * 16 + gq * 4] = o[i][h * (PD / 16) + d] * (1.0f / kPScale);
+            __syncthreads();
+            for (int idx = tid; idx < nr * (PD / 2); idx += NTH) {
+                const int rr = idx / (PD / 2), e = (idx % (PD / 2)) * 2;
+                float mp[4], M = -INFINITY, sm[4], den = 0.f;
+                f32x2 x[4], num = {0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    mp[w] = L.mx[w][rr];
+                    sm[w] = L.sum[w][rr];
+                    x[w] = *(const f32x2 *)&L.part[w][rr][e];
+                    M = fmaxf(M, mp[w]);
+                }
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float f = __expf(mp[w] - M);      // a wavefront without keys: exp(-inf) = 0, of sums that are 0
+                    den += f * sm[w];
+                    num[0] += f * x[w][0];
+                    num[1] += f * x[w][1];
+                }
+                float *out = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
+                *(f32x2 *)(out + h * PD + e) = num;
+                if (h == 0 && e == 0) *(f32x2 *)(out + DH) = (f32x2){M, den};
+            }
+            __syncthreads();
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -206,37 +463,53 @@ static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
     return (int)hipGetLastError();
 }
 
-template <int DH, bool F16, int NT, int RP>
-static int launch_mfma_as(const AttnArgs &a, const LaunchCtx &c) {
-    const size_t lds = sizeof(AttnMfmaLds<DH, RP>);
+template <int DH, bool F16, int RT, int NRH>
+static int launch_dec_as(const AttnArgs &a, const LaunchCtx &c) {
+    const size_t lds = sizeof(AttnDecLds<DH, RT, NRH>);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_attn_mfma<DH, F16, NT, RP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_attn_dec<DH, F16, RT, NRH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    int grid = a.Hkv * a.S;
-    if (grid > 8 * c.n_wg) grid = 8 * c.n_wg;
-    hipLaunchKernelGGL((k_attn_mfma<DH, F16, NT, RP>), dim3(grid), dim3(NT), lds, (hipStream_t)c.stream, a);
+    hipLaunchKernelGGL((k_attn_dec<DH, F16, RT, NRH>), dim3(a.Hkv * a.S), dim3(256 * NRH), lds, (hipStream_t)c.stream, a);
     return (int)hipGetLastError();
 }
 
+// More than 16 query rows: two wavefronts per block of keys, a row tile each, while an item is one or two blocks per wavefront
+// and there is at most one item per compute unit (the chain through an item is what counts then); else one wavefront
+// with both tiles, whose workgroups can share a compute unit.  Layer step of the 8B shape, 8 rows: context 1201 110.4
+// against 112.5 us, 4096 114.3 / 115.5, 6000 114.4 / 114.9, 9203 (three blocks per wavefront) 120.1 / 119.0.
 template <int DH, bool F16>
-static int launch_mfma(const AttnArgs &a, const LaunchCtx &c) {
-    const int rows = (a.Hq / a.Hkv) * a.m;
-    if (rows <= 16 && a.Hkv * a.S > c.n_wg) return launch_mfma_as<DH, F16, 256, 8>(a, c);
-    return launch_mfma_as<DH, F16, kAttnThreads, kAttnRowsPerPass>(a, c);
+static int launch_dec(const AttnArgs &a, const LaunchCtx &c) {
+    if (a.R <= 16) return launch_dec_as<DH, F16, 1, 1>(a, c);
+    if (a.C <= 2 * attn_chunk(a.kv_elem, a.dh) && a.Hkv * a.S <= c.n_wg) return launch_dec_as<DH, F16, 1, 2>(a, c);
+    return launch_dec_as<DH, F16, 2, 1>(a, c);
+}
+
+// Positions per item for a stand-alone launch, k times the smallest item: one item per compute unit if k = 4 is enough for
+// that, else two.  (An item that shares its compute unit runs slower, but a chain of many blocks is longer still.)
+// Measured, layer step: 8B shape, 1 row, context 9203: k = 3 (192 items) 100.7 us, k = 2 (288) 103.2, k = 1 (576) 107.5;
+// 13B shape (40 kv heads), 1 row, context 4096: k = 3 (440 items) 143.2 us, k = 5 (280) 149.7, k = 2 (640) 147.1.
+int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg) {
+    const int c = attn_chunk(kv_elem, dh);
+    if (kv_elem == kElemF32) return c;
+    auto items = [&](int k) { return (long)n_kv_heads * ((pos0 + (long)k * c - 1) / ((long)k * c)); };
+    for (int k = 1; k <= 4; ++k)
+        if (items(k) <= n_wg) return k * c;
+    for (int k = 2;; ++k)                                  // ends: with one item per kv head at the latest
+        if (items(k) <= 2L * n_wg || items(k) <= n_kv_heads) return k * c;
 }
 
 int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
     int rc;
     if (a.kv_elem == kElemBF16) {
-        if (a.dh == 128) rc = launch_mfma<128, false>(a, c);
-        else if (a.dh == 64) rc = launch_mfma<64, false>(a, c);
+        if (a.dh == 128) rc = launch_dec<128, false>(a, c);
+        else if (a.dh == 64) rc = launch_dec<64, false>(a, c);
         else return (int)hipErrorInvalidValue;
     } else if (a.kv_elem == kElemF16) {
-        if (a.dh == 128) rc = launch_mfma<128, true>(a, c);
-        else if (a.dh == 64) rc = launch_mfma<64, true>(a, c);
+        if (a.dh == 128) rc = launch_dec<128, true>(a, c);
+        else if (a.dh == 64) rc = launch_dec<64, true>(a, c);
         else return (int)hipErrorInvalidValue;
     } else {
         if (a.dh == 128) rc = launch_valu<float, 128>(a, c);

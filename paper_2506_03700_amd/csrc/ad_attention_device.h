@@ -1,6 +1,6 @@
-// Device side of the attention phase for a bf16 KV cache: work items of the split-context MFMA attention and
-// the fold of the splits.  Included by the stand-alone attention kernels (ad_attention.hip) and by the fused
-// layer-step kernel (ad_layer_fused.hip); the `Io` policy (ad_gemm_device.h) says how data exchanged between
+// Device side of the attention phase for a 16-bit KV cache: work items of the split-context MFMA attention as the fused
+// layer-step kernel (ad_layer_fused.hip) runs them, and the fold of the splits, which the stand-alone kernels
+// (ad_attention.hip, with work items of their own) use too; the `Io` policy (ad_gemm_device.h) says how data exchanged between
 // workgroups -- q/k/v rows in, partials out and in, packed output -- is accessed.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -27,9 +27,10 @@ constexpr int kAttnWaves = 4;            // key blocks of an item that are proce
 constexpr int kAttnRowsPerPass = 32;
 constexpr int kAttnSlots = 5;   // 4 cached blocks + the call's own rows
 
-// RP: query rows per pass (a multiple of 8; more rows take more passes)
-template <int DH, int RP = kAttnRowsPerPass>
+// RP: query rows per pass (more rows take more passes)
+template <int DH>
 struct AttnMfmaLds {
+    static constexpr int RP = kAttnRowsPerPass;
     bf16x8 qb[(RP / 8) * (DH / 32) * 64];                // [row block][k-step][lane]
     uint16_t knew[8 * DH];                               // the call's own K rows, cache type: [row][dim]
     uint16_t vnewT[DH * 8];                              // the call's own V rows, transposed: [dim][row]
@@ -75,10 +76,10 @@ __device__ __forceinline__ void attn_load_kv(const AttnArgs &a, int item, AttnKv
 // `kv`: register block for the cached K/V; if `preloaded`, it already holds (or has in flight) the block of the
 // first item, wg.
 // F16: the cache, and the 16-bit halves of the queries and probabilities, are fp16 (else bf16).
-template <int DH, int NTHREADS, class Io, bool F16, int RP = kAttnRowsPerPass>
-__device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<DH, RP> &L, int wg, int nwg, AttnKv<DH> &kv, bool preloaded,
+template <int DH, int NTHREADS, class Io, bool F16>
+__device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<DH> &L, int wg, int nwg, AttnKv<DH> &kv, bool preloaded,
                                                 long long kv_off = 0) {
-    constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, PL = DH + 4;
+    constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, PL = DH + 4, RP = kAttnRowsPerPass;
     constexpr int NRH = NTHREADS / 256;      // wavefronts per key block
     const int tid = thread_index(), lane = tid & 63, wave = (tid >> 6) & 3, rh = tid >> 8;
     const int n = lane & 15, gq = lane >> 4;

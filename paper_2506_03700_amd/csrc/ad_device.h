@@ -72,6 +72,25 @@ __device__ __forceinline__ void warm_kernel_args() {
 // the same type as the weights they meet in an MFMA: bf16 for fp32 and bf16 models, fp16 for fp16 models.
 enum ElemKind : int { ELEM_F32 = 0, ELEM_BF16 = 1, ELEM_F16 = 2 };
 
+typedef __attribute__((__vector_size__(4 * sizeof(uint16_t)))) uint16_t u16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(uint16_t)))) uint16_t u16x8;
+
+template <bool F16>
+__device__ __forceinline__ uint16_t to16(float v) {
+    if constexpr (F16) return __builtin_bit_cast(uint16_t, (_Float16)v);
+    else return __builtin_bit_cast(uint16_t, (__bf16)v);       // rounds to nearest even in hardware
+}
+template <bool F16>
+__device__ __forceinline__ float from16(uint16_t b) { return F16 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b); }
+// v is rounded to fp32 before it is split: as a product it could otherwise be fused into one of the two uses of hi (a
+// multiplication that rounds to fp16 at once) and not into the other, and at a tie the two would differ
+template <bool F16>
+__device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
+    if constexpr (F16) asm("" : "+v"(v));
+    hi = to16<F16>(v);
+    lo = to16<F16>(v - from16<F16>(hi));
+}
+
 // x = hi + lo with hi, lo in the 16-bit type (F16: half precision, else bf16)
 template <bool F16>
 __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo) {

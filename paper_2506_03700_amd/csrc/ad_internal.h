@@ -207,7 +207,8 @@ int launch_sample_row(const SampleArgs &, void *stream);
 int launch_verify_sampled(const VerifySampledArgs &, void *stream);
 int launch_layer_fused(const FusedArgs &, const LaunchCtx &);   // n_wg must not exceed the number of compute units
 int fused_phase_workgroups(int n_tiles, int n_wg);               // workgroups that own row tiles of a GEMM phase
-int attn_chunk(int kv_elem, int dh);   // cached positions per attention work item
+int attn_chunk(int kv_elem, int dh);   // cached positions per attention work item (fused layer step), and the fewest
+int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg);   // the same for a stand-alone launch
 int device_info(int *n_cu);
 const char *hip_error_text(int code);
 int stream_sync(void *stream);

@@ -19,25 +19,6 @@ namespace ad {
 
 namespace {
 
-typedef __attribute__((__vector_size__(4 * sizeof(uint16_t)))) uint16_t u16x4;
-typedef __attribute__((__vector_size__(8 * sizeof(uint16_t)))) uint16_t u16x8;
-
-template <bool F16>
-__device__ __forceinline__ uint16_t to16(float v) {
-    if constexpr (F16) return __builtin_bit_cast(uint16_t, (_Float16)v);
-    else return __builtin_bit_cast(uint16_t, (__bf16)v);       // rounds to nearest even in hardware
-}
-template <bool F16>
-__device__ __forceinline__ float from16(uint16_t b) { return F16 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b); }
-// v is rounded to fp32 before it is split: as a product it could otherwise be fused into one of the two uses of hi (a
-// multiplication that rounds to fp16 at once) and not into the other, and at a tie the two would differ
-template <bool F16>
-__device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
-    if constexpr (F16) asm("" : "+v"(v));
-    hi = to16<F16>(v);
-    lo = to16<F16>(v - from16<F16>(hi));
-}
-
 // 16-byte unit of token t, inputs k .. k + 7 (k a multiple of 8), in activation tiles with KT k-steps (plane 0 = hi)
 __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
     return (((size_t)(t >> 4) * KT + (k >> 5)) * 2 + plane) * 64 + (t & 15) + 16 * ((k & 31) >> 3);
