@@ -289,6 +289,12 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
                     num[0] += f * x[w][0];
                     num[1] += f * x[w][1];
                 }
+                if (a.S == 1) {                             // nothing to fold: the output itself, packed for the Wo GEMM
+                    const int r = r0 + rr, t = div_small(r, a.mul_G), kk = (g * G + (r - t * G)) * DH + h * PD + e;
+                    store_act_io<IoPlain, F16>((uint16_t *)a.Bo, a.Bo_KT, kk, t, num[0] / den);
+                    store_act_io<IoPlain, F16>((uint16_t *)a.Bo, a.Bo_KT, kk + 1, t, num[1] / den);
+                    continue;
+                }
                 float *out = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
                 *(f32x2 *)(out + h * PD + e) = num;
                 if (h == 0 && e == 0) *(f32x2 *)(out + DH) = (f32x2){M, den};
@@ -330,7 +336,7 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
     float *qs = (float *)lds_raw;                   // [kValuMaxRows][DH]
     float *sc = qs + kValuMaxRows * DH;             // [kValuMaxRows][MAXK]
     float *st = sc + kValuMaxRows * MAXK;           // [kValuMaxRows][2]
-    KVT *Ks = (KVT *)(st + kValuMaxRows * 2 + 4);   // [MAXK][KROW]
+    KVT *Ks = (KVT *)(st + kValuMaxRows * 2 + kValuThreads);   // [MAXK][KROW]
     KVT *Vs = Ks + MAXK * KROW;
     const int n_items = a.Hkv * a.S;
     const size_t PR = DH + 2;
@@ -346,10 +352,8 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
             const int j = idx / DH, e = idx % DH;
             Ks[j * KROW + e] = Kg[(size_t)(c0 + j) * DH + e];
         }
-        for (int idx = tid; idx < nc * DH; idx += kValuThreads) {
-            const int e = idx / nc, j = idx % nc;
-            Vs[j * KROW + e] = Vg[(size_t)e * a.stride + c0 + j];
-        }
+        for (int idx = tid; idx < DH * 64; idx += kValuThreads)
+            for (int j = idx & 63; j < nc; j += 64) Vs[j * KROW + (idx >> 6)] = Vg[(size_t)(idx >> 6) * a.stride + c0 + j];
         if (last) {
             for (int idx = tid; idx < a.m * half; idx += kValuThreads) {
                 const int t = idx / half, i = idx % half;
@@ -381,15 +385,18 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
                 qs[rr * DH + i + half] = (x * sn + y * c) * a.scale;
             }
             __syncthreads();
-            for (int p = tid; p < nr * nk; p += kValuThreads) {
-                const int rr = p / nk, j = p % nk, t = (r0 + rr) / G;
+            // four lanes per (row, key): with few rows and keys most threads would otherwise watch one do a whole dot product
+            for (int p = tid; p < nr * nk * 4; p += kValuThreads) {
+                const int pair = p >> 2, rr = pair / nk, j = pair - rr * nk, t = (r0 + rr) / G, e0 = (p & 3) * (DH / 4);
                 float acc = 0.f;
-                const KVT *kr = Ks + j * KROW;
-                const float *qr = qs + rr * DH;
-#pragma unroll 8
-                for (int e = 0; e < DH; ++e) acc += qr[e] * kv_to_f32<KVT>(kr[e]);
+                const KVT *kr = Ks + j * KROW + e0;
+                const float *qr = qs + rr * DH + e0;
+#pragma unroll
+                for (int e = 0; e < DH / 4; ++e) acc += qr[e] * kv_to_f32<KVT>(kr[e]);
+                acc += __shfl_xor(acc, 1);
+                acc += __shfl_xor(acc, 2);
                 if (j >= nc && j - nc > t) acc = -INFINITY;     // causal mask among the call's own rows
-                sc[rr * MAXK + j] = acc;
+                if ((p & 3) == 0) sc[rr * MAXK + j] = acc;
             }
             __syncthreads();
             for (int rr = wave; rr < nr; rr += kValuThreads / 64) {
@@ -410,10 +417,29 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
                 }
             }
             __syncthreads();
+            // the keys of an output are dealt to as many threads as there are to spare, added up in thread order
+            int parts = kValuThreads / (nr * DH);
+            parts = parts > 8 ? 8 : parts < 1 ? 1 : parts;
+            float *red = st + kValuMaxRows * 2;                 // [kValuThreads], parts > 1 only
+            if (parts > 1 && tid < parts * nr * DH) {
+                const int part = tid / (nr * DH), o = tid - part * (nr * DH), rr = o / DH, e = o % DH;
+                float acc = 0.f;
+                for (int j = part; j < nk; j += parts) acc += sc[rr * MAXK + j] * kv_to_f32<KVT>(Vs[j * KROW + e]);
+                red[tid] = acc;
+            }
+            if (parts > 1) __syncthreads();
             for (int idx = tid; idx < nr * DH; idx += kValuThreads) {
                 const int rr = idx / DH, e = idx % DH;
                 float acc = 0.f;
-                for (int j = 0; j < nk; ++j) acc += sc[rr * MAXK + j] * kv_to_f32<KVT>(Vs[j * KROW + e]);
+                if (parts > 1)
+                    for (int p = 0; p < parts; ++p) acc += red[p * nr * DH + idx];
+                else
+                    for (int j = 0; j < nk; ++j) acc += sc[rr * MAXK + j] * kv_to_f32<KVT>(Vs[j * KROW + e]);
+                if (a.S == 1) {                             // nothing to fold: the output itself, packed for the Wo GEMM
+                    const int r = r0 + rr, t = r / G;
+                    store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + r % G) * DH + e, t, acc / st[rr * 2 + 1]);
+                    continue;
+                }
                 float *pr = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
                 pr[e] = acc;
                 if (e == 0) {
@@ -442,7 +468,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // launchers
 // ---------------------------------------------------------------------------------------------------
 constexpr size_t valu_lds_bytes(size_t kv_elem, int dh) {
-    return (size_t)kValuMaxRows * dh * 4 + (size_t)kValuMaxRows * valu_max_keys(kv_elem, dh) * 4 + kValuMaxRows * 2 * 4 + 16 +
+    return (size_t)kValuMaxRows * dh * 4 + (size_t)kValuMaxRows * valu_max_keys(kv_elem, dh) * 4 + kValuMaxRows * 2 * 4 + kValuThreads * 4 +
            2 * (size_t)valu_max_keys(kv_elem, dh) * (dh + 16 / kv_elem) * kv_elem;
 }
 
@@ -489,11 +515,14 @@ static int launch_dec(const AttnArgs &a, const LaunchCtx &c) {
 
 // Positions per item for a stand-alone launch, k times the smallest item: one item per compute unit if k = 4 is enough for
 // that, else two.  (An item that shares its compute unit runs slower, but a chain of many blocks is longer still.)
+// Contexts up to two items' length get one item per kv head, which writes the attention output itself: 8B shape, 4 rows,
+// context 100 100.7 -> 97.3 us, 200 99.7 -> 97.6 (three items in one: 99.6 -> 98.9 with 4 rows, 110.8 -> 115.8 with 8).
 // Measured, layer step: 8B shape, 1 row, context 9203: k = 3 (192 items) 100.7 us, k = 2 (288) 103.2, k = 1 (576) 107.5;
 // 13B shape (40 kv heads), 1 row, context 4096: k = 3 (440 items) 143.2 us, k = 5 (280) 149.7, k = 2 (640) 147.1.
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg) {
     const int c = attn_chunk(kv_elem, dh);
     if (kv_elem == kElemF32) return c;
+    if (pos0 <= 2 * c) return pos0 <= c ? c : 2 * c;       // one item per kv head: nothing to fold, one kernel less
     auto items = [&](int k) { return (long)n_kv_heads * ((pos0 + (long)k * c - 1) / ((long)k * c)); };
     for (int k = 1; k <= 4; ++k)
         if (items(k) <= n_wg) return k * c;
@@ -516,7 +545,7 @@ int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
         else if (a.dh == 64) rc = launch_valu<float, 64>(a, c);
         else return (int)hipErrorInvalidValue;
     }
-    if (rc) return rc;
+    if (rc || a.S == 1) return rc;
     const int rows = a.Hq * a.m;
     hipLaunchKernelGGL(k_attn_combine, dim3((rows + 3) / 4), dim3(256), 0, (hipStream_t)c.stream, a);
     return (int)hipGetLastError();

@@ -160,7 +160,7 @@ struct EmbedArgs {
 
 // Scratch of a draw or a sampled verification: per-segment statistics of its rows.  The model's vocabulary partials serve (free
 // between head evaluations).
-constexpr size_t kSampleScratchBytes = 32768;
+constexpr size_t kSampleScratchBytes = 131072;
 
 // Sampled decoding (Sec. 2.2).  inv_t = 1 / temperature; u, u_accept, u_resample, u_final are uniform draws in [0, 1).
 struct SampleArgs {

@@ -20,7 +20,7 @@ namespace ad {
 
 namespace {
 
-constexpr int kSampleThreads = 256;
+constexpr int kSampleThreads = 512;              // measured against 256 and 1024: 8 rows of 128256 logits 46.7, 51.8, 51.3 us a call
 constexpr int kSampleWaves = kSampleThreads / 64;
 constexpr int kSegIds = 2048;                    // ids per segment, until there are as many segments as a workgroup has threads
 
@@ -85,31 +85,47 @@ template <class W>
 __device__ __forceinline__ int sample_segments(W w, const SegStat *seg, float mx, float inv_t, int V, int n_seg, int seg_ids, float u, SampleLds &L,
                                                float *w_tok, float *total_out) {
     const int tid = threadIdx.x;
-    const float mine = tid < n_seg ? rescaled(seg[tid], mx, inv_t) : 0.f;
-    float total;
-    const float before = block_exclusive_scan(mine, L, &total);
+    float total, target;
+    int s = 0;
     if (tid == 0) {
         L.best = 0x7fffffff;
         L.last_pos = -1;
+        L.bcast[1] = 0.f;
     }
-    __syncthreads();
-    const float target = u * total;
-    if (mine > 0.f && before + mine > target) atomicMin(&L.best, tid);
-    __syncthreads();
-    const int s = L.best;
-    if (s != 0x7fffffff && tid == s) L.bcast[1] = before;
-    __syncthreads();
+    if (n_seg == 1) {
+        total = rescaled(seg[0], mx, inv_t);
+        target = u * total;
+        if (!(total > target)) s = 0x7fffffff;
+        __syncthreads();
+    } else {
+        const float mine = tid < n_seg ? rescaled(seg[tid], mx, inv_t) : 0.f;
+        const float before = block_exclusive_scan(mine, L, &total);
+        target = u * total;
+        if (mine > 0.f && before + mine > target) atomicMin(&L.best, tid);
+        __syncthreads();
+        s = L.best;
+        if (s != 0x7fffffff && tid == s) L.bcast[1] = before;
+        __syncthreads();
+    }
     int tok = -1;
     if (s != 0x7fffffff) {
         // walk the segment: thread t owns consecutive ids, added up in id order
         const int per = (seg_ids + kSampleThreads - 1) / kSampleThreads;
         const int end = min(V, (s + 1) * seg_ids), j0 = min(end, s * seg_ids + tid * per), j1 = min(end, j0 + per);
-        float local = 0.f;
+        constexpr int kKeep = kSegIds / kSampleThreads;      // weights that are kept (longer segments form them again)
+        float x[kKeep], local = 0.f;
         int last = -1;
-        for (int j = j0; j < j1; ++j) {
-            const float x = w(j);
-            local += x;
-            if (x > 0.f) last = j;
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) x[i] = j0 + i < j1 ? w(j0 + i) : 0.f;
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) {
+            local += x[i];
+            if (x[i] > 0.f) last = j0 + i;
+        }
+        for (int j = j0 + kKeep; j < j1; ++j) {
+            const float y = w(j);
+            local += y;
+            if (y > 0.f) last = j;
         }
         float seg_total;
         const float at = L.bcast[1] + block_exclusive_scan(local, L, &seg_total);
@@ -117,14 +133,18 @@ __device__ __forceinline__ int sample_segments(W w, const SegStat *seg, float mx
         __syncthreads();
         if (at + local > target || at > target) {
             float c = at;
-            for (int j = j0; j < j1; ++j) {
-                const float x = w(j);
-                c += x;
-                if (c > target && x > 0.f) {
-                    atomicMin(&L.best, j);
-                    break;
-                }
+            int hit = 0x7fffffff;
+#pragma unroll
+            for (int i = 0; i < kKeep; ++i) {
+                c += x[i];
+                if (c > target && x[i] > 0.f && hit == 0x7fffffff) hit = j0 + i;
             }
+            for (int j = j0 + kKeep; j < j1 && hit == 0x7fffffff; ++j) {
+                const float y = w(j);
+                c += y;
+                if (c > target && y > 0.f) hit = j;
+            }
+            if (hit != 0x7fffffff) atomicMin(&L.best, hit);
         }
         if (last >= 0) atomicMax(&L.last_pos, last);
         __syncthreads();
@@ -163,29 +183,43 @@ struct ResidualWeight {
     const float *zf, *zq; float mf, lsf, mq, lsq, inv_t, c;
     __device__ __forceinline__ float log_p(int j) const { return (zf[j] - mf) * inv_t - lsf; }
     __device__ __forceinline__ float log_q(int j) const { return (zq[j] - mq) * inv_t - lsq; }
-    __device__ __forceinline__ float operator()(int j) const {
-        const float a = log_p(j), b = log_q(j);
-        return a > b ? expf(a - c) * -expm1f(b - a) : 0.f;
-    }
+    __device__ __forceinline__ float weight(float a, float b) const { return a > b ? expf(a - c) * -expm1f(b - a) : 0.f; }
+    __device__ __forceinline__ float operator()(int j) const { return weight(log_p(j), log_q(j)); }
 };
 
-// Statistics of segment blockIdx.x of row blockIdx.y: rows [0, n_first) start at z0, the others at z1.
+// Statistics of the ids [j0, j1) of a row, to every thread
+__device__ __forceinline__ SegStat segment_stat(const float *z, int j0, int j1, float inv_t, SampleLds &L) {
+    constexpr int kKeep = kSegIds / kSampleThreads;          // values that are kept (longer segments read them again)
+    float v[kKeep], m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int j = j0 + (int)threadIdx.x + i * kSampleThreads;
+        v[i] = j < j1 ? z[j] : -INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) m = fmaxf(m, v[i]);
+    for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) m = fmaxf(m, z[j]);
+    m = block_max(m, L);
+    float s = 0.f;
+    if (m != -INFINITY) {
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) s += expf((v[i] - m) * inv_t);
+        for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) s += expf((z[j] - m) * inv_t);
+    }
+    float total;
+    (void)block_exclusive_scan(s, L, &total);
+    return SegStat{m, total};
+}
+
+// Segment blockIdx.x of row blockIdx.y: rows [0, n_first) start at z0, the others at z1.
 struct SegArgs { const float *z0, *z1; int n_first, V, n_seg, seg_ids; float inv_t; SegStat *out; };
 
 __global__ void __launch_bounds__(kSampleThreads) k_segment_stats(SegArgs a) {
     __shared__ SampleLds L;
-    const int r = blockIdx.y, tid = threadIdx.x;
+    const int r = blockIdx.y, j0 = blockIdx.x * a.seg_ids;
     const float *z = r < a.n_first ? a.z0 + (size_t)r * a.V : a.z1 + (size_t)(r - a.n_first) * a.V;
-    const int j0 = blockIdx.x * a.seg_ids, j1 = min(a.V, j0 + a.seg_ids);
-    float m = -INFINITY;
-    for (int j = j0 + tid; j < j1; j += kSampleThreads) m = fmaxf(m, z[j]);
-    m = block_max(m, L);
-    float s = 0.f;
-    if (m != -INFINITY)
-        for (int j = j0 + tid; j < j1; j += kSampleThreads) s += expf((z[j] - m) * a.inv_t);
-    float total;
-    (void)block_exclusive_scan(s, L, &total);
-    if (tid == 0) a.out[(size_t)r * a.n_seg + blockIdx.x] = SegStat{m, total};
+    const SegStat st = segment_stat(z, j0, min(a.V, j0 + a.seg_ids), a.inv_t, L);
+    if (threadIdx.x == 0) a.out[(size_t)r * a.n_seg + blockIdx.x] = st;
 }
 
 // (max z, sum exp((z - max) * inv_t)) of a row from its segments, by one wavefront, to all its lanes
@@ -206,8 +240,16 @@ __device__ __forceinline__ SegStat row_from_segments(const SegStat *seg, int n_s
     return SegStat{m, s};
 }
 
+// seg: the segments' statistics, or null for a row of one segment, whose statistics are formed here (one kernel less)
 __global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, const SegStat *seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
+    __shared__ SegStat only;
+    if (!seg) {
+        const SegStat st = segment_stat(a.z, 0, a.V, a.inv_t, L);
+        if (threadIdx.x == 0) only = st;
+        __syncthreads();
+        seg = &only;
+    }
     const float mx = block_max((int)threadIdx.x < n_seg ? seg[threadIdx.x].mx : -INFINITY, L);
     float w_tok, total;
     const int tok = sample_segments(SoftmaxWeight{a.z, mx, a.inv_t}, seg, mx, a.inv_t, a.V, n_seg, seg_ids, a.u, L, &w_tok, &total);
@@ -217,42 +259,81 @@ __global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, con
     }
 }
 
+// The same of up to two rows of one segment, straight from their logits (all loads go out before either row is reduced).
+__device__ __forceinline__ void rows_from_logits(const float *z0, const float *z1, int V, float inv_t, SegStat &s0, SegStat &s1) {
+    constexpr int N = kSegIds / 64;
+    const int lane = threadIdx.x & 63;
+    float v[2][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[0][i] = lane + 64 * i < V ? z0[lane + 64 * i] : -INFINITY;
+        v[1][i] = z1 && lane + 64 * i < V ? z1[lane + 64 * i] : -INFINITY;
+    }
+    SegStat out[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < N; ++i) m = fmaxf(m, v[r][i]);
+        m = wave_max(m);
+        float s = 0.f;
+        if (m != -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) s += expf((v[r][i] - m) * inv_t);
+        }
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        out[r] = SegStat{m, s};
+    }
+    s0 = out[0];
+    s1 = out[1];
+}
+
 // Eq. 2 over the drafts, computed by every workgroup that needs the outcome (the same sums in the same order).
 struct Decision { int n_acc, rejected; SegStat f, q; };      // of row n_acc: statistics of its final and draft logits
 
 __device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const SegStat *seg, int n_seg, bool write_ratio) {
-    __shared__ SegStat row[15];
-    __shared__ int s_nacc, s_rejected;
+    __shared__ SegStat row[16];
+    __shared__ int s_rejected;                       // the first rejected draft, n_draft if none is
     const int wave = threadIdx.x >> 6, n_draft = a.m - 1;
-    for (int r = wave; r < 2 * a.m - 1; r += kSampleWaves) {
-        const SegStat st = row_from_segments(seg + (size_t)r * n_seg, n_seg, a.inv_t);
-        if ((threadIdx.x & 63) == 0) row[r] = st;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int nacc = n_draft, rejected = 0;
-        for (int k = 0; k < n_draft; ++k) {
-            float ratio = 0.f;
-            if (!rejected) {
-                const int t = a.draft[k];
-                // p*(t) / p_draft(t) through the logarithms, so that two tiny probabilities still have a ratio
-                const float lp = (a.zf[(size_t)k * a.V + t] - row[k].mx) * a.inv_t - logf(row[k].sum);
-                const float lq = (a.zq[(size_t)k * a.V + t] - row[a.m + k].mx) * a.inv_t - logf(row[a.m + k].sum);
-                ratio = expf(lp - lq);
-                if (!(a.u_accept[k] < fminf(1.0f, ratio))) {
-                    rejected = 1;
-                    nacc = k;
-                }
-            }
-            if (write_ratio && a.ratio_out) a.ratio_out[k] = ratio;
+    const int n_rows = 2 * a.m - 1;
+    if (seg) {
+        for (int r = wave; r < n_rows; r += kSampleWaves) {
+            const SegStat st = row_from_segments(seg + (size_t)r * n_seg, n_seg, a.inv_t);
+            if ((threadIdx.x & 63) == 0) row[r] = st;
         }
-        s_nacc = nacc;
-        s_rejected = rejected;
+    } else if (wave < n_rows) {
+        static_assert(2 * kSampleWaves >= 15, "two rows per wavefront are all there are");
+        auto logits = [&](int r) { return r < a.m ? a.zf + (size_t)r * a.V : a.zq + (size_t)(r - a.m) * a.V; };
+        const int r1 = wave + kSampleWaves;
+        SegStat s0, s1;
+        rows_from_logits(logits(wave), r1 < n_rows ? logits(r1) : nullptr, a.V, a.inv_t, s0, s1);
+        if ((threadIdx.x & 63) == 0) {
+            row[wave] = s0;
+            if (r1 < n_rows) row[r1] = s1;
+        }
+    }
+    // a lane per draft
+    const int k = threadIdx.x, t = k < n_draft ? a.draft[k] : 0;
+    const float zf = k < n_draft ? a.zf[(size_t)k * a.V + t] : 0.f, zq = k < n_draft ? a.zq[(size_t)k * a.V + t] : 0.f;
+    __syncthreads();
+    if (wave == 0) {
+        float ratio = 0.f;
+        bool rejected = false;
+        if (k < n_draft) {
+            // p*(t) / p_draft(t) through the logarithms, so that two tiny probabilities still have a ratio
+            const float lp = (zf - row[k].mx) * a.inv_t - logf(row[k].sum), lq = (zq - row[a.m + k].mx) * a.inv_t - logf(row[a.m + k].sum);
+            ratio = expf(lp - lq);
+            rejected = !(a.u_accept[k] < fminf(1.0f, ratio));
+        }
+        const unsigned long long mask = __ballot(rejected);
+        const int first = mask ? __ffsll(mask) - 1 : n_draft;
+        if (k == 0) s_rejected = first;
+        if (write_ratio && a.ratio_out && k < n_draft) a.ratio_out[k] = k <= first ? ratio : 0.f;
     }
     __syncthreads();
     Decision d;
-    d.n_acc = s_nacc;
-    d.rejected = s_rejected;
+    d.n_acc = s_rejected;
+    d.rejected = s_rejected < n_draft;
     d.f = row[d.n_acc];
     d.q = d.rejected ? row[a.m + d.n_acc] : SegStat{0.f, 0.f};
     return d;
@@ -262,41 +343,75 @@ __device__ __forceinline__ ResidualWeight residual_of(const VerifySampledArgs &a
     return ResidualWeight{a.zf + (size_t)d.n_acc * a.V, a.zq + (size_t)d.n_acc * a.V, d.f.mx, logf(d.f.sum), d.q.mx, logf(d.q.sum), a.inv_t, 0.f};
 }
 
-// The residual's segments if a draft was rejected: (largest log p* where p* exceeds p_draft, sum of the weights relative to it).
+// Statistics of the ids [j0, j1) of the residual: (largest log p* where p* exceeds p_draft, sum of the weights relative to
+// it), to every thread.
+__device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j1, SampleLds &L) {
+    constexpr int kKeep = kSegIds / kSampleThreads;          // ids whose log-probabilities are kept (longer segments form them again)
+    float la[kKeep], lb[kKeep], c = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int j = j0 + (int)threadIdx.x + i * kSampleThreads;
+        la[i] = j < j1 ? w.log_p(j) : -INFINITY;
+        lb[i] = j < j1 ? w.log_q(j) : -INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (la[i] > lb[i]) c = fmaxf(c, la[i]);
+    for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) {
+        const float a = w.log_p(j);
+        if (a > w.log_q(j)) c = fmaxf(c, a);
+    }
+    w.c = block_max(c, L);
+    float s = 0.f;
+    if (w.c != -INFINITY) {
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) s += w.weight(la[i], lb[i]);
+        for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) s += w(j);
+    }
+    float total;
+    (void)block_exclusive_scan(s, L, &total);
+    return SegStat{w.c, total};
+}
+
+// The residual's segments, if a draft was rejected.
 __global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out) {
     __shared__ SampleLds L;
     const Decision d = decide(a, seg, n_seg, false);
     if (!d.rejected) return;
-    ResidualWeight w = residual_of(a, d);
-    const int j0 = blockIdx.x * seg_ids, j1 = min(a.V, j0 + seg_ids);
-    float c = -INFINITY;
-    for (int j = j0 + threadIdx.x; j < j1; j += kSampleThreads) {
-        const float la = w.log_p(j);
-        if (la > w.log_q(j)) c = fmaxf(c, la);
-    }
-    w.c = block_max(c, L);
-    float s = 0.f;
-    if (w.c != -INFINITY)
-        for (int j = j0 + threadIdx.x; j < j1; j += kSampleThreads) s += w(j);
-    float total;
-    (void)block_exclusive_scan(s, L, &total);
-    if (threadIdx.x == 0) out[blockIdx.x] = SegStat{w.c, total};
+    const int j0 = blockIdx.x * seg_ids;
+    const SegStat st = residual_stat(residual_of(a, d), j0, min(a.V, j0 + seg_ids), L);
+    if (threadIdx.x == 0) out[blockIdx.x] = st;
 }
 
+// seg, res_seg: null for rows of one segment, whose statistics are formed here (this kernel is then the only one)
 __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
+    __shared__ SegStat only;
     const Decision d = decide(a, seg, n_seg, true);
     const int r = d.n_acc;
     int tok = -1;
     float w_tok, total;
     if (d.rejected) {
         ResidualWeight w = residual_of(a, d);
+        if (!res_seg) {
+            const SegStat st = residual_stat(w, 0, a.V, L);
+            if (threadIdx.x == 0) only = st;
+            __syncthreads();
+            res_seg = &only;
+        }
         w.c = block_max((int)threadIdx.x < n_seg ? res_seg[threadIdx.x].mx : -INFINITY, L);
         if (w.c != -INFINITY) tok = sample_segments(w, res_seg, w.c, 1.0f, a.V, n_seg, seg_ids, a.u_resample[r], L, &w_tok, &total);
         __syncthreads();
     }
+    const SegStat *row_seg = seg + (size_t)r * n_seg;
+    if (!seg) {
+        __syncthreads();
+        if (threadIdx.x == 0) only = d.f;
+        __syncthreads();
+        row_seg = &only;
+    }
     if (tok < 0)       // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
-        tok = sample_segments(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, seg + (size_t)r * n_seg, d.f.mx, a.inv_t, a.V, n_seg, seg_ids,
+        tok = sample_segments(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, row_seg, d.f.mx, a.inv_t, a.V, n_seg, seg_ids,
                               d.rejected ? a.u_resample[r] : a.u_final, L, &w_tok, &total);
     if (threadIdx.x == 0) {
         *a.n_accept_out = r;
@@ -319,8 +434,8 @@ int launch_sample_row(const SampleArgs &a, void *stream) {
     if (a.V < 1 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    SegStat *seg = (SegStat *)a.scratch;
-    hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 1), dim3(kSampleThreads), 0, (hipStream_t)stream,
+    SegStat *seg = n_seg > 1 ? (SegStat *)a.scratch : nullptr;
+    if (seg) hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 1), dim3(kSampleThreads), 0, (hipStream_t)stream,
                        SegArgs{a.z, nullptr, 1, a.V, n_seg, seg_ids, a.inv_t, seg});
     const int rc = (int)hipGetLastError();
     if (rc) return rc;
@@ -334,14 +449,18 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
         if (a.draft[k] < 0 || a.draft[k] >= a.V) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    SegStat *seg = (SegStat *)a.scratch, *res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
+    SegStat *seg = nullptr, *res_seg = nullptr;
     const dim3 wg(kSampleThreads);
-    hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
-    int rc = (int)hipGetLastError();
-    if (rc) return rc;
-    if (a.m > 1) {
-        hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
+    int rc;
+    if (n_seg > 1) {
+        seg = (SegStat *)a.scratch;
+        res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
+        hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
         if ((rc = (int)hipGetLastError())) return rc;
+        if (a.m > 1) {
+            hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
+            if ((rc = (int)hipGetLastError())) return rc;
+        }
     }
     hipLaunchKernelGGL(k_verify_sampled, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
     return (int)hipGetLastError();
