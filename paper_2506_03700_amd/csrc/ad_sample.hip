@@ -259,33 +259,22 @@ __global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, con
     }
 }
 
-// The same of up to two rows of one segment, straight from their logits (all loads go out before either row is reduced).
-__device__ __forceinline__ void rows_from_logits(const float *z0, const float *z1, int V, float inv_t, SegStat &s0, SegStat &s1) {
-    constexpr int N = kSegIds / 64;
+// The same of a row of one segment, straight from its logits.
+__device__ __forceinline__ SegStat row_from_logits(const float *z, int V, float inv_t) {
     const int lane = threadIdx.x & 63;
-    float v[2][N];
+    float v[kSegIds / 64], m = -INFINITY, s = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        v[0][i] = lane + 64 * i < V ? z0[lane + 64 * i] : -INFINITY;
-        v[1][i] = z1 && lane + 64 * i < V ? z1[lane + 64 * i] : -INFINITY;
+    for (int i = 0; i < kSegIds / 64; ++i) {
+        v[i] = lane + 64 * i < V ? z[lane + 64 * i] : -INFINITY;
+        m = fmaxf(m, v[i]);
     }
-    SegStat out[2];
+    m = wave_max(m);
+    if (m != -INFINITY) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        float m = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < N; ++i) m = fmaxf(m, v[r][i]);
-        m = wave_max(m);
-        float s = 0.f;
-        if (m != -INFINITY) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) s += expf((v[r][i] - m) * inv_t);
-        }
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        out[r] = SegStat{m, s};
+        for (int i = 0; i < kSegIds / 64; ++i) s += expf((v[i] - m) * inv_t);
     }
-    s0 = out[0];
-    s1 = out[1];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    return SegStat{m, s};
 }
 
 // Eq. 2 over the drafts, computed by every workgroup that needs the outcome (the same sums in the same order).
@@ -301,16 +290,10 @@ __device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const Seg
             const SegStat st = row_from_segments(seg + (size_t)r * n_seg, n_seg, a.inv_t);
             if ((threadIdx.x & 63) == 0) row[r] = st;
         }
-    } else if (wave < n_rows) {
-        static_assert(2 * kSampleWaves >= 15, "two rows per wavefront are all there are");
-        auto logits = [&](int r) { return r < a.m ? a.zf + (size_t)r * a.V : a.zq + (size_t)(r - a.m) * a.V; };
-        const int r1 = wave + kSampleWaves;
-        SegStat s0, s1;
-        rows_from_logits(logits(wave), r1 < n_rows ? logits(r1) : nullptr, a.V, a.inv_t, s0, s1);
-        if ((threadIdx.x & 63) == 0) {
-            row[wave] = s0;
-            if (r1 < n_rows) row[r1] = s1;
-        }
+    } else if (wave < n_rows) {                      // (at most a row per wavefront)
+        const int r = wave;
+        const SegStat st = row_from_logits(r < a.m ? a.zf + (size_t)r * a.V : a.zq + (size_t)(r - a.m) * a.V, a.V, a.inv_t);
+        if ((threadIdx.x & 63) == 0) row[r] = st;
     }
     // a lane per draft
     const int k = threadIdx.x, t = k < n_draft ? a.draft[k] : 0;
@@ -383,7 +366,7 @@ __global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySamp
     if (threadIdx.x == 0) out[blockIdx.x] = st;
 }
 
-// seg, res_seg: null for rows of one segment, whose statistics are formed here (this kernel is then the only one)
+// seg, res_seg: null where the statistics of rows of one segment, of their residual, are formed here
 __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
     __shared__ SegStat only;
@@ -452,15 +435,17 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     SegStat *seg = nullptr, *res_seg = nullptr;
     const dim3 wg(kSampleThreads);
     int rc;
-    if (n_seg > 1) {
+    // rows of one segment: up to as many as a workgroup has wavefronts are cheaper to reduce in the last kernel than in one of
+    // their own (2048 logits, 3 rows: 33.6 against 35.4 us a call), and the residual always is
+    if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
-        res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
         hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
         if ((rc = (int)hipGetLastError())) return rc;
-        if (a.m > 1) {
-            hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
-            if ((rc = (int)hipGetLastError())) return rc;
-        }
+    }
+    if (n_seg > 1 && a.m > 1) {
+        res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
+        hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
+        if ((rc = (int)hipGetLastError())) return rc;
     }
     hipLaunchKernelGGL(k_verify_sampled, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
     return (int)hipGetLastError();
