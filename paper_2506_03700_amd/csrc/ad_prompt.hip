@@ -446,17 +446,19 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// attention: one workgroup per kv head and 128 query rows (row r = token r / G, head r % G of the group)
+// attention: one workgroup per kv head and 64 query rows (row r = token r / G, head r % G of the group)
 // ---------------------------------------------------------------------------------------------------
 // The products are those of the decode kernel (ad_attention_device.h): S^T = K q^T with the rows of the two score tiles
 // assigned to keys so that a lane ends up with 8 consecutive keys of its query row, which is the B operand layout of
-// O^T = V^T P^T; queries and probabilities are split hi/lo.  A wavefront holds 32 query rows; the workgroup's four
-// wavefronts share the K and V tiles of 32 positions, staged in LDS one block ahead, and run the softmax online.
-constexpr int kPromptAttnRows = 128;
+// O^T = V^T P^T; queries and probabilities are split hi/lo.  A wavefront holds 16 query rows; the workgroup's four
+// wavefronts share the K and V tiles of 32 positions, staged in LDS one block ahead, and run the softmax online.  Bound by
+// the chain through a block (scores, softmax, second product) more than by its arithmetic: 16 rows a wavefront and twice
+// the workgroups beat 32, 8B shape, 1024 tokens 45.1 against 55.7 us, 128 tokens 8.9 / 12.0, 1024 after 7168 313 / 354.
+constexpr int kPromptAttnRows = 64;
 
 template <int DH, bool F16>
 __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
-    constexpr int KS = DH / 32, DT = DH / 16, RT = 2;
+    constexpr int KS = DH / 32, DT = DH / 16, RT = kPromptAttnRows / 64;
     constexpr int KU = 2 * KS * 64, VU = DT * 64, NL = (KU + VU) / 256;
     __shared__ bf16x8 lds[2][KU + VU];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, gq = lane >> 4;
