@@ -93,6 +93,7 @@ static int launch_one(const GemmArgs &g, int grid, hipStream_t s) {
 // 16-bit weights: the instance whose B registers cover the wavefront's K slice (d_model <= 4096, <= 6144, <= 8192)
 template <bool F16>
 static int stationary16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
+    if (nks <= 8) return launch_one<1, GEMM_STATIONARY, 1, F16>(g, grid, s);
     if (nks <= 16) return launch_one<1, GEMM_STATIONARY, 2, F16>(g, grid, s);
     if (nks <= 24) return launch_one<1, GEMM_STATIONARY, 3, F16>(g, grid, s);
     return launch_one<1, GEMM_STATIONARY, kKsMaxWide / 4, F16>(g, grid, s);
@@ -108,7 +109,7 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     if (g.mode == GEMM_STATIONARY) {
         const int nks = (g.KT + kStatWaves - 1) / kStatWaves;     // most k-steps of a wavefront
         if (nks > (planes == 1 ? kKsMaxWide : kKsMax) || g.K < 8) return (int)hipErrorInvalidValue;
-        if (planes != 1) rc = launch_one<3, GEMM_STATIONARY, kKsMax / 2>(g, grid, s);
+        if (planes != 1) rc = nks <= 2 ? launch_one<3, GEMM_STATIONARY, 1>(g, grid, s) : launch_one<3, GEMM_STATIONARY, kKsMax / 2>(g, grid, s);
         else if (f16) rc = stationary16<true>(g, nks, grid, s);
         else rc = stationary16<false>(g, nks, grid, s);
     } else {
@@ -116,7 +117,7 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
         else rc = f16 ? launch_one<1, GEMM_STREAMED, 0, true>(g, grid, s) : launch_one<1, GEMM_STREAMED, 0>(g, grid, s);
     }
     if (rc) return rc;
-    if (g.epi == EPI_HEAD) {
+    if (g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag)) {       // (the logits alone need no reduction)
         GemmArgs h = g;
         h.n_parts = grid;
         hipLaunchKernelGGL(k_head_combine, dim3(1), dim3(512), 0, s, h);
