@@ -95,6 +95,7 @@ __device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
 template <bool F16>
 __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo) {
     if constexpr (F16) {
+        asm("" : "+v"(x));        // rounded to fp32 first, see split16
         hi = f32_to_f16_bits(x);
         lo = f32_to_f16_bits(x - f16_bits_to_f32(hi));
     } else {
