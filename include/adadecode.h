@@ -249,7 +249,8 @@ ad_status ad_generate(const ad_model *, ad_kv *, const int32_t *prompt, int32_t 
 /* ---- measurement ------------------------------------------------------------------------------------
  * Samples one of the library's two big kernels: AD_PROF_GEMM, the weight-streaming GEMM kernel (the vocabulary
  * pass of Eq. 1 / Eq. 2, and every projection of the layer step in AD_LAYER_KERNELS mode), or AD_PROF_LAYER,
- * the fused layer-step kernel (AD_LAYER_FUSED mode).  Every `period`-th launch of that kind is bracketed by a
+ * the fused layer-step kernel (AD_LAYER_FUSED mode); the prompt pass of ad_generate runs kernels of its own, which are
+ * neither counted nor sampled.  Every `period`-th launch of that kind is bracketed by a
  * pair of events on the launch stream.  ad_profile_stop synchronises, and reports the number of launches
  * seen, the number sampled, the summed duration of the sampled launches and the bytes those launches had to
  * move (GEMM: rows x inputs x element size of the matrix; layer step: its weights, the KV rows read and the KV

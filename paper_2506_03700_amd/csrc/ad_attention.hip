@@ -11,7 +11,8 @@
 // the causal mask).  All G*m query rows of the group are processed against each K/V element while it is in
 // registers or LDS, so the cache is read once.  An item writes one unnormalised partial (o[dh], max, sum)
 // per query row; a second, small kernel folds the partials of each row in split order (fixed order:
-// results are reproducible) and packs the result as the activation block of the Wo GEMM.  There is no
+// results are reproducible) and packs the result as the activation block of the Wo GEMM; an item that is its head's
+// only one writes that block itself.  There is no
 // fence or atomic inside either kernel: the kernel boundary orders them.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
