@@ -189,14 +189,14 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
                 }
                 bm = fmaxf(bm, __shfl_xor(bm, 16));
                 bm = fmaxf(bm, __shfl_xor(bm, 32));
-                const float nm = fmaxf(mx[i], bm);          // finite: every row sees the first key of every block it is given
-                const float alpha = __expf(mx[i] - nm);
+                const float nm = fmaxf(mx[i], bm), ref = softmax_ref(nm);
+                const float alpha = __expf(mx[i] - ref);
                 mx[i] = nm;
                 float add = 0.f;
                 u16x8 h8, l8;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    const float p = __expf(w[c] - nm);
+                    const float p = __expf(w[c] - ref);
                     add += p;
                     uint16_t hi, lo;
                     split16<F16>(p * kPScale, hi, lo);
@@ -283,9 +283,10 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
                     x[w] = *(const f32x2 *)&L.part[w][rr][e];
                     M = fmaxf(M, mp[w]);
                 }
+                const float ref = softmax_ref(M);
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
-                    const float f = __expf(mp[w] - M);      // a wavefront without keys: exp(-inf) = 0, of sums that are 0
+                    const float f = __expf(mp[w] - ref);    // a wavefront without keys: exp(-inf) = 0, of sums that are 0
                     den += f * sm[w];
                     num[0] += f * x[w][0];
                     num[1] += f * x[w][1];

@@ -91,6 +91,10 @@ __device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
     lo = to16<F16>(v - from16<F16>(hi));
 }
 
+// The value that scores are taken relative to in a softmax: their maximum m, or 0 where every score so far is minus
+// infinity (a key whose entry in the cache overflowed): exp(-inf - 0) gives such keys the weight 0, exp(-inf - m) is not a number.
+__device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 // x = hi + lo with hi, lo in the 16-bit type (F16: half precision, else bf16)
 template <bool F16>
 __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo) {

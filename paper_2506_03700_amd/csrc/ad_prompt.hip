@@ -555,14 +555,14 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
                 }
                 bm = fmaxf(bm, __shfl_xor(bm, 16));
                 bm = fmaxf(bm, __shfl_xor(bm, 32));
-                const float nm = fmaxf(mx[i], bm);               // finite: every row sees position 0, which is in block 0
-                const float alpha = __expf(mx[i] - nm);
+                const float nm = fmaxf(mx[i], bm), ref = softmax_ref(nm);
+                const float alpha = __expf(mx[i] - ref);
                 mx[i] = nm;
                 float add = 0.f;
                 u16x8 h8, l8;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    const float p = __expf(sc[c] - nm);
+                    const float p = __expf(sc[c] - ref);
                     add += p;
                     uint16_t hi, lo;
                     split16<F16>(p * kPScale, hi, lo);
