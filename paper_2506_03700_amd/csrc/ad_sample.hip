@@ -205,6 +205,13 @@ __device__ __forceinline__ SegStat segment_stat(const float *z, int j0, int j1, 
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) s += expf((v[i] - m) * inv_t);
         for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) s += expf((z[j] - m) * inv_t);
+    } else {
+        // nothing but -inf, whose weight is 0, and values that are no numbers (fmaxf passes them by): those stay in the sum
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i)
+            if (v[i] != v[i]) s = v[i];
+        for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads)
+            if (z[j] != z[j]) s = z[j];
     }
     float total;
     (void)block_exclusive_scan(s, L, &total);

@@ -57,3 +57,25 @@ def test_draws_and_verification_at_segment_edges(ad, V):
             r = np.maximum(p - q, 0.0)
             assert nxt == t or r[nxt] > 0 and r[t] / r.sum() < 0.9999
     g.close()
+
+
+@pytest.mark.parametrize("V", [2049, 8192])
+def test_a_segment_that_is_not_a_number_shows(ad, V):
+    """A row's sum is no number if one of its logits is none, also where a whole segment consists of such values."""
+    import torch
+    n_seg = -(-V // 2048)
+    seg = -(-V // n_seg)
+    g = ad.Model(SMALL.with_(vocab=V), synth.make_weights(SMALL.with_(vocab=V), seed=0), max_pos=8)
+    rng = np.random.default_rng(V)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    for s in range(n_seg):
+        for bad in (slice(s * seg, (s + 1) * seg), slice(s * seg, s * seg + 1)):
+            z = rng.standard_normal((3, V)).astype(np.float32)
+            z[0, bad] = np.nan
+            z[0, s * seg + 1] = -np.inf          # and a masked id among them
+            tok, prob = g.ad_sample_logits(dev(z[0]), 0.8, 0.5)
+            assert np.isnan(prob) and tok == np.flatnonzero(np.isfinite(z[0]))[-1]
+            d = V - 1 if s == 0 else 0
+            n, nxt, ratio = g.ad_verify_sampled(dev(z[:2]), dev(z[2:]), [d], 0.8, [0.5], [0.5], 0.5)
+            assert np.isnan(ratio[0])
+    g.close()
