@@ -334,6 +334,15 @@ static size_t prompt_layout(const ad_config &c, int32_t max_pos, char *base, ad_
         p.rows = max_pos < kPromptRows ? (max_pos + kPromptAlign - 1) / kPromptAlign * kPromptAlign : kPromptRows;
         Layout L;
         make_layout(c, L);
+        // activation tiles are addressed with a 32-bit byte offset: fewer rows for the widest inputs (1024 up to 1 048 544), none
+        // where not even one workgroup's tokens fit
+        int64_t widest = L.d > L.dq ? L.d : L.dq;
+        if (L.f > widest) widest = L.f;
+        while (p.rows && prompt_act_bytes(p.rows, widest) >> 32) p.rows -= kPromptAlign;
+        if (!p.rows) {
+            if (pr) *pr = p;
+            return 0;
+        }
         auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += align_up(bytes); return q; };
         p.x = (float *)take((size_t)p.rows * L.d * 4);
         p.scale = (float *)take((size_t)p.rows * 4);

@@ -82,3 +82,26 @@ def test_storage_without_the_scratch_is_a_cache_too(ad):
     g.kv = kv
     follow_up(shape, g, o, synth.make_prompt(shape, 1, 71))
     g.close()
+
+
+def test_activations_of_four_gigabytes(ad):
+    """1024 tokens' inputs to the down projection would take 4.5 GB: fewer tokens to a pass, and the same caches as by layer steps
+    (the last tokens of a pass are the ones whose tiles lie furthest)."""
+    shape = synth.TINY.with_(name="wide-ffn", dtype=synth.BF16, tied_head=False, n_q_heads=1, n_kv_heads=1, d_model=16, d_ffn=1100000, vocab=64,
+                             n_layers=2, exit_layers=())
+    w = synth.make_weights(shape, seed=7)
+    # (the sums over 1.1 million inputs are to show next to the residual, and not to drown it)
+    w["layers.0.w_down"] = synth.store_as(synth.as_f32(w["layers.0.w_down"]) * 20, shape.dtype)
+    n, m = 1024, 8
+    g = ad.Model(shape, w, max_pos=n + 8)
+    prompt = synth.make_prompt(shape, 2, n)
+    g.ad_generate(prompt, 1, 2.0, 0)
+    k, v = g.kv_read(2, n)
+    g.kv_truncate(0)
+    for s in range(0, n, m):
+        h = g.ad_embed(prompt[s:s + m])
+        g.ad_layer_steps(1, 2, h, np.arange(s, s + m))
+    k0, v0 = g.kv_read(2, n)
+    check_kv(shape.dtype, k, k0, "K of layer 2")
+    check_kv(shape.dtype, v, v0, "V of layer 2")
+    g.close()

@@ -58,6 +58,20 @@ def test_size_queries_and_config_checks_without_gpu():
     assert L.ad_kv_truncate(None, 0) == ad.AD_EINVAL
 
 
+@pytest.mark.parametrize("d_ffn,rows", [(64, 1024), (1048544, 1024), (1048552, 896), (1100000, 896), (8388576, 128), (8388608, 0)])
+def test_activation_tiles_of_the_prompt_pass_stay_within_32_bit_offsets(d_ffn, rows):
+    """A cache's scratch holds the activations of as many prompt tokens as a 32-bit byte offset reaches, in steps of 128."""
+    L = ad.lib()
+    shape = synth.TINY.with_(dtype=synth.BF16, n_layers=2, exit_layers=(), d_model=16, n_q_heads=1, n_kv_heads=1)
+    size = lambda f: L.ad_kv_bytes(C.byref(ad.make_config(shape.with_(d_ffn=f))), 2000)
+    up = lambda b: (b + 255) // 256 * 256
+    tiles = lambda r, k: r * ((k + 31) // 32 * 32) * 4
+    # rows, their factors, tiles of d_model, fp32 pieces (q, k, v of 3 x 64 outputs), queries and attention output, tiles of d_ffn
+    scratch = lambda f, r: up(r * 16 * 4) + up(r * 4) + up(tiles(r, 16)) + up(r * 192 * 4) + 2 * up(tiles(r, 64)) + up(tiles(r, f))
+    assert tiles(rows, d_ffn) < 2 ** 32
+    assert size(d_ffn) == size(8) - scratch(8, 1024) + (scratch(d_ffn, rows) if rows else 0)
+
+
 # ---- scheduler over scripted heads -------------------------------------------------------------------
 
 def _events(ev):
