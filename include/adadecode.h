@@ -93,7 +93,8 @@ ad_status ad_model_destroy(ad_model *);
  *        then  V [kv head][head_dim][position 0..stride)   (transposed: positions are contiguous)
  * Entries at positions >= the layer's length are dead, not zeroed.  Behind the entries the storage holds the library's
  * scratch, of which the last part (16-bit models) lets ad_generate run up to 1024 prompt tokens through a layer at once;
- * ad_kv_create accepts storage without that part, and prompts then go through the layers 8 rows at a time. */
+ * ad_kv_create accepts storage without that part, and prompts then go through the layers 8 rows at a time.
+ * At most 2^24 positions at head_dim 128 and 2^25 at 64: beyond them ad_kv_bytes returns 0 and ad_kv_create AD_ERANGE. */
 size_t    ad_kv_bytes(const ad_config *, int32_t max_pos);
 /* Also fills the cache's rotary table on `stream` and synchronises it. */
 ad_status ad_kv_create(const ad_model *, void *kv_storage /*dev*/, size_t kv_storage_bytes, int32_t max_pos, void *stream,

@@ -317,6 +317,12 @@ static size_t attn_part_bytes(const ad_config &c, int32_t max_pos) {
     return align_up((size_t)c.n_q_heads * 8 * S * (c.head_dim + 2) * 4);
 }
 
+// The rotary table is indexed with 32 bits, and so are, in bytes, the positions of a kv head by the attention kernels (16 777 216
+// positions at head_dim 128, twice as many at 64).
+static bool max_pos_ok(const ad_config &c, int32_t max_pos) {
+    return ((int64_t)max_pos + 63) / 64 * 64 * c.head_dim <= (int64_t)1 << 31;
+}
+
 // What a cache cannot do without: the entries, the attention partials, the rotary table.
 static size_t kv_core_bytes(const ad_config &c, int32_t max_pos) {
     const size_t elem = c.dtype == AD_F32 ? 4 : 2;
@@ -359,12 +365,14 @@ static size_t prompt_layout(const ad_config &c, int32_t max_pos, char *base, ad_
 size_t ad_kv_bytes(const ad_config *cfg, int32_t max_pos) {
     const char *why;
     if (!config_ok(cfg, &why) || max_pos < 1) { fail(AD_EINVAL, "ad_kv_bytes: %s", max_pos < 1 ? "max_pos < 1" : why); return 0; }
+    if (!max_pos_ok(*cfg, max_pos)) { fail(AD_ERANGE, "ad_kv_bytes: max_pos %d is more positions than a cache can have", max_pos); return 0; }
     return kv_core_bytes(*cfg, max_pos) + prompt_layout(*cfg, max_pos, nullptr, nullptr);
 }
 
 ad_status ad_kv_create(const ad_model *model, void *kv_storage, size_t kv_storage_bytes, int32_t max_pos, void *stream, ad_kv **out) {
     if (!model || !kv_storage || !out || max_pos < 1) return (ad_status)fail(AD_EINVAL, "ad_kv_create: bad argument");
     if (((uintptr_t)kv_storage & 255u) != 0) return (ad_status)fail(AD_EINVAL, "ad_kv_create: storage must be 256-byte aligned");
+    if (!max_pos_ok(model->cfg, max_pos)) return (ad_status)fail(AD_ERANGE, "ad_kv_create: max_pos %d is more positions than a cache can have", max_pos);
     const size_t need = kv_core_bytes(model->cfg, max_pos);
     if (kv_storage_bytes < need) return (ad_status)fail(AD_ENOMEM, "ad_kv_create: storage has %zu bytes, %zu needed", kv_storage_bytes, need);
     ad_kv *kv = new (std::nothrow) ad_kv();

@@ -58,6 +58,16 @@ def test_size_queries_and_config_checks_without_gpu():
     assert L.ad_kv_truncate(None, 0) == ad.AD_EINVAL
 
 
+@pytest.mark.parametrize("head_dim,most", [(64, 1 << 25), (128, 1 << 24)])
+def test_a_cache_has_no_more_positions_than_its_tables_index(head_dim, most):
+    """Beyond them the rotary table's index overflowed while the cache was created."""
+    L = ad.lib()
+    cfg = ad.make_config(synth.TINY.with_(n_layers=1, exit_layers=(), head_dim=head_dim))
+    assert L.ad_kv_bytes(C.byref(cfg), most) > 0
+    for max_pos in (most + 1, 2 ** 31 - 1):
+        assert L.ad_kv_bytes(C.byref(cfg), max_pos) == 0 and b"positions" in L.ad_last_error()
+
+
 @pytest.mark.parametrize("d_ffn,rows", [(64, 1024), (1048544, 1024), (1048552, 896), (1100000, 896), (8388576, 128), (8388608, 0)])
 def test_activation_tiles_of_the_prompt_pass_stay_within_32_bit_offsets(d_ffn, rows):
     """A cache's scratch holds the activations of as many prompt tokens as a 32-bit byte offset reaches, in steps of 128."""
