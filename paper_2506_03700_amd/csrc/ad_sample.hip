@@ -287,12 +287,19 @@ __device__ __forceinline__ SegStat row_from_logits(const float *z, int V, float 
 // Eq. 2 over the drafts, computed by every workgroup that needs the outcome (the same sums in the same order).
 struct Decision { int n_acc, rejected; SegStat f, q; };      // of row n_acc: statistics of its final and draft logits
 
+// Where the rows' statistics come from.  A kernel is built for one source: in one kernel for all, which also reduced the rows of one
+// segment, 5 and 8 rows of 2048 logits took 37.9 us a call and not 36.1.
+enum RowSource { ROWS_LOGITS, ROWS_SEGMENT, ROWS_SEGMENTS };     // the logits, one segment per row, several
+
+template <RowSource SRC>
 __device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const SegStat *seg, int n_seg, bool write_ratio) {
     __shared__ SegStat row[16];
     __shared__ int s_rejected;                       // the first rejected draft, n_draft if none is
     const int wave = threadIdx.x >> 6, n_draft = a.m - 1;
     const int n_rows = 2 * a.m - 1;
-    if (seg) {
+    if (SRC == ROWS_SEGMENT) {
+        if ((int)threadIdx.x < n_rows) row[threadIdx.x] = seg[threadIdx.x];
+    } else if (SRC == ROWS_SEGMENTS) {
         for (int r = wave; r < n_rows; r += kSampleWaves) {
             const SegStat st = row_from_segments(seg + (size_t)r * n_seg, n_seg, a.inv_t);
             if ((threadIdx.x & 63) == 0) row[r] = st;
@@ -366,24 +373,25 @@ __device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j
 // The residual's segments, if a draft was rejected.
 __global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out) {
     __shared__ SampleLds L;
-    const Decision d = decide(a, seg, n_seg, false);
+    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, false);
     if (!d.rejected) return;
     const int j0 = blockIdx.x * seg_ids;
     const SegStat st = residual_stat(residual_of(a, d), j0, min(a.V, j0 + seg_ids), L);
     if (threadIdx.x == 0) out[blockIdx.x] = st;
 }
 
-// seg, res_seg: null where the statistics of rows of one segment, of their residual, are formed here
+// seg: null for ROWS_LOGITS; res_seg: null but for ROWS_SEGMENTS (a residual of one segment is formed here)
+template <RowSource SRC>
 __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
     __shared__ SegStat only;
-    const Decision d = decide(a, seg, n_seg, true);
+    const Decision d = decide<SRC>(a, seg, n_seg, true);
     const int r = d.n_acc;
     int tok = -1;
     float w_tok, total;
     if (d.rejected) {
         ResidualWeight w = residual_of(a, d);
-        if (!res_seg) {
+        if (SRC != ROWS_SEGMENTS) {
             const SegStat st = residual_stat(w, 0, a.V, L);
             if (threadIdx.x == 0) only = st;
             __syncthreads();
@@ -393,12 +401,13 @@ __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampled
         if (w.c != -INFINITY) tok = sample_segments(w, res_seg, w.c, 1.0f, a.V, n_seg, seg_ids, a.u_resample[r], L, &w_tok, &total);
         __syncthreads();
     }
-    const SegStat *row_seg = seg + (size_t)r * n_seg;
-    if (!seg) {
+    const SegStat *row_seg = &only;
+    if (SRC == ROWS_SEGMENTS) {
+        row_seg = seg + (size_t)r * n_seg;
+    } else {
         __syncthreads();
         if (threadIdx.x == 0) only = d.f;
         __syncthreads();
-        row_seg = &only;
     }
     if (tok < 0)       // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
         tok = sample_segments(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, row_seg, d.f.mx, a.inv_t, a.V, n_seg, seg_ids,
@@ -443,7 +452,8 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     const dim3 wg(kSampleThreads);
     int rc;
     // rows of one segment: up to as many as a workgroup has wavefronts are cheaper to reduce in the last kernel than in one of
-    // their own (2048 logits, 3 rows: 33.6 against 35.4 us a call), and the residual always is
+    // their own (2048 logits, 3 rows: 33.6 against 35.4 us a call; more take a kernel of their own, one kernel for 15 rows took
+    // 39.5 against 38.2), and the residual always is
     if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
         hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
@@ -454,7 +464,9 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
         hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
         if ((rc = (int)hipGetLastError())) return rc;
     }
-    hipLaunchKernelGGL(k_verify_sampled, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
+    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
+    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
+    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
     return (int)hipGetLastError();
 }
 

@@ -59,6 +59,38 @@ def test_draws_and_verification_at_segment_edges(ad, V):
     g.close()
 
 
+@pytest.mark.parametrize("V", [301, 2047, 2048, 2049])
+def test_rows_of_one_segment_and_of_two(ad, V):
+    """Rows of one segment, up to four and more (whose statistics come from the last kernel, from one of their own), and of two: no
+    draft rejected, the first, one in the middle, the last."""
+    import torch
+    g = ad.Model(SMALL.with_(vocab=V), synth.make_weights(SMALL.with_(vocab=V), seed=0), max_pos=8)
+    rng = np.random.default_rng(V)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    for m in (1, 2, 4, 5, 8):
+        for bad in sorted({None, 0, (m - 1) // 2, m - 2} if m > 1 else {None}, key=str):
+            print(f"case V={V} m={m} rejected {bad}", flush=True)
+            zf = rng.standard_normal((m, V)).astype(np.float32)
+            zq = (zf[:m - 1] + 0.1 * rng.standard_normal((m - 1, V))).astype(np.float32)
+            draft = rng.integers(0, V, m - 1).astype(np.int32)
+            if bad is not None:
+                zq[bad, draft[bad]] += 12.0
+            ur, uf = rng.random(m - 1).astype(np.float32), float(np.float32(rng.random()))
+            n, nxt, ratio = g.ad_verify_sampled(dev(zf), dev(zq) if m > 1 else None, draft, 0.7, np.full(m - 1, 0.3, np.float32), ur, uf)
+            assert n == (m - 1 if bad is None else bad)
+            p = lambda z: orc.softmax_t(z.astype(np.float64), 0.7)
+            for k in range(m - 1):
+                want = p(zf[k])[draft[k]] / p(zq[k])[draft[k]] if k <= n else 0.0
+                assert abs(ratio[k] - want) <= 1e-5 * want
+            if bad is None:
+                want, margin = orc.sample_cdf(p(zf[n]), uf)
+            else:
+                _, want, _, margin = orc.accept_or_resample(p(zf[n]), p(zq[n]), int(draft[n]), 0.3, float(ur[n]))
+            # (fp32 sums of V weights in another order: the draw may fall to the other side of a boundary it is this close to)
+            assert nxt == want or margin < 1e-5
+    g.close()
+
+
 @pytest.mark.parametrize("V", [2049, 8192])
 def test_a_segment_that_is_not_a_number_shows(ad, V):
     """A row's sum is no number if one of its logits is none, also where a whole segment consists of such values."""
