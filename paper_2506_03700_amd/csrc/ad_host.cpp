@@ -398,8 +398,11 @@ ad_status ad_kv_create(const ad_model *model, void *kv_storage, size_t kv_storag
     const size_t prompt_bytes = prompt_layout(c, max_pos, nullptr, nullptr);
     if (!rc && prompt_bytes && kv_storage_bytes >= need + prompt_bytes) {
         prompt_layout(c, max_pos, kv->storage + need, &kv->pr);
-        // (zeroed: the padding of the activation tiles is read and multiplied by the weights' zero padding)
-        rc = launch_zero(kv->storage + need, prompt_bytes, stream);
+        // all of it is written before it is read, but for the inputs that fill the last operand tile of a width that is no
+        // multiple of 32: the weights have zeros there, and so must the activations have (zero times NaN is NaN)
+        const Layout &L = model->lay;
+        if (L.d % 32) rc = launch_zero(kv->pr.Bd, prompt_act_bytes(kv->pr.rows, L.d), stream);
+        if (!rc && L.f % 32) rc = launch_zero(kv->pr.Bg, prompt_act_bytes(kv->pr.rows, L.f), stream);
     }
     if (!rc) rc = stream_sync(stream);
     if (rc) { delete kv; return (ad_status)hip_fail(rc, "ad_kv_create: rotary table"); }

@@ -84,6 +84,29 @@ def test_storage_without_the_scratch_is_a_cache_too(ad):
     g.close()
 
 
+@pytest.mark.parametrize("shape", [ODD, ODD.with_(name="odd-f16", dtype=synth.F16), DH128, MHA], ids=lambda s: s.name)
+def test_nothing_is_read_that_was_not_written(ad, shape):
+    """A cache in storage full of NaN gives the same bits as one in zeros, prompt after prompt."""
+    import torch
+    w = synth.make_weights(shape, seed=8, norm_jitter=0.2)
+    g = ad.Model(shape, w, max_pos=320)
+    want = []
+    for fill in (0, 255):
+        g.L.ad_kv_destroy(g.kv)
+        g.kv_storage.fill_(fill)
+        kv = C.c_void_p()
+        assert g.L.ad_kv_create(g.model, C.c_void_p(g.kv_storage.data_ptr()), g.kv_storage.numel(), 320,
+                                C.c_void_p(torch.cuda.current_stream().cuda_stream), C.byref(kv)) == ad.AD_OK
+        g.kv = kv
+        for i, n in enumerate((17, 10, 140, 70, 300)):
+            g.ad_generate(synth.make_prompt(shape, n, n), 3, 2.0, 0)
+            got = [a for l in range(1, shape.n_layers + 1) for a in g.kv_read(l, n)]
+            if fill == 0:
+                want.append(got)
+            assert all(np.array_equal(a, b) and np.all(np.isfinite(a)) for a, b in zip(got, want[i])), (fill, n)
+    g.close()
+
+
 def test_activations_of_four_gigabytes(ad):
     """1024 tokens' inputs to the down projection would take 4.5 GB: fewer tokens to a pass, and the same caches as by layer steps
     (the last tokens of a pass are the ones whose tiles lie furthest)."""
