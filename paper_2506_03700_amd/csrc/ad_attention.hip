@@ -517,8 +517,10 @@ static int launch_dec(const AttnArgs &a, const LaunchCtx &c) {
 
 // Positions per item for a stand-alone launch, k times the smallest item: one item per compute unit if k = 4 is enough for
 // that, else two.  (An item that shares its compute unit runs slower, but a chain of many blocks is longer still.)
-// Contexts up to two items' length get one item per kv head, which writes the attention output itself: 8B shape, 4 rows,
-// context 100 100.7 -> 97.3 us, 200 99.7 -> 97.6 (three items in one: 99.6 -> 98.9 with 4 rows, 110.8 -> 115.8 with 8).
+// Contexts up to two items' length get one item per kv head, which writes the attention output itself.  Layer of a stretch, two
+// items and the fold against one item, context 256, 1 / 8 rows: 8B shape 94.3 -> 92.1 / 109.3 -> 109.0 us, 13B 132.7 -> 130.0 /
+// 159.2 -> 156.7, 2 kv heads of 64 dimensions 32.7 -> 29.2 / 36.5 -> 33.1; slower only with 64 query rows on a lone kv head of 128
+// (1 row 40.0 -> 37.4, 8 rows 56.3 -> 58.8).  Three items in one: 8B, 4 rows 99.6 -> 98.9, 8 rows 110.8 -> 115.8.
 // Measured, layer step: 8B shape, 1 row, context 9203: k = 3 (192 items) 100.7 us, k = 2 (288) 103.2, k = 1 (576) 107.5;
 // 13B shape (40 kv heads), 1 row, context 4096: k = 3 (440 items) 143.2 us, k = 5 (280) 149.7, k = 2 (640) 147.1.
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg) {
