@@ -103,8 +103,8 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
                 const float *vp = kp + (size_t)a.Hkv * DH;
                 const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
                 const float x = kp[i], y = kp[i + half];
-                const uint16_t k0 = f32_to_16<F16>(x * c - y * sn), k1 = f32_to_16<F16>(x * sn + y * c);
-                const uint16_t v0 = f32_to_16<F16>(vp[i]), v1 = f32_to_16<F16>(vp[i + half]);
+                const uint16_t k0 = to16<F16>(x * c - y * sn), k1 = to16<F16>(x * sn + y * c);
+                const uint16_t v0 = to16<F16>(vp[i]), v1 = to16<F16>(vp[i + half]);
                 L.knew[t * DH + i] = k0;
                 L.knew[t * DH + i + half] = k1;
                 L.vnewT[i * 8 + t] = v0;
@@ -307,30 +307,17 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// any cache type: plain vector-ALU kernel (used for fp32 caches, where the model is small)
+// fp32 cache: plain vector-ALU kernel (the model is small)
 // ---------------------------------------------------------------------------------------------------
-template <typename KVT>
-__device__ __forceinline__ float kv_to_f32(KVT v);
-template <>
-__device__ __forceinline__ float kv_to_f32<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ float kv_to_f32<uint16_t>(uint16_t v) { return bf16_bits_to_f32(v); }
-template <typename KVT>
-__device__ __forceinline__ KVT f32_to_kv(float v);
-template <>
-__device__ __forceinline__ float f32_to_kv<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ uint16_t f32_to_kv<uint16_t>(float v) { return f32_to_bf16_bits(v); }
-
 constexpr int kValuThreads = 1024;
 constexpr int kValuMaxRows = 32;
 // keys per work item: a chunk of cached positions plus up to 8 new rows; sized so that the K and V tiles fit LDS
-constexpr int valu_max_keys(size_t kv_elem, int dh) { return (kv_elem * dh <= 256) ? 136 : 72; }
+constexpr int valu_max_keys(int dh) { return dh <= 64 ? 136 : 72; }
 
-template <typename KVT, int DH>
+template <int DH>
 __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
-    constexpr int KROW = DH + 16 / sizeof(KVT);       // padded row against LDS bank conflicts
-    constexpr int MAXK = valu_max_keys(sizeof(KVT), DH);
+    constexpr int KROW = DH + 4;      // padded row against LDS bank conflicts
+    constexpr int MAXK = valu_max_keys(DH);
     constexpr int half = DH / 2;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -338,8 +325,8 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
     float *qs = (float *)lds_raw;                   // [kValuMaxRows][DH]
     float *sc = qs + kValuMaxRows * DH;             // [kValuMaxRows][MAXK]
     float *st = sc + kValuMaxRows * MAXK;           // [kValuMaxRows][2]
-    KVT *Ks = (KVT *)(st + kValuMaxRows * 2 + kValuThreads);   // [MAXK][KROW]
-    KVT *Vs = Ks + MAXK * KROW;
+    float *Ks = (float *)(st + kValuMaxRows * 2 + kValuThreads);   // [MAXK][KROW]
+    float *Vs = Ks + MAXK * KROW;
     const int n_items = a.Hkv * a.S;
     const size_t PR = DH + 2;
 
@@ -349,7 +336,7 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
         const int nc = (c1 > c0) ? c1 - c0 : 0;
         const bool last = (s == a.S - 1);
         const int nk = nc + (last ? a.m : 0);
-        KVT *Kg = (KVT *)a.Kc + (size_t)g * a.stride * DH, *Vg = (KVT *)a.Vc + (size_t)g * DH * a.stride;
+        float *Kg = (float *)a.Kc + (size_t)g * a.stride * DH, *Vg = (float *)a.Vc + (size_t)g * DH * a.stride;
         for (int idx = tid; idx < nc * DH; idx += kValuThreads) {
             const int j = idx / DH, e = idx % DH;
             Ks[j * KROW + e] = Kg[(size_t)(c0 + j) * DH + e];
@@ -363,8 +350,8 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
                 const float *vp = kp + (size_t)a.Hkv * DH;
                 const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
                 const float x = kp[i], y = kp[i + half];
-                const KVT k0 = f32_to_kv<KVT>(x * c - y * sn), k1 = f32_to_kv<KVT>(x * sn + y * c);
-                const KVT v0 = f32_to_kv<KVT>(vp[i]), v1 = f32_to_kv<KVT>(vp[i + half]);
+                const float k0 = x * c - y * sn, k1 = x * sn + y * c;
+                const float v0 = vp[i], v1 = vp[i + half];
                 Ks[(nc + t) * KROW + i] = k0;
                 Ks[(nc + t) * KROW + i + half] = k1;
                 Vs[(nc + t) * KROW + i] = v0;
@@ -391,10 +378,10 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
             for (int p = tid; p < nr * nk * 4; p += kValuThreads) {
                 const int pair = p >> 2, rr = pair / nk, j = pair - rr * nk, t = (r0 + rr) / G, e0 = (p & 3) * (DH / 4);
                 float acc = 0.f;
-                const KVT *kr = Ks + j * KROW + e0;
+                const float *kr = Ks + j * KROW + e0;
                 const float *qr = qs + rr * DH + e0;
 #pragma unroll
-                for (int e = 0; e < DH / 4; ++e) acc += qr[e] * kv_to_f32<KVT>(kr[e]);
+                for (int e = 0; e < DH / 4; ++e) acc += qr[e] * kr[e];
                 acc += __shfl_xor(acc, 1);
                 acc += __shfl_xor(acc, 2);
                 if (j >= nc && j - nc > t) acc = -INFINITY;     // causal mask among the call's own rows
@@ -426,7 +413,7 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
             if (parts > 1 && tid < parts * nr * DH) {
                 const int part = tid / (nr * DH), o = tid - part * (nr * DH), rr = o / DH, e = o % DH;
                 float acc = 0.f;
-                for (int j = part; j < nk; j += parts) acc += sc[rr * MAXK + j] * kv_to_f32<KVT>(Vs[j * KROW + e]);
+                for (int j = part; j < nk; j += parts) acc += sc[rr * MAXK + j] * Vs[j * KROW + e];
                 red[tid] = acc;
             }
             if (parts > 1) __syncthreads();
@@ -436,7 +423,7 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
                 if (parts > 1)
                     for (int p = 0; p < parts; ++p) acc += red[p * nr * DH + idx];
                 else
-                    for (int j = 0; j < nk; ++j) acc += sc[rr * MAXK + j] * kv_to_f32<KVT>(Vs[j * KROW + e]);
+                    for (int j = 0; j < nk; ++j) acc += sc[rr * MAXK + j] * Vs[j * KROW + e];
                 if (a.S == 1) {                             // nothing to fold: the output itself, packed for the Wo GEMM
                     const int r = r0 + rr, t = r / G;
                     store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + r % G) * DH + e, t, acc / st[rr * 2 + 1]);
@@ -469,25 +456,24 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-constexpr size_t valu_lds_bytes(size_t kv_elem, int dh) {
-    return (size_t)kValuMaxRows * dh * 4 + (size_t)kValuMaxRows * valu_max_keys(kv_elem, dh) * 4 + kValuMaxRows * 2 * 4 + kValuThreads * 4 +
-           2 * (size_t)valu_max_keys(kv_elem, dh) * (dh + 16 / kv_elem) * kv_elem;
+constexpr size_t valu_lds_bytes(int dh) {
+    return ((size_t)kValuMaxRows * (dh + valu_max_keys(dh) + 2) + kValuThreads + 2 * (size_t)valu_max_keys(dh) * (dh + 4)) * 4;
 }
 
-int attn_chunk(int kv_elem, int dh) { return kv_elem != kElemF32 ? 128 : valu_max_keys(4, dh) - 8; }
+int attn_chunk(int kv_elem, int dh) { return kv_elem != kElemF32 ? 128 : valu_max_keys(dh) - 8; }
 
-template <typename KVT, int DH>
+template <int DH>
 static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
-    const size_t lds = valu_lds_bytes(sizeof(KVT), DH);
+    const size_t lds = valu_lds_bytes(DH);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_attn_valu<KVT, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_attn_valu<DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
     int grid = a.Hkv * a.S;
     if (grid > 4 * c.n_wg) grid = 4 * c.n_wg;
-    hipLaunchKernelGGL((k_attn_valu<KVT, DH>), dim3(grid), dim3(kValuThreads), lds, (hipStream_t)c.stream, a);
+    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(grid), dim3(kValuThreads), lds, (hipStream_t)c.stream, a);
     return (int)hipGetLastError();
 }
 
@@ -545,8 +531,8 @@ int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
         else if (a.dh == 64) rc = launch_dec<64, true>(a, c);
         else return (int)hipErrorInvalidValue;
     } else {
-        if (a.dh == 128) rc = launch_valu<float, 128>(a, c);
-        else if (a.dh == 64) rc = launch_valu<float, 64>(a, c);
+        if (a.dh == 128) rc = launch_valu<128>(a, c);
+        else if (a.dh == 64) rc = launch_valu<64>(a, c);
         else return (int)hipErrorInvalidValue;
     }
     if (rc || a.S == 1) return rc;

@@ -1,4 +1,4 @@
-// Device side of the attention phase for a 16-bit KV cache: work items of the split-context MFMA attention as the fused
+// Device side of the attention phase: work items of the split-context MFMA attention over a bf16 KV cache as the fused
 // layer-step kernel (ad_layer_fused.hip) runs them, and the fold of the splits, which the stand-alone kernels
 // (ad_attention.hip, with work items of their own) use too; the `Io` policy (ad_gemm_device.h) says how data exchanged between
 // workgroups -- q/k/v rows in, partials out and in, packed output -- is accessed.
@@ -13,7 +13,7 @@
 namespace ad {
 
 // ---------------------------------------------------------------------------------------------------
-// bf16 cache: MFMA kernel.  4 wavefronts per item, each takes one block of 32 cached positions.
+// work items: 8 wavefronts, two to a block of 32 cached positions
 // ---------------------------------------------------------------------------------------------------
 // Scores  S^T[key][row] = K[key][:] . q[row][:]  : A operand = K rows straight from the cache (lane (i, gq)
 // holds 8 consecutive dims of one key), B operand = the rotated, pre-scaled queries split into bf16 hi/lo
@@ -23,7 +23,7 @@ namespace ad {
 //   O^T[dim][row] = V^T[dim][key] . P^T[key][row]
 // whose A operand is a 128-bit load from the transposed V cache.  P is split hi/lo over the column pair
 // as well, so both products carry about 16 mantissa bits of the activations.
-constexpr int kAttnWaves = 4;            // key blocks of an item that are processed at once
+constexpr int kAttnThreads = 512;
 constexpr int kAttnRowsPerPass = 32;
 constexpr int kAttnSlots = 5;   // 4 cached blocks + the call's own rows
 
@@ -37,9 +37,8 @@ struct AttnMfmaLds {
     float part[kAttnSlots * RP * (DH + 4)];              // rows padded to 16 bytes for 128-bit LDS stores
 };
 
-// Work items wg, wg + nwg, ... of the attention phase.  NTHREADS is 256 (4 wavefronts: wavefront w takes key
-// block w and all row blocks) or 512 (8 wavefronts: wavefronts w and w + 4 both take key block w and share its
-// row blocks of 8 query rows between them).
+// Work items wg, wg + nwg, ... of the attention phase: wavefronts w and w + 4 both take key block w and share its row blocks
+// of 8 query rows between them.
 // The wavefront's cached block of an item: K rows and V columns as MFMA A operands.
 template <int DH>
 struct AttnKv {
@@ -48,7 +47,7 @@ struct AttnKv {
 
 // Loads wavefront (tid >> 6) & 3's block of 32 cached positions of work item `item` (nothing if the block is
 // empty or the wavefront has no query rows).  Does not depend on the queries, so it can be issued early.
-template <int DH, int NTHREADS>
+template <int DH>
 __device__ __forceinline__ void attn_load_kv(const AttnArgs &a, int item, AttnKv<DH> &kv, long long kv_off = 0) {
     constexpr int KS = DH / 32, DT = DH / 16;
     const int tid = thread_index(), lane = tid & 63, wave = (tid >> 6) & 3, rh = tid >> 8;
@@ -75,12 +74,11 @@ __device__ __forceinline__ void attn_load_kv(const AttnArgs &a, int item, AttnKv
 
 // `kv`: register block for the cached K/V; if `preloaded`, it already holds (or has in flight) the block of the
 // first item, wg.
-// F16: the cache, and the 16-bit halves of the queries and probabilities, are fp16 (else bf16).
-template <int DH, int NTHREADS, class Io, bool F16>
+template <int DH, class Io>
 __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<DH> &L, int wg, int nwg, AttnKv<DH> &kv, bool preloaded,
                                                 long long kv_off = 0) {
     constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, PL = DH + 4, RP = kAttnRowsPerPass;
-    constexpr int NRH = NTHREADS / 256;      // wavefronts per key block
+    constexpr int NRH = kAttnThreads / 256;      // wavefronts per key block
     const int tid = thread_index(), lane = tid & 63, wave = (tid >> 6) & 3, rh = tid >> 8;
     const int n = lane & 15, gq = lane >> 4;
     const int G = a.G, R = a.R;
@@ -98,14 +96,14 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
 
         if (last) {
             // the call's own rows: rotate k, round to bf16, append to the cache, keep a copy in LDS
-            for (int idx = tid; idx < a.m * half; idx += NTHREADS) {
+            for (int idx = tid; idx < a.m * half; idx += kAttnThreads) {
                 const int t = idx / half, i = idx % half;
                 const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
                 const float *vp = kp + (size_t)a.Hkv * DH;
                 const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
                 const float x = Io::ld(kp + i), y = Io::ld(kp + i + half);
-                const uint16_t k0 = f32_to_16<F16>(x * c - y * sn), k1 = f32_to_16<F16>(x * sn + y * c);
-                const uint16_t v0 = f32_to_16<F16>(Io::ld(vp + i)), v1 = f32_to_16<F16>(Io::ld(vp + i + half));
+                const uint16_t k0 = f32_to_bf16_bits(x * c - y * sn), k1 = f32_to_bf16_bits(x * sn + y * c);
+                const uint16_t v0 = f32_to_bf16_bits(Io::ld(vp + i)), v1 = f32_to_bf16_bits(Io::ld(vp + i + half));
                 L.knew[t * DH + i] = k0;
                 L.knew[t * DH + i + half] = k1;
                 L.vnewT[i * 8 + t] = v0;
@@ -125,14 +123,14 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
             const int nblk = (nr + 7) / 8;
             // this wavefront's cached block goes in flight first: it does not depend on the queries (a later pass
             // over more rows loads it again, from L2: the registers are reused for the call's own rows below)
-            if (!(preloaded && item == wg && r0 == 0)) attn_load_kv<DH, NTHREADS>(a, item, kv, kv_off);
+            if (!(preloaded && item == wg && r0 == 0)) attn_load_kv<DH>(a, item, kv, kv_off);
             // queries: rotate, scale, split hi/lo, store in B-operand order.  Each thread first issues the loads of
             // all its elements (at most 8 for 32 rows of 128 dims), then does the arithmetic.
-            constexpr int QIT = (RP * half + NTHREADS - 1) / NTHREADS;
+            constexpr int QIT = (RP * half + kAttnThreads - 1) / kAttnThreads;
             float qx[QIT], qy[QIT], qc[QIT], qs_[QIT];
 #pragma unroll
             for (int it = 0; it < QIT; ++it) {
-                const int idx = tid + it * NTHREADS, rr = idx / half, i = idx % half, r = r0 + rr;
+                const int idx = tid + it * kAttnThreads, rr = idx / half, i = idx % half, r = r0 + rr;
                 qx[it] = qy[it] = qc[it] = qs_[it] = 0.f;
                 if (idx < nblk * 8 * half && rr < nr) {
                     const int t = div_small(r, a.mul_G), hq = g * G + (r - t * G);
@@ -145,18 +143,18 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
             }
 #pragma unroll
             for (int it = 0; it < QIT; ++it) {
-                const int idx = tid + it * NTHREADS, rr = idx / half, i = idx % half;
+                const int idx = tid + it * kAttnThreads, rr = idx / half, i = idx % half;
                 if (idx < nblk * 8 * half) {
                     const float q0 = (qx[it] * qc[it] - qy[it] * qs_[it]) * a.scale;
                     const float q1 = (qx[it] * qs_[it] + qy[it] * qc[it]) * a.scale;
                     const int b = rr >> 3, col = rr & 7;
                     uint16_t hi, lo;
                     int d = i;
-                    split_hi_lo<F16>(q0, hi, lo);
+                    split_hi_lo<false>(q0, hi, lo);
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col) * 8 + (d & 7)] = hi;
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col + 8) * 8 + (d & 7)] = lo;
                     d = i + half;
-                    split_hi_lo<F16>(q1, hi, lo);
+                    split_hi_lo<false>(q1, hi, lo);
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col) * 8 + (d & 7)] = hi;
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col + 8) * 8 + (d & 7)] = lo;
                 }
@@ -166,7 +164,7 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
             // this wavefront's key blocks: one cached block (row blocks rh, rh + NRH, ...), and, in the item that
             // holds the end of the cache, the call's own rows: row block b of those goes to wavefront NW - 1 - b, so
             // that the wavefronts with the least cached work (none at all while m <= 2) take them in parallel
-            constexpr int NW = NTHREADS / 64;
+            constexpr int NW = kAttnThreads / 64;
             const int wave8 = tid >> 6;
             for (int pass = 0; pass < 2; ++pass) {
                 const bool is_new = (pass == 1);
@@ -203,16 +201,13 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                         vreg[dt] = cv;
                     }
                 }
-                // Half precision has a narrow exponent range: probabilities below 2^-14 of their block's maximum would
-                // be subnormal.  They enter the MFMA scaled by 2^10 (exact), and the products are scaled back.
-                constexpr float kPScale = F16 ? 1024.0f : 1.0f;
                 for (int b = b_first; b < nblk; b += b_step) {
                     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int j = 0; j < KS; ++j) {
                         const bf16x8 q = L.qb[(b * KS + j) * 64 + lane];
-                        s0 = mma16<F16>(kreg[0][j], q, s0);
-                        s1 = mma16<F16>(kreg[1][j], q, s1);
+                        s0 = mma16<false>(kreg[0][j], q, s0);
+                        s1 = mma16<false>(kreg[1][j], q, s1);
                     }
                     // lane (n, gq) now holds, for query row b*8 + (n & 7), the keys gq*8 + 0..3 (s0) and
                     // gq*8 + 4..7 (s1) of the block: hi part in columns 0..7, lo part in columns 8..15
@@ -240,7 +235,7 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                         const float p = (sc[c] == -INFINITY) ? 0.f : __expf(sc[c] - mx);
                         sum += p;
                         uint16_t hi, lo;
-                        split_hi_lo<F16>(p * kPScale, hi, lo);
+                        split_hi_lo<false>(p, hi, lo);
                         pb.u[c] = (n < 8) ? hi : lo;
                     }
                     sum += __shfl_xor(sum, 16);
@@ -250,12 +245,12 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
                         o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                        o[dt] = mma16<F16>(vreg[dt], pb.v, o[dt]);
+                        o[dt] = mma16<false>(vreg[dt], pb.v, o[dt]);
                     }
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) o[dt][c] = add_lane_xor8(o[dt][c]) * (1.0f / kPScale);
+                        for (int c = 0; c < 4; ++c) o[dt][c] = add_lane_xor8(o[dt][c]);
                         if (n < 8 && rr < nr) *(f32x4 *)(prow + dt * 16 + gq * 4) = o[dt];
                     }
                     if (n < 8 && gq == 0 && rr < nr) {
@@ -269,7 +264,7 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
             // neighbouring dimensions of a row (DH / 2 threads, whole wavefronts, per row), derives the blocks' weights
             // exp(max_p - M) itself from their (max, sum) pairs (the same LDS words for the whole wavefront), and stores
             // eight bytes
-            for (int idx = tid; idx < nr * half; idx += NTHREADS) {
+            for (int idx = tid; idx < nr * half; idx += kAttnThreads) {
                 const int rr = idx / half, e = (idx % half) * 2;
                 float mp[kAttnSlots], M = -INFINITY;
 #pragma unroll

@@ -34,7 +34,7 @@
 
 namespace ad {
 
-constexpr int kFusedThreads = 512;
+constexpr int kFusedThreads = kAttnThreads;
 constexpr long long kBarrierTimeoutTicks = 20000000;   // 0.2 s of the 100 MHz wall clock
 
 struct GridBarrier {
@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         stamp();
         // ---- 1. q, k, v = W (RMSNorm(x)) -----------------------------------------------------------------
         AttnKv<DH> kv;
-        auto pre_attn = [&]() { attn_load_kv<DH, kFusedThreads>(f.attn, wg, kv, kv_off); };   // the cached K/V block of the first item
+        auto pre_attn = [&]() { attn_load_kv<DH>(f.attn, wg, kv, kv_off); };   // the cached K/V block of the first item
         if (wg < f.nwg_qkv) {
             // first layer: x was written before the launch and is requested ahead of the weights; later layers: the
             // weights went in flight at the barrier that made x visible
@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         stamp();
 
         // ---- 2. rotary embedding, KV append, attention partials ----------------------------------------------
-        attn_mfma_items<DH, kFusedThreads, IoAgent, false>(f.attn, L.attn, wg, nwg, kv, true, kv_off);
+        attn_mfma_items<DH, IoAgent>(f.attn, L.attn, wg, nwg, kv, true, kv_off);
         stamp();
         if (!bar.sync(false, NoTail())) return;
         stamp();

@@ -458,7 +458,7 @@ constexpr int kPromptAttnRows = 64;
 
 template <int DH, bool F16>
 __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
-    constexpr int KS = DH / 32, DT = DH / 16, RT = kPromptAttnRows / 64;
+    constexpr int KS = DH / 32, DT = DH / 16;
     constexpr int KU = 2 * KS * 64, VU = DT * 64, NL = (KU + VU) / 256;
     __shared__ bf16x8 lds[2][KU + VU];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, gq = lane >> 4;
@@ -469,21 +469,15 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
     const int n_key = a.pos0 + r_last / a.G + 1;                 // keys the block's last row sees
     const int n_kb = (n_key + 31) / 32;
 
-    const int row0 = r_blk + wave * 16 * RT;
+    const int row0 = r_blk + wave * 16, row = row0 + n;          // this wavefront's first row, this lane's row
     const bf16x8 *Q = (const bf16x8 *)a.Q + ((size_t)kvh * (a.q_rows / 16) + row0 / 16) * KS * 128;
-    bf16x8 q[RT][KS][2];
-    int t_row[RT], see[RT];
+    const int t_row = (row < R ? row : R - 1) / a.G, see = a.pos0 + t_row;      // its token and last visible position
+    bf16x8 q[KS][2];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        const int r = row0 + i * 16 + n;
-        t_row[i] = (r < R ? r : R - 1) / a.G;
-        see[i] = a.pos0 + t_row[i];                              // last visible position
+    for (int j = 0; j < KS; ++j)
 #pragma unroll
-        for (int j = 0; j < KS; ++j)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) q[i][j][p] = Q[((i * KS + j) * 2 + p) * 64 + lane];
-    }
-    const int w_last = (row0 + 16 * RT < R ? row0 + 16 * RT : R) - 1;
+        for (int p = 0; p < 2; ++p) q[j][p] = Q[(j * 2 + p) * 64 + lane];
+    const int w_last = (row0 + 16 < R ? row0 + 16 : R) - 1;
     const int w_key = row0 < R ? a.pos0 + w_last / a.G + 1 : 0;  // keys this wavefront's last row sees
     const int w_full = row0 < R ? a.pos0 + row0 / a.G + 1 : 0;   // keys all its rows see
 
@@ -512,15 +506,10 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
     };
 
     constexpr float kPScale = F16 ? 1024.0f : 1.0f;              // keeps small probabilities out of fp16's subnormals
-    f32x4 o[RT][DT];
-    float mx[RT], sum[RT];
+    f32x4 o[DT];
+    float mx = -INFINITY, sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        mx[i] = -INFINITY;
-        sum[i] = 0.f;
-#pragma unroll
-        for (int d = 0; d < DT; ++d) o[i][d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
+    for (int d = 0; d < DT; ++d) o[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
     load(0);
     store(lds[0]);
     if (n_kb > 1) load(1);
@@ -528,63 +517,51 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
     for (int kb = 0; kb < n_kb; ++kb) {
         const bf16x8 *cur = lds[kb & 1];
         if (kb * 32 < w_key) {
-            f32x4 s[RT][2];
-#pragma unroll
-            for (int i = 0; i < RT; ++i) s[i][0] = s[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
                 const bf16x8 k0 = cur[j * 64 + lane], k1 = cur[(KS + j) * 64 + lane];
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int i = 0; i < RT; ++i) {
-                        s[i][0] = mma16<F16>(k0, q[i][j][p], s[i][0]);
-                        s[i][1] = mma16<F16>(k1, q[i][j][p], s[i][1]);
-                    }
+                for (int p = 0; p < 2; ++p) {
+                    s0 = mma16<F16>(k0, q[j][p], s0);
+                    s1 = mma16<F16>(k1, q[j][p], s1);
+                }
             }
             const bool masked = kb * 32 + 32 > w_full;           // some row of this wavefront does not see the whole block
-            bf16x8 ph[RT], pl[RT];
+            float sc[8], bm = -INFINITY;
 #pragma unroll
-            for (int i = 0; i < RT; ++i) {
-                float sc[8], bm = -INFINITY;
+            for (int c = 0; c < 8; ++c) {
+                sc[c] = c < 4 ? s0[c & 3] : s1[c & 3];
+                if (masked && kb * 32 + gq * 8 + c > see) sc[c] = -INFINITY;
+                bm = fmaxf(bm, sc[c]);
+            }
+            bm = fmaxf(bm, __shfl_xor(bm, 16));
+            bm = fmaxf(bm, __shfl_xor(bm, 32));
+            const float nm = fmaxf(mx, bm), ref = softmax_ref(nm);
+            const float alpha = __expf(mx - ref);
+            mx = nm;
+            float add = 0.f;
+            u16x8 h8, l8;
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    sc[c] = s[i][c >> 2][c & 3];
-                    if (masked && kb * 32 + gq * 8 + c > see[i]) sc[c] = -INFINITY;
-                    bm = fmaxf(bm, sc[c]);
-                }
-                bm = fmaxf(bm, __shfl_xor(bm, 16));
-                bm = fmaxf(bm, __shfl_xor(bm, 32));
-                const float nm = fmaxf(mx[i], bm), ref = softmax_ref(nm);
-                const float alpha = __expf(mx[i] - ref);
-                mx[i] = nm;
-                float add = 0.f;
-                u16x8 h8, l8;
+            for (int c = 0; c < 8; ++c) {
+                const float p = __expf(sc[c] - ref);
+                add += p;
+                uint16_t hi, lo;
+                split16<F16>(p * kPScale, hi, lo);
+                h8[c] = hi;
+                l8[c] = lo;
+            }
+            const bf16x8 ph = __builtin_bit_cast(bf16x8, h8), pl = __builtin_bit_cast(bf16x8, l8);
+            sum = sum * alpha + add;
+            if (!__all(alpha == 1.0f)) {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const float p = __expf(sc[c] - ref);
-                    add += p;
-                    uint16_t hi, lo;
-                    split16<F16>(p * kPScale, hi, lo);
-                    h8[c] = hi;
-                    l8[c] = lo;
-                }
-                ph[i] = __builtin_bit_cast(bf16x8, h8);
-                pl[i] = __builtin_bit_cast(bf16x8, l8);
-                sum[i] = sum[i] * alpha + add;
-                if (!__all(alpha == 1.0f)) {
-#pragma unroll
-                    for (int d = 0; d < DT; ++d) o[i][d] *= alpha;
-                }
+                for (int d = 0; d < DT; ++d) o[d] *= alpha;
             }
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
                 const bf16x8 v = cur[KU + d * 64 + lane];
-#pragma unroll
-                for (int i = 0; i < RT; ++i) {
-                    o[i][d] = mma16<F16>(v, ph[i], o[i][d]);
-                    o[i][d] = mma16<F16>(v, pl[i], o[i][d]);
-                }
+                o[d] = mma16<F16>(v, ph, o[d]);
+                o[d] = mma16<F16>(v, pl, o[d]);
             }
         }
         if (kb + 1 < n_kb) {
@@ -594,29 +571,24 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
         __syncthreads();
     }
     // lane (n, gq): query row n of the tile, dims d*16 + gq*4 .. +3
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    const float inv = 1.0f / (sum * kPScale);
+    if (row < R) {
+        const int hq = kvh * a.G + (row - t_row * a.G);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        float den = sum[i];
-        den += __shfl_xor(den, 16);
-        den += __shfl_xor(den, 32);
-        const float inv = 1.0f / (den * kPScale);
-        const int r = row0 + i * 16 + n;
-        if (r < R) {
-            const int hq = kvh * a.G + (r - t_row[i] * a.G);
+        for (int d = 0; d < DT; ++d) {
+            u16x4 h4, l4;
 #pragma unroll
-            for (int d = 0; d < DT; ++d) {
-                u16x4 h4, l4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint16_t hi, lo;
-                    split16<F16>(o[i][d][e] * inv, hi, lo);
-                    h4[e] = hi;
-                    l4[e] = lo;
-                }
-                const int k = hq * DH + d * 16 + (gq >> 1) * 8;
-                *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row[i], k, a.Bo_KT, 0)) + (gq & 1) * 4) = h4;
-                *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row[i], k, a.Bo_KT, 1)) + (gq & 1) * 4) = l4;
+            for (int e = 0; e < 4; ++e) {
+                uint16_t hi, lo;
+                split16<F16>(o[d][e] * inv, hi, lo);
+                h4[e] = hi;
+                l4[e] = lo;
             }
+            const int k = hq * DH + d * 16 + (gq >> 1) * 8;
+            *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row, k, a.Bo_KT, 0)) + (gq & 1) * 4) = h4;
+            *(u16x4 *)((uint16_t *)((bf16x8 *)a.Bo + act_unit(t_row, k, a.Bo_KT, 1)) + (gq & 1) * 4) = l4;
         }
     }
 }
