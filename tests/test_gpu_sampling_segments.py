@@ -1,5 +1,5 @@
-"""GPU: draws and sampled verification at the edges of the segments a logits row is cut into (2048 ids each; longer ones beyond
-256 of them), with masked ids and masked segments, against the oracle."""
+"""GPU: draws and sampled verification at the edges of the segments a logits row is cut into (of equal length, at most 2048 ids, but no
+more than 512 of them: longer ones beyond 1 048 576 ids), with masked ids and masked segments, against the oracle."""
 import numpy as np
 import pytest
 
@@ -20,14 +20,21 @@ def ad():
     return binding
 
 
-@pytest.mark.parametrize("V", [1, 2047, 2048, 2049, 4097, 600001])
+def segment_length(V):
+    n = min(-(-V // 2048), 512)
+    return -(-V // n)
+
+
+# 2049: two segments of 1025 and 1024 ids; 4097: three of 1366; 600001: 293 of 2048; 1100003: 512 of 2149, more than a thread keeps
+@pytest.mark.parametrize("V", [1, 2047, 2048, 2049, 4097, 600001, 1100003])
 def test_draws_and_verification_at_segment_edges(ad, V):
     import torch
-    seg = 2048 if V <= 2048 * 256 else -(-V // 256)
+    seg = segment_length(V)
     g = ad.Model(SMALL.with_(vocab=V), synth.make_weights(SMALL.with_(vocab=V), seed=0), max_pos=8)
     rng = np.random.default_rng(V)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
-    edges = sorted({t for t in (0, 1, seg - 1, seg, seg + 1, V - 2, V - 1) if 0 <= t < V})
+    last = (V - 1) // seg * seg              # the last segment's first id
+    edges = sorted({t for t in (0, 1, seg - 1, seg, seg + 1, last - 1, last, V - 2, V - 1) if 0 <= t < V})
     for t in edges:
         print(f"case V={V} token {t}", flush=True)
         z = (rng.standard_normal(V) * 0.5).astype(np.float32)
@@ -45,17 +52,35 @@ def test_draws_and_verification_at_segment_edges(ad, V):
             want, margin = orc.sample_cdf(p, u)
             assert tok in edges and abs(prob - p[tok]) <= 1e-5 * p[tok]
             assert tok == want or margin < 1e-6
-        # a rejected draft whose residual is one token at a segment's edge: p* and p_draft differ at t and at the draft only
-        if V > 1:
+        # a rejected draft: p* exceeds p_draft by far at t, and little or nowhere else; then at all the edges
+        for more in ((), edges) if V > 1 else ():
             zf = (rng.standard_normal((2, V)) * 0.5).astype(np.float32)
             zq = zf[:1].copy()
             d = edges[0] if t != edges[0] else edges[-1]
-            zf[0, t] = zq[0, d] = 14.0
-            n, nxt, ratio = g.ad_verify_sampled(dev(zf), dev(zq), [d], 1.0, [0.5], [float(np.float32(rng.random()))], 0.5)
+            zf[0, list(more)] = 12.0 + rng.random(len(more)).astype(np.float32)
+            zf[0, t] = 14.0
+            zf[0, d] = zq[0, d]
+            zq[0, d] = 14.0
+            ur = float(np.float32(rng.random()))
+            n, nxt, ratio = g.ad_verify_sampled(dev(zf), dev(zq), [d], 1.0, [0.5], [ur], 0.5)
             p, q = orc.softmax_t(zf[0].astype(np.float64), 1.0), orc.softmax_t(zq[0].astype(np.float64), 1.0)
-            assert n == 0 and abs(ratio[0] - p[d] / q[d]) <= 1e-4 * p[d] / q[d]
-            r = np.maximum(p - q, 0.0)
-            assert nxt == t or r[nxt] > 0 and r[t] / r.sum() < 0.9999
+            acc, want, _, margin = orc.accept_or_resample(p, q, d, 0.5, ur)
+            assert n == 0 and not acc and abs(ratio[0] - p[d] / q[d]) <= 1e-4 * p[d] / q[d]
+            # (fp32 sums of V weights: the draw may fall to the other side of a boundary it is this close to)
+            assert nxt == want or margin < 1e-5
+    # the spread of a real row: draws all over it, then with one of its segments masked
+    for u in rng.random(6).astype(np.float32):
+        z = (rng.standard_normal(V) * 0.5).astype(np.float32)
+        s = int(rng.integers(0, (V - 1) // seg + 1))
+        for masked in (0, seg):
+            if masked and V <= seg:
+                continue
+            z[s * seg:s * seg + masked] = -np.inf
+            p = orc.softmax_t(z.astype(np.float64), 1.0)
+            tok, prob = g.ad_sample_logits(dev(z), 1.0, float(u))
+            want, margin = orc.sample_cdf(p, float(u))
+            # (the target may fall between neighbours of about 1 / V each: the drawn id's own share and no more lies between)
+            assert p[min(tok, want):max(tok, want) + 1].sum() <= p[tok] + p[want] + 1e-5 and abs(prob - p[tok]) <= 1e-5 * p[tok]
     g.close()
 
 
@@ -95,8 +120,8 @@ def test_rows_of_one_segment_and_of_two(ad, V):
 def test_a_segment_that_is_not_a_number_shows(ad, V):
     """A row's sum is no number if one of its logits is none, also where a whole segment consists of such values."""
     import torch
-    n_seg = -(-V // 2048)
-    seg = -(-V // n_seg)
+    seg = segment_length(V)
+    n_seg = -(-V // seg)
     g = ad.Model(SMALL.with_(vocab=V), synth.make_weights(SMALL.with_(vocab=V), seed=0), max_pos=8)
     rng = np.random.default_rng(V)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
