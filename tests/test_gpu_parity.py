@@ -150,8 +150,9 @@ D6144 = synth.WIDE_LAYER.with_(name="d6144-layer", d_model=6144, n_q_heads=40, n
 @pytest.mark.parametrize("shape,ctx,mode", [(synth.LLAMA8B_LAYER, 4096, 0), (synth.LLAMA8B_LAYER, 4096, 1), (L13, 1000, 0), (L13, 1000, 1),
                                             (L8_F16, 4096, 0), (L13_F16, 1000, 0), (L13_F32, 300, 0),
                                             (synth.WIDE_LAYER, 2048, 0), (WIDE_BF16, 500, 0), (D6144, 300, 0),
-                                            # more attention work items than compute units: the attention variant with
-                                            # small workgroups (all m for 40 kv heads; m <= 4, two passes from m = 3, for the 8B shape)
+                                            # attention items of three blocks of keys per wavefront (240 items of the 13B
+                                            # shape, 176 of the 8B shape, whose more than 16 query rows, m > 4, then go
+                                            # to one wavefront with two row tiles)
                                             (L13, 2100, 0), (synth.LLAMA8B_LAYER, 8300, 0)],
                          ids=["8b-layer-kernels", "8b-layer-fused", "13b-layer-kernels", "13b-layer-fused",
                               "8b-layer-f16-kernels", "13b-layer-f16-kernels", "13b-layer-f32-kernels",
