@@ -172,7 +172,8 @@ ad_status ad_head_logits(const ad_model *, int32_t layer, const void *hidden, in
  * cumulative probability exceeds u).  temperature > 0 scales the logits: p = softmax(z / temperature).
  *
  * ad_sample_logits: token ~ softmax(logits / temperature) with the draw u; prob = that token's probability
- * (the quantity Eq. 1 compares with gamma).  logits: dev [vocab] fp32.  token, prob: pinned host or dev. */
+ * (the quantity Eq. 1 compares with gamma).  logits: dev [vocab] fp32.  token, prob: pinned host or dev.  Uses the
+ * model's scratch (the vocabulary pass's partials): calls on one model must be stream-ordered. */
 ad_status ad_sample_logits(const ad_model *, const void *logits, float temperature, float u, int32_t *token, float *prob,
                            void *stream);
 

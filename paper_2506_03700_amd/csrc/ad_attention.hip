@@ -37,7 +37,7 @@ namespace ad {
 // holds the end of the cache then takes the call's own rows as one more block.  The four wavefronts' results meet in LDS.
 //
 // An item is a chain of dependent steps, whatever its size, so what counts is its length and how many run at once (a layer's
-// cache at context 9203 is read in 6 us).  Layer step of the 8B shape against the kernel this replaces (hi and lo parts in the
+// cache at context 9203 is read in 6 us).  Layer step of the 8B shape, one layer over and over, against the kernel this replaces (hi and lo parts in the
 // two halves of a tile's columns, two wavefronts per block, every item 128 positions): context 9203, 8 rows 142.8 -> 119 us, 1
 // row 106.8 -> 100.7; 4096, 4 rows 105.4 -> 102.2; 13B shape, 4096, 8 rows 179.9 -> 171.5.  RT row
 // tiles per wavefront, NRH wavefronts per block of keys (each with RT tiles of its own), up to 16 * RT * NRH query rows per pass.
@@ -507,7 +507,7 @@ static int launch_dec(const AttnArgs &a, const LaunchCtx &c) {
 // items and the fold against one item, context 256, 1 / 8 rows: 8B shape 94.3 -> 92.1 / 109.3 -> 109.0 us, 13B 132.7 -> 130.0 /
 // 159.2 -> 156.7, 2 kv heads of 64 dimensions 32.7 -> 29.2 / 36.5 -> 33.1; slower only with 64 query rows on a lone kv head of 128
 // (1 row 40.0 -> 37.4, 8 rows 56.3 -> 58.8).  Three items in one: 8B, 4 rows 99.6 -> 98.9, 8 rows 110.8 -> 115.8.
-// Measured, layer step: 8B shape, 1 row, context 9203: k = 3 (192 items) 100.7 us, k = 2 (288) 103.2, k = 1 (576) 107.5;
+// Measured, layer step, one layer over and over: 8B shape, 1 row, context 9203: k = 3 (192 items) 100.7 us, k = 2 (288) 103.2, k = 1 (576) 107.5;
 // 13B shape (40 kv heads), 1 row, context 4096: k = 3 (440 items) 143.2 us, k = 5 (280) 149.7, k = 2 (640) 147.1.
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg) {
     const int c = attn_chunk(kv_elem, dh);
