@@ -16,23 +16,15 @@ namespace ad {
 // NCHMAX (stationary mode): chunks of k-steps per tile and wavefront that the B registers cover.  Chunks have 8
 // k-steps for 16-bit weights, except in the widest instance (NCHMAX 8), whose 32 B registers leave room for
 // chunks of 4 only; fp32 weights (three planes per k-step) have chunks of 2.
-template <int NPL, int MODE, int NCHMAX, bool F16>
-__global__ void __launch_bounds__(MODE == GEMM_STATIONARY ? kStatThreads : kThreads) k_gemm(GemmArgs g) {
+template <int NPL, int NCHMAX, bool F16>
+__global__ void __launch_bounds__(kStatThreads) k_gemm(GemmArgs g) {
     warm_kernel_args<sizeof(GemmArgs)>();
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     GemmLds &L = *reinterpret_cast<GemmLds *>(lds_raw);
-    if constexpr (MODE == GEMM_STATIONARY) {
-        constexpr int CH = NPL == 1 ? (NCHMAX > 3 ? 4 : 8) : 2;
-        StatStream<NPL, CH> S;
-        S.init(g, blockIdx.x, 0x7fffffff);       // every workgroup of this launch has tiles (the grid size is an argument fetch away)
-        gemm_stationary<NPL, CH, NCHMAX, IoPlain, -1, F16, false>(g, S, L, NoTail());
-    } else {
-        constexpr int U = NPL == 1 ? 4 : 2;
-        StreamStream<NPL, U, kWaves> S;
-        S.init(g, blockIdx.x, 0x7fffffff);
-        S.prefetch(g);
-        gemm_streamed<NPL, U, kWaves, IoPlain, -1, false, F16>(g, S, L, NoTail());
-    }
+    constexpr int CH = NPL == 1 ? (NCHMAX > 3 ? 4 : 8) : 2;
+    StatStream<NPL, CH> S;
+    S.init(g, blockIdx.x, 0x7fffffff);       // every workgroup of this launch has tiles (the grid size is an argument fetch away)
+    gemm_stationary<NPL, CH, NCHMAX, IoPlain, -1, F16, false>(g, S, L, NoTail());
 }
 
 // Second pass of the vocabulary reduction: fold the per-workgroup (max, sum of exp, argmax) partials in
@@ -76,27 +68,27 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
     }
 }
 
-template <int NPL, int MODE, int NCHMAX, bool F16 = false>
+template <int NPL, int NCHMAX, bool F16 = false>
 static int launch_one(const GemmArgs &g, int grid, hipStream_t s) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm<NPL, MODE, NCHMAX, F16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GemmLds));
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemm<NPL, NCHMAX, F16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GemmLds));
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
     GemmArgs ga = g;
     set_tile_partition(ga, grid);
-    hipLaunchKernelGGL((k_gemm<NPL, MODE, NCHMAX, F16>), dim3(grid), dim3(MODE == GEMM_STATIONARY ? kStatThreads : kThreads), sizeof(GemmLds), s, ga);
+    hipLaunchKernelGGL((k_gemm<NPL, NCHMAX, F16>), dim3(grid), dim3(kStatThreads), sizeof(GemmLds), s, ga);
     return (int)hipGetLastError();
 }
 
 // 16-bit weights: the instance whose B registers cover the wavefront's K slice (d_model <= 4096, <= 6144, <= 8192)
 template <bool F16>
 static int stationary16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
-    if (nks <= 8) return launch_one<1, GEMM_STATIONARY, 1, F16>(g, grid, s);
-    if (nks <= 16) return launch_one<1, GEMM_STATIONARY, 2, F16>(g, grid, s);
-    if (nks <= 24) return launch_one<1, GEMM_STATIONARY, 3, F16>(g, grid, s);
-    return launch_one<1, GEMM_STATIONARY, kKsMaxWide / 4, F16>(g, grid, s);
+    if (nks <= 8) return launch_one<1, 1, F16>(g, grid, s);
+    if (nks <= 16) return launch_one<1, 2, F16>(g, grid, s);
+    if (nks <= 24) return launch_one<1, 3, F16>(g, grid, s);
+    return launch_one<1, kKsMaxWide / 4, F16>(g, grid, s);
 }
 
 int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
@@ -105,17 +97,13 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     hipStream_t s = (hipStream_t)c.stream;
     const bool f16 = g.elem == kElemF16;
     if ((planes == 1) != (g.elem != kElemF32)) return (int)hipErrorInvalidValue;     // fp32 weights are three bf16 planes
+    if (proj_covers(g, planes, c.n_wg)) return launch_proj(g, planes, c);
+    const int nks = (g.KT + kStatWaves - 1) / kStatWaves;     // most k-steps of a wavefront
+    if (nks > (planes == 1 ? kKsMaxWide : kKsMax) || g.K < 8) return (int)hipErrorInvalidValue;
     int rc;
-    if (g.mode == GEMM_STATIONARY) {
-        const int nks = (g.KT + kStatWaves - 1) / kStatWaves;     // most k-steps of a wavefront
-        if (nks > (planes == 1 ? kKsMaxWide : kKsMax) || g.K < 8) return (int)hipErrorInvalidValue;
-        if (planes != 1) rc = nks <= 2 ? launch_one<3, GEMM_STATIONARY, 1>(g, grid, s) : launch_one<3, GEMM_STATIONARY, kKsMax / 2>(g, grid, s);
-        else if (f16) rc = stationary16<true>(g, nks, grid, s);
-        else rc = stationary16<false>(g, nks, grid, s);
-    } else {
-        if (planes != 1) rc = launch_one<3, GEMM_STREAMED, 0>(g, grid, s);
-        else rc = f16 ? launch_one<1, GEMM_STREAMED, 0, true>(g, grid, s) : launch_one<1, GEMM_STREAMED, 0>(g, grid, s);
-    }
+    if (planes != 1) rc = nks <= 2 ? launch_one<3, 1>(g, grid, s) : launch_one<3, kKsMax / 2>(g, grid, s);
+    else if (f16) rc = stationary16<true>(g, nks, grid, s);
+    else rc = stationary16<false>(g, nks, grid, s);
     if (rc) return rc;
     if (g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag)) {       // (the logits alone need no reduction)
         GemmArgs h = g;

@@ -120,9 +120,9 @@ void make_layout(const ad_config &c, Layout &L) {
     s += align_up(act_packed_bytes(L.dq));                     // Bo (attention output)
     s += align_up(act_packed_bytes(L.f));                      // Bg (SwiGLU output)
     s += align_up(act_packed_bytes(L.d));                      // Bx (x' * ffn norm weight, packed by the Wo epilogue)
-    s += align_up((size_t)(L.d / 16) * 8 * 4);                 // per-tile sums of squares of x'
+    s += align_up((size_t)(L.d / 8) * 8 * 4);                 // sums of squares of x' per half tile of rows (fused layer step: per tile)
     s += align_up(act_packed_bytes(L.d));                      // Bq (y * next layer's attention norm weight, packed by the down epilogue)
-    s += align_up((size_t)(L.d / 16) * 8 * 4);                 // per-tile sums of squares of y
+    s += align_up((size_t)(L.d / 8) * 8 * 4);                 // the same of y
     s += align_up((size_t)8 * L.nqkv * 4);                     // qkv
     s += 2 * align_up((size_t)8 * L.d * 4);                    // x1, rows
     s += align_up((size_t)4096 * 8 * 4 * 4);                   // head partials (up to 4096 workgroups)
@@ -266,9 +266,9 @@ ad_status ad_model_create(const ad_config *cfg, const ad_layer_weights *layers, 
     m->Bo = take(act_packed_bytes(L.dq));
     m->Bg = take(act_packed_bytes(L.f));
     m->Bx = take(act_packed_bytes(L.d));
-    m->ssq = (float *)take((size_t)(L.d / 16) * 8 * 4);
+    m->ssq = (float *)take((size_t)(L.d / 8) * 8 * 4);
     m->Bq = take(act_packed_bytes(L.d));
-    m->ssq_q = (float *)take((size_t)(L.d / 16) * 8 * 4);
+    m->ssq_q = (float *)take((size_t)(L.d / 8) * 8 * 4);
     m->qkv = (float *)take((size_t)8 * L.nqkv * 4);
     m->x1 = (float *)take((size_t)8 * L.d * 4);
     m->rows = (float *)take((size_t)8 * L.d * 4);
@@ -518,7 +518,7 @@ static void qkv_args(const ad_model *m, int32_t ly, const void *hidden, int32_t 
     gq.elem = ek;
     gq.W = lp.wqkv; gq.NT = L.nqkv / 16; gq.KT = L.kt_d; gq.N = L.nqkv; gq.K = L.d; gq.m = n; gq.mode = GEMM_STATIONARY;
     gq.inv_dim = 1.0f / (float)L.d; gq.eps = c.rms_eps;
-    if (from_prev) { gq.B = m->Bq; gq.ssq_in = m->ssq_q; gq.ssq_tiles = L.d / 16; }
+    if (from_prev) { gq.B = m->Bq; gq.ssq_in = m->ssq_q; gq.ssq_tiles = m->layer_mode == AD_LAYER_FUSED ? L.d / 16 : L.d / 8; }
     else { gq.x = (const float *)hidden; gq.ldx = L.d; gq.norm_w = lp.attn_norm; gq.norm_elem = ek; }
     gq.epi = EPI_STORE; gq.out = m->qkv; gq.ld = L.nqkv;
 }
@@ -581,7 +581,7 @@ static int layer_steps(const ad_model *m, ad_kv *kv, int32_t layer, int32_t coun
         memset(&gg, 0, sizeof gg);
         gg.elem = ek;
         gg.W = lp.wgu; gg.NT = (2 * L.f) / 16; gg.KT = L.kt_d; gg.N = 2 * L.f; gg.K = L.d; gg.m = n; gg.mode = GEMM_STATIONARY;
-        gg.B = m->Bx; gg.ssq_in = m->ssq; gg.ssq_tiles = go.NT; gg.inv_dim = 1.0f / (float)L.d; gg.eps = c.rms_eps;
+        gg.B = m->Bx; gg.ssq_in = m->ssq; gg.ssq_tiles = fused ? go.NT : 2 * go.NT; gg.inv_dim = 1.0f / (float)L.d; gg.eps = c.rms_eps;
         gg.epi = EPI_SWIGLU; gg.Bnext = m->Bg; gg.Bnext_KT = L.kt_f;
         // 5. y = x' + Wd g
         memset(&gd, 0, sizeof gd);

@@ -197,6 +197,8 @@ int launch_embed(const EmbedArgs &, void *stream);
 int launch_rope_table(const RopeArgs &, void *stream);
 int gemm_max_stationary_k(int planes);   // largest d_model the stationary GEMM variants cover
 int launch_gemm(const GemmArgs &, int planes, const LaunchCtx &);   // EPI_HEAD: also launches the vocabulary combine
+bool proj_covers(const GemmArgs &, int planes, int n_wg);           // launch_gemm's choice for projections with few tiles per workgroup
+int launch_proj(const GemmArgs &, int planes, const LaunchCtx &);
 int head_grid(int n_tiles, int n_wg);                               // workgroups launch_gemm uses for n_tiles row tiles
 // The library's own static device array for the vocabulary pass's per-workgroup partials (room for kStaticHeadParts
 // workgroups): its address on the current device, resolved on first use per device.  Allocates nothing.

@@ -1,0 +1,423 @@
+// Projections with few row tiles per workgroup (at most two): Wo, down, the QKV projection of models up to the 8B shape, the
+// exit-head transform, and every projection of small models.     out[t][n] = sum_k W[n][k] * act[t][k],  m <= 8 tokens
+//
+// Such a launch lasts 3 to 25 us, and what it spends beyond reading its weights is a chain: argument fetch, first
+// loads, products, sum over the wavefronts, store.  A wavefront issues an instruction every 5 cycles or so (16 wavefronts
+// on a compute unit: every 16), so 400 instructions on that chain are a microsecond, and this kernel is written for few of them:
+// 8 wavefronts, each with a contiguous run of k-steps of all the workgroup's rows, straight-line loads with constant offsets, no
+// masks on tokens past the call's (a column of the product depends on its own column of the operand only, and is not stored),
+// the sum over the wavefronts by one wavefront per 8 rows.
+//
+// Rows are dealt in halves of a tile (8 rows: 128 bytes of each of the tile's four lane groups, whole cache lines), H = 2, 3 or 4
+// halves per workgroup (in whole tiles the 13B shape's 320 tiles are two each on 160 of 256 compute units).  Three halves are one
+// tile and the lower or upper half of a neighbour; one load fetches the half tile's rows of two k-steps, the lanes of operand
+// rows 8..15 taking the second, and two products use one half of the result each.
+//
+// Layer step, against the kernels this replaces (2500 to 8700 instructions, 16 or 8 wavefronts; here 850 to 1900): 8B shape, bf16,
+// context 4096, 1 row 97.2 -> 92.4 us (QKV 13.0 -> 10.4, Wo 9.9 -> 7.9, down 21.7 -> 19.7), context 9203, 8 rows 122.1 -> 113.5; 13B shape, 2
+// rows 136.6 -> 129.8 (Wo 14.0 -> 12.3, down 32.0 -> 24.5); tiny fp32 model, a token 136 -> 100 us.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "ad_device.h"
+#include "ad_gemm_device.h"
+#include "ad_internal.h"
+
+namespace ad {
+
+namespace {
+
+constexpr int kProjWaves = 8;
+constexpr int kProjThreads = kProjWaves * 64;
+constexpr int kStripBytes = 8192;            // a wavefront's 8 k-steps of activations, in operand order
+
+// k-steps per batch of loads; two batches are in flight
+constexpr int proj_batch(int npl) { return npl == 1 ? 8 : 2; }
+constexpr int proj_slots(int h) { return (h + 1) / 2; }         // blocks of 8 tokens x 16 rows a wavefront leaves behind
+constexpr size_t proj_lds_bytes(int h, bool from_x) {
+    return (size_t)kProjWaves * (from_x ? kStripBytes : proj_slots(h) * 512) + kProjWaves * 8 * 4;
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sum over the 8 lanes of an aligned group of 8
+__device__ __forceinline__ float sum8(float v) {
+    v = dpp_add<0xB1>(v);        // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);        // quad_perm [2, 3, 0, 1]
+    return dpp_add<0x141>(v);    // row_half_mirror: the other four
+}
+// sum over the wavefront, in every lane
+__device__ __forceinline__ float sum64(float v) {
+    v = sum8(v);
+    v = dpp_add<0x140>(v);       // row_mirror: the other eight of 16
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+// NPL: planes of a weight tile (fp32 models three).  H: halves of a row tile per workgroup.  FROM_X: the activations are fp32 rows
+// (times a norm weight, with 1 / rms applied to the result), else a packed block, with or without sums of squares for 1 / rms.
+template <int NPL, int H, bool F16, bool FROM_X>
+__global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
+    warm_kernel_args<sizeof(GemmArgs)>();
+    constexpr int NF = H / 2, U = proj_batch(NPL), NS = proj_slots(H), TB = NPL * 1024;   // whole tiles, batch, slots, bytes of a tile
+    constexpr bool HALF = H & 1;
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, gq = lane >> 4;
+    constexpr int WB = FROM_X ? kStripBytes : NS * 512;         // bytes of a wavefront's part of the LDS
+    float *ssq_part = (float *)(lds_raw + kProjWaves * WB);
+
+    const int u0 = blockIdx.x * H, KT = g.KT, last_tile = g.NT - 1;
+    const int full0 = (u0 + 1) >> 1;                            // the whole tiles; the half one lies before or after them
+    const int upper = u0 & 1;                                   // (H = 3) the half tile is its tile's upper half
+    const int half_tile = upper ? full0 - 1 : full0 + NF;
+    // the wavefront's k-steps [ka, kb): pairs of them where a load covers two
+    int ka, kb;
+    if (HALF) {
+        const int kp = (KT + 1) >> 1;
+        ka = 2 * ((kp * wave) / kProjWaves);
+        kb = 2 * ((kp * (wave + 1)) / kProjWaves);
+        kb = kb < KT ? kb : KT;
+    } else {
+        ka = (KT * wave) / kProjWaves;
+        kb = (KT * (wave + 1)) / kProjWaves;
+    }
+    // k-steps that a batch may load: its own, past them the last one again (or, without any, some valid one)
+    const int k_ok = kb > ka ? kb - 1 : (ka < KT ? ka : KT - 1);
+
+    // weights: uniform base, 32-bit byte offsets (a packed matrix has less than 4 GiB)
+    const char *W = (const char *)g.W;
+    unsigned wf[NF], wh = 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const int t = full0 + f < last_tile ? full0 + f : last_tile;
+        wf[f] = (unsigned)t * (unsigned)KT * (unsigned)TB + (unsigned)lane * 16u;
+    }
+    const int hi_row = (lane >> 3) & 1;                         // this lane's operand row is in 8..15
+    if (HALF) {
+        const int t = half_tile < last_tile ? half_tile : last_tile;
+        wh = (unsigned)t * (unsigned)KT * (unsigned)TB + (unsigned)((lane & 48) + upper * 8 + (lane & 7)) * 16u;
+    }
+    auto ld = [](const char *p) { return __builtin_nontemporal_load((const bf16x8 *)p); };
+    struct Tiles { bf16x8 f[NF][U][NPL], h[HALF ? U / 2 : 1][NPL]; };
+    auto load_w = [&](Tiles &a, int k) {
+        if (k + U <= kb) {
+            const unsigned o = (unsigned)k * TB;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const char *p = W + (size_t)(wf[f] + o);
+#pragma unroll
+                for (int j = 0; j < U; ++j)
+#pragma unroll
+                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = ld(p + j * TB + q * 1024);
+            }
+            if (HALF) {
+                const char *p = W + (size_t)(wh + o + (unsigned)hi_row * TB);
+#pragma unroll
+                for (int j = 0; j < U / 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < NPL; ++q) a.h[j][q] = ld(p + 2 * j * TB + q * 1024);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const unsigned o = (unsigned)(k + j < k_ok ? k + j : k_ok) * TB;
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = ld(W + (size_t)(wf[f] + o) + q * 1024);
+            }
+            if (HALF) {
+#pragma unroll
+                for (int j = 0; j < U / 2; ++j) {
+                    const int kk = k + 2 * j + hi_row;
+                    const unsigned o = wh + (unsigned)(kk < k_ok ? kk : k_ok) * TB;
+#pragma unroll
+                    for (int q = 0; q < NPL; ++q) a.h[j][q] = ld(W + (size_t)o + q * 1024);
+                }
+            }
+        }
+    };
+    // activations: lanes of tokens past the call's read token 0's (the same cache lines)
+    const unsigned bo = (unsigned)((n & 7) < g.m ? (n & 7) : 0) * (unsigned)KT * 128u + (unsigned)((n >> 3) * 64 + gq * 16);
+    auto load_b = [&](bf16x8 (&b)[U], int k) {
+        const char *B = (const char *)g.B;
+        if (k + U <= kb) {
+            const char *p = B + (size_t)(bo + (unsigned)k * 128u);
+#pragma unroll
+            for (int j = 0; j < U; ++j) b[j] = *(const bf16x8 *)(p + j * 128);
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) b[j] = *(const bf16x8 *)(B + (bo + (unsigned)(k + j < k_ok ? k + j : k_ok) * 128u));
+        }
+    };
+    f32x4 acc[NF], acch[2];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    acch[0] = acch[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto mma_step = [&](const Tiles &a, const bf16x8 (&b)[U], int j) {
+#pragma unroll
+        for (int q = 0; q < NPL; ++q) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) acc[f] = mma16<F16>(a.f[f][j][q], b[j], acc[f]);
+            if (HALF) acch[j & 1] = mma16<F16>(a.h[j / 2][q], b[j], acch[j & 1]);
+        }
+    };
+    auto mma = [&](const Tiles &a, const bf16x8 (&b)[U], int k) {
+        if (k + U <= kb) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) mma_step(a, b, j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if (k + j < kb) mma_step(a, b, j);
+        }
+    };
+
+    // an output of the epilogue: wavefront h takes half h of the workgroup's rows (SwiGLU: tile h), lane = token * 8 + row
+    const int et = lane >> 3, ei = lane & 7, unit = u0 + wave, row = unit * 8 + ei;
+    const bool on = wave < H && et < g.m && row < g.N;
+    float resid = 0.f, next_w = 0.f;
+    auto load_resid = [&]() {
+        if (g.epi == EPI_RESID && on) {
+            resid = g.resid[(size_t)et * g.ld + row];
+            if (g.Bnext) next_w = NPL == 3 ? ((const float *)g.next_norm_w)[row] : from16<F16>(((const uint16_t *)g.next_norm_w)[row]);
+        }
+    };
+
+    Tiles a0, a1;
+    bf16x8 b0[U], b1[U];
+    if constexpr (FROM_X) {
+        // The wavefront's own k-steps (at most 2 * U), in passes of 8 = 256 inputs: lane l takes inputs 4l .. 4l+3 of every token,
+        // multiplies by the norm weights, splits and writes them in operand order into its strip of LDS, from which each lane
+        // reads its operand registers.  Units of 16 bytes are permuted (u -> u ^ ((u >> 4) & 15)) so that the 8-byte writes of a
+        // wavefront, which all go to the same operand column, spread over the LDS banks.
+        constexpr int NP = (2 * U + 7) / 8, PK = U < 4 ? 2 * U : 8;      // passes, k-steps per pass
+        f32x4 xr[NP][8], wn[NP];
+        u16x4 wr[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int k = (ka + p * 8) * 32 + lane * 4, kc = k < g.K - 4 ? k : g.K - 4;
+            if (NPL == 3) wn[p] = *(const f32x4 *)((const float *)g.norm_w + kc);
+            else wr[p] = *(const u16x4 *)((const uint16_t *)g.norm_w + kc);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (t < g.m) xr[p][t] = *(const f32x4 *)(g.x + (size_t)t * g.ldx + kc);
+        }
+        load_w(a0, ka);
+        load_w(a1, ka + U);
+        uint16_t *strip16 = (uint16_t *)(lds_raw + wave * WB);
+        const bf16x8 *strip = (const bf16x8 *)strip16;
+        auto sw = [](int u) { return u ^ ((u >> 4) & 15); };
+        float ssq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            if (NPL != 3) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) wn[p][e] = from16<F16>(wr[p][e]);
+            }
+            const int ks = ka + p * 8 + (lane >> 3), k = ks * 32 + (lane & 7) * 4;
+            const bool k_on = ks < kb && k < g.K;
+            const int uu = (lane >> 3) * 64 + ((lane & 7) >> 1) * 16;    // unit of column 0
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (t < g.m) {
+                    u16x4 hi, lo;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float xv = k_on ? xr[p][t][e] : 0.f;
+                        ssq[t] += xv * xv;
+                        uint16_t h, l;
+                        split16<F16>(xv * wn[p][e], h, l);
+                        hi[e] = h;
+                        lo[e] = l;
+                    }
+                    *(u16x4 *)(strip16 + sw(uu + t) * 8 + (lane & 1) * 4) = hi;
+                    *(u16x4 *)(strip16 + sw(uu + 8 + t) * 8 + (lane & 1) * 4) = lo;
+                }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+#pragma unroll
+            for (int jj = 0; jj < PK; ++jj) {
+                const int j = p * 8 + jj;
+                if (j < U) b0[j % U] = strip[sw(jj * 64 + lane)];
+                else b1[j % U] = strip[sw(jj * 64 + lane)];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            if (t < g.m) {
+                const float v = sum64(ssq[t]);
+                if (lane == 0) ssq_part[wave * 8 + t] = v;
+            }
+        mma(a0, b0, ka);
+        mma(a1, b1, ka + U);
+    } else {
+        load_b(b0, ka);
+        load_w(a0, ka);
+        load_b(b1, ka + U);
+        load_w(a1, ka + U);
+        load_resid();
+        if (g.ssq_in && wave < g.m) {
+            // wavefront t adds up token t's partial sums of squares, per lane and then over the lanes (fixed order)
+            float v = 0.f;
+            for (int i = lane; i < g.ssq_tiles; i += 64) v += g.ssq_in[(size_t)i * 8 + wave];
+            v = sum64(v);
+            if (lane == 0) ssq_part[wave] = v;
+        }
+        // While four whole batches remain, the loads of the loop are unconditional, so that each product waits for its own
+        // operands only.
+        int k = ka;
+#pragma nounroll
+        for (; k + 4 * U <= kb; k += 2 * U) {
+            mma(a0, b0, k);
+            load_b(b0, k + 2 * U);
+            load_w(a0, k + 2 * U);
+            mma(a1, b1, k + U);
+            load_b(b1, k + 3 * U);
+            load_w(a1, k + 3 * U);
+        }
+#pragma nounroll
+        for (; k < kb; k += 2 * U) {
+            mma(a0, b0, k);
+            if (k + 2 * U < kb) {
+                load_b(b0, k + 2 * U);
+                load_w(a0, k + 2 * U);
+            }
+            mma(a1, b1, k + U);
+            if (k + 3 * U < kb) {
+                load_b(b1, k + 3 * U);
+                load_w(a1, k + 3 * U);
+            }
+        }
+    }
+    // columns n and n + 8 hold the hi and lo products of token n; the wavefront's slots: [slot][token][16 rows]
+    float *slot = (float *)(lds_raw + wave * WB);
+    if (HALF) {
+        // rows 0..7 of the first product and 8..15 of the second are the half tile's, each over its own k-steps
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float v = add_lane_xor8(gq < 2 ? acch[0][e] : acch[1][e]);
+            acch[0][e] = v;
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[f][e] = add_lane_xor8(acc[f][e]);
+    if (n < g.m) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) *(f32x4 *)(slot + f * 128 + n * 16 + gq * 4) = acc[f];
+        if (HALF) *(f32x4 *)(slot + NF * 128 + n * 16 + gq * 4) = acch[0];
+    }
+    __syncthreads();
+    if (wave >= H) return;
+
+    float scale = 1.0f;
+    if (FROM_X) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kProjWaves; ++w) s += ssq_part[w * 8 + et];
+        scale = 1.0f / sqrtf(s * g.inv_dim + g.eps);
+    } else if (g.ssq_in) {
+        scale = 1.0f / sqrtf(ssq_part[et] * g.inv_dim + g.eps);
+    }
+    const float *base = (const float *)lds_raw + et * 16 + ei;
+    constexpr int WF = WB / 4;                                  // floats from one wavefront's slots to the next one's
+    auto sum_rows = [&](const float *p) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kProjWaves; ++w) v += p[w * WF];
+        return v;
+    };
+    if (g.epi == EPI_SWIGLU) {
+        // rows 0..7 of a tile are gate, 8..15 up of the same features
+        const int f = (full0 + wave) * 8 + ei;
+        if (!HALF && wave < NF && et < g.m && f * 2 < g.N) {
+            const float gate = scale * sum_rows(base + wave * 128), up = scale * sum_rows(base + wave * 128 + 8);
+            uint16_t hi, lo;
+            split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
+            ((uint16_t *)g.Bnext)[act_index(f, et, g.Bnext_KT)] = hi;
+            ((uint16_t *)g.Bnext)[act_index(f, 8 + et, g.Bnext_KT)] = lo;
+        }
+        return;
+    }
+    if (!on) return;
+    float v;
+    if (HALF && (upper ? wave == 0 : wave == H - 1)) {
+        const float *p = base + NF * 128;
+        v = sum_rows(p) + sum_rows(p + 8);
+    } else {
+        const int r = wave - (HALF ? upper : 0);                // half r of the whole tiles
+        v = sum_rows(base + (r >> 1) * 128 + (r & 1) * 8);
+    }
+    v *= scale;
+    if (g.epi == EPI_STORE) {
+        g.out[(size_t)et * g.ld + row] = v;
+    } else if (g.epi == EPI_PACK) {
+        uint16_t hi, lo;
+        split16<F16>(v, hi, lo);
+        ((uint16_t *)g.Bnext)[act_index(row, et, g.Bnext_KT)] = hi;
+        ((uint16_t *)g.Bnext)[act_index(row, 8 + et, g.Bnext_KT)] = lo;
+    } else {
+        const float y = resid + v;
+        g.out[(size_t)et * g.ld + row] = y;
+        if (g.Bnext) {
+            // input of the next projection: y * norm weight, packed; and these 8 rows' share of sum(y^2)
+            uint16_t hi, lo;
+            split16<F16>(y * next_w, hi, lo);
+            ((uint16_t *)g.Bnext)[act_index(row, et, g.Bnext_KT)] = hi;
+            ((uint16_t *)g.Bnext)[act_index(row, 8 + et, g.Bnext_KT)] = lo;
+            const float q = sum8(y * y);
+            if (ei == 0) g.ssq_out[(size_t)unit * 8 + et] = q;
+        }
+    }
+}
+
+template <int NPL, int H, bool F16, bool FROM_X>
+int launch_as(const GemmArgs &g, hipStream_t s) {
+    constexpr size_t lds = proj_lds_bytes(H, FROM_X);
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_proj<NPL, H, F16, FROM_X>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return (int)e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((k_proj<NPL, H, F16, FROM_X>), dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g);
+    return (int)hipGetLastError();
+}
+
+template <int NPL, int H, bool F16>
+int launch_src(const GemmArgs &g, hipStream_t s) {
+    return g.x ? launch_as<NPL, H, F16, true>(g, s) : launch_as<NPL, H, F16, false>(g, s);
+}
+
+template <int NPL, bool F16>
+int launch_halves(const GemmArgs &g, int halves, hipStream_t s) {
+    if (halves == 2) return launch_src<NPL, 2, F16>(g, s);
+    if (halves == 3) return launch_src<NPL, 3, F16>(g, s);
+    return launch_src<NPL, 4, F16>(g, s);
+}
+
+}  // namespace
+
+bool proj_covers(const GemmArgs &g, int planes, int n_wg) {
+    if (g.mode == GEMM_STREAMED) return true;
+    if (g.epi == EPI_HEAD || g.NT > 2 * n_wg) return false;
+    return !g.x || (g.norm_w && g.KT <= kProjWaves * 2 * proj_batch(planes));
+}
+
+int launch_proj(const GemmArgs &g, int planes, const LaunchCtx &c) {
+    int halves = (2 * g.NT + c.n_wg - 1) / c.n_wg;
+    if (halves < 2) halves = 2;
+    if (halves > 3 || (halves == 3 && g.epi == EPI_SWIGLU)) halves = 4;
+    hipStream_t s = (hipStream_t)c.stream;
+    if (planes != 1) return launch_halves<3, false>(g, halves, s);
+    return g.elem == kElemF16 ? launch_halves<1, true>(g, halves, s) : launch_halves<1, false>(g, halves, s);
+}
+
+}  // namespace ad
