@@ -132,7 +132,7 @@ def main():
     achieved = avg_bytes / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
     kernel = ("ad::k_layer_fused (one decoder-layer step over the call's m rows as one persistent kernel: QKV, attention, "
               "Wo, gate/up, down; bytes = the layer's weights + KV rows read and written)") if fused else \
-             ("ad::k_gemm (weight-streaming skinny GEMM: every projection of the layer step and the vocabulary pass)")
+             ("ad::k_proj and ad::k_rows (weight-streaming skinny GEMM: every projection of the layer step and the vocabulary pass)")
     roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "time_base": "a pair of events on the launch stream around each sampled launch (every 7th), i.e. from the end of the "

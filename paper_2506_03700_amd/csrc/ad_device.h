@@ -107,6 +107,14 @@ __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo)
 // infinity (a key whose entry in the cache overflowed): exp(-inf - 0) gives such keys the weight 0, exp(-inf - m) is not a number.
 __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.f : m; }
 
+// merges (max, sum of exp relative to it, argmax); the lower index wins among equal values
+__device__ __forceinline__ void max_merge(float &M, float &S, int &I, float m2, float s2, int i2) {
+    if (m2 > M || (m2 == M && i2 < I)) I = i2;
+    const float nm = fmaxf(M, m2), ref = softmax_ref(nm);
+    S = S * __expf(M - ref) + s2 * __expf(m2 - ref);
+    M = nm;
+}
+
 // D += A (16 rows x 32) * B (32 x 16 columns), 16-bit operands of the model's type, fp32 accumulation
 template <bool F16>
 __device__ __forceinline__ f32x4 mma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {

@@ -1,34 +1,17 @@
-// Stand-alone launches of the weight-streaming skinny GEMM (device code in ad_gemm_device.h): every projection
-// of the decoder layer when the layer step runs as separate kernels, the exit-head transform, and the LM head
-// of Eq. 1 / Eq. 2 with its vocabulary reduction.
+// Stand-alone launches of the projections, when the layer step runs as separate kernels, and of the LM head of Eq. 1 / Eq. 2: which
+// kernel (ad_proj.hip: few row tiles per workgroup, ad_rows.hip: many), and the second pass of the vocabulary reduction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <string.h>
 
 #include <mutex>
 
 #include "ad_device.h"
-#include "ad_gemm_device.h"
 #include "ad_internal.h"
 
 namespace ad {
 
-// NCHMAX (stationary mode): chunks of k-steps per tile and wavefront that the B registers cover.  Chunks have 8
-// k-steps for 16-bit weights, except in the widest instance (NCHMAX 8), whose 32 B registers leave room for
-// chunks of 4 only; fp32 weights (three planes per k-step) have chunks of 2.
-template <int NPL, int NCHMAX, bool F16>
-__global__ void __launch_bounds__(kStatThreads) k_gemm(GemmArgs g) {
-    warm_kernel_args<sizeof(GemmArgs)>();
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    GemmLds &L = *reinterpret_cast<GemmLds *>(lds_raw);
-    constexpr int CH = NPL == 1 ? (NCHMAX > 3 ? 4 : 8) : 2;
-    StatStream<NPL, CH> S;
-    S.init(g, blockIdx.x, 0x7fffffff);       // every workgroup of this launch has tiles (the grid size is an argument fetch away)
-    gemm_stationary<NPL, CH, NCHMAX, IoPlain, -1, F16, false>(g, S, L, NoTail());
-}
-
-// Second pass of the vocabulary reduction: fold the per-workgroup (max, sum of exp, argmax) partials in
-// workgroup order (fixed order; the lowest token id wins ties), one wavefront per token, then apply the
+// Second pass of the vocabulary reduction: fold the per-workgroup (max, sum of exp, argmax) partials in a
+// fixed order (the lowest token id wins ties), one wavefront per token, then apply the
 // verification rule of Eq. 2 at temperature 0 if asked.
 __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
     __shared__ int idx_sh[8];
@@ -37,15 +20,20 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
         const int t = wave;
         float M = -INFINITY, S = 0.f;
         int I = 0x7fffffff;
-        for (int w = lane; w < g.n_parts; w += 64) {
-            const float *p = g.head_part + ((size_t)w * 8 + t) * 4;
-            lse_merge(M, S, I, p[0], p[1], __float_as_int(p[2]));
+        const f32x4 *part = (const f32x4 *)g.head_part + t;
+        for (int w0 = 0; w0 < g.n_parts; w0 += 256) {           // four partials per lane are in flight
+            f32x4 p[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int w = w0 + i * 64 + lane;
+                p[i] = part[(size_t)(w < g.n_parts ? w : 0) * 8];
+                if (w >= g.n_parts) p[i] = (f32x4){-INFINITY, 0.f, __int_as_float(0x7fffffff), 0.f};
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) max_merge(M, S, I, p[i][0], p[i][1], __float_as_int(p[i][2]));
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            const float m2 = __shfl_xor(M, off), s2 = __shfl_xor(S, off);
-            const int i2 = __shfl_xor(I, off);
-            lse_merge(M, S, I, m2, s2, i2);
-        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) max_merge(M, S, I, __shfl_xor(M, off), __shfl_xor(S, off), __shfl_xor(I, off));
         if (lane == 0) {
             idx_sh[t] = I;
             if (g.tok_out) g.tok_out[t] = I;
@@ -68,42 +56,12 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
     }
 }
 
-template <int NPL, int NCHMAX, bool F16 = false>
-static int launch_one(const GemmArgs &g, int grid, hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm<NPL, NCHMAX, F16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GemmLds));
-        if (e != hipSuccess) return (int)e;
-        attr_set = true;
-    }
-    GemmArgs ga = g;
-    set_tile_partition(ga, grid);
-    hipLaunchKernelGGL((k_gemm<NPL, NCHMAX, F16>), dim3(grid), dim3(kStatThreads), sizeof(GemmLds), s, ga);
-    return (int)hipGetLastError();
-}
-
-// 16-bit weights: the instance whose B registers cover the wavefront's K slice (d_model <= 4096, <= 6144, <= 8192)
-template <bool F16>
-static int stationary16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
-    if (nks <= 8) return launch_one<1, 1, F16>(g, grid, s);
-    if (nks <= 16) return launch_one<1, 2, F16>(g, grid, s);
-    if (nks <= 24) return launch_one<1, 3, F16>(g, grid, s);
-    return launch_one<1, kKsMaxWide / 4, F16>(g, grid, s);
-}
-
 int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     // equal numbers of row tiles per workgroup: with per = ceil(NT / n_wg) tiles each, ceil(NT / per) workgroups
     const int grid = head_grid(g.NT, c.n_wg);
     hipStream_t s = (hipStream_t)c.stream;
-    const bool f16 = g.elem == kElemF16;
     if ((planes == 1) != (g.elem != kElemF32)) return (int)hipErrorInvalidValue;     // fp32 weights are three bf16 planes
-    if (proj_covers(g, planes, c.n_wg)) return launch_proj(g, planes, c);
-    const int nks = (g.KT + kStatWaves - 1) / kStatWaves;     // most k-steps of a wavefront
-    if (nks > (planes == 1 ? kKsMaxWide : kKsMax) || g.K < 8) return (int)hipErrorInvalidValue;
-    int rc;
-    if (planes != 1) rc = nks <= 2 ? launch_one<3, 1>(g, grid, s) : launch_one<3, kKsMax / 2>(g, grid, s);
-    else if (f16) rc = stationary16<true>(g, nks, grid, s);
-    else rc = stationary16<false>(g, nks, grid, s);
+    int rc = proj_covers(g, planes, c.n_wg) ? launch_proj(g, planes, c) : launch_rows(g, planes, grid, c);
     if (rc) return rc;
     if (g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag)) {       // (the logits alone need no reduction)
         GemmArgs h = g;
@@ -149,7 +107,5 @@ int head_grid(int n_tiles, int n_wg) {
     const int grid = (n_tiles + per - 1) / (per < 1 ? 1 : per);
     return grid < 1 ? 1 : grid;
 }
-
-int gemm_max_stationary_k(int planes) { return (planes == 1 ? kKsMaxWide : kKsMax) * kStatWaves * 32; }
 
 }  // namespace ad

@@ -1,6 +1,6 @@
-// Device side of the weight-streaming skinny GEMM   out[t][n] = sum_k W[n][k] * act[t][k]   for m <= 8 tokens,
-// with the epilogues of the layer step and of the vocabulary pass fused in.  Included by the stand-alone GEMM
-// kernel (ad_gemm.hip) and by the fused layer-step kernel (ad_layer_fused.hip).
+// Device side of the weight-streaming skinny GEMM   out[t][n] = sum_k W[n][k] * act[t][k]   for m <= 8 tokens inside the fused
+// layer-step kernel (ad_layer_fused.hip; stand-alone launches have kernels of their own, ad_proj.hip and ad_rows.hip), with
+// the epilogues of the layer step fused in.
 //
 // The contraction is bound by reading W once from HBM (about m flop per byte), so the code is organised
 // around the weight stream: W is stored as 1 KiB MFMA A-operand tiles (see ad_internal.h), a workgroup owns
@@ -9,7 +9,7 @@
 // the 2m hi/lo activation columns; it is idle most of the time.
 //
 // Two ways of feeding the activations (the B operand):
-//  * stationary (QKV, gate/up, exit-head transform, LM head: several row tiles per workgroup, K = d):
+//  * stationary (QKV, gate/up: several row tiles per workgroup, K = d):
 //    8 wavefronts per workgroup; wavefront w owns a fixed K slice for all the workgroup's tiles and keeps its
 //    slice of B in registers.
 //    B is built in the prologue straight from the fp32 activations: x * norm_w split into bf16 hi/lo
@@ -21,7 +21,7 @@
 // Partial accumulators meet in LDS and are summed in wavefront order (fixed order: reproducible).
 //
 // Each mode is split into a *stream* object, which can put the first weight batches in flight before anything
-// that depends on the activations exists (the fused kernel does so before a grid barrier), and the function
+// that depends on the activations exists (before a grid barrier), and the function
 // that consumes it.  The `Io` policy says how data exchanged between workgroups is read and written: plain
 // loads and stores when a kernel boundary orders producer and consumer, agent-scope atomics when both run
 // inside one kernel.
@@ -37,9 +37,7 @@ namespace ad {
 constexpr int kTilesPerRound = 8;       // row tiles reduced together
 constexpr int kStatWaves = 8;           // stationary mode: wavefronts per workgroup (512 threads, up to 256 registers each)
 constexpr int kStatThreads = kStatWaves * 64;
-constexpr int kKsMax = 20;              // stationary mode, fp32 weights and the fused layer kernel: most k-steps per
-                                        // wavefront (K <= 8 * 20 * 32 = 5120)
-constexpr int kKsMaxWide = 32;          // stationary mode, 16-bit weights: K <= 8 * 32 * 32 = 8192
+constexpr int kKsMax = 20;              // stationary mode: most k-steps per wavefront (K <= 8 * 20 * 32 = 5120)
 
 struct GemmLds {
     // stationary: [tile 0..8)[wave][token 0..8)[row 0..16)      streamed: [slot][col 0..16)[row 0..16)
@@ -47,8 +45,6 @@ struct GemmLds {
     float red[kTilesPerRound * 128];    // [tile][token][row]
     float ssq_part[kWaves * 8];
     float scale[8];
-    float run_max[8], run_sum[8];
-    int run_idx[8];
 };
 
 // ---- how data shared between workgroups is accessed ------------------------------------------------------
@@ -116,70 +112,26 @@ struct NoTail {
 
 __device__ __forceinline__ int part_start(int tot, int w, int nw) { return (int)(((long)tot * w) / nw); }
 
-// merge (max, sumexp, argmax) pairs; the lower index wins ties
-__device__ __forceinline__ void lse_merge(float &M, float &S, int &I, float m2, float s2, int i2) {
-    if (m2 > M || (m2 == M && i2 < I)) I = i2;
-    const float nm = fmaxf(M, m2);
-    if (nm == -INFINITY) { M = nm; S = 0.f; return; }
-    S = S * __expf(M - nm) + s2 * __expf(m2 - nm);
-    M = nm;
-}
-
 // ---- epilogue on a reduced round: L.red[T*128 + t*16 + i] holds row (ta+T)*16+i of token t -------------
-// EPI: the epilogue kind when it is known at compile time, or -1 to take g.epi.
+// EPI: the epilogue's kind.
 template <class Io, int EPI, bool F16>
-__device__ __forceinline__ void epilogue(const GemmArgs &g, GemmLds &L, int ta, int nt, int tid, int lane, int wave, int nthreads) {
-    const int epi = EPI >= 0 ? EPI : g.epi;
-    if (epi == EPI_STORE) {
+__device__ __forceinline__ void epilogue(const GemmArgs &g, GemmLds &L, int ta, int nt, int tid, int nthreads) {
+    if (EPI == EPI_STORE) {
         for (int idx = tid; idx < nt * 128; idx += nthreads) {
             const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
             if (t < g.m && n < g.N) Io::st(g.out + (size_t)t * g.ld + n, L.scale[t] * L.red[idx]);
         }
-    } else if (epi == EPI_RESID) {
+    } else if (EPI == EPI_RESID) {
         for (int idx = tid; idx < nt * 128; idx += nthreads) {
             const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
             if (t < g.m && n < g.N) Io::st(g.out + (size_t)t * g.ld + n, Io::ld(g.resid + (size_t)t * g.ld + n) + L.scale[t] * L.red[idx]);
         }
-    } else if (epi == EPI_SWIGLU) {
+    } else {  // EPI_SWIGLU
         for (int idx = tid; idx < nt * 128; idx += nthreads) {
             const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, f = (ta + T) * 8 + i;
             if (t < g.m && i < 8 && f * 2 < g.N) {
                 const float gate = L.scale[t] * L.red[idx], up = L.scale[t] * L.red[idx + 8];
                 store_act_io<Io, F16>((uint16_t *)g.Bnext, g.Bnext_KT, f, t, gate / (1.0f + __expf(-gate)) * up);
-            }
-        }
-    } else if (epi == EPI_PACK) {
-        for (int idx = tid; idx < nt * 128; idx += nthreads) {
-            const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-            if (t < g.m && n < g.N) store_act_io<Io, F16>((uint16_t *)g.Bnext, g.Bnext_KT, n, t, L.scale[t] * L.red[idx]);
-        }
-    } else {  // EPI_HEAD: running (max, sum of exp, argmax) per token over this workgroup's rows
-        if (g.logits) {
-            for (int idx = tid; idx < nt * 128; idx += nthreads) {
-                const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-                if (t < g.m && n < g.N) g.logits[(size_t)t * g.N + n] = L.scale[t] * L.red[idx];
-            }
-        }
-        if (wave < g.m) {
-            const int t = wave;
-            float M = -INFINITY, S = 0.f;
-            int I = 0x7fffffff;
-            for (int j = lane; j < nt * 16; j += 64) {
-                const int n = (ta + (j >> 4)) * 16 + (j & 15);
-                if (n < g.N) lse_merge(M, S, I, L.scale[t] * L.red[(j >> 4) * 128 + t * 16 + (j & 15)], 1.0f, n);
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                const float m2 = __shfl_xor(M, off), s2 = __shfl_xor(S, off);
-                const int i2 = __shfl_xor(I, off);
-                lse_merge(M, S, I, m2, s2, i2);
-            }
-            if (lane == 0) {
-                float rm = L.run_max[t], rsum = L.run_sum[t];
-                int ri = L.run_idx[t];
-                lse_merge(rm, rsum, ri, M, S, I);
-                L.run_max[t] = rm;
-                L.run_sum[t] = rsum;
-                L.run_idx[t] = ri;
             }
         }
     }
@@ -278,12 +230,6 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
     const int tid = thread_index(), lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, gq = lane >> 4, t_lane = n & 7;
     const int t0 = S.t0, t1 = S.t1, ks0 = S.ks0, nks = S.nks, nch = S.nch, total = S.total;
-    const int epi = EPI >= 0 ? EPI : g.epi;
-    if (epi == EPI_HEAD && tid < 8) {
-        L.run_max[tid] = -INFINITY;
-        L.run_sum[tid] = 0.f;
-        L.run_idx[tid] = 0x7fffffff;
-    }
     bf16x8 b[KSB];
 
     // B slice of this wavefront.  Its K slice is read in passes of 8 k-steps = 256 inputs: lane l takes inputs
@@ -442,7 +388,7 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
             L.red[idx] = v;
         }
         __syncthreads();
-        epilogue<Io, EPI, F16>(g, L, ta, nt, tid, lane, wave, kThreads);
+        epilogue<Io, EPI, F16>(g, L, ta, nt, tid, kThreads);
         __syncthreads();
     };
 
@@ -517,12 +463,6 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
     tail();
     __builtin_amdgcn_sched_barrier(0);
     if (t1 > t0) finish_round(t1);
-    if (epi == EPI_HEAD && tid < g.m) {
-        float *p = g.head_part + ((size_t)blockIdx.x * 8 + tid) * 4;
-        p[0] = L.run_max[tid];
-        p[1] = L.run_sum[tid];
-        p[2] = __int_as_float(L.run_idx[tid]);
-    }
 }
 
 // ---- streamed mode -----------------------------------------------------------------------------------------
@@ -578,7 +518,6 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
     constexpr int RP = (kTilesPerRound * 128 + NTHREADS - 1) / NTHREADS;   // residual entries per thread and round
     const int tid = thread_index(), lane = tid & 63, wave = tid >> 6;
     const int t0 = S.t0, t1 = S.t1;
-    const int epi = EPI >= 0 ? EPI : g.epi;
     if (tid < 8) L.scale[tid] = 1.0f;
     const bool bact = (lane & 7) < g.m;
     const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -626,7 +565,7 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
         };
         // residual values of this thread's output entries (and the next GEMM's norm weights for them), ahead of the stream
         float rpre[RP], npre[RP];
-        if (epi == EPI_RESID) {
+        if (EPI == EPI_RESID) {
 #pragma unroll
             for (int j = 0; j < RP; ++j) {
                 const int idx = tid + j * NTHREADS, T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
@@ -696,7 +635,7 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
             }
             return v;
         };
-        if (epi == EPI_RESID) {
+        if (EPI == EPI_RESID) {
             // each thread sums its own output entries and finishes them
 #pragma unroll
             for (int j = 0; j < RP; ++j) {
@@ -722,7 +661,7 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
                 L.red[idx] = t < g.m ? tile_sum(T, t, i) : 0.f;
             }
             __syncthreads();
-            epilogue<Io, EPI, F16>(g, L, ta, nt, tid, lane, wave, NTHREADS);
+            epilogue<Io, EPI, F16>(g, L, ta, nt, tid, NTHREADS);
         }
         __syncthreads();
         if (ONE_ROUND) break;     // (said here as well, so that the body is not compiled as a loop)

@@ -75,7 +75,7 @@ bool config_ok(const ad_config *c, const char **why) {
         if (i && c->exit_layers[i] <= c->exit_layers[i - 1]) { *why = "exit layers must ascend"; return false; }
     }
     if (!(c->rope_base > 0.f) || !(c->rms_eps >= 0.f)) { *why = "bad rope_base / rms_eps"; return false; }
-    if (c->d_model > gemm_max_stationary_k(c->dtype == AD_F32 ? 3 : 1)) { *why = "d_model above 8192 (fp32 models: 5120) is not supported"; return false; }
+    if (c->d_model > rows_max_k(c->dtype == AD_F32 ? 3 : 1)) { *why = "d_model above 8192 (fp32 models: 5120) is not supported"; return false; }
     {
         // the kernels address a packed matrix with a 32-bit byte offset
         const int planes = c->dtype == AD_F32 ? 3 : 1;

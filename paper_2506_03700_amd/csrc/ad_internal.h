@@ -195,10 +195,11 @@ int launch_copy(const void *src, void *dst, size_t bytes, void *stream);
 int launch_zero(void *dst, size_t bytes, void *stream);
 int launch_embed(const EmbedArgs &, void *stream);
 int launch_rope_table(const RopeArgs &, void *stream);
-int gemm_max_stationary_k(int planes);   // largest d_model the stationary GEMM variants cover
+int rows_max_k(int planes);                // largest d_model that the projections' kernels cover
 int launch_gemm(const GemmArgs &, int planes, const LaunchCtx &);   // EPI_HEAD: also launches the vocabulary combine
 bool proj_covers(const GemmArgs &, int planes, int n_wg);           // launch_gemm's choice for projections with few tiles per workgroup
 int launch_proj(const GemmArgs &, int planes, const LaunchCtx &);
+int launch_rows(const GemmArgs &, int planes, int grid, const LaunchCtx &);
 int head_grid(int n_tiles, int n_wg);                               // workgroups launch_gemm uses for n_tiles row tiles
 // The library's own static device array for the vocabulary pass's per-workgroup partials (room for kStaticHeadParts
 // workgroups): its address on the current device, resolved on first use per device.  Allocates nothing.

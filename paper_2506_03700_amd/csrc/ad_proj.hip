@@ -20,48 +20,28 @@
 #include <stdint.h>
 
 #include "ad_device.h"
-#include "ad_gemm_device.h"
 #include "ad_internal.h"
+#include "ad_proj_device.h"
 
 namespace ad {
 
 namespace {
 
-constexpr int kProjWaves = 8;
-constexpr int kProjThreads = kProjWaves * 64;
-constexpr int kStripBytes = 8192;            // a wavefront's 8 k-steps of activations, in operand order
-
-// k-steps per batch of loads; two batches are in flight
+// k-steps per batch of loads; two batches are in flight.  A wavefront of at most four k-steps (K <= 1024) takes batches of two: a
+// batch that it cannot fill repeats its last k-step, and with batches of 8 the 16-bit kernels of the tiny models took 6 us each.
 constexpr int proj_batch(int npl) { return npl == 1 ? 8 : 2; }
+constexpr int kProjSmallBatch = 2;
 constexpr int proj_slots(int h) { return (h + 1) / 2; }         // blocks of 8 tokens x 16 rows a wavefront leaves behind
 constexpr size_t proj_lds_bytes(int h, bool from_x) {
     return (size_t)kProjWaves * (from_x ? kStripBytes : proj_slots(h) * 512) + kProjWaves * 8 * 4;
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-// sum over the 8 lanes of an aligned group of 8
-__device__ __forceinline__ float sum8(float v) {
-    v = dpp_add<0xB1>(v);        // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);        // quad_perm [2, 3, 0, 1]
-    return dpp_add<0x141>(v);    // row_half_mirror: the other four
-}
-// sum over the wavefront, in every lane
-__device__ __forceinline__ float sum64(float v) {
-    v = sum8(v);
-    v = dpp_add<0x140>(v);       // row_mirror: the other eight of 16
-    v += __shfl_xor(v, 16);
-    return v + __shfl_xor(v, 32);
-}
-
-// NPL: planes of a weight tile (fp32 models three).  H: halves of a row tile per workgroup.  FROM_X: the activations are fp32 rows
+// NPL: planes of a weight tile (fp32 models three).  H: halves of a row tile per workgroup.  U: k-steps per batch.  FROM_X: the activations are fp32 rows
 // (times a norm weight, with 1 / rms applied to the result), else a packed block, with or without sums of squares for 1 / rms.
-template <int NPL, int H, bool F16, bool FROM_X>
+template <int NPL, int H, int U, bool F16, bool FROM_X>
 __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     warm_kernel_args<sizeof(GemmArgs)>();
-    constexpr int NF = H / 2, U = proj_batch(NPL), NS = proj_slots(H), TB = NPL * 1024;   // whole tiles, batch, slots, bytes of a tile
+    constexpr int NF = H / 2, NS = proj_slots(H), TB = NPL * 1024;   // whole tiles, slots, bytes of a tile
     constexpr bool HALF = H & 1;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, gq = lane >> 4;
@@ -99,7 +79,6 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
         const int t = half_tile < last_tile ? half_tile : last_tile;
         wh = (unsigned)t * (unsigned)KT * (unsigned)TB + (unsigned)((lane & 48) + upper * 8 + (lane & 7)) * 16u;
     }
-    auto ld = [](const char *p) { return __builtin_nontemporal_load((const bf16x8 *)p); };
     struct Tiles { bf16x8 f[NF][U][NPL], h[HALF ? U / 2 : 1][NPL]; };
     auto load_w = [&](Tiles &a, int k) {
         if (k + U <= kb) {
@@ -110,14 +89,14 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
 #pragma unroll
                 for (int j = 0; j < U; ++j)
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = ld(p + j * TB + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = load_weights(p + j * TB + q * 1024);
             }
             if (HALF) {
                 const char *p = W + (size_t)(wh + o + (unsigned)hi_row * TB);
 #pragma unroll
                 for (int j = 0; j < U / 2; ++j)
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.h[j][q] = ld(p + 2 * j * TB + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.h[j][q] = load_weights(p + 2 * j * TB + q * 1024);
             }
         } else {
 #pragma unroll
@@ -126,7 +105,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
 #pragma unroll
                 for (int f = 0; f < NF; ++f)
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = ld(W + (size_t)(wf[f] + o) + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = load_weights(W + (size_t)(wf[f] + o) + q * 1024);
             }
             if (HALF) {
 #pragma unroll
@@ -134,7 +113,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
                     const int kk = k + 2 * j + hi_row;
                     const unsigned o = wh + (unsigned)(kk < k_ok ? kk : k_ok) * TB;
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.h[j][q] = ld(W + (size_t)o + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.h[j][q] = load_weights(W + (size_t)o + q * 1024);
                 }
             }
         }
@@ -189,86 +168,27 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     Tiles a0, a1;
     bf16x8 b0[U], b1[U];
     if constexpr (FROM_X) {
-        // The wavefront's own k-steps (at most 2 * U), in passes of 8 = 256 inputs: lane l takes inputs 4l .. 4l+3 of every token,
-        // multiplies by the norm weights, splits and writes them in operand order into its strip of LDS, from which each lane
-        // reads its operand registers.  Units of 16 bytes are permuted (u -> u ^ ((u >> 4) & 15)) so that the 8-byte writes of a
-        // wavefront, which all go to the same operand column, spread over the LDS banks.
-        constexpr int NP = (2 * U + 7) / 8, PK = U < 4 ? 2 * U : 8;      // passes, k-steps per pass
-        f32x4 xr[NP][8], wn[NP];
-        u16x4 wr[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int k = (ka + p * 8) * 32 + lane * 4, kc = k < g.K - 4 ? k : g.K - 4;
-            if (NPL == 3) wn[p] = *(const f32x4 *)((const float *)g.norm_w + kc);
-            else wr[p] = *(const u16x4 *)((const uint16_t *)g.norm_w + kc);
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (t < g.m) xr[p][t] = *(const f32x4 *)(g.x + (size_t)t * g.ldx + kc);
-        }
-        load_w(a0, ka);
-        load_w(a1, ka + U);
-        uint16_t *strip16 = (uint16_t *)(lds_raw + wave * WB);
-        const bf16x8 *strip = (const bf16x8 *)strip16;
-        auto sw = [](int u) { return u ^ ((u >> 4) & 15); };
-        float ssq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            if (NPL != 3) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) wn[p][e] = from16<F16>(wr[p][e]);
-            }
-            const int ks = ka + p * 8 + (lane >> 3), k = ks * 32 + (lane & 7) * 4;
-            const bool k_on = ks < kb && k < g.K;
-            const int uu = (lane >> 3) * 64 + ((lane & 7) >> 1) * 16;    // unit of column 0
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (t < g.m) {
-                    u16x4 hi, lo;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float xv = k_on ? xr[p][t][e] : 0.f;
-                        ssq[t] += xv * xv;
-                        uint16_t h, l;
-                        split16<F16>(xv * wn[p][e], h, l);
-                        hi[e] = h;
-                        lo[e] = l;
-                    }
-                    *(u16x4 *)(strip16 + sw(uu + t) * 8 + (lane & 1) * 4) = hi;
-                    *(u16x4 *)(strip16 + sw(uu + 8 + t) * 8 + (lane & 1) * 4) = lo;
-                }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-#pragma unroll
-            for (int jj = 0; jj < PK; ++jj) {
-                const int j = p * 8 + jj;
-                if (j < U) b0[j % U] = strip[sw(jj * 64 + lane)];
-                else b1[j % U] = strip[sw(jj * 64 + lane)];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            if (t < g.m) {
-                const float v = sum64(ssq[t]);
-                if (lane == 0) ssq_part[wave * 8 + t] = v;
-            }
+        operand_from_rows<NPL, 2 * U, F16>(
+            g, ka, kb, lane, (uint16_t *)(lds_raw + wave * WB), ssq_part + wave * 8,
+            [&]() {
+                load_w(a0, ka);
+                if (ka + U < kb) load_w(a1, ka + U);
+            },
+            [&](int j, bf16x8 v) {
+                if (j < U) b0[j % U] = v;
+                else b1[j % U] = v;
+            });
         mma(a0, b0, ka);
         mma(a1, b1, ka + U);
     } else {
         load_b(b0, ka);
         load_w(a0, ka);
-        load_b(b1, ka + U);
-        load_w(a1, ka + U);
-        load_resid();
-        if (g.ssq_in && wave < g.m) {
-            // wavefront t adds up token t's partial sums of squares, per lane and then over the lanes (fixed order)
-            float v = 0.f;
-            for (int i = lane; i < g.ssq_tiles; i += 64) v += g.ssq_in[(size_t)i * 8 + wave];
-            v = sum64(v);
-            if (lane == 0) ssq_part[wave] = v;
+        if (ka + U < kb) {
+            load_b(b1, ka + U);
+            load_w(a1, ka + U);
         }
+        load_resid();
+        if (g.ssq_in) sum_ssq(g, wave, lane, ssq_part);
         // While four whole batches remain, the loads of the loop are unconditional, so that each product waits for its own
         // operands only.
         int k = ka;
@@ -317,15 +237,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     __syncthreads();
     if (wave >= H) return;
 
-    float scale = 1.0f;
-    if (FROM_X) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < kProjWaves; ++w) s += ssq_part[w * 8 + et];
-        scale = 1.0f / sqrtf(s * g.inv_dim + g.eps);
-    } else if (g.ssq_in) {
-        scale = 1.0f / sqrtf(ssq_part[et] * g.inv_dim + g.eps);
-    }
+    const float scale = FROM_X || g.ssq_in ? inv_rms<FROM_X>(g, ssq_part, et) : 1.0f;
     const float *base = (const float *)lds_raw + et * 16 + ei;
     constexpr int WF = WB / 4;                                  // floats from one wavefront's slots to the next one's
     auto sum_rows = [&](const float *p) {
@@ -339,10 +251,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
         const int f = (full0 + wave) * 8 + ei;
         if (!HALF && wave < NF && et < g.m && f * 2 < g.N) {
             const float gate = scale * sum_rows(base + wave * 128), up = scale * sum_rows(base + wave * 128 + 8);
-            uint16_t hi, lo;
-            split16<F16>(gate / (1.0f + __expf(-gate)) * up, hi, lo);
-            ((uint16_t *)g.Bnext)[act_index(f, et, g.Bnext_KT)] = hi;
-            ((uint16_t *)g.Bnext)[act_index(f, 8 + et, g.Bnext_KT)] = lo;
+            store_act<F16>(g.Bnext, g.Bnext_KT, f, et, gate / (1.0f + __expf(-gate)) * up);
         }
         return;
     }
@@ -359,41 +268,38 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     if (g.epi == EPI_STORE) {
         g.out[(size_t)et * g.ld + row] = v;
     } else if (g.epi == EPI_PACK) {
-        uint16_t hi, lo;
-        split16<F16>(v, hi, lo);
-        ((uint16_t *)g.Bnext)[act_index(row, et, g.Bnext_KT)] = hi;
-        ((uint16_t *)g.Bnext)[act_index(row, 8 + et, g.Bnext_KT)] = lo;
+        store_act<F16>(g.Bnext, g.Bnext_KT, row, et, v);
     } else {
         const float y = resid + v;
         g.out[(size_t)et * g.ld + row] = y;
         if (g.Bnext) {
             // input of the next projection: y * norm weight, packed; and these 8 rows' share of sum(y^2)
-            uint16_t hi, lo;
-            split16<F16>(y * next_w, hi, lo);
-            ((uint16_t *)g.Bnext)[act_index(row, et, g.Bnext_KT)] = hi;
-            ((uint16_t *)g.Bnext)[act_index(row, 8 + et, g.Bnext_KT)] = lo;
+            store_act<F16>(g.Bnext, g.Bnext_KT, row, et, y * next_w);
             const float q = sum8(y * y);
             if (ei == 0) g.ssq_out[(size_t)unit * 8 + et] = q;
         }
     }
 }
 
-template <int NPL, int H, bool F16, bool FROM_X>
+template <int NPL, int H, int U, bool F16, bool FROM_X>
 int launch_as(const GemmArgs &g, hipStream_t s) {
     constexpr size_t lds = proj_lds_bytes(H, FROM_X);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_proj<NPL, H, F16, FROM_X>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_proj<NPL, H, U, F16, FROM_X>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_proj<NPL, H, F16, FROM_X>), dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g);
+    hipLaunchKernelGGL((k_proj<NPL, H, U, F16, FROM_X>), dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g);
     return (int)hipGetLastError();
 }
 
 template <int NPL, int H, bool F16>
 int launch_src(const GemmArgs &g, hipStream_t s) {
-    return g.x ? launch_as<NPL, H, F16, true>(g, s) : launch_as<NPL, H, F16, false>(g, s);
+    constexpr int U = proj_batch(NPL);
+    if (NPL == 1 && g.KT <= kProjWaves * 2 * kProjSmallBatch)
+        return g.x ? launch_as<NPL, H, kProjSmallBatch, F16, true>(g, s) : launch_as<NPL, H, kProjSmallBatch, F16, false>(g, s);
+    return g.x ? launch_as<NPL, H, U, F16, true>(g, s) : launch_as<NPL, H, U, F16, false>(g, s);
 }
 
 template <int NPL, bool F16>
