@@ -107,6 +107,47 @@ __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo)
 // infinity (a key whose entry in the cache overflowed): exp(-inf - 0) gives such keys the weight 0, exp(-inf - m) is not a number.
 __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.f : m; }
 
+// ---- sums, maxima and scans over a wavefront, in register moves between lanes (no trip through LDS) ----
+// v of the lane that DPP control CTRL names; `none` where there is no such lane
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v, float none = 0.f) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float read_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+// sum over the 8 lanes of an aligned group of 8
+__device__ __forceinline__ float sum8(float v) {
+    v += dpp<0xB1>(v);           // quad_perm [1, 0, 3, 2]
+    v += dpp<0x4E>(v);           // quad_perm [2, 3, 0, 1]
+    return v + dpp<0x141>(v);    // row_half_mirror: the other four
+}
+// sum over the wavefront
+__device__ __forceinline__ float sum64(float v) {
+    v = sum8(v);
+    v += dpp<0x140>(v);          // row_mirror: the other eight of 16
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+// largest value of the wavefront (values that are no numbers are passed by)
+__device__ __forceinline__ float max64(float v) {
+    v = fmaxf(v, dpp<0xB1>(v));
+    v = fmaxf(v, dpp<0x4E>(v));
+    v = fmaxf(v, dpp<0x141>(v));
+    v = fmaxf(v, dpp<0x140>(v));
+    return fmaxf(fmaxf(read_lane(v, 0), read_lane(v, 16)), fmaxf(read_lane(v, 32), read_lane(v, 48)));
+}
+// sum over the lanes before this one; *total: over all
+__device__ __forceinline__ float scan64(float v, int lane, float *total) {
+    float in = v;                // inclusive within a row of 16 lanes
+    in += dpp<0x111>(in);        // row_shr 1, 2, 4, 8
+    in += dpp<0x112>(in);
+    in += dpp<0x114>(in);
+    in += dpp<0x118>(in);
+    const float r0 = read_lane(in, 15), r1 = r0 + read_lane(in, 31), r2 = r1 + read_lane(in, 47);
+    *total = r2 + read_lane(in, 63);
+    const float ex = dpp<0x111>(in);
+    const int row = lane >> 4;
+    return ex + (row == 0 ? 0.f : row == 1 ? r0 : row == 2 ? r1 : r2);
+}
+
 // merges (max, sum of exp relative to it, argmax); the lower index wins among equal values
 __device__ __forceinline__ void max_merge(float &M, float &S, int &I, float m2, float s2, int i2) {
     if (m2 > M || (m2 == M && i2 < I)) I = i2;

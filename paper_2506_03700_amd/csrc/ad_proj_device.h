@@ -12,24 +12,6 @@ constexpr int kProjWaves = 8;
 constexpr int kProjThreads = kProjWaves * 64;
 constexpr int kStripBytes = 8192;            // a wavefront's 8 k-steps of activations, in operand order
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-// sum over the 8 lanes of an aligned group of 8
-__device__ __forceinline__ float sum8(float v) {
-    v = dpp_add<0xB1>(v);        // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);        // quad_perm [2, 3, 0, 1]
-    return dpp_add<0x141>(v);    // row_half_mirror: the other four
-}
-// sum over the wavefront, in every lane
-__device__ __forceinline__ float sum64(float v) {
-    v = sum8(v);
-    v = dpp_add<0x140>(v);       // row_mirror: the other eight of 16
-    v += __shfl_xor(v, 16);
-    return v + __shfl_xor(v, 32);
-}
-
 __device__ __forceinline__ bf16x8 load_weights(const char *p) { return __builtin_nontemporal_load((const bf16x8 *)p); }
 
 // The B operand of this wavefront's k-steps [ka, kb), at most KS of them, from fp32 rows: put(j, v) receives the operand registers of

@@ -6,71 +6,55 @@
 // Every draw is a uniform number u in [0, 1) handed in by the caller and turned into a token by inversion of
 // the cumulative distribution in token-id order: the first id whose cumulative weight exceeds u * (total
 // weight).  A row is cut into segments of consecutive ids, one workgroup each: a first kernel leaves each segment's maximum
-// and sum of weights, a second one (one workgroup) finds the segment that holds the target from those and walks that
-// segment alone.  What bounds these calls is not the row (0.5 MB) but the chain of dependent loads, reductions and kernel
+// and sum of weights, a second one (one workgroup) finds the segment that holds the target from those (in every wavefront at once)
+// and walks that segment alone.  What bounds these calls is not the row (0.5 MB) but the chain of dependent loads, reductions and kernel
 // boundaries: with one workgroup that passed over the whole row three times a draw from 128256 logits took 97 us on the
-// GPU; the sums are added up in a fixed order (no float atomics), so everything is deterministic.
+// GPU, with segments and every reduction and scan through LDS 12.5, now that they move between registers and the wavefronts repeat
+// what is small instead of waiting for one of them 6.4 (a call 31.8 -> 26.2; verification of 6 rows 21.3 -> 15.1, a call 46.9 ->
+// 37.4); the sums are added up in a fixed order (no float atomics), so everything is deterministic.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include "ad_device.h"
 #include "ad_internal.h"
 
 namespace ad {
 
 namespace {
 
-constexpr int kSampleThreads = 512;              // measured against 256 and 1024: 8 rows of 128256 logits 46.7, 51.8, 51.3 us a call
+constexpr int kSampleThreads = 512;              // against 256: 4 rows of 128256 logits 35.4, 37.6 us a call, 1 and 8 rows alike
 constexpr int kSampleWaves = kSampleThreads / 64;
 constexpr int kSegIds = 2048;                    // ids per segment, until there are as many segments as a workgroup has threads
 
 struct SampleLds {
-    float wave_val[kSampleWaves];
-    float bcast[4];
-    int best;
+    float wave_val[2][kSampleWaves];
+    int wave_id[2][kSampleWaves];
     int last_pos;
 };
 
 // (largest value, sum of the weights relative to it) of a segment
 struct SegStat { float mx, sum; };
 
-__device__ __forceinline__ float wave_max(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
-}
-
-// max over the workgroup, returned to every thread
-__device__ __forceinline__ float block_max(float v, SampleLds &L) {
-    v = wave_max(v);
+// max over the workgroup, returned to every thread (slot: which of the two exchanges in LDS)
+__device__ __forceinline__ float block_max(float v, SampleLds &L, int slot) {
+    v = max64(v);
+    if ((threadIdx.x & 63) == 0) L.wave_val[slot][threadIdx.x >> 6] = v;
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) L.wave_val[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = L.wave_val[0];
+    float r = L.wave_val[slot][0];
 #pragma unroll
-    for (int w = 1; w < kSampleWaves; ++w) r = fmaxf(r, L.wave_val[w]);
+    for (int w = 1; w < kSampleWaves; ++w) r = fmaxf(r, L.wave_val[slot][w]);
     return r;
 }
 
-// Exclusive prefix of `local` over the threads in thread order (fixed association: butterfly-free scan inside a
-// wavefront, then the wavefront totals in order); *total receives the sum over the workgroup.
-__device__ __forceinline__ float block_exclusive_scan(float local, SampleLds &L, float *total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float incl = local;
-    for (int off = 1; off < 64; off <<= 1) {
-        const float up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-    }
+__device__ __forceinline__ float block_sum(float v, SampleLds &L, int slot) {
+    v = sum64(v);
+    if ((threadIdx.x & 63) == 0) L.wave_val[slot][threadIdx.x >> 6] = v;
     __syncthreads();
-    if (lane == 63) L.wave_val[wave] = incl;
-    __syncthreads();
-    float before = 0.f, all = 0.f;
+    float r = L.wave_val[slot][0];
 #pragma unroll
-    for (int w = 0; w < kSampleWaves; ++w) {
-        if (w < wave) before += L.wave_val[w];
-        all += L.wave_val[w];
-    }
-    *total = all;
-    return before + (incl - local);
+    for (int w = 1; w < kSampleWaves; ++w) r += L.wave_val[slot][w];
+    return r;
 }
 
 // a segment's sum relative to the row's largest value (a segment without weight has none, whatever its maximum)
@@ -78,37 +62,80 @@ __device__ __forceinline__ float rescaled(SegStat s, float mx, float inv_t) {
     return (s.sum == 0.f) ? 0.f : s.sum * expf((s.mx - mx) * inv_t);
 }
 
-// Inversion draw over the weights w(j) >= 0 of a row whose segments' statistics are in `seg` (thread t: segment t; the
-// weights are relative to mx, a segment's to its own maximum, which inv_t scales).  Returns (to every thread) the token, its
-// weight and the total weight.  No id of positive weight: token -1.
+constexpr int kLaneSegs = kSampleThreads / 64;           // most segments per lane of a wavefront
+
+// A row's segments in the registers of a wavefront (every wavefront of the workgroup does the same, which saves the barriers):
+// lane l holds segments l * per .. + per - 1.
+struct RowSegs {
+    SegStat v[kLaneSegs];
+    int per, lane;
+    __device__ __forceinline__ void load(const SegStat *seg, int n_seg) {
+        lane = threadIdx.x & 63;
+        per = (n_seg + 63) >> 6;
+#pragma unroll
+        for (int i = 0; i < kLaneSegs; ++i) {
+            v[i] = SegStat{-INFINITY, 0.f};
+            if (i < per && lane * per + i < n_seg) v[i] = seg[lane * per + i];
+        }
+    }
+    __device__ __forceinline__ void one(SegStat s) {     // a row of one segment
+        lane = threadIdx.x & 63;
+        per = 1;
+        v[0] = lane == 0 ? s : SegStat{-INFINITY, 0.f};
+    }
+    __device__ __forceinline__ float max() const {
+        float m = v[0].mx;
+#pragma unroll
+        for (int i = 1; i < kLaneSegs; ++i)
+            if (i < per) m = fmaxf(m, v[i].mx);
+        return max64(m);
+    }
+    // turns the sums into weights relative to mx; returns this lane's
+    __device__ __forceinline__ float rescale(float mx, float inv_t) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < kLaneSegs; ++i)
+            if (i < per) {
+                v[i].sum = rescaled(v[i], mx, inv_t);
+                s += v[i].sum;
+            }
+        return s;
+    }
+};
+
+// What a draw gives every thread: the token (-1: no id of positive weight), the total weight; `owner` is set in the one thread
+// that is to report it, with the token's weight w.
+struct Draw { int tok; float total, w; bool owner; };
+
+// Inversion draw over the weights w(j) >= 0 of a row whose segments are in `segs`, rescaled (segment's weights are relative to its
+// own maximum); `mine`: this lane's share of the total.  The draw is a chain: one wavefront-wide scan finds the segment, its ids
+// are loaded, one scan over the workgroup finds the id (two barriers).
 template <class W>
-__device__ __forceinline__ int sample_segments(W w, const SegStat *seg, float mx, float inv_t, int V, int n_seg, int seg_ids, float u, SampleLds &L,
-                                               float *w_tok, float *total_out) {
-    const int tid = threadIdx.x;
-    float total, target;
-    int s = 0;
-    if (tid == 0) {
-        L.best = 0x7fffffff;
-        L.last_pos = -1;
-        L.bcast[1] = 0.f;
-    }
-    if (n_seg == 1) {
-        total = rescaled(seg[0], mx, inv_t);
-        target = u * total;
-        if (!(total > target)) s = 0x7fffffff;
-        __syncthreads();
-    } else {
-        const float mine = tid < n_seg ? rescaled(seg[tid], mx, inv_t) : 0.f;
-        const float before = block_exclusive_scan(mine, L, &total);
-        target = u * total;
-        if (mine > 0.f && before + mine > target) atomicMin(&L.best, tid);
-        __syncthreads();
-        s = L.best;
-        if (s != 0x7fffffff && tid == s) L.bcast[1] = before;
-        __syncthreads();
-    }
-    int tok = -1;
-    if (s != 0x7fffffff) {
+__device__ __forceinline__ Draw draw_from(W w, const RowSegs &segs, float mine, int V, int seg_ids, float u, SampleLds &L) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float total;
+    const float before = scan64(mine, lane, &total), target = u * total;
+    Draw d{-1, total, 0.f, false};
+    const unsigned long long hits = __ballot(mine > 0.f && before + mine > target);
+    if (hits) {
+        // the first lane that reaches the target, and in it the first segment that does (the two sums may round differently:
+        // then its last segment with weight)
+        int s = 0;
+        float at_s = before, c = before;
+        bool found = false;
+#pragma unroll
+        for (int i = 0; i < kLaneSegs; ++i)
+            if (i < segs.per) {
+                if (!found && segs.v[i].sum > 0.f) {
+                    s = lane * segs.per + i;
+                    at_s = c;
+                    found = c + segs.v[i].sum > target;
+                }
+                c += segs.v[i].sum;
+            }
+        const int l0 = __ffsll(hits) - 1;
+        s = __builtin_amdgcn_readlane(s, l0);
+        at_s = read_lane(at_s, l0);
         // walk the segment: thread t owns consecutive ids, added up in id order
         const int per = (seg_ids + kSampleThreads - 1) / kSampleThreads;
         const int end = min(V, (s + 1) * seg_ids), j0 = min(end, s * seg_ids + tid * per), j1 = min(end, j0 + per);
@@ -127,31 +154,62 @@ __device__ __forceinline__ int sample_segments(W w, const SegStat *seg, float mx
             local += y;
             if (y > 0.f) last = j;
         }
-        float seg_total;
-        const float at = L.bcast[1] + block_exclusive_scan(local, L, &seg_total);
-        if (tid == 0) L.best = 0x7fffffff;
+        float wave_total;
+        float at = scan64(local, lane, &wave_total);
+        const unsigned long long live = __ballot(last >= 0);
+        if (lane == 0) L.wave_val[0][wave] = wave_total;
+        if (live && lane == 63 - __clzll(live)) L.wave_id[0][wave] = last;
+        if (!live && lane == 0) L.wave_id[0][wave] = -1;
         __syncthreads();
+        float ahead = 0.f;
+        int seg_last = -1;
+#pragma unroll
+        for (int k = 0; k < kSampleWaves; ++k) {
+            ahead += k < wave ? L.wave_val[0][k] : 0.f;
+            if (L.wave_id[0][k] >= 0) seg_last = L.wave_id[0][k];
+        }
+        at += at_s + ahead;
+        int hit = 0x7fffffff;
+        float w_hit = 0.f;
         if (at + local > target || at > target) {
-            float c = at;
-            int hit = 0x7fffffff;
+            float c2 = at;
 #pragma unroll
             for (int i = 0; i < kKeep; ++i) {
-                c += x[i];
-                if (c > target && x[i] > 0.f && hit == 0x7fffffff) hit = j0 + i;
+                c2 += x[i];
+                if (c2 > target && x[i] > 0.f && hit == 0x7fffffff) {
+                    hit = j0 + i;
+                    w_hit = x[i];
+                }
             }
             for (int j = j0 + kKeep; j < j1 && hit == 0x7fffffff; ++j) {
                 const float y = w(j);
-                c += y;
-                if (c > target && y > 0.f) hit = j;
+                c2 += y;
+                if (c2 > target && y > 0.f) {
+                    hit = j;
+                    w_hit = y;
+                }
             }
-            if (hit != 0x7fffffff) atomicMin(&L.best, hit);
         }
-        if (last >= 0) atomicMax(&L.last_pos, last);
+        // the wavefront's lowest id (its first lane with one), then the lowest of the wavefronts'
+        const unsigned long long got = __ballot(hit != 0x7fffffff);
+        const int wave_hit = got ? __builtin_amdgcn_readlane(hit, __ffsll(got) - 1) : 0x7fffffff;
+        if (lane == 0) L.wave_id[1][wave] = wave_hit;
         __syncthreads();
-        // the two ways of adding the segment up may round differently: then its last id of positive weight
-        tok = (L.best != 0x7fffffff) ? L.best : L.last_pos;
+        int tok = 0x7fffffff;
+#pragma unroll
+        for (int k = 0; k < kSampleWaves; ++k) tok = min(tok, L.wave_id[1][k]);
+        if (tok != 0x7fffffff) {
+            d.tok = tok;
+            d.w = w_hit;
+            d.owner = hit == tok;
+        } else if (seg_last >= 0) {
+            // the two ways of adding the segment up may round differently: then its last id of positive weight
+            d.tok = seg_last;
+            d.owner = tid == 0;
+            if (d.owner) d.w = w(seg_last);
+        }
     }
-    if (tok < 0) {
+    if (d.tok < 0) {
         // rounding left nothing above the target (u * total == total), or a sum is not a number: the row's last id of
         // positive weight
         __syncthreads();
@@ -162,11 +220,11 @@ __device__ __forceinline__ int sample_segments(W w, const SegStat *seg, float mx
         __syncthreads();
         if (last >= 0) atomicMax(&L.last_pos, last);
         __syncthreads();
-        tok = L.last_pos;
+        d.tok = L.last_pos;
+        d.owner = tid == 0;
+        d.w = d.owner && d.tok >= 0 ? w(d.tok) : 0.f;
     }
-    *w_tok = tok >= 0 ? w(tok) : 0.f;
-    *total_out = total;
-    return tok;
+    return d;
 }
 
 struct SoftmaxWeight {
@@ -199,7 +257,7 @@ __device__ __forceinline__ SegStat segment_stat(const float *z, int j0, int j1, 
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) m = fmaxf(m, v[i]);
     for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) m = fmaxf(m, z[j]);
-    m = block_max(m, L);
+    m = block_max(m, L, 0);
     float s = 0.f;
     if (m != -INFINITY) {
 #pragma unroll
@@ -213,9 +271,7 @@ __device__ __forceinline__ SegStat segment_stat(const float *z, int j0, int j1, 
         for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads)
             if (z[j] != z[j]) s = z[j];
     }
-    float total;
-    (void)block_exclusive_scan(s, L, &total);
-    return SegStat{m, total};
+    return SegStat{m, block_sum(s, L, 1)};
 }
 
 // Segment blockIdx.x of row blockIdx.y: rows [0, n_first) start at z0, the others at z1.
@@ -229,40 +285,28 @@ __global__ void __launch_bounds__(kSampleThreads) k_segment_stats(SegArgs a) {
     if (threadIdx.x == 0) a.out[(size_t)r * a.n_seg + blockIdx.x] = st;
 }
 
-// (max z, sum exp((z - max) * inv_t)) of a row from its segments, by one wavefront, to all its lanes
-__device__ __forceinline__ SegStat row_from_segments(const SegStat *seg, int n_seg, float inv_t) {
-    const int lane = threadIdx.x & 63;
-    SegStat v[kSampleThreads / 64];
-    float m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kSampleThreads / 64; ++i) {
-        v[i] = lane + 64 * i < n_seg ? seg[lane + 64 * i] : SegStat{-INFINITY, 0.f};
-        m = fmaxf(m, v[i].mx);
-    }
-    m = wave_max(m);
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < kSampleThreads / 64; ++i) s += rescaled(v[i], m, inv_t);
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    return SegStat{m, s};
+// (max z, sum exp((z - max) * inv_t)) of a row from its segments, by one wavefront
+__device__ __forceinline__ SegStat row_from_segments(RowSegs &segs, float inv_t) {
+    const float m = segs.max();
+    return SegStat{m, sum64(segs.rescale(m, inv_t))};
 }
 
 // seg: the segments' statistics, or null for a row of one segment, whose statistics are formed here (one kernel less)
 __global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, const SegStat *seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
-    __shared__ SegStat only;
-    if (!seg) {
+    RowSegs segs;
+    if (seg) {
+        segs.load(seg, n_seg);
+    } else {
         const SegStat st = segment_stat(a.z, 0, a.V, a.inv_t, L);
-        if (threadIdx.x == 0) only = st;
+        segs.one(st);
         __syncthreads();
-        seg = &only;
     }
-    const float mx = block_max((int)threadIdx.x < n_seg ? seg[threadIdx.x].mx : -INFINITY, L);
-    float w_tok, total;
-    const int tok = sample_segments(SoftmaxWeight{a.z, mx, a.inv_t}, seg, mx, a.inv_t, a.V, n_seg, seg_ids, a.u, L, &w_tok, &total);
-    if (threadIdx.x == 0) {
-        *a.tok_out = tok;
-        *a.prob_out = w_tok / total;
+    const float mx = segs.max(), mine = segs.rescale(mx, a.inv_t);
+    const Draw d = draw_from(SoftmaxWeight{a.z, mx, a.inv_t}, segs, mine, a.V, seg_ids, a.u, L);
+    if (d.owner) {
+        *a.tok_out = d.tok;
+        *a.prob_out = d.w / d.total;
     }
 }
 
@@ -275,62 +319,62 @@ __device__ __forceinline__ SegStat row_from_logits(const float *z, int V, float 
         v[i] = lane + 64 * i < V ? z[lane + 64 * i] : -INFINITY;
         m = fmaxf(m, v[i]);
     }
-    m = wave_max(m);
+    m = max64(m);
     if (m != -INFINITY) {
 #pragma unroll
         for (int i = 0; i < kSegIds / 64; ++i) s += expf((v[i] - m) * inv_t);
     }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    return SegStat{m, s};
+    return SegStat{m, sum64(s)};
 }
 
 // Eq. 2 over the drafts, computed by every workgroup that needs the outcome (the same sums in the same order).
 struct Decision { int n_acc, rejected; SegStat f, q; };      // of row n_acc: statistics of its final and draft logits
 
-// Where the rows' statistics come from.  A kernel is built for one source: in one kernel for all, which also reduced the rows of one
-// segment, 5 and 8 rows of 2048 logits took 37.9 us a call and not 36.1.
+// Where the rows' statistics come from.  A kernel is built for one source: one kernel for all, which also reduced the rows of one
+// segment, took 37.9 us a call for 5 and 8 rows of 2048 logits when three kernels took 36.1 (31.7 now).
 enum RowSource { ROWS_LOGITS, ROWS_SEGMENT, ROWS_SEGMENTS };     // the logits, one segment per row, several
 
 template <RowSource SRC>
 __device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const SegStat *seg, int n_seg, bool write_ratio) {
     __shared__ SegStat row[16];
-    __shared__ int s_rejected;                       // the first rejected draft, n_draft if none is
-    const int wave = threadIdx.x >> 6, n_draft = a.m - 1;
-    const int n_rows = 2 * a.m - 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_draft = a.m - 1, n_rows = 2 * a.m - 1;
+    // a lane per draft, in every wavefront
+    const int k = lane, t = k < n_draft ? a.draft[k] : 0;
+    const float zf = k < n_draft ? a.zf[(size_t)k * a.V + t] : 0.f, zq = k < n_draft ? a.zq[(size_t)k * a.V + t] : 0.f;
     if (SRC == ROWS_SEGMENT) {
         if ((int)threadIdx.x < n_rows) row[threadIdx.x] = seg[threadIdx.x];
     } else if (SRC == ROWS_SEGMENTS) {
-        for (int r = wave; r < n_rows; r += kSampleWaves) {
-            const SegStat st = row_from_segments(seg + (size_t)r * n_seg, n_seg, a.inv_t);
-            if ((threadIdx.x & 63) == 0) row[r] = st;
+        RowSegs s0, s1;                              // at most two rows per wavefront
+        const int r1 = wave + kSampleWaves;
+        if (wave < n_rows) s0.load(seg + (size_t)wave * n_seg, n_seg);
+        if (r1 < n_rows) s1.load(seg + (size_t)r1 * n_seg, n_seg);
+        if (wave < n_rows) {
+            const SegStat st = row_from_segments(s0, a.inv_t);
+            if (lane == 0) row[wave] = st;
+        }
+        if (r1 < n_rows) {
+            const SegStat st = row_from_segments(s1, a.inv_t);
+            if (lane == 0) row[r1] = st;
         }
     } else if (wave < n_rows) {                      // (at most a row per wavefront)
         const int r = wave;
         const SegStat st = row_from_logits(r < a.m ? a.zf + (size_t)r * a.V : a.zq + (size_t)(r - a.m) * a.V, a.V, a.inv_t);
-        if ((threadIdx.x & 63) == 0) row[r] = st;
-    }
-    // a lane per draft
-    const int k = threadIdx.x, t = k < n_draft ? a.draft[k] : 0;
-    const float zf = k < n_draft ? a.zf[(size_t)k * a.V + t] : 0.f, zq = k < n_draft ? a.zq[(size_t)k * a.V + t] : 0.f;
-    __syncthreads();
-    if (wave == 0) {
-        float ratio = 0.f;
-        bool rejected = false;
-        if (k < n_draft) {
-            // p*(t) / p_draft(t) through the logarithms, so that two tiny probabilities still have a ratio
-            const float lp = (zf - row[k].mx) * a.inv_t - logf(row[k].sum), lq = (zq - row[a.m + k].mx) * a.inv_t - logf(row[a.m + k].sum);
-            ratio = expf(lp - lq);
-            rejected = !(a.u_accept[k] < fminf(1.0f, ratio));
-        }
-        const unsigned long long mask = __ballot(rejected);
-        const int first = mask ? __ffsll(mask) - 1 : n_draft;
-        if (k == 0) s_rejected = first;
-        if (write_ratio && a.ratio_out && k < n_draft) a.ratio_out[k] = k <= first ? ratio : 0.f;
+        if (lane == 0) row[r] = st;
     }
     __syncthreads();
+    float ratio = 0.f;
+    bool rejected = false;
+    if (k < n_draft) {
+        // p*(t) / p_draft(t) through the logarithms, so that two tiny probabilities still have a ratio
+        const float lp = (zf - row[k].mx) * a.inv_t - logf(row[k].sum), lq = (zq - row[a.m + k].mx) * a.inv_t - logf(row[a.m + k].sum);
+        ratio = expf(lp - lq);
+        rejected = !(a.u_accept[k] < fminf(1.0f, ratio));
+    }
+    const unsigned long long mask = __ballot(rejected);
     Decision d;
-    d.n_acc = s_rejected;
-    d.rejected = s_rejected < n_draft;
+    d.n_acc = mask ? __ffsll(mask) - 1 : n_draft;    // the first rejected draft, n_draft if none is
+    d.rejected = d.n_acc < n_draft;
+    if (write_ratio && wave == 0 && a.ratio_out && k < n_draft) a.ratio_out[k] = k <= d.n_acc ? ratio : 0.f;
     d.f = row[d.n_acc];
     d.q = d.rejected ? row[a.m + d.n_acc] : SegStat{0.f, 0.f};
     return d;
@@ -358,63 +402,62 @@ __device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j
         const float a = w.log_p(j);
         if (a > w.log_q(j)) c = fmaxf(c, a);
     }
-    w.c = block_max(c, L);
+    w.c = block_max(c, L, 0);
     float s = 0.f;
     if (w.c != -INFINITY) {
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) s += w.weight(la[i], lb[i]);
         for (int j = j0 + (int)threadIdx.x + kKeep * kSampleThreads; j < j1; j += kSampleThreads) s += w(j);
     }
-    float total;
-    (void)block_exclusive_scan(s, L, &total);
-    return SegStat{w.c, total};
+    return SegStat{w.c, block_sum(s, L, 1)};
 }
 
-// The residual's segments, if a draft was rejected.
-__global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out) {
+// The decision, and the residual's segments if a draft was rejected.  The first workgroup leaves the decision (and the ratios) for the
+// last kernel, which then needs neither the rows' statistics nor the drafts.
+__global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out, Decision *dec) {
     __shared__ SampleLds L;
-    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, false);
+    const bool first = blockIdx.x == 0;
+    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, first);
+    if (first && threadIdx.x == 0) *dec = d;
     if (!d.rejected) return;
     const int j0 = blockIdx.x * seg_ids;
     const SegStat st = residual_stat(residual_of(a, d), j0, min(a.V, j0 + seg_ids), L);
     if (threadIdx.x == 0) out[blockIdx.x] = st;
 }
 
-// seg: null for ROWS_LOGITS; res_seg: null but for ROWS_SEGMENTS (a residual of one segment is formed here)
+// seg: null for ROWS_LOGITS; res_seg, dec: of the kernel before (several segments and more than one row), else null and the decision is
+// taken here (a residual of one segment is formed here)
 template <RowSource SRC>
-__global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, int n_seg, int seg_ids) {
+__global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, const Decision *dec, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
-    __shared__ SegStat only;
-    const Decision d = decide<SRC>(a, seg, n_seg, true);
+    RowSegs segs;
+    Decision d;
+    if (SRC == ROWS_SEGMENTS && dec) {
+        segs.load(res_seg, n_seg);                   // (whatever the decision: not used if no draft was rejected)
+        d = *dec;
+    } else {
+        d = decide<SRC>(a, seg, n_seg, true);
+    }
     const int r = d.n_acc;
-    int tok = -1;
-    float w_tok, total;
+    Draw dr{-1, 0.f, 0.f, false};
     if (d.rejected) {
         ResidualWeight w = residual_of(a, d);
-        if (SRC != ROWS_SEGMENTS) {
-            const SegStat st = residual_stat(w, 0, a.V, L);
-            if (threadIdx.x == 0) only = st;
-            __syncthreads();
-            res_seg = &only;
-        }
-        w.c = block_max((int)threadIdx.x < n_seg ? res_seg[threadIdx.x].mx : -INFINITY, L);
-        if (w.c != -INFINITY) tok = sample_segments(w, res_seg, w.c, 1.0f, a.V, n_seg, seg_ids, a.u_resample[r], L, &w_tok, &total);
+        if (SRC != ROWS_SEGMENTS) segs.one(residual_stat(w, 0, a.V, L));
         __syncthreads();
+        w.c = segs.max();
+        const float mine = segs.rescale(w.c, 1.0f);
+        if (w.c != -INFINITY) dr = draw_from(w, segs, mine, a.V, seg_ids, a.u_resample[r], L);
     }
-    const SegStat *row_seg = &only;
-    if (SRC == ROWS_SEGMENTS) {
-        row_seg = seg + (size_t)r * n_seg;
-    } else {
+    if (dr.tok < 0) {  // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
+        if (SRC == ROWS_SEGMENTS) segs.load(seg + (size_t)r * n_seg, n_seg);
+        else segs.one(d.f);
         __syncthreads();
-        if (threadIdx.x == 0) only = d.f;
-        __syncthreads();
+        const float mine = segs.rescale(d.f.mx, a.inv_t);
+        dr = draw_from(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, segs, mine, a.V, seg_ids, d.rejected ? a.u_resample[r] : a.u_final, L);
     }
-    if (tok < 0)       // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
-        tok = sample_segments(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, row_seg, d.f.mx, a.inv_t, a.V, n_seg, seg_ids,
-                              d.rejected ? a.u_resample[r] : a.u_final, L, &w_tok, &total);
-    if (threadIdx.x == 0) {
+    if (dr.owner) {
         *a.n_accept_out = r;
-        *a.next_out = tok;
+        *a.next_out = dr.tok;
     }
 }
 
@@ -427,7 +470,7 @@ void segments(int V, int *n_seg, int *seg_ids) {
 
 }  // namespace
 
-static_assert(sizeof(SegStat) * 16 * kSampleThreads <= kSampleScratchBytes, "the segments of 15 rows and of a residual");
+static_assert(sizeof(SegStat) * 16 * kSampleThreads + sizeof(Decision) <= kSampleScratchBytes, "the segments of 15 rows and of a residual, the decision");
 
 int launch_sample_row(const SampleArgs &a, void *stream) {
     if (a.V < 1 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
@@ -449,11 +492,12 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
     SegStat *seg = nullptr, *res_seg = nullptr;
+    Decision *dec = nullptr;
     const dim3 wg(kSampleThreads);
     int rc;
     // rows of one segment: up to as many as a workgroup has wavefronts are cheaper to reduce in the last kernel than in one of
-    // their own (2048 logits, 3 rows: 33.6 against 35.4 us a call; more take a kernel of their own, one kernel for 15 rows took
-    // 39.5 against 38.2), and the residual always is
+    // their own (2048 logits, 3 rows: 28.5 against 29.3 us a call, 4 rows 31.2 / 31.9; more take a kernel of their own), and the
+    // residual always is
     if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
         hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
@@ -461,12 +505,13 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     }
     if (n_seg > 1 && a.m > 1) {
         res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
-        hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg);
+        dec = (Decision *)(seg + (size_t)16 * kSampleThreads);
+        hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg, dec);
         if ((rc = (int)hipGetLastError())) return rc;
     }
-    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
-    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
-    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
+    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
+    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
+    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
     return (int)hipGetLastError();
 }
 
