@@ -6,7 +6,8 @@
 //   V [kv head][head_dim][position 0..stride)   (transposed, so that 8 consecutive positions of one
 //                                                dimension are one 128-bit load: the MFMA operand of P.V)
 //
-// Work item (kv head g, split s): cache positions [s*C, min((s+1)*C, pos0)) of head g; the last split also
+// Work item (kv head g, split s): cache positions [s*C, min((s+1)*C, pos0)) of head g (none in the last split, where the
+// call's own rows are an item of their own); the last split also
 // takes the call's own m rows (rotated, rounded to the cache type, appended to the cache, attended to under
 // the causal mask).  All G*m query rows of the group are processed against each K/V element while it is in
 // registers or LDS, so the cache is read once.  An item writes one unnormalised partial (o[dh], max, sum)
@@ -33,8 +34,9 @@ namespace ad {
 // layout of O^T = V^T P^T, K and V^T loaded from the cache straight into operand registers.  Query rows fill all 16
 // columns of a tile and their hi and lo parts are two operands (not two halves of the columns), so no score, exponential
 // or output is computed twice.  Wavefront w takes blocks w, w + 4, ... of the item under an online softmax (its next K is
-// requested as soon as the scores are formed, its next V after the second product); the last wavefront of the item that
-// holds the end of the cache then takes the call's own rows as one more block.  The four wavefronts' results meet in LDS.
+// requested as soon as the scores are formed, its next V after the second product); the last wavefront of the last item
+// (an item without cached positions, where that leaves one item per compute unit; else the one that holds the end of the
+// cache) takes the call's own rows as one more block.  The four wavefronts' results meet in LDS.
 //
 // An item is a chain of dependent steps, whatever its size, so what counts is its length and how many run at once (a layer's
 // cache at context 9203 is read in 6 us).  Layer step of the 8B shape, one layer over and over, against the kernel this replaces (hi and lo parts in the
@@ -53,7 +55,7 @@ struct AttnDecLds {
 };
 
 template <int DH, bool F16, int RT, int NRH>
-__global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
+__global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArgs a) {
     warm_kernel_args<sizeof(AttnArgs)>();
     constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, RP = RT * NRH * 16, NTH = 256 * NRH;
     constexpr float kPScale = F16 ? 1024.0f : 1.0f;        // keeps small probabilities out of fp16's subnormals
@@ -64,7 +66,7 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
     const int G = a.G, R = a.R;
     const int item = blockIdx.x, g = div_small(item, a.mul_S), s = item - g * a.S;
     const int c0 = s * a.C, c1 = (c0 + a.C < a.pos0) ? c0 + a.C : a.pos0;
-    const int nc = (c1 > c0) ? c1 - c0 : 0, nbc = (nc + 31) / 32;
+    const int nc = (c1 > c0) ? c1 - c0 : 0, nbc = (nc + 31) / 32;       // (none in an item of the own rows alone: c0 >= pos0)
     const bool last = (s == a.S - 1);
     uint16_t *Kg = (uint16_t *)a.Kc + (size_t)g * a.stride * DH;
     uint16_t *Vg = (uint16_t *)a.Vc + (size_t)g * DH * a.stride;
@@ -307,55 +309,59 @@ __global__ void __launch_bounds__(256 * NRH, 2) k_attn_dec(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp32 cache: plain vector-ALU kernel (the model is small)
+// fp32 cache: vector-ALU kernel (the model is small)
 // ---------------------------------------------------------------------------------------------------
-constexpr int kValuThreads = 1024;
+// An item is a chain of instructions and three barriers.  K and V go from the cache into registers, once for all query rows and before
+// anything else: a thread holds 16 dimensions of one key (DH / 16 neighbouring lanes have the rest) and 16 keys of one dimension
+// (512 / DH neighbouring lanes have the rest); dot products and sums are finished by moves between lanes.  Against the kernel
+// before it (1024 threads, K and V through LDS, all query rows of a head in one workgroup): 4 heads of 64, context 47, 1 row 6.1 ->
+// 4.1 us; 2 kv heads, context 500, 12 query rows per head 14.3 -> 4.7 (10.2 with all rows in one workgroup).
+constexpr int kValuThreads = 512;
 constexpr int kValuMaxRows = 32;
-// keys per work item: a chunk of cached positions plus up to 8 new rows; sized so that the K and V tiles fit LDS
-constexpr int valu_max_keys(int dh) { return dh <= 64 ? 136 : 72; }
+constexpr int valu_chunk(int dh) { return kValuThreads * 16 / dh; }      // cached positions per item: a key per DH / 16 threads
 
 template <int DH>
-__global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
-    constexpr int KROW = DH + 4;      // padded row against LDS bank conflicts
-    constexpr int MAXK = valu_max_keys(DH);
-    constexpr int half = DH / 2;
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+__global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
+    warm_kernel_args<sizeof(AttnArgs)>();
+    constexpr int C = valu_chunk(DH), LK = DH / 16, TE = kValuThreads / DH, half = DH / 2, MAXK = C + 8, PR = DH + 2;
+    __shared__ __attribute__((aligned(16))) float qs[kValuMaxRows][DH], sc[kValuMaxRows][MAXK], knew[8][DH], vnew[8][DH];
+    __shared__ float st[kValuMaxRows][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = a.Hq / a.Hkv, R = G * a.m;
-    float *qs = (float *)lds_raw;                   // [kValuMaxRows][DH]
-    float *sc = qs + kValuMaxRows * DH;             // [kValuMaxRows][MAXK]
-    float *st = sc + kValuMaxRows * MAXK;           // [kValuMaxRows][2]
-    float *Ks = (float *)(st + kValuMaxRows * 2 + kValuThreads);   // [MAXK][KROW]
-    float *Vs = Ks + MAXK * KROW;
-    const int n_items = a.Hkv * a.S;
-    const size_t PR = DH + 2;
-
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int g = item / a.S, s = item % a.S;
-        const int c0 = s * a.C, c1 = (c0 + a.C < a.pos0) ? c0 + a.C : a.pos0;
-        const int nc = (c1 > c0) ? c1 - c0 : 0;
-        const bool last = (s == a.S - 1);
-        const int nk = nc + (last ? a.m : 0);
-        float *Kg = (float *)a.Kc + (size_t)g * a.stride * DH, *Vg = (float *)a.Vc + (size_t)g * DH * a.stride;
-        for (int idx = tid; idx < nc * DH; idx += kValuThreads) {
-            const int j = idx / DH, e = idx % DH;
-            Ks[j * KROW + e] = Kg[(size_t)(c0 + j) * DH + e];
+    const int G = a.G, R = a.R;
+    const int g = blockIdx.y, s = blockIdx.x;
+    const int c0 = s * C, c1 = (c0 + C < a.pos0) ? c0 + C : a.pos0;
+    const int nc = (c1 > c0) ? c1 - c0 : 0;
+    const bool last = (s == a.S - 1);
+    const int r_first = blockIdx.z * a.rows_wg, r_end = r_first + a.rows_wg < R ? r_first + a.rows_wg : R;     // this workgroup's query rows
+    float *Kg = (float *)a.Kc + (size_t)g * a.stride * DH, *Vg = (float *)a.Vc + (size_t)g * DH * a.stride;
+    const int key = tid / LK, d0 = (tid % LK) * 16;             // products with K: key, first dimension
+    const int e = tid / TE, part = tid % TE;                    // products with V: dimension, keys (i * TE + part) * 4 .. + 3
+    f32x4 k[4], v[4];
+    {
+        const float *kp = Kg + (size_t)(key < nc ? c0 + key : 0) * DH + d0;     // keys past the item's are masked at use
+#pragma unroll
+        for (int i = 0; i < 4; ++i) k[i] = *(const f32x4 *)(kp + i * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = (i * TE + part) * 4;                  // (a group that starts before the item's end lies inside the cache row)
+            v[i] = *(const f32x4 *)(Vg + (size_t)e * a.stride + (j < nc ? c0 + j : 0));
         }
-        for (int idx = tid; idx < DH * 64; idx += kValuThreads)
-            for (int j = idx & 63; j < nc; j += 64) Vs[j * KROW + (idx >> 6)] = Vg[(size_t)(idx >> 6) * a.stride + c0 + j];
-        if (last) {
-            for (int idx = tid; idx < a.m * half; idx += kValuThreads) {
-                const int t = idx / half, i = idx % half;
-                const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
-                const float *vp = kp + (size_t)a.Hkv * DH;
-                const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
-                const float x = kp[i], y = kp[i + half];
-                const float k0 = x * c - y * sn, k1 = x * sn + y * c;
-                const float v0 = vp[i], v1 = vp[i + half];
-                Ks[(nc + t) * KROW + i] = k0;
-                Ks[(nc + t) * KROW + i + half] = k1;
-                Vs[(nc + t) * KROW + i] = v0;
-                Vs[(nc + t) * KROW + i + half] = v1;
+    }
+    if (last) {
+        // the call's own rows: rotate k, append to the cache, keep a copy in LDS
+        for (int idx = tid; idx < a.m * half; idx += kValuThreads) {
+            const int t = idx / half, i = idx % half;
+            const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
+            const float *vp = kp + (size_t)a.Hkv * DH;
+            const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
+            const float x = kp[i], y = kp[i + half];
+            const float k0 = x * c - y * sn, k1 = x * sn + y * c;
+            const float v0 = vp[i], v1 = vp[i + half];
+            knew[t][i] = k0;
+            knew[t][i + half] = k1;
+            vnew[t][i] = v0;
+            vnew[t][i + half] = v1;
+            if (blockIdx.z == 0) {
                 const size_t p = (size_t)(a.pos0 + t);
                 Kg[p * DH + i] = k0;
                 Kg[p * DH + i + half] = k1;
@@ -363,81 +369,104 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnArgs a) {
                 Vg[(size_t)(i + half) * a.stride + p] = v1;
             }
         }
-        for (int r0 = 0; r0 < R; r0 += kValuMaxRows) {
-            const int nr = (R - r0 < kValuMaxRows) ? R - r0 : kValuMaxRows;
-            for (int idx = tid; idx < nr * half; idx += kValuThreads) {
-                const int rr = idx / half, i = idx % half, r = r0 + rr, t = r / G, hq = g * G + r % G;
-                const float *qp = a.qkv + (size_t)t * a.ld + (size_t)hq * DH;
-                const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
-                const float x = qp[i], y = qp[i + half];
-                qs[rr * DH + i] = (x * c - y * sn) * a.scale;
-                qs[rr * DH + i + half] = (x * sn + y * c) * a.scale;
-            }
-            __syncthreads();
-            // four lanes per (row, key): with few rows and keys most threads would otherwise watch one do a whole dot product
-            for (int p = tid; p < nr * nk * 4; p += kValuThreads) {
-                const int pair = p >> 2, rr = pair / nk, j = pair - rr * nk, t = (r0 + rr) / G, e0 = (p & 3) * (DH / 4);
-                float acc = 0.f;
-                const float *kr = Ks + j * KROW + e0;
-                const float *qr = qs + rr * DH + e0;
+    }
 #pragma unroll
-                for (int e = 0; e < DH / 4; ++e) acc += qr[e] * kr[e];
-                acc += __shfl_xor(acc, 1);
-                acc += __shfl_xor(acc, 2);
-                if (j >= nc && j - nc > t) acc = -INFINITY;     // causal mask among the call's own rows
-                if ((p & 3) == 0) sc[rr * MAXK + j] = acc;
-            }
-            __syncthreads();
-            for (int rr = wave; rr < nr; rr += kValuThreads / 64) {
-                float mx = -INFINITY;
-                for (int j = lane; j < nk; j += 64) mx = fmaxf(mx, sc[rr * MAXK + j]);
-                for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-                float sum = 0.f;
-                for (int j = lane; j < nk; j += 64) {
-                    const float sv = sc[rr * MAXK + j];
-                    const float pv = (sv == -INFINITY) ? 0.f : __expf(sv - mx);
-                    sc[rr * MAXK + j] = pv;
-                    sum += pv;
-                }
-                for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-                if (lane == 0) {
-                    st[rr * 2] = mx;
-                    st[rr * 2 + 1] = sum;
-                }
-            }
-            __syncthreads();
-            // the keys of an output are dealt to as many threads as there are to spare, added up in thread order
-            int parts = kValuThreads / (nr * DH);
-            parts = parts > 8 ? 8 : parts < 1 ? 1 : parts;
-            float *red = st + kValuMaxRows * 2;                 // [kValuThreads], parts > 1 only
-            if (parts > 1 && tid < parts * nr * DH) {
-                const int part = tid / (nr * DH), o = tid - part * (nr * DH), rr = o / DH, e = o % DH;
-                float acc = 0.f;
-                for (int j = part; j < nk; j += parts) acc += sc[rr * MAXK + j] * Vs[j * KROW + e];
-                red[tid] = acc;
-            }
-            if (parts > 1) __syncthreads();
-            for (int idx = tid; idx < nr * DH; idx += kValuThreads) {
-                const int rr = idx / DH, e = idx % DH;
-                float acc = 0.f;
-                if (parts > 1)
-                    for (int p = 0; p < parts; ++p) acc += red[p * nr * DH + idx];
-                else
-                    for (int j = 0; j < nk; ++j) acc += sc[rr * MAXK + j] * Vs[j * KROW + e];
-                if (a.S == 1) {                             // nothing to fold: the output itself, packed for the Wo GEMM
-                    const int r = r0 + rr, t = r / G;
-                    store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + r % G) * DH + e, t, acc / st[rr * 2 + 1]);
-                    continue;
-                }
-                float *pr = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
-                pr[e] = acc;
-                if (e == 0) {
-                    pr[DH] = st[rr * 2];
-                    pr[DH + 1] = st[rr * 2 + 1];
-                }
-            }
-            __syncthreads();
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if ((i * TE + part) * 4 + c >= nc) v[i][c] = 0.f;   // dead positions may hold anything
+    auto sum_lanes = [](float x, int n) {                       // over n = 4 or 8 neighbouring lanes
+        x += dpp<0xB1>(x);
+        x += dpp<0x4E>(x);
+        if (n == 8) x += dpp<0x141>(x);
+        return x;
+    };
+    for (int r0 = r_first; r0 < r_end; r0 += kValuMaxRows) {
+        const int nr = (r_end - r0 < kValuMaxRows) ? r_end - r0 : kValuMaxRows;
+        for (int idx = tid; idx < nr * half; idx += kValuThreads) {
+            const int rr = idx / half, i = idx % half, r = r0 + rr, t = div_small(r, a.mul_G), hq = g * G + (r - t * G);
+            const float *qp = a.qkv + (size_t)t * a.ld + (size_t)hq * DH;
+            const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
+            const float x = qp[i], y = qp[i + half];
+            qs[rr][i] = (x * c - y * sn) * a.scale;
+            qs[rr][i + half] = (x * sn + y * c) * a.scale;
         }
+        __syncthreads();
+        auto dot = [&](int rr, const f32x4 (&kk)[4]) {
+            float acc = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4 q = *(const f32x4 *)&qs[rr][d0 + i * 4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc += q[c] * kk[i][c];
+            }
+            return sum_lanes(acc, LK);
+        };
+        for (int rr = 0; rr < nr; ++rr) {
+            const float x = dot(rr, k);
+            if (tid % LK == 0) sc[rr][key] = key < nc ? x : -INFINITY;
+        }
+        if (last && key < 8) {                                  // (whole groups of lanes that add up; keys past the call's are masked)
+            f32x4 kk[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kk[i] = *(const f32x4 *)&knew[key][d0 + i * 4];
+            for (int rr = 0; rr < nr; ++rr) {
+                const float x = dot(rr, kk);
+                const int t = div_small(r0 + rr, a.mul_G);      // causal mask among the call's own rows
+                if (tid % LK == 0) sc[rr][C + key] = key < a.m && key <= t ? x : -INFINITY;
+            }
+        }
+        __syncthreads();
+        for (int rr = wave; rr < nr; rr += kValuThreads / 64) {
+            constexpr int NV = (MAXK + 63) / 64;
+            float x[NV], mx = -INFINITY, sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int j = i * 64 + lane;
+                x[i] = j < (last ? MAXK : C) ? sc[rr][j] : -INFINITY;
+                mx = fmaxf(mx, x[i]);
+            }
+            mx = max64(mx);
+            const float ref = softmax_ref(mx);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const float p = __expf(x[i] - ref);
+                if (i * 64 + lane < MAXK) sc[rr][i * 64 + lane] = p;
+                sum += p;
+            }
+            sum = sum64(sum);
+            if (lane == 0) {
+                st[rr][0] = mx;
+                st[rr][1] = sum;
+            }
+        }
+        __syncthreads();
+        for (int rr = 0; rr < nr; ++rr) {
+            float acc = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4 p = *(const f32x4 *)&sc[rr][(i * TE + part) * 4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc += p[c] * v[i][c];
+            }
+            if (last)
+                for (int t = part; t < a.m; t += TE) acc += sc[rr][C + t] * vnew[t][e];
+            acc = sum_lanes(acc, TE);
+            if (part == 0) {
+                if (a.S == 1) {                                 // nothing to fold: the output itself, packed for the Wo GEMM
+                    const int r = r0 + rr, t = div_small(r, a.mul_G);
+                    store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + (r - t * G)) * DH + e, t, acc / st[rr][1]);
+                } else {
+                    float *pr = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
+                    pr[e] = acc;
+                    if (e == 0) {
+                        pr[DH] = st[rr][0];
+                        pr[DH + 1] = st[rr][1];
+                    }
+                }
+            }
+        }
+        if (r0 + kValuMaxRows < r_end) __syncthreads();
     }
 }
 
@@ -516,24 +545,17 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-constexpr size_t valu_lds_bytes(int dh) {
-    return ((size_t)kValuMaxRows * (dh + valu_max_keys(dh) + 2) + kValuThreads + 2 * (size_t)valu_max_keys(dh) * (dh + 4)) * 4;
-}
-
-int attn_chunk(int kv_elem, int dh) { return kv_elem != kElemF32 ? 128 : valu_max_keys(dh) - 8; }
+int attn_chunk(int kv_elem, int dh) { return kv_elem != kElemF32 ? 128 : valu_chunk(dh); }
 
 template <int DH>
 static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
-    const size_t lds = valu_lds_bytes(DH);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_attn_valu<DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return (int)e;
-        attr_set = true;
-    }
-    int grid = a.Hkv * a.S;
-    if (grid > 4 * c.n_wg) grid = 4 * c.n_wg;
-    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(grid), dim3(kValuThreads), lds, (hipStream_t)c.stream, a);
+    // A head's query rows are dealt to several workgroups, down to two each, while there are compute units to spare (each reads the
+    // head's positions for itself).
+    AttnArgs b = a;
+    const int spare = c.n_wg / (a.Hkv * a.S), most = (a.R + 1) / 2;
+    const int nz = spare < 1 ? 1 : spare < most ? spare : most;
+    b.rows_wg = (a.R + nz - 1) / nz;
+    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(a.S, a.Hkv, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
     return (int)hipGetLastError();
 }
 
@@ -550,14 +572,15 @@ static int launch_dec_as(const AttnArgs &a, const LaunchCtx &c) {
     return (int)hipGetLastError();
 }
 
-// More than 16 query rows: two wavefronts per block of keys, a row tile each, while an item is one or two blocks per wavefront
-// and there is at most one item per compute unit (the chain through an item is what counts then); else one wavefront
-// with both tiles, whose workgroups can share a compute unit.  Layer step of the 8B shape, 8 rows: context 1201 110.4
-// against 112.5 us, 4096 114.3 / 115.5, 6000 114.4 / 114.9, 9203 (three blocks per wavefront) 120.1 / 119.0.
+// More than 16 query rows: two wavefronts per block of keys, a row tile each, while an item is one block per wavefront (the chain
+// through an item is what counts then); else one wavefront with both tiles (and all the registers that takes: held to 256 of
+// them it spilled 25, and the 8B shape's step of 8 rows at context 9203 took 111.0 us and not 106.1).  Layer step of the 8B shape,
+// 5 / 8 rows, two wavefronts against one: context 300 93.5 / 99.6 us, 94.0 / 100.2; 4096 97.6 / 105.1, 98.4 / 105.5; 6000 (two
+// blocks per wavefront) 98.1 / 104.5, 97.6 / 104.1; 9203 (three) 101.8 / 108.3, 99.9 / 106.6.
 template <int DH, bool F16>
 static int launch_dec(const AttnArgs &a, const LaunchCtx &c) {
     if (a.R <= 16) return launch_dec_as<DH, F16, 1, 1>(a, c);
-    if (a.C <= 2 * attn_chunk(a.kv_elem, a.dh) && a.Hkv * a.S <= c.n_wg) return launch_dec_as<DH, F16, 1, 2>(a, c);
+    if (a.C <= attn_chunk(a.kv_elem, a.dh) || a.S == 1) return launch_dec_as<DH, F16, 1, 2>(a, c);
     return launch_dec_as<DH, F16, 2, 1>(a, c);
 }
 
@@ -578,6 +601,13 @@ int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg) {
         if (items(k) <= n_wg) return k * c;
     for (int k = 2;; ++k)                                  // ends: with one item per kv head at the latest
         if (items(k) <= 2L * n_wg || items(k) <= n_kv_heads) return k * c;
+}
+
+// The own rows are a second chain (rotation, append, one more block) behind the last item's own: on a compute unit of their own if
+// there is one to spare.  Layer step of the 8B shape, 1 row, context 2048 88.1 -> 86.0 us, 8 rows 103.1 -> 100.8, 300 and 1201 alike;
+// with 264 items for 256 compute units (context 4096) 88.7 -> 89.3.
+bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg) {
+    return kv_elem != kElemF32 && S > 1 && (long)n_kv_heads * (S + 1) <= n_wg;
 }
 
 int launch_attn(const AttnArgs &a, const LaunchCtx &c) {

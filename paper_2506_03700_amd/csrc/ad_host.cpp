@@ -568,6 +568,7 @@ static int layer_steps(const ad_model *m, ad_kv *kv, int32_t layer, int32_t coun
         a.stride = kv->stride; a.pos0 = pos[0]; a.m = n; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.dh = L.dh;
         a.C = fused ? attn_chunk(ek, L.dh) : attn_chunk_for(ek, L.dh, c.n_kv_heads, pos[0], m->n_wg);
         a.S = pos[0] > 0 ? (pos[0] + a.C - 1) / a.C : 1;
+        if (!fused && attn_own_item(ek, c.n_kv_heads, a.S, m->n_wg)) ++a.S;      // the call's own rows are an item of their own
         a.part = kv->part; a.Bo = m->Bo; a.Bo_KT = L.kt_q; a.scale = 1.0f / sqrtf((float)L.dh); a.kv_elem = ek;
         attn_finish(a);
         // 3. x' = x + Wo o

@@ -118,6 +118,7 @@ struct AttnArgs {
     // first load: query heads per kv head, query rows per kv head, and the multipliers of div_small() for S, G and R
     int G, R;
     unsigned mul_S, mul_G, mul_R;
+    int rows_wg;          // fp32 kernel: query rows per workgroup (set by its launcher)
 };
 // x / d == (x * div_multiplier(d)) >> 32 for 0 <= x < 65536 and 1 < d < 65536 (the error of the rounded-up reciprocal,
 // x / 2^32, stays below the 1 / d that separates x / d from the next integer); d == 1, whose multiplier would be
@@ -212,6 +213,7 @@ int launch_layer_fused(const FusedArgs &, const LaunchCtx &);   // n_wg must not
 int fused_phase_workgroups(int n_tiles, int n_wg);               // workgroups that own row tiles of a GEMM phase
 int attn_chunk(int kv_elem, int dh);   // cached positions per attention work item (fused layer step), and the fewest
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg);   // the same for a stand-alone launch
+bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg);      // whether the call's own rows are an item of their own there
 int device_info(int *n_cu);
 const char *hip_error_text(int code);
 int stream_sync(void *stream);

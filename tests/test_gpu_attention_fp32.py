@@ -1,0 +1,63 @@
+"""GPU parity of the fp32 cache's attention where its split changes: 128 (head_dim 128: 64) cached positions per workgroup, one
+workgroup per head up to there, a head's query rows dealt to workgroups while compute units are to spare (all in one, and in two
+passes of 32, with 32 kv heads at 1001 positions), ragged ends of the cache."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2506_03700_amd import synth
+from tolerances import check_kv, check_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ad():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2506_03700_amd import binding
+    binding.lib()
+    return binding
+
+
+def shape(hq, hkv, dh):
+    return synth.ModelShape(f"h{hq}-{hkv}x{dh}-f32", 1, 64, hq, hkv, dh, 64, 64, 10000.0, (), synth.F32, False)
+
+
+CASES = [(shape(4, 1, 64), (0, 1, 3, 127, 128, 129, 300), (1, 5, 8)),
+         (shape(3, 1, 128), (1, 63, 64, 65, 200), (1, 2, 7, 8)),
+         (shape(256, 32, 64), (1001,), (8,)),
+         (shape(40, 40, 128), (501,), (3,))]
+
+
+@pytest.mark.parametrize("s,ctxs,rows", CASES, ids=lambda x: getattr(x, "name", None))
+def test_layer_step_attention(ad, s, ctxs, rows):
+    import torch
+    w = synth.make_weights(s, seed=2, norm_jitter=0.2)
+    # (synthetic weights shrink the attention output's projection by 0.05; here it is to show)
+    w["layers.0.wo"] = synth.store_as(synth.as_f32(w["layers.0.wo"]) * 20, s.dtype)
+    n = max(ctxs) + 8
+    g, o = ad.Model(s, w, max_pos=n), orc.Oracle(s, w, max_pos=n)
+    # positions that no call has filled hold values that are no numbers
+    K, V = g.kv_views()
+    K.fill_(float("nan"))
+    V.fill_(float("nan"))
+    k, v = synth.make_kv_prefill(s, 3, 0, max(ctxs))
+    g.kv_fill(1, k, v)
+    o.kv_write(1, 0, k, v)
+    for ctx in sorted(ctxs, reverse=True):           # (a call's rows overwrite positions that a longer context no longer uses)
+        for m in rows:
+            print(f"case {s.name} context {ctx} rows {m}", flush=True)
+            g.kv_set_len(1, ctx)
+            o.kv_set_len(1, ctx)
+            h = synth.make_hidden(s, 10 * ctx + m, m)
+            pos = np.arange(ctx, ctx + m)
+            hg = torch.from_numpy(h).to("cuda:0")
+            g.ad_layer_step(1, hg, pos)
+            ho = o.layer_step(1, h, pos)
+            check_rows(s.dtype, hg.cpu().numpy(), ho, f"rows at context {ctx}, {m} rows")
+            kg, vg = g.kv_read(1, ctx + m)
+            ko, vo = o.kv_read(1, ctx, m)
+            check_kv(s.dtype, kg[ctx:], ko, "K")
+            check_kv(s.dtype, vg[ctx:], vo, "V")
+    g.close()
