@@ -683,13 +683,16 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
         const LayerPacked &lp = m->layers[l];
         PromptQkv q;
         memset(&q, 0, sizeof q);
-        if ((rc = project(lp.wqkv, kv->pr.Bd, L.kt_d, L.nqkv, &q.n_split))) return hip_fail(rc, "prompt pass: qkv");
-        q.part = kv->pr.pieces; q.scale = kv->pr.scale; q.M = n; q.nqkv = L.nqkv; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
+        // nobody asks the last layer's queries anything
+        const bool last = l + 1 == c.n_layers;
+        q.head0 = last ? c.n_q_heads : 0; q.ld = L.nqkv - q.head0 * L.dh;
+        if ((rc = project(lp.wqkv + (size_t)(q.head0 * L.dh / 16) * L.kt_d * 1024u, kv->pr.Bd, L.kt_d, q.ld, &q.n_split))) return hip_fail(rc, "prompt pass: qkv");
+        q.part = kv->pr.pieces; q.scale = kv->pr.scale; q.M = n; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
         q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
         q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
         q.stride = kv->stride; q.pos0 = pos0; q.q_rows = kv->pr.rows * q.G; q.Q = kv->pr.Q; q.q_scale = 1.0f / sqrtf((float)L.dh); q.f16 = f16;
         if ((rc = launch_prompt_qkv(q, stream))) return hip_fail(rc, "prompt pass: rotation");
-        if (l + 1 == c.n_layers) break;
+        if (last) break;
         PromptAttn a;
         memset(&a, 0, sizeof a);
         a.Q = kv->pr.Q; a.Kc = q.Kc; a.Vc = q.Vc; a.stride = kv->stride; a.pos0 = pos0; a.M = n; a.Hq = q.Hq; a.Hkv = q.Hkv; a.dh = L.dh; a.G = q.G;

@@ -54,9 +54,9 @@ struct PromptRows {
 
 // q, k, v of M tokens from the pieces: rotated and scaled queries in operand tiles, K and V into the cache
 struct PromptQkv {
-    const float *part;        // [n_split][M][nqkv]
+    const float *part;        // [n_split][M][ld]: heads head0 .. of q, k, v
     const float *scale;       // [M], see PromptRows
-    int n_split, M, nqkv, Hq, Hkv, dh, G;
+    int n_split, M, ld, head0, Hq, Hkv, dh, G;
     const float *rope;        // rows pos0 ..
     void *Kc, *Vc;            // the layer's cache (see AttnArgs)
     int stride, pos0;         // pos0: a multiple of 64

@@ -7,7 +7,7 @@
 //
 // Per layer: k_prompt_gemm (q, k, v) -> k_prompt_qkv (rotation, KV append, query tiles) -> k_prompt_attn ->
 // k_prompt_gemm (Wo) -> k_prompt_rows (residual, RMSNorm, tiles) -> k_prompt_gemm (gate/up, SwiGLU) ->
-// k_prompt_gemm (down) -> k_prompt_rows.
+// k_prompt_gemm (down) -> k_prompt_rows.  The last layer is its K and V alone.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -29,8 +29,7 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // ---------------------------------------------------------------------------------------------------
 // A workgroup of NWR x NWT wavefronts computes BR = NWR * WR row tiles x BT = NWT * WT token tiles; a wavefront holds
 // WR x WT accumulators.  Both operands lie in memory in MFMA operand order, so tiles are copied as they are and every LDS
-// access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.  Activations are staged in LDS (two
-// stages: while one is multiplied the next is on its way in registers, loaded a whole stage ahead).
+// access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.  Activations are staged in LDS.
 //
 // The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
 // the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
@@ -64,6 +63,7 @@ struct PromptAcc {
 #pragma unroll
             for (int j = 0; j < WT; ++j) acc[i][j] = sum[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
+    // empties the accumulators into the sums
     __device__ __forceinline__ void flush() {
 #pragma unroll
         for (int i = 0; i < WR; ++i)
@@ -72,6 +72,17 @@ struct PromptAcc {
                 sum[i][j] += acc[i][j];
                 acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
+    }
+    // the same for those whose turn is k-step s of kFlush: a few at every k-step, so that the additions go by between products
+    __device__ __forceinline__ void flush_some(int s) {
+#pragma unroll
+        for (int i = 0; i < WR; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j)
+                if ((i * WT + j) * kFlush / (WR * WT) == s) {
+                    sum[i][j] += acc[i][j];
+                    acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
     }
     // stores the sums of the tiles rt0 .., tt0 ..; a tile's lane (n, gq) holds token n, rows gq*4 .. +3
     template <bool F16, int EPI>
@@ -109,20 +120,27 @@ struct PromptAcc {
     }
 };
 
-// More than 64 tokens: bound by the matrix cores, and next to them by what moves through LDS.  A wavefront therefore loads
-// its weight tiles from memory straight into registers, one k-step ahead (the NWT wavefronts that share them find them in
-// the compute unit's cache); only the activations, which NWR wavefronts share, go through LDS.  Measured at 1024 tokens,
-// executed TFLOP/s (hi and lo products both counted), 28672 x 4096 / 4096 x 14336, each pair of figures from one run:
-// weights in registers 1057 / 1223, staged in LDS 985 / 1015 (both 4 x 4 tiles by 4 x 2 wavefronts).  2 x 4 tiles by 4 x 2
-// wavefronts (two workgroups per compute unit) are as fast as 4 x 4 (one) from 512 tokens on and faster below (128 tokens,
-// 28672 x 4096: 79 against 102 us), and leave half the pieces to add up; two k-steps per stage lose 6 to 25 %.
+// 1 KiB from memory straight into LDS: lane l's 16 bytes go to unit l of dst (the same for all lanes)
+__device__ __forceinline__ void copy_to_lds(const void *src, bf16x8 *dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+
+// More than 64 tokens: bound by the matrix cores and, with them, by the power that operands on the move take (with operands of zeros
+// the same launches run 20 to 45 % faster).  A wavefront loads its weight tiles from memory straight into registers, one k-step
+// ahead (the NWT wavefronts that share them find them in the compute unit's cache); the activations, which NWR wavefronts share,
+// are copied from memory into LDS without a way through registers, two k-steps ahead (three stages).  A step ends when all
+// but its own copies have landed, then a barrier.  Measured at 1024 tokens, us and executed TFLOP/s (hi and lo products
+// both counted), 6144 x 4096, 4096 x 4096, 4096 x 14336, 28672 x 4096: 112, 62, 222, 456 (920, 1110, 1080, 1055) against
+// 123, 65, 232, 468 with two stages through registers and all accumulators emptied at once.  2 x 4 tiles by 4 x 2 wavefronts (two
+// workgroups per compute unit) against 4 x 4 by 2 x 2 (two) and by 4 x 2 (one): 119, 64, 224, 446 and 123, 69, 223, 486; 512 tokens
+// 57, 35, 104, 245 against 60, 36, 104, 241 and 62, 40, 107, 248.
 template <int WR, int WT, int NWR, int NWT, bool F16, int EPI>
 __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
-    constexpr int NTH = 64 * NWR * NWT, BR = WR * NWR, BT = WT * NWT;
-    constexpr int AU = BT * 128, NA = AU / NTH;                 // 16-byte units of activations per stage, loads per thread
-    static_assert(AU % NTH == 0, "a stage is a whole number of loads per thread");
-    __shared__ bf16x8 lds[2][AU];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = NWR * NWT, BR = WR * NWR, BT = WT * NWT;
+    constexpr int AU = BT * 128, NA = BT * 2 / NW;              // 16-byte units of activations per stage, copies per wavefront
+    static_assert(BT * 2 % NW == 0 && NA < 16 && kFlush % 2 == 0, "a stage is a whole number of copies per wavefront");
+    __shared__ bf16x8 lds[3][AU];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % NWR, wt = wave / NWR;
     const PromptTile T = prompt_tile(g);
 
@@ -135,58 +153,79 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int u = tid + i * NTH;
-        aoff[i] = ((unsigned)(T.tb * BT + (u >> 7)) * (unsigned)g.KT * 128u + (unsigned)(u & 127)) << 4;
+        const int u = wave * NA + i;                            // token tile and plane
+        aoff[i] = ((unsigned)(T.tb * BT + (u >> 1)) * (unsigned)g.KT * 128u + (unsigned)((u & 1) * 64 + lane)) << 4;
     }
     const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
-    bf16x8 w0[WR], w1[WR], areg[NA];
+    bf16x8 w0[WR], w1[WR];
+    const int k_last = T.k1 - 1;                                // loads past the piece repeat its last k-step
     auto load_w = [&](bf16x8 (&w)[WR], int k) {
+        const unsigned o = (unsigned)(k < k_last ? k : k_last) << 10;
 #pragma unroll
-        for (int r = 0; r < WR; ++r) w[r] = *(const bf16x8 *)(Wb + (woff[r] + ((unsigned)k << 10)));
+        for (int r = 0; r < WR; ++r) w[r] = *(const bf16x8 *)(Wb + (woff[r] + o));
     };
-    auto load_a = [&](int k) {
+    auto copy_a = [&](bf16x8 *stage, int k) {
+        const unsigned o = (unsigned)(k < k_last ? k : k_last) << 11;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) areg[i] = *(const bf16x8 *)(Ab + (aoff[i] + ((unsigned)k << 11)));
-    };
-    auto store_a = [&](bf16x8 *s) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) s[tid + i * NTH] = areg[i];
+        for (int i = 0; i < NA; ++i) copy_to_lds(Ab + (aoff[i] + o), stage + (wave * NA + i) * 64);
     };
     PromptAcc<WR, WT> C;
     C.clear();
     const int n_step = T.k1 - T.k0;
-    // k-step s: multiply w with stage s & 1 while wn and the stage after it are filled for the k-step that follows
-    auto step = [&](const bf16x8 (&w)[WR], bf16x8 (&wn)[WR], int s) {
-        load_w(wn, s + 1 < n_step ? T.k0 + s + 1 : T.k0 + s);
-        const bf16x8 *cur = lds[s & 1] + wt * WT * 128 + lane;
+    // k-step s from stage `cur`: the weights of the next one and the activations of the one after it (into the stage that was read in
+    // the step before) are requested first.  turn: which accumulators it empties (-1: none).
+    auto step = [&](const bf16x8 (&w)[WR], bf16x8 (&wn)[WR], int s, const bf16x8 *cur, bf16x8 *put, int turn) {
+        load_w(wn, T.k0 + s + 1);
+        copy_a(put, T.k0 + s + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (turn >= 0) C.flush_some(turn);
+        const bf16x8 *p = cur + wt * WT * 128 + lane;
         bf16x8 bh[WT], bl[WT];
 #pragma unroll
         for (int t = 0; t < WT; ++t) {
-            bh[t] = cur[t * 128];
-            bl[t] = cur[t * 128 + 64];
+            bh[t] = p[t * 128];
+            bl[t] = p[t * 128 + 64];
         }
 #pragma unroll
-        for (int r = 0; r < WR; ++r) {
+        for (int r = 0; r < WR; ++r)
 #pragma unroll
             for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bh[t], C.acc[r][t]);
 #pragma unroll
+        for (int r = 0; r < WR; ++r)
+#pragma unroll
             for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bl[t], C.acc[r][t]);
-        }
-        if ((s + 1) % kFlush == 0) C.flush();
-        if (s + 1 < n_step) {
-            store_a(lds[(s + 1) & 1]);
-            if (s + 2 < n_step) load_a(T.k0 + s + 2);
-        }
-        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        // all but the newest NA requests, this step's copies, have landed: the next step's weights and stage are there.  (Bits of
+        // the immediate: vmcnt 0-3, 14-15; expcnt 4-6 and lgkmcnt 8-11, all ones, are not waited for.)
+        __builtin_amdgcn_s_waitcnt(0x0F70 | NA);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
     };
-    load_a(T.k0);
+    bf16x8 *l0 = lds[0], *l1 = lds[1], *l2 = lds[2];
+    auto rotate = [&]() {                                       // two steps on
+        bf16x8 *x = l0;
+        l0 = l2;
+        l2 = l1;
+        l1 = x;
+    };
+    copy_a(l0, T.k0);
     load_w(w0, T.k0);
-    store_a(lds[0]);
-    if (n_step > 1) load_a(T.k0 + 1);
-    __syncthreads();
-    for (int s = 0; s < n_step; s += 2) {
-        step(w0, w1, s);
-        if (s + 1 < n_step) step(w1, w0, s + 1);
+    copy_a(l1, T.k0 + 1);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_barrier();
+    int s = 0;
+    for (; s + kFlush <= n_step; s += kFlush) {
+#pragma unroll
+        for (int j = 0; j < kFlush; j += 2) {
+            step(w0, w1, s + j, l0, l2, j);
+            step(w1, w0, s + j + 1, l1, l0, j + 1);
+            rotate();
+        }
+    }
+    for (; s < n_step; s += 2) {
+        step(w0, w1, s, l0, l2, -1);
+        if (s + 1 < n_step) step(w1, w0, s + 1, l1, l0, -1);
+        rotate();
     }
     C.flush();
     C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
@@ -351,18 +390,20 @@ __global__ void __launch_bounds__(256) k_prompt_embed(PromptEmbed a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// rotation, KV append, query tiles: one workgroup per 64 tokens and head (q heads, then k heads, then v heads)
+// rotation, KV append, query tiles: one workgroup per 64 tokens and head (q heads, if they are there, then k heads, then v heads)
 // ---------------------------------------------------------------------------------------------------
 constexpr int kQkvTokens = 64;
 
 template <int DH, bool F16>
 __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
     constexpr int half = DH / 2, NC = half / 8;         // groups of 8 dimensions in the lower half
-    const int t0 = blockIdx.x * kQkvTokens, head = blockIdx.y, tid = threadIdx.x;
-    auto load8 = [&](int t, int col, float (&o)[8]) {
+    const int t0 = blockIdx.x * kQkvTokens, head = a.head0 + blockIdx.y, tid = threadIdx.x;
+    const int col0 = (int)blockIdx.y * DH;
+    auto load8 = [&](int t, int c, float (&o)[8]) {               // columns c .. of this head
+        const int col = col0 + c;
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
         for (int p = 0; p < a.n_split; ++p) {
-            const float *src = a.part + ((size_t)p * a.M + t) * a.nqkv + col;
+            const float *src = a.part + ((size_t)p * a.M + t) * a.ld + col;
             s0 += *(const f32x4 *)src;
             s1 += *(const f32x4 *)(src + 4);
         }
@@ -379,8 +420,8 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
             const int tl = idx / NC, c = idx % NC, t = t0 + tl;
             if (t >= a.M) break;
             float x[8], y[8], r0[8], r1[8];
-            load8(t, head * DH + c * 8, x);
-            load8(t, head * DH + half + c * 8, y);
+            load8(t, c * 8, x);
+            load8(t, half + c * 8, y);
             const float *rp = a.rope + ((size_t)t * half + c * 8) * 2;
             const float mul = is_q ? a.q_scale : 1.0f;
 #pragma unroll
@@ -432,7 +473,7 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
         for (int idx = tid; idx < kQkvTokens * (DH / 8); idx += 256) {
             const int tl = idx / (DH / 8), c = idx % (DH / 8), t = t0 + tl;
             float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (t < a.M) load8(t, head * DH + c * 8, x);
+            if (t < a.M) load8(t, c * 8, x);
 #pragma unroll
             for (int e = 0; e < 8; ++e) vt[c * 8 + e][tl] = to16<F16>(x[e]);
         }
@@ -663,7 +704,7 @@ int launch_prompt_rows(const PromptRows &a, void *stream) {
 
 template <int DH, bool F16>
 static int launch_qkv_as(const PromptQkv &a, hipStream_t s) {
-    hipLaunchKernelGGL((k_prompt_qkv<DH, F16>), dim3((a.M + kQkvTokens - 1) / kQkvTokens, a.Hq + 2 * a.Hkv), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_prompt_qkv<DH, F16>), dim3((a.M + kQkvTokens - 1) / kQkvTokens, a.Hq + 2 * a.Hkv - a.head0), dim3(256), 0, s, a);
     return (int)hipGetLastError();
 }
 int launch_prompt_qkv(const PromptQkv &a, void *stream) {
