@@ -54,6 +54,16 @@ struct AttnDecLds {
     float part[4][RP][PD + 4];                             // rows padded to 16 bytes for 128-bit LDS stores
 };
 
+// inputs k, k + 1 (k even: the pair is one word) of token t in the packed input of the Wo projection
+template <bool F16>
+__device__ __forceinline__ void store_act_pair(const AttnArgs &a, int k, int t, float v0, float v1) {
+    uint16_t h0, l0, h1, l1;
+    split16<F16>(v0, h0, l0);
+    split16<F16>(v1, h1, l1);
+    *(uint32_t *)((uint16_t *)a.Bo + act_index(k, t, a.Bo_KT)) = (uint32_t)h0 | (uint32_t)h1 << 16;
+    *(uint32_t *)((uint16_t *)a.Bo + act_index(k, 8 + t, a.Bo_KT)) = (uint32_t)l0 | (uint32_t)l1 << 16;
+}
+
 template <int DH, bool F16, int RT, int NRH>
 __global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArgs a) {
     warm_kernel_args<sizeof(AttnArgs)>();
@@ -98,8 +108,9 @@ __global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArg
             load_v(wave);
         }
         if (last && r0 == 0) {
-            // the call's own rows: rotate k, round to the cache type, append to the cache, keep a copy in LDS
-            for (int idx = tid; idx < a.m * half; idx += NTH) {
+            // the call's own rows: rotate k, round to the cache type, append to the cache, keep a copy in LDS (from the last thread
+            // down: the first ones have the queries)
+            for (int idx = NTH - 1 - tid; idx < a.m * half; idx += NTH) {
                 const int t = idx / half, i = idx % half;
                 const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
                 const float *vp = kp + (size_t)a.Hkv * DH;
@@ -189,8 +200,7 @@ __global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArg
                     if (IS_NEW ? (key >= a.m || key > t_row) : key >= live) w[c] = -INFINITY;
                     bm = fmaxf(bm, w[c]);
                 }
-                bm = fmaxf(bm, __shfl_xor(bm, 16));
-                bm = fmaxf(bm, __shfl_xor(bm, 32));
+                bm = max_rows(bm);
                 const float nm = fmaxf(mx[i], bm), ref = softmax_ref(nm);
                 const float alpha = __expf(mx[i] - ref);
                 mx[i] = nm;
@@ -257,9 +267,7 @@ __global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArg
         // dimensions at a time: a thread takes two neighbouring dimensions of a row and derives the wavefronts' weights itself.
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-            float den = sum[i];
-            den += __shfl_xor(den, 16);
-            den += __shfl_xor(den, 32);
+            const float den = sum_rows(sum[i]);
             if (gq == 0) {
                 L.mx[wave][row_w + i * 16 + n] = mx[i];
                 L.sum[wave][row_w + i * 16 + n] = den;
@@ -295,8 +303,7 @@ __global__ void __launch_bounds__(256 * NRH, RT == 1 ? 2 : 1) k_attn_dec(AttnArg
                 }
                 if (a.S == 1) {                             // nothing to fold: the output itself, packed for the Wo GEMM
                     const int r = r0 + rr, t = div_small(r, a.mul_G), kk = (g * G + (r - t * G)) * DH + h * PD + e;
-                    store_act_io<IoPlain, F16>((uint16_t *)a.Bo, a.Bo_KT, kk, t, num[0] / den);
-                    store_act_io<IoPlain, F16>((uint16_t *)a.Bo, a.Bo_KT, kk + 1, t, num[1] / den);
+                    store_act_pair<F16>(a, kk, t, num[0] / den, num[1] / den);
                     continue;
                 }
                 float *out = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
@@ -534,12 +541,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
         d += w * st[i][1];
         y += w * part[i][tid];
     }
-    uint16_t h0, l0, h1, l1;
-    split16<F16>(y[0] / d, h0, l0);
-    split16<F16>(y[1] / d, h1, l1);
-    const int k = hq * DH + e;                                  // even: the pair is one word
-    *(uint32_t *)((uint16_t *)a.Bo + act_index(k, t, a.Bo_KT)) = (uint32_t)h0 | (uint32_t)h1 << 16;
-    *(uint32_t *)((uint16_t *)a.Bo + act_index(k, 8 + t, a.Bo_KT)) = (uint32_t)l0 | (uint32_t)l1 << 16;
+    store_act_pair<F16>(a, hq * DH + e, t, y[0] / d, y[1] / d);
 }
 
 // ---------------------------------------------------------------------------------------------------

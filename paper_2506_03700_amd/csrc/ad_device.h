@@ -134,6 +134,34 @@ __device__ __forceinline__ float max64(float v) {
     v = fmaxf(v, dpp<0x140>(v));
     return fmaxf(fmaxf(read_lane(v, 0), read_lane(v, 16)), fmaxf(read_lane(v, 32), read_lane(v, 48)));
 }
+// largest value, and sum, over the four lanes l, l ^ 16, l ^ 32, l ^ 48
+__device__ __forceinline__ void across_rows(float v, float &a, float &b, float &c, float &e) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const auto q = __builtin_amdgcn_permlane16_swap(p[0], p[0], false, false), r = __builtin_amdgcn_permlane16_swap(p[1], p[1], false, false);
+    a = __uint_as_float(q[0]);
+    b = __uint_as_float(q[1]);
+    c = __uint_as_float(r[0]);
+    e = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float max_rows(float v) {
+    float a, b, c, e;
+    across_rows(v, a, b, c, e);
+    return fmaxf(fmaxf(a, b), fmaxf(c, e));
+}
+__device__ __forceinline__ float sum_rows(float v) {
+    float a, b, c, e;
+    across_rows(v, a, b, c, e);
+    return (a + b) + (c + e);
+}
+// smallest value of the wavefront
+__device__ __forceinline__ int min64(int v) {
+    auto m = [](int x, int y) { return x < y ? x : y; };
+    v = m(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false));
+    v = m(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false));
+    v = m(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false));
+    v = m(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false));
+    return m(m(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), m(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
 // sum over the lanes before this one; *total: over all
 __device__ __forceinline__ float scan64(float v, int lane, float *total) {
     float in = v;                // inclusive within a row of 16 lanes

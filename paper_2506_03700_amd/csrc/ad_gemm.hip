@@ -29,11 +29,23 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
                 p[i] = part[(size_t)(w < g.n_parts ? w : 0) * 8];
                 if (w >= g.n_parts) p[i] = (f32x4){-INFINITY, 0.f, __int_as_float(0x7fffffff), 0.f};
             }
+            float m = M;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) max_merge(M, S, I, p[i][0], p[i][1], __float_as_int(p[i][2]));
+            for (int i = 0; i < 4; ++i) m = fmaxf(m, p[i][0]);
+            const float ref = softmax_ref(m);
+            S *= __expf(M - ref);
+            if (m > M) I = 0x7fffffff;
+            M = m;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                S += p[i][1] * __expf(p[i][0] - ref);
+                const int id = __float_as_int(p[i][2]);
+                if (p[i][0] == m && id < I) I = id;
+            }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) max_merge(M, S, I, __shfl_xor(M, off), __shfl_xor(S, off), __shfl_xor(I, off));
+        const float m = max64(M), ref = softmax_ref(m);
+        S = sum64(S * __expf(M - ref));
+        I = min64(M == m ? I : 0x7fffffff);
         if (lane == 0) {
             idx_sh[t] = I;
             if (g.tok_out) g.tok_out[t] = I;
@@ -61,11 +73,13 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     const int grid = head_grid(g.NT, c.n_wg);
     hipStream_t s = (hipStream_t)c.stream;
     if ((planes == 1) != (g.elem != kElemF32)) return (int)hipErrorInvalidValue;     // fp32 weights are three bf16 planes
-    int rc = proj_covers(g, planes, c.n_wg) ? launch_proj(g, planes, c) : launch_rows(g, planes, grid, c);
+    GemmArgs h = g;
+    h.head_stats = g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag);       // (the logits alone need no reduction)
+    const bool few = proj_covers(g, planes, c.n_wg);
+    int rc = few ? launch_proj(h, planes, c) : launch_rows(h, planes, grid, c);
     if (rc) return rc;
-    if (g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag)) {       // (the logits alone need no reduction)
-        GemmArgs h = g;
-        h.n_parts = grid;
+    if (h.head_stats) {
+        h.n_parts = few ? proj_head_parts(g.NT, c.n_wg) : grid;
         hipLaunchKernelGGL(k_head_combine, dim3(1), dim3(512), 0, s, h);
         rc = (int)hipGetLastError();
     }
@@ -100,6 +114,11 @@ int static_head_scratch(float **ptr) {
     }
     *ptr = addr[dev];
     return 0;
+}
+
+int head_parts(int n_tiles, int n_wg) {
+    const int a = head_grid(n_tiles, n_wg), b = n_tiles <= 2 * n_wg ? proj_head_parts(n_tiles, n_wg) : 0;
+    return a > b ? a : b;
 }
 
 int head_grid(int n_tiles, int n_wg) {

@@ -785,9 +785,9 @@ ad_status ad_verify_static(const ad_model *m, const void *hidden, const int32_t 
                            int32_t *row_argmax, void *stream) {
     if (!m || !hidden || !n_accept || !next_token || (n > 1 && !draft)) return (ad_status)fail(AD_EINVAL, "ad_verify_static: null argument");
     if (n < 1 || n > m->cfg.m_max) return (ad_status)fail(AD_ERANGE, "ad_verify_static: m = %d outside 1..%d", n, m->cfg.m_max);
-    const int parts = head_grid((m->lay.V + 15) / 16, m->n_wg);
+    const int parts = head_parts((m->lay.V + 15) / 16, m->n_wg);
     if (parts > kStaticHeadParts)
-        return (ad_status)fail(AD_ERANGE, "ad_verify_static: the vocabulary pass would run on %d workgroups, the static scratch holds the partials of %d",
+        return (ad_status)fail(AD_ERANGE, "ad_verify_static: the vocabulary pass would leave %d partials, the static scratch holds %d",
                                parts, kStaticHeadParts);
     float *part = nullptr;
     const int rc = static_head_scratch(&part);

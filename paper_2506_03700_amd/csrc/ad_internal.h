@@ -77,8 +77,9 @@ struct GemmArgs {
     const float *ssq_in;
     int ssq_tiles;
     // head
-    float *head_part;     // [nwg][8][4] (max, sumexp, argmax as int bits, unused)
-    int n_parts;          // workgroups that wrote head_part (set by the launcher)
+    float *head_part;     // [partial][8][4] (max, sumexp, argmax as int bits, unused), of a workgroup or one of its wavefronts
+    int n_parts;          // partials in head_part (set by the launcher)
+    int head_stats;       // whether partials are wanted at all (set by the launcher)
     float *logits;        // null or [m][N]
     int32_t *tok_out;     // [m] (or null)
     float *conf_out;      // [m] (or null)
@@ -201,7 +202,9 @@ int launch_gemm(const GemmArgs &, int planes, const LaunchCtx &);   // EPI_HEAD:
 bool proj_covers(const GemmArgs &, int planes, int n_wg);           // launch_gemm's choice for projections with few tiles per workgroup
 int launch_proj(const GemmArgs &, int planes, const LaunchCtx &);
 int launch_rows(const GemmArgs &, int planes, int grid, const LaunchCtx &);
+int proj_head_parts(int n_tiles, int n_wg);
 int head_grid(int n_tiles, int n_wg);                               // workgroups launch_gemm uses for n_tiles row tiles
+int head_parts(int n_tiles, int n_wg);                              // most partials of a vocabulary pass
 // The library's own static device array for the vocabulary pass's per-workgroup partials (room for kStaticHeadParts
 // workgroups): its address on the current device, resolved on first use per device.  Allocates nothing.
 constexpr int kStaticHeadParts = 4096;

@@ -1,5 +1,5 @@
 // Projections with few row tiles per workgroup (at most two): Wo, down, the QKV projection of models up to the 8B shape, the
-// exit-head transform, and every projection of small models.     out[t][n] = sum_k W[n][k] * act[t][k],  m <= 8 tokens
+// exit-head transform, and every projection and the vocabulary pass of small models.     out[t][n] = sum_k W[n][k] * act[t][k],  m <= 8 tokens
 //
 // Such a launch lasts 3 to 25 us, and what it spends beyond reading its weights is a chain: argument fetch, first
 // loads, products, sum over the wavefronts, store.  A wavefront issues an instruction every 5 cycles or so (16 wavefronts
@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
         }
         return;
     }
-    if (!on) return;
+    if (g.epi != EPI_HEAD && !on) return;
     float v;
     if (HALF && (upper ? wave == 0 : wave == H - 1)) {
         const float *p = base + NF * 128;
@@ -265,7 +265,22 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
         v = sum_rows(base + (r >> 1) * 128 + (r & 1) * 8);
     }
     v *= scale;
-    if (g.epi == EPI_STORE) {
+    if (g.epi == EPI_HEAD) {
+        if (g.logits && on) g.logits[(size_t)et * g.N + row] = v;
+        if (g.head_stats) {
+            // (max, sum of exp, argmax) of these 8 rows, a partial of each wavefront
+            float M = on ? v : -INFINITY, S = on ? 1.0f : 0.f;
+            int I = on ? row : 0x7fffffff;
+#pragma unroll
+            for (int off = 4; off > 0; off >>= 1) max_merge(M, S, I, __shfl_xor(M, off), __shfl_xor(S, off), __shfl_xor(I, off));
+            if (ei == 0 && et < g.m) {
+                float *o = g.head_part + ((size_t)unit * 8 + et) * 4;
+                o[0] = M;
+                o[1] = S;
+                o[2] = __int_as_float(I);
+            }
+        }
+    } else if (g.epi == EPI_STORE) {
         g.out[(size_t)et * g.ld + row] = v;
     } else if (g.epi == EPI_PACK) {
         store_act<F16>(g.Bnext, g.Bnext_KT, row, et, v);
@@ -313,14 +328,24 @@ int launch_halves(const GemmArgs &g, int halves, hipStream_t s) {
 
 bool proj_covers(const GemmArgs &g, int planes, int n_wg) {
     if (g.mode == GEMM_STREAMED) return true;
-    if (g.epi == EPI_HEAD || g.NT > 2 * n_wg) return false;
+    if (g.NT > 2 * n_wg) return false;
     return !g.x || (g.norm_w && g.KT <= kProjWaves * 2 * proj_batch(planes));
 }
 
+// halves of a row tile per workgroup: 2, 3 or 4
+static int proj_halves(int n_tiles, int n_wg) {
+    const int h = (2 * n_tiles + n_wg - 1) / n_wg;
+    return h < 2 ? 2 : h > 3 ? 4 : h;
+}
+
+int proj_head_parts(int n_tiles, int n_wg) {
+    const int h = proj_halves(n_tiles, n_wg);
+    return (2 * n_tiles + h - 1) / h * h;
+}
+
 int launch_proj(const GemmArgs &g, int planes, const LaunchCtx &c) {
-    int halves = (2 * g.NT + c.n_wg - 1) / c.n_wg;
-    if (halves < 2) halves = 2;
-    if (halves > 3 || (halves == 3 && g.epi == EPI_SWIGLU)) halves = 4;
+    int halves = proj_halves(g.NT, c.n_wg);
+    if (halves == 3 && g.epi == EPI_SWIGLU) halves = 4;
     hipStream_t s = (hipStream_t)c.stream;
     if (planes != 1) return launch_halves<3, false>(g, halves, s);
     return g.elem == kElemF16 ? launch_halves<1, true>(g, halves, s) : launch_halves<1, false>(g, halves, s);

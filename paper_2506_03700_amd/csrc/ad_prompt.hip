@@ -576,8 +576,7 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
                 if (masked && kb * 32 + gq * 8 + c > see) sc[c] = -INFINITY;
                 bm = fmaxf(bm, sc[c]);
             }
-            bm = fmaxf(bm, __shfl_xor(bm, 16));
-            bm = fmaxf(bm, __shfl_xor(bm, 32));
+            bm = max_rows(bm);
             const float nm = fmaxf(mx, bm), ref = softmax_ref(nm);
             const float alpha = __expf(mx - ref);
             mx = nm;
@@ -612,8 +611,7 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
         __syncthreads();
     }
     // lane (n, gq): query row n of the tile, dims d*16 + gq*4 .. +3
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
+    sum = sum_rows(sum);
     const float inv = 1.0f / (sum * kPScale);
     if (row < R) {
         const int hq = kvh * a.G + (row - t_row * a.G);

@@ -145,8 +145,10 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_rows(GemmArgs g) {
                 if (row < g.N) o[0] = v0;
                 if (row + 8 < g.N) o[8] = v1;
             }
-            if (row < g.N) max_merge(best_m, best_s, best_i, v0, 1.0f, row);
-            if (row + 8 < g.N) max_merge(best_m, best_s, best_i, v1, 1.0f, row + 8);
+            if (g.head_stats) {
+                if (row < g.N) max_merge(best_m, best_s, best_i, v0, 1.0f, row);
+                if (row + 8 < g.N) max_merge(best_m, best_s, best_i, v1, 1.0f, row + 8);
+            }
         }
     };
 
@@ -193,7 +195,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_rows(GemmArgs g) {
     end_tile();
     finish(set, t1 - slot, slot);
 
-    if (g.epi == EPI_HEAD) {
+    if (g.epi == EPI_HEAD && g.head_stats) {
         // per token: over the 8 lanes, then over the wavefronts, which the partials' reader folds in workgroup order
 #pragma unroll
         for (int off = 4; off > 0; off >>= 1) max_merge(best_m, best_s, best_i, __shfl_xor(best_m, off), __shfl_xor(best_s, off), __shfl_xor(best_i, off));
