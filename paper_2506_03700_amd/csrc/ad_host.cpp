@@ -179,7 +179,9 @@ struct ad_kv {
     std::vector<int32_t> len;
     // scratch of the prompt pass, behind the rest of the storage (pr.rows == 0: none): up to pr.rows tokens at once; rows
     // [rows][d] and their 1 / rms, activation tiles of d, dq (queries, attention output) and f inputs, fp32 pieces of the projections
-    struct Prompt { int32_t rows; float *x, *scale, *pieces; char *Bd, *Q, *Bo, *Bg; } pr;
+    // pieces of q/k/v and of Wo may run on into Bg, which nobody holds then, those of down start at Q (nor Q, Bo then): the more pieces
+    // fit, the more workgroups a short prompt's projections have
+    struct Prompt { int32_t rows; float *x, *scale, *pieces, *down_pieces; size_t pieces_floats, down_floats; char *Bd, *Q, *Bo, *Bg; } pr;
 };
 
 extern "C" {
@@ -353,10 +355,16 @@ static size_t prompt_layout(const ad_config &c, int32_t max_pos, char *base, ad_
         p.x = (float *)take((size_t)p.rows * L.d * 4);
         p.scale = (float *)take((size_t)p.rows * 4);
         p.Bd = take(prompt_act_bytes(p.rows, L.d));
-        p.pieces = (float *)take(prompt_part_floats(p.rows, L.nqkv, L.d) * 4);
+        const size_t q_off = off;
         p.Q = take(prompt_act_bytes(p.rows, L.dq));
         p.Bo = take(prompt_act_bytes(p.rows, L.dq));
+        const size_t pieces_off = off;
+        p.pieces = (float *)take(prompt_part_floats(p.rows, L.nqkv, L.d) * 4);
+        p.down_pieces = (float *)p.Q;
+        p.down_floats = (off - q_off) / 4;
+        p.pieces_floats = (off - pieces_off) / 4;
         p.Bg = take(prompt_act_bytes(p.rows, L.f));
+        if (L.f % 32 == 0) p.pieces_floats = (off - pieces_off) / 4;      // (else Bg's last tile has zeros that must stay)
     }
     if (pr) *pr = p;
     return off;
@@ -668,15 +676,15 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
     }
     PromptRows rows;
     memset(&rows, 0, sizeof rows);
-    rows.x = kv->pr.x; rows.part = kv->pr.pieces; rows.M = n; rows.d = L.d; rows.KT = L.kt_d; rows.elem = ek;
+    rows.x = kv->pr.x; rows.M = n; rows.d = L.d; rows.KT = L.kt_d; rows.elem = ek;
     rows.inv_dim = 1.0f / (float)L.d; rows.eps = c.rms_eps; rows.B = kv->pr.Bd; rows.scale = kv->pr.scale;
     rows.norm_w = m->layers[0].attn_norm;
     if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
-    auto project = [&](const void *W, const void *B, int kt, int out_rows, int *n_split) {
+    auto project = [&](const void *W, const void *B, int kt, int out_rows, int *n_split, float *part, size_t part_floats) {
         PromptGemm g;
         memset(&g, 0, sizeof g);
         g.W = W; g.B = B; g.NT = out_rows / 16; g.KT = kt; g.N = out_rows; g.M = n; g.f16 = f16;
-        g.part = kv->pr.pieces; g.part_floats = prompt_part_floats(kv->pr.rows, L.nqkv, L.d); g.scale = kv->pr.scale; g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
+        g.part = part; g.part_floats = part_floats; g.scale = kv->pr.scale; g.Bnext = kv->pr.Bg; g.Bnext_KT = L.kt_f;
         return launch_prompt_gemm(g, n_split == nullptr, m->n_wg, n_split, stream);
     };
     for (int32_t l = 0; l < c.n_layers; ++l) {
@@ -686,7 +694,7 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
         // nobody asks the last layer's queries anything
         const bool last = l + 1 == c.n_layers;
         q.head0 = last ? c.n_q_heads : 0; q.ld = L.nqkv - q.head0 * L.dh;
-        if ((rc = project(lp.wqkv + (size_t)(q.head0 * L.dh / 16) * L.kt_d * 1024u, kv->pr.Bd, L.kt_d, q.ld, &q.n_split))) return hip_fail(rc, "prompt pass: qkv");
+        if ((rc = project(lp.wqkv + (size_t)(q.head0 * L.dh / 16) * L.kt_d * 1024u, kv->pr.Bd, L.kt_d, q.ld, &q.n_split, kv->pr.pieces, kv->pr.pieces_floats))) return hip_fail(rc, "prompt pass: qkv");
         q.part = kv->pr.pieces; q.scale = kv->pr.scale; q.M = n; q.Hq = c.n_q_heads; q.Hkv = c.n_kv_heads; q.dh = L.dh; q.G = c.n_q_heads / c.n_kv_heads;
         q.rope = kv->rope + (size_t)pos0 * (L.dh / 2) * 2;
         q.Kc = kv->storage + (size_t)l * kv->layer_bytes; q.Vc = (char *)q.Kc + kv->half_bytes;
@@ -698,11 +706,13 @@ static int prompt_pass(const ad_model *m, ad_kv *kv, const int32_t *tokens, int3
         a.Q = kv->pr.Q; a.Kc = q.Kc; a.Vc = q.Vc; a.stride = kv->stride; a.pos0 = pos0; a.M = n; a.Hq = q.Hq; a.Hkv = q.Hkv; a.dh = L.dh; a.G = q.G;
         a.q_rows = q.q_rows; a.Bo = kv->pr.Bo; a.Bo_KT = L.kt_q; a.f16 = f16;
         if ((rc = launch_prompt_attn(a, stream))) return hip_fail(rc, "prompt pass: attention");
-        if ((rc = project(lp.wo, kv->pr.Bo, L.kt_q, L.d, &rows.n_split))) return hip_fail(rc, "prompt pass: wo");
+        if ((rc = project(lp.wo, kv->pr.Bo, L.kt_q, L.d, &rows.n_split, kv->pr.pieces, kv->pr.pieces_floats))) return hip_fail(rc, "prompt pass: wo");
+        rows.part = kv->pr.pieces;
         rows.norm_w = lp.ffn_norm;
         if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
-        if ((rc = project(lp.wgu, kv->pr.Bd, L.kt_d, 2 * L.f, nullptr))) return hip_fail(rc, "prompt pass: gate/up");
-        if ((rc = project(lp.wd, kv->pr.Bg, L.kt_f, L.d, &rows.n_split))) return hip_fail(rc, "prompt pass: down");
+        if ((rc = project(lp.wgu, kv->pr.Bd, L.kt_d, 2 * L.f, nullptr, nullptr, 0))) return hip_fail(rc, "prompt pass: gate/up");
+        if ((rc = project(lp.wd, kv->pr.Bg, L.kt_f, L.d, &rows.n_split, kv->pr.down_pieces, kv->pr.down_floats))) return hip_fail(rc, "prompt pass: down");
+        rows.part = kv->pr.down_pieces;
         rows.norm_w = m->layers[l + 1].attn_norm;
         if ((rc = launch_prompt_rows(rows, stream))) return hip_fail(rc, "prompt pass: norm");
     }

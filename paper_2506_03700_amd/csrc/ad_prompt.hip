@@ -29,7 +29,7 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // ---------------------------------------------------------------------------------------------------
 // A workgroup of NWR x NWT wavefronts computes BR = NWR * WR row tiles x BT = NWT * WT token tiles; a wavefront holds
 // WR x WT accumulators.  Both operands lie in memory in MFMA operand order, so tiles are copied as they are and every LDS
-// access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.  Activations are staged in LDS.
+// access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.
 //
 // The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
 // the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
@@ -120,67 +120,81 @@ struct PromptAcc {
     }
 };
 
+constexpr int prompt_stage_units(int br, int bt) { return br * 64 + bt * 128; }
+
 // 1 KiB from memory straight into LDS: lane l's 16 bytes go to unit l of dst (the same for all lanes)
 __device__ __forceinline__ void copy_to_lds(const void *src, bf16x8 *dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
-// More than 64 tokens: bound by the matrix cores and, with them, by the power that operands on the move take (with operands of zeros
-// the same launches run 20 to 45 % faster).  A wavefront loads its weight tiles from memory straight into registers, one k-step
-// ahead (the NWT wavefronts that share them find them in the compute unit's cache); the activations, which NWR wavefronts share,
-// are copied from memory into LDS without a way through registers, two k-steps ahead (three stages).  A step ends when all
-// but its own copies have landed, then a barrier.  Measured at 1024 tokens, us and executed TFLOP/s (hi and lo products
-// both counted), 6144 x 4096, 4096 x 4096, 4096 x 14336, 28672 x 4096: 112, 62, 222, 456 (920, 1110, 1080, 1055) against
-// 123, 65, 232, 468 with two stages through registers and all accumulators emptied at once.  2 x 4 tiles by 4 x 2 wavefronts (two
-// workgroups per compute unit) against 4 x 4 by 2 x 2 (two) and by 4 x 2 (one): 119, 64, 224, 446 and 123, 69, 223, 486; 512 tokens
-// 57, 35, 104, 245 against 60, 36, 104, 241 and 62, 40, 107, 248.
-template <int WR, int WT, int NWR, int NWT, bool F16, int EPI>
+// From about 128 tokens on bound by the matrix cores and, with them, by the power that operands on the move take (with operands of
+// zeros the same launches run 20 to 45 % faster); below by the weights' way from memory.  Weights and activations are copied from
+// memory into LDS without a way through registers, NST - 1 k-steps ahead; a step waits for its own stage, and for everyone to be
+// done with the one before it, whose place the newest copies take.  Stages: as many as leave room for two workgroups per compute unit
+// (5 and 4 of 12 and 16 KiB, 3 of 24).  Measured with weights that no cache holds, us for 6144 x 4096, 4096 x 4096, 4096 x 14336,
+// 28672 x 4096, against weights straight into registers a k-step ahead (up to 64 tokens: both through registers into LDS):
+//     32 tokens   13.6    9.0   22.4   44.6     13.0   10.4   25.9   51.4
+//     64          16.7   10.5   24.9   48.3     17.6   12.5   30.4   61.6
+//    128          24.3   16.0   37.2   72.3     26.2   19.7   51.4  106.6
+//    256          36.6   24.1   59.5  125       37.0   24.3   67.5  128.6
+//   1024         102.8   64.5  207    425      105.1   64.2  198.6  435.8
+// (executed rate at 1024 tokens, hi and lo products both counted: 1.0 to 1.16 PFLOP/s).  4 x 4 tiles by 4 x 2 wavefronts and 4 stages, one
+// workgroup per compute unit: 1024 tokens 105.7, 65.3, 194, 435, 96 tokens 98 us for 28672 x 4096 (69.9 with 2 x 4).
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI>
 __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
     constexpr int NW = NWR * NWT, BR = WR * NWR, BT = WT * NWT;
-    constexpr int AU = BT * 128, NA = BT * 2 / NW;              // 16-byte units of activations per stage, copies per wavefront
-    static_assert(BT * 2 % NW == 0 && NA < 16 && kFlush % 2 == 0, "a stage is a whole number of copies per wavefront");
-    __shared__ bf16x8 lds[3][AU];
+    constexpr int SU = prompt_stage_units(BR, BT), NC = (BR + BT * 2) / NW;     // 16-byte units per stage, copies per wavefront
+    constexpr int FLY = NC * (NST - 2);                         // copies of a wavefront that may be in flight when a step begins
+    static_assert((BR + BT * 2) % NW == 0 && FLY < 64 && NST >= 3, "a stage is a whole number of copies per wavefront");
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    bf16x8 *lds = (bf16x8 *)lds_raw;                            // [NST][weight tiles, activation tiles]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % NWR, wt = wave / NWR;
     const PromptTile T = prompt_tile(g);
 
-    unsigned woff[WR], aoff[NA];
+    const char *src[NC];
+    unsigned off[NC];
+    int shift[NC];                                              // log2 of the bytes from one k-step to the next
 #pragma unroll
-    for (int r = 0; r < WR; ++r) {
-        int rt = T.rb * BR + wr * WR + r;
-        if (rt > g.NT - 1) rt = g.NT - 1;                       // past the last row tile: its products are not stored
-        woff[r] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)lane) << 4;
+    for (int i = 0; i < NC; ++i) {
+        const int u = wave * NC + i;                            // 1 KiB of a stage: a weight tile, or a token tile's plane
+        if (u < BR) {
+            int rt = T.rb * BR + u;
+            if (rt > g.NT - 1) rt = g.NT - 1;                   // past the last row tile: its products are not stored
+            src[i] = (const char *)g.W;
+            off[i] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)lane) << 4;
+            shift[i] = 10;
+        } else {
+            const int v = u - BR;
+            src[i] = (const char *)g.B;
+            off[i] = ((unsigned)(T.tb * BT + (v >> 1)) * (unsigned)g.KT * 128u + (unsigned)((v & 1) * 64 + lane)) << 4;
+            shift[i] = 11;
+        }
     }
+    const int k_last = T.k1 - 1;                                // copies past the piece repeat its last k-step
+    auto copy = [&](int stage, int k) {
+        const int kk = k < k_last ? k : k_last;
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const int u = wave * NA + i;                            // token tile and plane
-        aoff[i] = ((unsigned)(T.tb * BT + (u >> 1)) * (unsigned)g.KT * 128u + (unsigned)((u & 1) * 64 + lane)) << 4;
-    }
-    const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
-    bf16x8 w0[WR], w1[WR];
-    const int k_last = T.k1 - 1;                                // loads past the piece repeat its last k-step
-    auto load_w = [&](bf16x8 (&w)[WR], int k) {
-        const unsigned o = (unsigned)(k < k_last ? k : k_last) << 10;
-#pragma unroll
-        for (int r = 0; r < WR; ++r) w[r] = *(const bf16x8 *)(Wb + (woff[r] + o));
-    };
-    auto copy_a = [&](bf16x8 *stage, int k) {
-        const unsigned o = (unsigned)(k < k_last ? k : k_last) << 11;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) copy_to_lds(Ab + (aoff[i] + o), stage + (wave * NA + i) * 64);
+        for (int i = 0; i < NC; ++i) copy_to_lds(src[i] + (size_t)(off[i] + ((unsigned)kk << shift[i])), lds + stage * SU + (wave * NC + i) * 64);
     };
     PromptAcc<WR, WT> C;
     C.clear();
     const int n_step = T.k1 - T.k0;
-    // k-step s from stage `cur`: the weights of the next one and the activations of the one after it (into the stage that was read in
-    // the step before) are requested first.  turn: which accumulators it empties (-1: none).
-    auto step = [&](const bf16x8 (&w)[WR], bf16x8 (&wn)[WR], int s, const bf16x8 *cur, bf16x8 *put, int turn) {
-        load_w(wn, T.k0 + s + 1);
-        copy_a(put, T.k0 + s + 2);
+    int cur = 0, put = NST - 1;
+    // turn: which accumulators the step empties (-1: none)
+    auto step = [&](int s, int turn) {
+        __builtin_amdgcn_sched_barrier(0);
+        // All but the newest FLY copies have landed.  (Bits of the immediate: vmcnt 0-3 and 14-15; expcnt 4-6 and lgkmcnt 8-11, all
+        // ones, are not waited for: a wavefront's reads of the stage before were over when it formed their products.)
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (FLY & 15) | (FLY >> 4 << 14));
+        __builtin_amdgcn_s_barrier();
+        copy(put, T.k0 + s + NST - 1);
         __builtin_amdgcn_sched_barrier(0);
         if (turn >= 0) C.flush_some(turn);
-        const bf16x8 *p = cur + wt * WT * 128 + lane;
-        bf16x8 bh[WT], bl[WT];
+        const bf16x8 *w = lds + cur * SU + wr * WR * 64 + lane, *p = lds + cur * SU + BR * 64 + wt * WT * 128 + lane;
+        bf16x8 a[WR], bh[WT], bl[WT];
+#pragma unroll
+        for (int r = 0; r < WR; ++r) a[r] = w[r * 64];
 #pragma unroll
         for (int t = 0; t < WT; ++t) {
             bh[t] = p[t * 128];
@@ -189,135 +203,23 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
 #pragma unroll
         for (int r = 0; r < WR; ++r)
 #pragma unroll
-            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bh[t], C.acc[r][t]);
+            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a[r], bh[t], C.acc[r][t]);
 #pragma unroll
         for (int r = 0; r < WR; ++r)
 #pragma unroll
-            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], bl[t], C.acc[r][t]);
-        __builtin_amdgcn_sched_barrier(0);
-        // all but the newest NA requests, this step's copies, have landed: the next step's weights and stage are there.  (Bits of
-        // the immediate: vmcnt 0-3, 14-15; expcnt 4-6 and lgkmcnt 8-11, all ones, are not waited for.)
-        __builtin_amdgcn_s_waitcnt(0x0F70 | NA);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
+            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a[r], bl[t], C.acc[r][t]);
+        put = cur;
+        cur = cur == NST - 1 ? 0 : cur + 1;
     };
-    bf16x8 *l0 = lds[0], *l1 = lds[1], *l2 = lds[2];
-    auto rotate = [&]() {                                       // two steps on
-        bf16x8 *x = l0;
-        l0 = l2;
-        l2 = l1;
-        l1 = x;
-    };
-    copy_a(l0, T.k0);
-    load_w(w0, T.k0);
-    copy_a(l1, T.k0 + 1);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int j = 0; j < NST - 1; ++j) copy(j, T.k0 + j);
     int s = 0;
     for (; s + kFlush <= n_step; s += kFlush) {
 #pragma unroll
-        for (int j = 0; j < kFlush; j += 2) {
-            step(w0, w1, s + j, l0, l2, j);
-            step(w1, w0, s + j + 1, l1, l0, j + 1);
-            rotate();
-        }
+        for (int j = 0; j < kFlush; ++j) step(s + j, j);
     }
-    for (; s < n_step; s += 2) {
-        step(w0, w1, s, l0, l2, -1);
-        if (s + 1 < n_step) step(w1, w0, s + 1, l1, l0, -1);
-        rotate();
-    }
-    C.flush();
-    C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
-}
-
-// Up to 64 tokens: bound by the weights' way from memory (28672 x 4096 for 32 tokens: 38.6 us, 6.1 TB/s), which is best
-// when all of a workgroup's threads have whole stages of them in flight: weights and activations of KS = 2 k-steps are
-// staged in LDS together (weights in registers as above, 32 tokens: 50.7 us).
-template <int WR, int WT, int NWR, int NWT, bool F16, int EPI>
-__global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm_few(PromptGemm g) {
-    constexpr int KS = 2, NTH = 64 * NWR * NWT, BR = WR * NWR, BT = WT * NWT;
-    constexpr int WU = BR * KS * 64, AU = BT * KS * 128;        // 16-byte units per stage
-    constexpr int NW_ = WU / NTH, NA = AU / NTH;                // loads per thread
-    static_assert(WU % NTH == 0 && AU % NTH == 0 && kFlush % KS == 0, "a stage is a whole number of loads per thread");
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    bf16x8 *lds = (bf16x8 *)lds_raw;                            // [2][WU + AU]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave % NWR, wt = wave / NWR;
-    const PromptTile T = prompt_tile(g);
-
-    unsigned woff[NW_], aoff[NA];
-    int wks[NW_], aks[NA];
-#pragma unroll
-    for (int i = 0; i < NW_; ++i) {
-        const int u = tid + i * NTH, in = u % (KS * 64);
-        int rt = T.rb * BR + u / (KS * 64);
-        if (rt > g.NT - 1) rt = g.NT - 1;                       // past the last row tile: its products are not stored
-        wks[i] = in >> 6;
-        woff[i] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)(in & 63)) << 4;
-    }
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const int u = tid + i * NTH, in = u % (KS * 128);
-        aks[i] = in >> 7;
-        aoff[i] = ((unsigned)(T.tb * BT + u / (KS * 128)) * (unsigned)g.KT * 128u + (unsigned)(in & 127)) << 4;
-    }
-    const char *Wb = (const char *)g.W, *Ab = (const char *)g.B;
-    bf16x8 wreg[NW_], areg[NA];
-    auto load = [&](int k) {                                    // k-steps past the matrix repeat its last one
-#pragma unroll
-        for (int i = 0; i < NW_; ++i) {
-            const int kk = k + wks[i] < g.KT - 1 ? k + wks[i] : g.KT - 1;
-            wreg[i] = *(const bf16x8 *)(Wb + (woff[i] + ((unsigned)kk << 10)));
-        }
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int kk = k + aks[i] < g.KT - 1 ? k + aks[i] : g.KT - 1;
-            areg[i] = *(const bf16x8 *)(Ab + (aoff[i] + ((unsigned)kk << 11)));
-        }
-    };
-    auto store = [&](bf16x8 *s) {
-#pragma unroll
-        for (int i = 0; i < NW_; ++i) s[tid + i * NTH] = wreg[i];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) s[WU + tid + i * NTH] = areg[i];
-    };
-    PromptAcc<WR, WT> C;
-    C.clear();
-    const int n_stage = (T.k1 - T.k0 + KS - 1) / KS;
-    load(T.k0);
-    store(lds);
-    if (n_stage > 1) load(T.k0 + KS);
-    __syncthreads();
-    for (int s = 0; s < n_stage; ++s) {
-        const bf16x8 *cur = lds + (s & 1) * (WU + AU);
-#pragma unroll
-        for (int j = 0; j < KS; ++j) {
-            if (T.k0 + s * KS + j < T.k1) {
-                bf16x8 bh[WT], bl[WT];
-#pragma unroll
-                for (int t = 0; t < WT; ++t) {
-                    const bf16x8 *p = cur + WU + ((wt * WT + t) * KS + j) * 128 + lane;
-                    bh[t] = p[0];
-                    bl[t] = p[64];
-                }
-#pragma unroll
-                for (int r = 0; r < WR; ++r) {
-                    const bf16x8 a = cur[((wr * WR + r) * KS + j) * 64 + lane];
-#pragma unroll
-                    for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a, bh[t], C.acc[r][t]);
-#pragma unroll
-                    for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a, bl[t], C.acc[r][t]);
-                }
-            }
-        }
-        if ((s + 1) % (kFlush / KS) == 0) C.flush();
-        if (s + 1 < n_stage) {
-            store(lds + ((s + 1) & 1) * (WU + AU));
-            if (s + 2 < n_stage) load(T.k0 + (s + 2) * KS);
-        }
-        __syncthreads();
-    }
+    for (; s < n_step; ++s) step(s, -1);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                         // the copies past the end land before the workgroup's LDS is another's
     C.flush();
     C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
 }
@@ -655,27 +557,26 @@ int plan_gemm(PromptGemm &g, int BR, int BT, int n_wg, int *n_split) {
     return 0;
 }
 
-template <int WT, bool F16, int EPI>
-int launch_gemm_few(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
-    constexpr size_t lds = 2 * (size_t)(8 * 2 * 64 + WT * 2 * 128) * 16;
-    if (int rc = plan_gemm<EPI>(g, 8, WT, n_wg, n_split)) return rc;
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI>
+int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
+    constexpr int BR = WR * NWR, BT = WT * NWT, lds = NST * prompt_stage_units(BR, BT) * 16;
+    if (int rc = plan_gemm<EPI>(g, BR, BT, n_wg, n_split)) return rc;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm_few<2, WT, 4, 1, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_prompt_gemm_few<2, WT, 4, 1, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(256), lds, s, g);
+    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(64 * NWR * NWT), lds, s, g);
     return (int)hipGetLastError();
 }
 
+// 128 rows by as many tokens as a prompt has, up to 128 (the others are products for nothing)
 template <bool F16, int EPI>
 int launch_gemm_sized(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
-    if (g.M <= 32) return launch_gemm_few<2, F16, EPI>(g, n_wg, n_split, s);       // 128 rows x 32 tokens
-    if (g.M <= 64) return launch_gemm_few<4, F16, EPI>(g, n_wg, n_split, s);       // 128 x 64
-    if (int rc = plan_gemm<EPI>(g, 8, 8, n_wg, n_split)) return rc;                // 128 x 128
-    hipLaunchKernelGGL((k_prompt_gemm<2, 4, 4, 2, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(512), 0, s, g);
-    return (int)hipGetLastError();
+    if (g.M <= 32) return launch_gemm_as<2, 2, 4, 1, 5, F16, EPI>(g, n_wg, n_split, s);
+    if (g.M <= 64) return launch_gemm_as<2, 2, 4, 2, 4, F16, EPI>(g, n_wg, n_split, s);
+    return launch_gemm_as<2, 4, 4, 2, 3, F16, EPI>(g, n_wg, n_split, s);
 }
 
 }  // namespace
