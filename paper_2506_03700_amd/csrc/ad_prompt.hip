@@ -227,11 +227,28 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
 // ---------------------------------------------------------------------------------------------------
 // residual, RMSNorm and operand tiles: one workgroup per token
 // ---------------------------------------------------------------------------------------------------
-constexpr int kRowsThreads = 256;
-constexpr int kRowsUnits = 4;          // units of 8 inputs per thread: d_model <= 8192
+// The pieces of four outputs, added up in order; four requests at a time are on their way.
+__device__ __forceinline__ f32x4 sum_pieces(const float *p, size_t step, int n) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int i = 0;
+    for (; i + 4 <= n; i += 4) {
+        f32x4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = *(const f32x4 *)(p + (size_t)(i + j) * step);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s += v[j];
+    }
+    for (; i < n; ++i) s += *(const f32x4 *)(p + (size_t)i * step);
+    return s;
+}
 
-template <bool F16>
+constexpr int kRowsMax = 8192;          // inputs (d_model)
+
+// One unit of 8 inputs per thread at d_model 4096 while there are compute units to spare, else two (63 tokens, 8 pieces: 11.1 us with two
+// and the pieces requested one after the other, 6.4 now; 1023 tokens, 2 pieces 25 us either way).
+template <bool F16, int kRowsThreads>
 __global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
+    constexpr int kRowsUnits = kRowsMax / 8 / kRowsThreads;     // units per thread
     __shared__ float wsum[kRowsThreads / 64];
     const int t = blockIdx.x, tid = threadIdx.x;
     float *x = a.x + (size_t)t * a.d;
@@ -244,8 +261,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
         if (u < nu) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                f32x4 s = {0.f, 0.f, 0.f, 0.f};
-                for (int p = 0; p < a.n_split; ++p) s += *(const f32x4 *)(a.part + ((size_t)p * a.M + t) * a.d + u * 8 + h * 4);
+                const f32x4 s = sum_pieces(a.part + (size_t)t * a.d + u * 8 + h * 4, (size_t)a.M * a.d, a.n_split);
                 v[i][h] = *(const f32x4 *)(x + u * 8 + h * 4);
                 if (a.n_split) {
                     v[i][h] += s;
@@ -255,10 +271,12 @@ __global__ void __launch_bounds__(kRowsThreads) k_prompt_rows(PromptRows a) {
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) ssq += __shfl_xor(ssq, off);
+    ssq = sum64(ssq);
     if ((tid & 63) == 0) wsum[tid >> 6] = ssq;
     __syncthreads();
-    const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < kRowsThreads / 64; ++w) total += wsum[w];
     if (tid == 0) a.scale[t] = 1.0f / sqrtf(total * a.inv_dim + a.eps);
 #pragma unroll
     for (int i = 0; i < kRowsUnits; ++i) {
@@ -292,23 +310,22 @@ __global__ void __launch_bounds__(256) k_prompt_embed(PromptEmbed a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// rotation, KV append, query tiles: one workgroup per 64 tokens and head (q heads, if they are there, then k heads, then v heads)
+// rotation, KV append, query tiles: one workgroup per 64 (few tokens: 16) tokens and head (q heads, if they are there, then k heads, then v heads)
 // ---------------------------------------------------------------------------------------------------
-constexpr int kQkvTokens = 64;
+constexpr int kQkvAlign = 64;           // V's dead positions are cleared up to a multiple of this
+constexpr int kFewTokens = 256;         // up to here workgroups of 16 tokens, and above of twice the threads per token: larger ones would leave
+                                        // compute units idle (63 tokens of the 8B shape: 48 workgroups of 64, 10.6 us, now 192)
 
-template <int DH, bool F16>
+template <int DH, int kQkvTokens, bool F16>
 __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
     constexpr int half = DH / 2, NC = half / 8;         // groups of 8 dimensions in the lower half
     const int t0 = blockIdx.x * kQkvTokens, head = a.head0 + blockIdx.y, tid = threadIdx.x;
     const int col0 = (int)blockIdx.y * DH;
     auto load8 = [&](int t, int c, float (&o)[8]) {               // columns c .. of this head
         const int col = col0 + c;
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-        for (int p = 0; p < a.n_split; ++p) {
-            const float *src = a.part + ((size_t)p * a.M + t) * a.ld + col;
-            s0 += *(const f32x4 *)src;
-            s1 += *(const f32x4 *)(src + 4);
-        }
+        const float *src = a.part + (size_t)t * a.ld + col;
+        const size_t step = (size_t)a.M * a.ld;
+        const f32x4 s0 = sum_pieces(src, step, a.n_split), s1 = sum_pieces(src + 4, step, a.n_split);
         const float scale = a.scale[t];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -595,20 +612,29 @@ int launch_prompt_embed(const PromptEmbed &a, void *stream) {
 }
 
 int launch_prompt_rows(const PromptRows &a, void *stream) {
-    if (a.M < 1 || a.d > kRowsThreads * kRowsUnits * 8 || a.elem == kElemF32) return (int)hipErrorInvalidValue;
-    if (a.elem == kElemF16) hipLaunchKernelGGL((k_prompt_rows<true>), dim3(a.M), dim3(kRowsThreads), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((k_prompt_rows<false>), dim3(a.M), dim3(kRowsThreads), 0, (hipStream_t)stream, a);
+    if (a.M < 1 || a.d > kRowsMax || a.elem == kElemF32) return (int)hipErrorInvalidValue;
+    hipStream_t s = (hipStream_t)stream;
+    const bool f16 = a.elem == kElemF16;
+    if (a.M <= kFewTokens) {
+        if (f16) hipLaunchKernelGGL((k_prompt_rows<true, 512>), dim3(a.M), dim3(512), 0, s, a);
+        else hipLaunchKernelGGL((k_prompt_rows<false, 512>), dim3(a.M), dim3(512), 0, s, a);
+    } else {
+        if (f16) hipLaunchKernelGGL((k_prompt_rows<true, 256>), dim3(a.M), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_prompt_rows<false, 256>), dim3(a.M), dim3(256), 0, s, a);
+    }
     return (int)hipGetLastError();
 }
 
 template <int DH, bool F16>
 static int launch_qkv_as(const PromptQkv &a, hipStream_t s) {
-    hipLaunchKernelGGL((k_prompt_qkv<DH, F16>), dim3((a.M + kQkvTokens - 1) / kQkvTokens, a.Hq + 2 * a.Hkv - a.head0), dim3(256), 0, s, a);
+    const int n = (a.M + kQkvAlign - 1) / kQkvAlign * kQkvAlign, heads = a.Hq + 2 * a.Hkv - a.head0;
+    if (a.M <= kFewTokens) hipLaunchKernelGGL((k_prompt_qkv<DH, 16, F16>), dim3(n / 16, heads), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_prompt_qkv<DH, 64, F16>), dim3(n / 64, heads), dim3(256), 0, s, a);
     return (int)hipGetLastError();
 }
 int launch_prompt_qkv(const PromptQkv &a, void *stream) {
     hipStream_t s = (hipStream_t)stream;
-    if (a.pos0 % kQkvTokens) return (int)hipErrorInvalidValue;
+    if (a.pos0 % kQkvAlign) return (int)hipErrorInvalidValue;
     if (a.dh == 128) return a.f16 ? launch_qkv_as<128, true>(a, s) : launch_qkv_as<128, false>(a, s);
     if (a.dh == 64) return a.f16 ? launch_qkv_as<64, true>(a, s) : launch_qkv_as<64, false>(a, s);
     return (int)hipErrorInvalidValue;
