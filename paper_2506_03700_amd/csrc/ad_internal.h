@@ -24,7 +24,7 @@ enum : int { kElemF32 = 0, kElemBF16 = 1, kElemF16 = 2 };   // host-side names o
 // cache line, and a call with m tokens touches m lines per k-step (KT * 1 KiB for a full block).
 constexpr int kTileRows = 16;
 constexpr int kTileK = 32;
-constexpr int kThreads = 1024;   // one workgroup per CU, 16 wavefronts
+constexpr int kThreads = 1024;   // LDS slots are laid out for up to 16 wavefronts
 constexpr int kWaves = kThreads / 64;
 
 inline size_t packed_bytes(int64_t N, int64_t K, int planes) {
@@ -68,9 +68,10 @@ struct GemmArgs {
     void *Bnext;          // packed activations written by the epilogue
     int Bnext_KT;         // k-steps of that block (the K of the GEMM that will read it, in units of 32)
     // EPI_RESID in streamed mode, optional (Bnext non-null): the epilogue also prepares the next GEMM's input, which is
-    // RMSNorm(out): it packs out * next_norm_w into Bnext and writes the sum of squares of its 16 outputs per token
-    // to ssq_out[tile][token].  The consumer (stationary mode, B = that block, ssq_in = those partials, ssq_tiles
-    // of them) only has to load its operand registers and add the partials up for the 1/rms factor.
+    // RMSNorm(out): it packs out * next_norm_w into Bnext and writes the sum of squares of its outputs per token to
+    // ssq_out[i][token], i a half tile of 8 rows (in the fused layer kernel a tile of 16).  The consumer (stationary mode,
+    // B = that block, ssq_in = those partials, ssq_tiles of them) only has to load its operand registers and add the
+    // partials up for the 1/rms factor.
     const void *next_norm_w;
     int next_norm_elem;
     float *ssq_out;

@@ -14,8 +14,8 @@ namespace ad {
 constexpr int kPromptAlign = 128;     // tokens of the largest workgroup tile
 constexpr int kPromptRows = 1024;     // most tokens per pass through the layers (a multiple of kPromptAlign)
 // Fewest tokens it is used for; up to 8 are one layer step per layer.  A whole ad_generate of one token, prompt pass against layer
-// steps, 9 / 16 / 33 tokens before the last: 8B shape, 8 layers 1.75 / 1.76 / 1.96 against 2.31 / 2.42 / 4.80 ms, tiny bf16 model
-// 0.28 / 0.28 / 0.30 against 0.41 / 0.41 / 0.78 ms; for 8 tokens one layer step per layer takes 1.60 ms (8B).
+// steps, 9 / 16 / 33 tokens before the last: 8B shape, 8 layers 1.50 / 1.51 / 1.61 against 2.13 / 2.25 / 4.45 ms, tiny bf16 model
+// 0.22 / 0.22 / 0.23 against 0.28 / 0.29 / 0.54 ms; for 8 tokens one layer step per layer takes 1.47 ms (8B).
 constexpr int kPromptMin = 9;
 constexpr int kPromptMaxSplit = 8;    // most pieces a contraction is cut into along K
 
