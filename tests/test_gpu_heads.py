@@ -1,0 +1,57 @@
+"""GPU: the vocabulary pass where its kernel changes: a workgroup's rows are 2, 3 or 4 halves of a 16-row tile (up to 4096, 6144 and
+8192 ids on 256 compute units), beyond that whole tiles."""
+import numpy as np
+import pytest
+
+from paper_2506_03700_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+F32, BF16, F16 = synth.F32, synth.BF16, synth.F16
+
+
+@pytest.fixture(scope="module")
+def ad():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2506_03700_amd import binding
+    binding.lib()
+    return binding
+
+
+def shape(V, dtype):
+    return synth.ModelShape(f"V{V}", 2, 64, 1, 1, 64, 64, V, 10000.0, (1,), dtype, False)
+
+
+def pointing_at(w, ids):
+    """Rows whose normalised value is the head's row of these ids: each has the largest logit of its row, by far."""
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(synth.as_f32(w["lm_head"])[ids] * 50)).to("cuda:0")
+
+
+@pytest.mark.parametrize("V,dtype", [(300, F32), (300, BF16), (5003, F16), (8192, BF16), (10000, F32), (10000, BF16)], ids=str)
+def test_logits_that_are_no_numbers_are_passed_by(ad, V, dtype):
+    """The token is the largest of the other logits, wherever in its group of rows the one that is no number lies; the confidence is none
+    either."""
+    s = shape(V, dtype)
+    w = synth.make_weights(s, seed=3)
+    best = np.array([3, 13, 16, 47, V // 2 + 1, V // 3, V - 9, V - 1])
+    hidden = pointing_at(w, best)
+    w["lm_head"] = w["lm_head"].copy()
+    bad = sorted({int(r) for b in best for r in (b & ~7, b | 7, b ^ 1, b ^ 4) if r < V} - set(best.tolist()))
+    w["lm_head"][bad] = {F32: np.nan, F16: np.nan, BF16: 0x7fc0}[dtype]
+    g = ad.Model(s, w, max_pos=8)
+    z = g.ad_head_logits(2, hidden).cpu().numpy()
+    assert np.array_equal(np.isnan(z), np.broadcast_to(np.isin(np.arange(V), bad), z.shape))
+    assert np.array_equal(np.nanargmax(z, axis=1), best)
+    for layer in (1, 2):
+        for r, b in enumerate(best):
+            print(f"case V {V} dtype {dtype} layer {layer} id {b}", flush=True)
+            tok, conf = g.ad_exit_head(layer, hidden[r])
+            assert tok == b and np.isnan(conf)
+    for static in (False, True):
+        n, nxt, arg = g.ad_verify(hidden, best[:-1] - 1, static=static)
+        assert n == 0 and nxt == best[0] and np.array_equal(arg, best)
+        n, nxt, arg = g.ad_verify(hidden, best[:-1], static=static)
+        assert n == 7 and nxt == best[7] and np.array_equal(arg, best)
+    g.close()
