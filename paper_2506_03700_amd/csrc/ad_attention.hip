@@ -493,7 +493,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
     const int tid = threadIdx.x, grp = tid / TG, e = 2 * (tid % TG), S = a.S;
     const int row = blockIdx.x, g = div_small(row, a.mul_R), r = row - g * a.R, t = div_small(r, a.mul_G), hq = g * a.G + (r - t * a.G);
     const float *base = a.part + ((size_t)g * S * a.R + r) * PR;
-    const unsigned sstride = (unsigned)a.R * PR;
+    const size_t sstride = (size_t)a.R * PR;                   // (an fp32 cache's splits grow with the context: beyond 32 bits in all)
     float M = -INFINITY, den = 0.f;
     f32x2 o = {0.f, 0.f};
     for (int s0 = grp; s0 < S; s0 += NG * KB) {
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 #pragma unroll
         for (int k = 0; k < KB; ++k) {                          // splits past the end repeat the group's first (weight 0)
             const int s = s0 + k * NG;
-            const float *p = base + (unsigned)(s < S ? s : s0) * sstride;
+            const float *p = base + (size_t)(s < S ? s : s0) * sstride;
             ms[k] = *(const f32x2 *)(p + DH);
             v[k] = *(const f32x2 *)(p + e);
         }

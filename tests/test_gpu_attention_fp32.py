@@ -61,3 +61,28 @@ def test_layer_step_attention(ad, s, ctxs, rows):
             check_kv(s.dtype, kg[ctx:], ko, "K")
             check_kv(s.dtype, vg[ctx:], vo, "V")
     g.close()
+
+
+def test_partials_beyond_32_bit_offsets(ad):
+    """8192 query rows on one kv head of 128 dimensions at 262400 positions leave 4100 splits' partials, 17 GB: more floats than 32 bits
+    count.  All cached keys are zeros, so every position has the same weight; the values of those in a late split are all there is."""
+    import torch
+    s = synth.ModelShape("h1024-1x128-f32", 1, 16, 1024, 1, 128, 8, 16, 10000.0, (), synth.F32, False)
+    ctx, m, first, n_late = 4100 * 64, 8, 4060 * 64, 64
+    assert 4060 * 1024 * m * 130 > 1 << 32
+    w = synth.make_weights(s, seed=4)
+    w["layers.0.w_down"] = np.zeros_like(w["layers.0.w_down"])
+    g = ad.Model(s, w, max_pos=ctx + m)
+    K, V = g.kv_views()
+    v = (np.random.default_rng(5).standard_normal(128) * 3000).astype(np.float32)
+    V[0, 0, :, first:first + n_late] = torch.from_numpy(v).to("cuda:0")[:, None]
+    g.kv_set_len(1, ctx)
+    h = synth.make_hidden(s, 6, m)
+    hg = torch.from_numpy(h).to("cuda:0")
+    g.ad_layer_step(1, hg, np.arange(ctx, ctx + m))
+    # The call's own rows: their weights are e^score against 1 (scores below 0.1 here) and their values below 1, eight of them
+    # against the late split's 64 of thousands: 1e-4 of the attention output at most.
+    want = np.tile(v.astype(np.float64) * n_late / ctx, 1024) @ w["layers.0.wo"].astype(np.float64).T
+    got = hg.cpu().numpy().astype(np.float64) - h
+    assert np.max(np.abs(got - want)) <= 1e-3 * np.max(np.abs(want)), (got, want)
+    g.close()
