@@ -2,8 +2,11 @@
 8192 ids on 256 compute units), beyond that whole tiles."""
 import numpy as np
 import pytest
+import torch
 
+from oracle import oracle as orc
 from paper_2506_03700_amd import synth
+from tolerances import check_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -12,7 +15,6 @@ F32, BF16, F16 = synth.F32, synth.BF16, synth.F16
 
 @pytest.fixture(scope="module")
 def ad():
-    import torch
     assert torch.cuda.is_available(), "these tests need the GPU"
     from paper_2506_03700_amd import binding
     binding.lib()
@@ -25,7 +27,6 @@ def shape(V, dtype):
 
 def pointing_at(w, ids):
     """Rows whose normalised value is the head's row of these ids: each has the largest logit of its row, by far."""
-    import torch
     return torch.from_numpy(np.ascontiguousarray(synth.as_f32(w["lm_head"])[ids] * 50)).to("cuda:0")
 
 
@@ -54,4 +55,19 @@ def test_logits_that_are_no_numbers_are_passed_by(ad, V, dtype):
         assert n == 0 and nxt == best[0] and np.array_equal(arg, best)
         n, nxt, arg = g.ad_verify(hidden, best[:-1], static=static)
         assert n == 7 and nxt == best[7] and np.array_equal(arg, best)
+    g.close()
+
+
+@pytest.mark.parametrize("d", [512, 528, 1024, 1040, 2048, 2064, 3072, 3088, 4096, 4112, 5120])
+def test_large_vocabularies_of_fp32_models(ad, d):
+    """The widths where a wavefront's share of the inputs, 2, 4, 8, 12, 16 or 20 operand tiles, is full, and the first of the next."""
+    s = synth.ModelShape(f"d{d}", 2, d, 1, 1, 64, 64, 8209, 10000.0, (1,), F32, False)
+    w = synth.make_weights(s, seed=7, norm_jitter=0.2)
+    g, o = ad.Model(s, w, max_pos=8), orc.Oracle(s, w, max_pos=8)
+    for m in (1, 5, 8):
+        print(f"case d {d} rows {m}", flush=True)
+        h = synth.make_hidden(s, m, m)
+        z = g.ad_head_logits(2, torch.from_numpy(h).to("cuda:0")).cpu().numpy()
+        for r in range(m):
+            check_rows(F32, z[r], o.head(-1, h[r], want_logits=True)[3], "logits")
     g.close()
