@@ -241,9 +241,14 @@ int launch_src(const GemmArgs &g, int grid, hipStream_t s) {
     return g.x ? launch_as<NPL, KS, F16, true>(g, grid, s) : launch_as<NPL, KS, F16, false>(g, grid, s);
 }
 
-// the instance whose registers hold the activations of a wavefront: 16-bit models of d_model <= 2048, 4096, 5120, 6144, 8192
+// The instance whose registers hold the activations of a wavefront: 16-bit models of d_model <= 512, 1024, 2048, 4096, 5120, 6144, 8192.  An
+// instance goes through its k-steps whether a wavefront has them or not (loads of its last one again, no products): with 8 as the fewest an
+// exit head of 128256 tokens took 56.9 us at d_model 512 and 55.6 at 1024, 27.6 and 42.4 with 2 and 4 (54.5 and 61.3 with the kernel before
+// this one).
 template <bool F16>
 int launch16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
+    if (nks <= 2) return launch_src<1, 2, F16>(g, grid, s);
+    if (nks <= 4) return launch_src<1, 4, F16>(g, grid, s);
     if (nks <= 8) return launch_src<1, 8, F16>(g, grid, s);
     if (nks <= 16) return launch_src<1, 16, F16>(g, grid, s);
     if (nks <= 20) return launch_src<1, 20, F16>(g, grid, s);
@@ -251,9 +256,8 @@ int launch16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
     return launch_src<1, 32, F16>(g, grid, s);
 }
 
-// the same for fp32 models of d_model <= 512, 1024, 2048, 3072, 4096, 5120.  An instance goes through its k-steps whether a wavefront
-// has them or not (loads of its last one again, no products): with 2 and 20 alone the logits of 32016 tokens took 68.6 us at d_model
-// 1024 and 86.0 at 2048, 31.0 and 61.3 with these (and 35.0 and 66.5 with the kernel before this one).
+// the same for fp32 models of d_model <= 512, 1024, 2048, 3072, 4096, 5120: with 2 and 20 k-steps alone the logits of 32016 tokens took
+// 68.6 us at d_model 1024 and 86.0 at 2048, 31.0 and 61.3 with these (and 35.0 and 66.5 with the kernel before this one)
 int launch32(const GemmArgs &g, int nks, int grid, hipStream_t s) {
     if (nks <= 2) return launch_src<3, 2, false>(g, grid, s);
     if (nks <= 4) return launch_src<3, 4, false>(g, grid, s);

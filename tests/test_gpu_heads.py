@@ -58,16 +58,18 @@ def test_logits_that_are_no_numbers_are_passed_by(ad, V, dtype):
     g.close()
 
 
-@pytest.mark.parametrize("d", [512, 528, 1024, 1040, 2048, 2064, 3072, 3088, 4096, 4112, 5120])
-def test_large_vocabularies_of_fp32_models(ad, d):
-    """The widths where a wavefront's share of the inputs, 2, 4, 8, 12, 16 or 20 operand tiles, is full, and the first of the next."""
-    s = synth.ModelShape(f"d{d}", 2, d, 1, 1, 64, 64, 8209, 10000.0, (1,), F32, False)
+@pytest.mark.parametrize("d,dtype", [(d, F32) for d in (512, 528, 1024, 1040, 2048, 2064, 3072, 3088, 4096, 4112, 5120)] +
+                         [(d, t) for d in (64, 512, 528, 1024, 1040) for t in (BF16, F16)], ids=str)
+def test_large_vocabularies(ad, d, dtype):
+    """The widths where a wavefront's share of the inputs, 2, 4, 8, 12, 16 or 20 operand tiles (16-bit models: 2 or 4), is full, and the
+    first of the next."""
+    s = synth.ModelShape(f"d{d}", 2, d, 1, 1, 64, 64, 8209, 10000.0, (1,), dtype, False)
     w = synth.make_weights(s, seed=7, norm_jitter=0.2)
     g, o = ad.Model(s, w, max_pos=8), orc.Oracle(s, w, max_pos=8)
     for m in (1, 5, 8):
-        print(f"case d {d} rows {m}", flush=True)
+        print(f"case d {d} dtype {dtype} rows {m}", flush=True)
         h = synth.make_hidden(s, m, m)
         z = g.ad_head_logits(2, torch.from_numpy(h).to("cuda:0")).cpu().numpy()
         for r in range(m):
-            check_rows(F32, z[r], o.head(-1, h[r], want_logits=True)[3], "logits")
+            check_rows(dtype, z[r], o.head(-1, h[r], want_logits=True)[3], "logits")
     g.close()
