@@ -330,10 +330,13 @@ int launch_halves(const GemmArgs &g, int halves, hipStream_t s) {
 
 }  // namespace
 
+// what a kernel that starts from fp32 rows has: their norm weights, two batches of k-steps per wavefront at most, no residual
+static bool rows_covered(const GemmArgs &g, int planes) { return g.norm_w && g.epi != EPI_RESID && g.KT <= kProjWaves * 2 * proj_batch(planes); }
+
 bool proj_covers(const GemmArgs &g, int planes, int n_wg) {
     if (g.mode == GEMM_STREAMED) return true;
     if (g.NT > 2 * n_wg) return false;
-    return !g.x || (g.norm_w && g.KT <= kProjWaves * 2 * proj_batch(planes));
+    return !g.x || rows_covered(g, planes);
 }
 
 // halves of a row tile per workgroup: 2, 3 or 4
@@ -348,6 +351,7 @@ int proj_head_parts(int n_tiles, int n_wg) {
 }
 
 int launch_proj(const GemmArgs &g, int planes, const LaunchCtx &c) {
+    if (g.x && !rows_covered(g, planes)) return (int)hipErrorInvalidValue;
     int halves = proj_halves(g.NT, c.n_wg);
     if (halves == 3 && g.epi == EPI_SWIGLU) halves = 4;
     hipStream_t s = (hipStream_t)c.stream;

@@ -273,7 +273,7 @@ int rows_max_k(int planes) { return (planes == 1 ? 32 : 20) * kProjWaves * 32; }
 
 int launch_rows(const GemmArgs &g, int planes, int grid, const LaunchCtx &c) {
     hipStream_t s = (hipStream_t)c.stream;
-    if (g.KT * 32 > rows_max_k(planes) || g.K < 8 || (g.x && !g.norm_w)) return (int)hipErrorInvalidValue;
+    if (g.KT * 32 > rows_max_k(planes) || g.K < 8 || (g.x && !g.norm_w) || g.epi == EPI_RESID) return (int)hipErrorInvalidValue;
     const int nks = (g.KT + kProjWaves - 1) / kProjWaves;       // most k-steps of a wavefront
     if (planes != 1) return launch32(g, nks, grid, s);
     return g.elem == kElemF16 ? launch16<true>(g, nks, grid, s) : launch16<false>(g, nks, grid, s);
