@@ -144,7 +144,9 @@ template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI>
 __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
     constexpr int NW = NWR * NWT, BR = WR * NWR, BT = WT * NWT;
     constexpr int SU = prompt_stage_units(BR, BT), NC = (BR + BT * 2) / NW;     // 16-byte units per stage, copies per wavefront
-    constexpr int FLY = NC * (NST - 2);                         // copies of a wavefront that may be in flight when a step begins
+    // Copies of a wavefront that may be in flight when a step begins.  The step's wait counts them, so that copies have to be issued in the
+    // order of their stages: no copy moves past the scheduling barriers between stages.
+    constexpr int FLY = NC * (NST - 2);
     static_assert((BR + BT * 2) % NW == 0 && FLY < 64 && NST >= 3, "a stage is a whole number of copies per wavefront");
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     bf16x8 *lds = (bf16x8 *)lds_raw;                            // [NST][weight tiles, activation tiles]
@@ -212,7 +214,10 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
         cur = cur == NST - 1 ? 0 : cur + 1;
     };
 #pragma unroll
-    for (int j = 0; j < NST - 1; ++j) copy(j, T.k0 + j);
+    for (int j = 0; j < NST - 1; ++j) {
+        copy(j, T.k0 + j);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     int s = 0;
     for (; s + kFlush <= n_step; s += kFlush) {
 #pragma unroll
