@@ -335,11 +335,17 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
     __shared__ float st[kValuMaxRows][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int G = a.G, R = a.R;
-    const int g = blockIdx.y, s = blockIdx.x;
+    // x / d for any x: the rounded-up reciprocal is never too small and, below 2^32, at most one too large (models of 32767 query heads
+    // per kv head and more have rows past the numbers that it is exact for)
+    auto quotient = [](int x, int d, unsigned mul) {
+        const int q = div_small(x, mul);
+        return q * d > x ? q - 1 : q;
+    };
+    const int item = blockIdx.x, g = quotient(item, a.S, a.mul_S), s = item - g * a.S;
     const int c0 = s * C, c1 = (c0 + C < a.pos0) ? c0 + C : a.pos0;
     const int nc = (c1 > c0) ? c1 - c0 : 0;
     const bool last = (s == a.S - 1);
-    const int r_first = blockIdx.z * a.rows_wg, r_end = r_first + a.rows_wg < R ? r_first + a.rows_wg : R;     // this workgroup's query rows
+    const int r_first = blockIdx.y * a.rows_wg, r_end = r_first + a.rows_wg < R ? r_first + a.rows_wg : R;     // this workgroup's query rows
     float *Kg = (float *)a.Kc + (size_t)g * a.stride * DH, *Vg = (float *)a.Vc + (size_t)g * DH * a.stride;
     const int key = tid / LK, d0 = (tid % LK) * 16;             // products with K: key, first dimension
     const int e = tid / TE, part = tid % TE;                    // products with V: dimension, keys (i * TE + part) * 4 .. + 3
@@ -368,7 +374,7 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
             knew[t][i + half] = k1;
             vnew[t][i] = v0;
             vnew[t][i + half] = v1;
-            if (blockIdx.z == 0) {
+            if (blockIdx.y == 0) {
                 const size_t p = (size_t)(a.pos0 + t);
                 Kg[p * DH + i] = k0;
                 Kg[p * DH + i + half] = k1;
@@ -391,7 +397,7 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
     for (int r0 = r_first; r0 < r_end; r0 += kValuMaxRows) {
         const int nr = (r_end - r0 < kValuMaxRows) ? r_end - r0 : kValuMaxRows;
         for (int idx = tid; idx < nr * half; idx += kValuThreads) {
-            const int rr = idx / half, i = idx % half, r = r0 + rr, t = div_small(r, a.mul_G), hq = g * G + (r - t * G);
+            const int rr = idx / half, i = idx % half, r = r0 + rr, t = quotient(r, G, a.mul_G), hq = g * G + (r - t * G);
             const float *qp = a.qkv + (size_t)t * a.ld + (size_t)hq * DH;
             const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
             const float x = qp[i], y = qp[i + half];
@@ -419,7 +425,7 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
             for (int i = 0; i < 4; ++i) kk[i] = *(const f32x4 *)&knew[key][d0 + i * 4];
             for (int rr = 0; rr < nr; ++rr) {
                 const float x = dot(rr, kk);
-                const int t = div_small(r0 + rr, a.mul_G);      // causal mask among the call's own rows
+                const int t = quotient(r0 + rr, G, a.mul_G);    // causal mask among the call's own rows
                 if (tid % LK == 0) sc[rr][C + key] = key < a.m && key <= t ? x : -INFINITY;
             }
         }
@@ -461,7 +467,7 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
             acc = sum_lanes(acc, TE);
             if (part == 0) {
                 if (a.S == 1) {                                 // nothing to fold: the output itself, packed for the Wo GEMM
-                    const int r = r0 + rr, t = div_small(r, a.mul_G);
+                    const int r = r0 + rr, t = quotient(r, G, a.mul_G);
                     store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + (r - t * G)) * DH + e, t, acc / st[rr][1]);
                 } else {
                     float *pr = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
@@ -557,7 +563,7 @@ static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
     const int spare = c.n_wg / (a.Hkv * a.S), most = (a.R + 1) / 2;
     const int nz = spare < 1 ? 1 : spare < most ? spare : most;
     b.rows_wg = (a.R + nz - 1) / nz;
-    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(a.S, a.Hkv, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
+    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(a.Hkv * a.S, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
     return (int)hipGetLastError();
 }
 

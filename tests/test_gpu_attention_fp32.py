@@ -63,6 +63,32 @@ def test_layer_step_attention(ad, s, ctxs, rows):
     g.close()
 
 
+def test_more_query_rows_than_reciprocals_are_exact_for(ad):
+    """40001 query heads on one kv head, 8 rows: three of the 320008 query rows (the last heads of tokens 5, 6 and 7) lie where the rounded-up
+    reciprocal of 40001 is one too large.  The output projection sees those heads and the first ones alone."""
+    import torch
+    G, m, ctx = 40001, 8, 3
+    mul = ((1 << 32) + G - 1) // G
+    assert [r for r in range(G - 1, m * G, G) if r * mul >> 32 != r // G] == [240005, 280006, 320007]
+    s = synth.ModelShape(f"h{G}-1x64-f32", 1, 16, G, 1, 64, 8, 16, 10000.0, (), synth.F32, False)
+    w = synth.make_weights(s, seed=8)
+    wo = np.zeros_like(w["layers.0.wo"])
+    for h in (0, 1, G - 2, G - 1):
+        wo[:, h * 64:(h + 1) * 64] = w["layers.0.wo"][:, h * 64:(h + 1) * 64] * 20
+    w["layers.0.wo"] = wo
+    g, o = ad.Model(s, w, max_pos=ctx + m), orc.Oracle(s, w, max_pos=ctx + m)
+    k, v = synth.make_kv_prefill(s, 3, 0, ctx)
+    g.kv_fill(1, k, v)
+    o.kv_write(1, 0, k, v)
+    g.kv_set_len(1, ctx)
+    o.kv_set_len(1, ctx)
+    h = synth.make_hidden(s, 9, m)
+    hg = torch.from_numpy(h).to("cuda:0")
+    g.ad_layer_step(1, hg, np.arange(ctx, ctx + m))
+    check_rows(s.dtype, hg.cpu().numpy() - h, o.layer_step(1, h, np.arange(ctx, ctx + m)) - h, "what the layer adds")
+    g.close()
+
+
 def test_partials_beyond_32_bit_offsets(ad):
     """8192 query rows on one kv head of 128 dimensions at 262400 positions leave 4100 splits' partials, 17 GB: more floats than 32 bits
     count.  All cached keys are zeros, so every position has the same weight; the values of those in a late split are all there is."""
