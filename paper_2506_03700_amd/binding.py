@@ -134,14 +134,19 @@ def make_config(shape, m_max: int = AD_M_MAX) -> Config:
     return cfg
 
 
-def _stream_handle(torch) -> int:
-    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it, without the Stream object
-    that takes 2.7 us to make (a draw from 128256 logits keeps the GPU busy for 6.4 us)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _current_stream(torch):
+    """(device, handle) of the current stream, as torch.cuda.current_stream() gives them, without the Stream object that takes
+    2.7 us to make (a draw from 128256 logits keeps the GPU busy for 6.4 us) where torch's own module has the two short ways."""
+    try:
+        dev = torch._C._cuda_getDevice()
+        return dev, torch._C._cuda_getCurrentRawStream(dev)
+    except AttributeError:
+        s = torch.cuda.current_stream()
+        return s.device_index, s.cuda_stream
 
 
 def _stream_ptr(torch):
-    return C.c_void_p(_stream_handle(torch))
+    return C.c_void_p(_current_stream(torch)[1])
 
 
 class Model:
@@ -203,7 +208,7 @@ class Model:
     def _synchronize(self) -> None:
         """Waits for the current stream."""
         torch = self.torch
-        dev, handle = torch._C._cuda_getDevice(), _stream_handle(torch)
+        dev, handle = _current_stream(torch)
         w = self._waited
         if w[0] != dev or w[1] != handle:
             w = self._waited = (dev, handle, torch.cuda.current_stream())
