@@ -20,7 +20,6 @@
 
 #include <type_traits>
 
-#include "ad_attention_device.h"
 #include "ad_device.h"
 #include "ad_internal.h"
 
@@ -468,7 +467,7 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
             if (part == 0) {
                 if (a.S == 1) {                                 // nothing to fold: the output itself, packed for the Wo GEMM
                     const int r = r0 + rr, t = quotient(r, G, a.mul_G);
-                    store_act_io<IoPlain, false>((uint16_t *)a.Bo, a.Bo_KT, (g * G + (r - t * G)) * DH + e, t, acc / st[rr][1]);
+                    store_act<false>(a.Bo, a.Bo_KT, (g * G + (r - t * G)) * DH + e, t, acc / st[rr][1]);
                 } else {
                     float *pr = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
                     pr[e] = acc;

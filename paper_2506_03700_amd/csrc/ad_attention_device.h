@@ -1,7 +1,7 @@
-// Device side of the attention phase: work items of the split-context MFMA attention over a bf16 KV cache as the fused
-// layer-step kernel (ad_layer_fused.hip) runs them, and the fold of the splits, which the stand-alone kernels
-// (ad_attention.hip, with work items of their own) use too; the `Io` policy (ad_gemm_device.h) says how data exchanged between
-// workgroups -- q/k/v rows in, partials out and in, packed output -- is accessed.
+// Device side of the attention phase of the fused layer-step kernel (ad_layer_fused.hip): work items of the split-context MFMA
+// attention over a bf16 KV cache, and the fold of the splits (stand-alone launches have kernels of their own, ad_attention.hip).
+// Data exchanged between workgroups -- q/k/v rows in, partials out and in, packed output -- is read and written with agent-scope
+// atomics (IoAgent, ad_gemm_device.h).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -74,7 +74,7 @@ __device__ __forceinline__ void attn_load_kv(const AttnArgs &a, int item, AttnKv
 
 // `kv`: register block for the cached K/V; if `preloaded`, it already holds (or has in flight) the block of the
 // first item, wg.
-template <int DH, class Io>
+template <int DH>
 __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<DH> &L, int wg, int nwg, AttnKv<DH> &kv, bool preloaded,
                                                 long long kv_off = 0) {
     constexpr int KS = DH / 32, DT = DH / 16, half = DH / 2, PR = DH + 2, PL = DH + 4, RP = kAttnRowsPerPass;
@@ -101,9 +101,9 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                 const float *kp = a.qkv + (size_t)t * a.ld + (size_t)a.Hq * DH + (size_t)g * DH;
                 const float *vp = kp + (size_t)a.Hkv * DH;
                 const float c = a.rope[(t * half + i) * 2], sn = a.rope[(t * half + i) * 2 + 1];
-                const float x = Io::ld(kp + i), y = Io::ld(kp + i + half);
+                const float x = IoAgent::ld(kp + i), y = IoAgent::ld(kp + i + half);
                 const uint16_t k0 = f32_to_bf16_bits(x * c - y * sn), k1 = f32_to_bf16_bits(x * sn + y * c);
-                const uint16_t v0 = f32_to_bf16_bits(Io::ld(vp + i)), v1 = f32_to_bf16_bits(Io::ld(vp + i + half));
+                const uint16_t v0 = f32_to_bf16_bits(IoAgent::ld(vp + i)), v1 = f32_to_bf16_bits(IoAgent::ld(vp + i + half));
                 L.knew[t * DH + i] = k0;
                 L.knew[t * DH + i + half] = k1;
                 L.vnewT[i * 8 + t] = v0;
@@ -135,8 +135,8 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                 if (idx < nblk * 8 * half && rr < nr) {
                     const int t = div_small(r, a.mul_G), hq = g * G + (r - t * G);
                     const float *qp = a.qkv + (size_t)t * a.ld + (size_t)hq * DH;
-                    qx[it] = Io::ld(qp + i);
-                    qy[it] = Io::ld(qp + i + half);
+                    qx[it] = IoAgent::ld(qp + i);
+                    qy[it] = IoAgent::ld(qp + i + half);
                     qc[it] = a.rope[(t * half + i) * 2];
                     qs_[it] = a.rope[(t * half + i) * 2 + 1];
                 }
@@ -150,11 +150,11 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                     const int b = rr >> 3, col = rr & 7;
                     uint16_t hi, lo;
                     int d = i;
-                    split_hi_lo<false>(q0, hi, lo);
+                    split_hi_lo(q0, hi, lo);
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col) * 8 + (d & 7)] = hi;
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col + 8) * 8 + (d & 7)] = lo;
                     d = i + half;
-                    split_hi_lo<false>(q1, hi, lo);
+                    split_hi_lo(q1, hi, lo);
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col) * 8 + (d & 7)] = hi;
                     qb16[(((b * KS + (d >> 5)) * 64) + ((d & 31) >> 3) * 16 + col + 8) * 8 + (d & 7)] = lo;
                 }
@@ -235,7 +235,7 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                         const float p = (sc[c] == -INFINITY) ? 0.f : __expf(sc[c] - mx);
                         sum += p;
                         uint16_t hi, lo;
-                        split_hi_lo<false>(p, hi, lo);
+                        split_hi_lo(p, hi, lo);
                         pb.u[c] = (n < 8) ? hi : lo;
                     }
                     sum += __shfl_xor(sum, 16);
@@ -292,8 +292,8 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
                     num[1] += on ? w * v[p][1] : 0.f;
                 }
                 float *out = a.part + (((size_t)g * a.S + s) * R + (r0 + rr)) * PR;
-                Io::st2(out + e, num);
-                if (e == 0) Io::st2(out + DH, (f32x2){M, den});
+                IoAgent::st2(out + e, num);
+                if (e == 0) IoAgent::st2(out + DH, (f32x2){M, den});
             }
             __syncthreads();
         }
@@ -306,7 +306,6 @@ __device__ __forceinline__ void attn_mfma_items(const AttnArgs &a, AttnMfmaLds<D
 // One wavefront per query row: the splits' (max, sum) pairs give the weights exp(max_s - M), then the lanes
 // accumulate the weighted partial outputs in split order, two dimensions per lane, 32 splits' rows in flight at a
 // time (at most 64 splits, i.e. one round trip to memory, for contexts up to 8192).
-template <class Io, bool F16>
 __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int row /* 0 .. Hkv * R */) {
     constexpr int NB = 32;                             // splits whose rows are in flight together
     const int DH = a.dh, PR = DH + 2, S = a.S;
@@ -323,20 +322,20 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int row /* 0
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             const int ss = (first + k < end) ? first + k : end - 1;
-            v[k] = e_on ? Io::ld2(base + (size_t)ss * sstride + e) : (f32x2){0.f, 0.f};
+            v[k] = e_on ? IoAgent::ld2(base + (size_t)ss * sstride + e) : (f32x2){0.f, 0.f};
         }
     };
     // the maxima of the groups of 64 splits after the first (contexts beyond 64 splits only)
     float M = -INFINITY;
-    for (int s = 64 + lane; s < S; s += 64) M = fmaxf(M, Io::ld(base + s * sstride + DH));
+    for (int s = 64 + lane; s < S; s += 64) M = fmaxf(M, IoAgent::ld(base + s * sstride + DH));
     float den = 0.f, o0 = 0.f, o1 = 0.f;
     for (int s0 = 0; s0 < S; s0 += 64) {
         const int ns = (S - s0 < 64) ? S - s0 : 64, sl = s0 + lane;
         // (max, sum) of split s0 + lane, and the first batch of rows: all loads are issued before any is used
         float pm = -INFINITY, ps = 0.f;
         if (sl < S) {
-            pm = Io::ld(base + sl * sstride + DH);
-            ps = Io::ld(base + sl * sstride + DH + 1);
+            pm = IoAgent::ld(base + sl * sstride + DH);
+            ps = IoAgent::ld(base + sl * sstride + DH + 1);
         }
         f32x2 v[NB];
         load_batch(v, s0, s0 + ns);
@@ -359,8 +358,8 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int row /* 0
         }
     }
     if (e_on) {
-        store_act_io<Io, F16>((uint16_t *)a.Bo, a.Bo_KT, hq * DH + e, t, o0 / den);
-        store_act_io<Io, F16>((uint16_t *)a.Bo, a.Bo_KT, hq * DH + e + 1, t, o1 / den);
+        store_act_agent((uint16_t *)a.Bo, a.Bo_KT, hq * DH + e, t, o0 / den);
+        store_act_agent((uint16_t *)a.Bo, a.Bo_KT, hq * DH + e + 1, t, o1 / den);
     }
 }
 

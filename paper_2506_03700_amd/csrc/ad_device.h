@@ -90,17 +90,12 @@ __device__ __forceinline__ void split16(float v, uint16_t &hi, uint16_t &lo) {
     lo = to16<F16>(v - from16<F16>(hi));
 }
 
-// The same for the layer step's projections and the fused layer step, with the bf16 rounding in integer arithmetic (same bits for
+// The same for bf16 in the fused layer step, with the rounding in integer arithmetic (same bits for
 // finite values): with the conversion instruction the fused step is 1 % slower at one row (8B shape, context 4096: 98.7 -> 99.7 us
 // a layer; 8 rows 117.1 -> 116.6).
-template <bool F16>
 __device__ __forceinline__ void split_hi_lo(float x, uint16_t &hi, uint16_t &lo) {
-    if constexpr (F16) {
-        split16<true>(x, hi, lo);
-    } else {
-        hi = f32_to_bf16_bits(x);
-        lo = f32_to_bf16_bits(x - bf16_bits_to_f32(hi));
-    }
+    hi = f32_to_bf16_bits(x);
+    lo = f32_to_bf16_bits(x - bf16_bits_to_f32(hi));
 }
 
 // The value that scores are taken relative to in a softmax: their maximum m, or 0 where every score so far is minus
@@ -243,6 +238,15 @@ __device__ __forceinline__ int div_small(int x, unsigned mul) { return mul ? (in
 // block of KT k-steps (see ad_internal.h)
 __device__ __forceinline__ size_t act_index(int k, int col, int KT) {
     return ((((size_t)(col & 7) * KT + (k >> 5)) * 2 + (col >> 3)) * 4 + ((k & 31) >> 3)) * 8 + (k & 7);
+}
+
+// v as input k of token t in a packed activation block of KT k-steps
+template <bool F16>
+__device__ __forceinline__ void store_act(void *B, int KT, int k, int t, float v) {
+    uint16_t hi, lo;
+    split16<F16>(v, hi, lo);
+    ((uint16_t *)B)[act_index(k, t, KT)] = hi;
+    ((uint16_t *)B)[act_index(k, 8 + t, KT)] = lo;
 }
 
 // index (in 16-byte units) of the MFMA B operand register of lane `lane` for k-step ks of such a block

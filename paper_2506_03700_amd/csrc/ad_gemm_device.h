@@ -22,9 +22,7 @@
 //
 // Each mode is split into a *stream* object, which can put the first weight batches in flight before anything
 // that depends on the activations exists (before a grid barrier), and the function
-// that consumes it.  The `Io` policy says how data exchanged between workgroups is read and written: plain
-// loads and stores when a kernel boundary orders producer and consumer, agent-scope atomics when both run
-// inside one kernel.
+// that consumes it.  Data exchanged between workgroups goes through IoAgent and IoAcquired below.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -41,22 +39,14 @@ constexpr int kKsMax = 20;              // stationary mode: most k-steps per wav
 
 struct GemmLds {
     // stationary: [tile 0..8)[wave][token 0..8)[row 0..16)      streamed: [slot][col 0..16)[row 0..16)
-    float slots[kTilesPerRound * kWaves * 8 * 16];
+    // and, before any of these, the stationary mode's strips of operands: [wave][k-step 0..8)[lane] of 16 bytes
+    float slots[kStatWaves * 8 * 64 * 4];
     float red[kTilesPerRound * 128];    // [tile][token][row]
-    float ssq_part[kWaves * 8];
+    float ssq_part[kStatWaves * 8];
     float scale[8];
 };
 
 // ---- how data shared between workgroups is accessed ------------------------------------------------------
-struct IoPlain {
-    static __device__ __forceinline__ float ld(const float *p) { return *p; }
-    static __device__ __forceinline__ f32x2 ld2(const float *p) { return *(const f32x2 *)p; }
-    static __device__ __forceinline__ f32x4 ld4(const float *p) { return *(const f32x4 *)p; }
-    static __device__ __forceinline__ bf16x8 ldb(const bf16x8 *p) { return *p; }
-    static __device__ __forceinline__ void st(float *p, float v) { *p = v; }
-    static __device__ __forceinline__ void st2(float *p, f32x2 v) { *(f32x2 *)p = v; }
-    static __device__ __forceinline__ void st16(uint16_t *p, uint16_t v) { *p = v; }
-};
 // Relaxed agent-scope atomics: stores go through to memory and loads do not use a stale copy in another
 // XCD's L2, so a grid barrier built from the same kind of atomics is enough to order them (the storing
 // wavefront waits for its stores to complete before it arrives at the barrier).
@@ -65,18 +55,6 @@ struct IoAgent {
     static __device__ __forceinline__ f32x2 ld2(const float *p) {
         union { uint64_t u; f32x2 v; } c;
         c.u = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return c.v;
-    }
-    static __device__ __forceinline__ f32x4 ld4(const float *p) {
-        union { uint64_t u[2]; f32x4 v; } c;
-        c.u[0] = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        c.u[1] = __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return c.v;
-    }
-    static __device__ __forceinline__ bf16x8 ldb(const bf16x8 *p) {
-        union { uint64_t u[2]; bf16x8 v; } c;
-        c.u[0] = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        c.u[1] = __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return c.v;
     }
     static __device__ __forceinline__ void st(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -93,45 +71,34 @@ struct IoAgent {
 // grid barrier that follows the producer's stores.
 struct IoAcquired : IoAgent {
     static __device__ __forceinline__ float ld(const float *p) { return *p; }
-    static __device__ __forceinline__ f32x2 ld2(const float *p) { return *(const f32x2 *)p; }
     static __device__ __forceinline__ f32x4 ld4(const float *p) { return *(const f32x4 *)p; }
     static __device__ __forceinline__ bf16x8 ldb(const bf16x8 *p) { return *p; }
 };
 
-template <class Io, bool F16>
-__device__ __forceinline__ void store_act_io(uint16_t *B, int KT, int k, int t, float v) {
+__device__ __forceinline__ void store_act_agent(uint16_t *B, int KT, int k, int t, float v) {
     uint16_t hi, lo;
-    split_hi_lo<F16>(v, hi, lo);
-    Io::st16(B + act_index(k, t, KT), hi);
-    Io::st16(B + act_index(k, 8 + t, KT), lo);
+    split_hi_lo(v, hi, lo);
+    IoAgent::st16(B + act_index(k, t, KT), hi);
+    IoAgent::st16(B + act_index(k, 8 + t, KT), lo);
 }
-
-struct NoTail {
-    __device__ __forceinline__ void operator()() const {}
-};
 
 __device__ __forceinline__ int part_start(int tot, int w, int nw) { return (int)(((long)tot * w) / nw); }
 
 // ---- epilogue on a reduced round: L.red[T*128 + t*16 + i] holds row (ta+T)*16+i of token t -------------
-// EPI: the epilogue's kind.
-template <class Io, int EPI, bool F16>
+// EPI: the epilogue's kind, EPI_STORE or EPI_SWIGLU (the streamed mode finishes its rows itself).
+template <int EPI>
 __device__ __forceinline__ void epilogue(const GemmArgs &g, GemmLds &L, int ta, int nt, int tid, int nthreads) {
     if (EPI == EPI_STORE) {
         for (int idx = tid; idx < nt * 128; idx += nthreads) {
             const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-            if (t < g.m && n < g.N) Io::st(g.out + (size_t)t * g.ld + n, L.scale[t] * L.red[idx]);
-        }
-    } else if (EPI == EPI_RESID) {
-        for (int idx = tid; idx < nt * 128; idx += nthreads) {
-            const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-            if (t < g.m && n < g.N) Io::st(g.out + (size_t)t * g.ld + n, Io::ld(g.resid + (size_t)t * g.ld + n) + L.scale[t] * L.red[idx]);
+            if (t < g.m && n < g.N) IoAgent::st(g.out + (size_t)t * g.ld + n, L.scale[t] * L.red[idx]);
         }
     } else {  // EPI_SWIGLU
         for (int idx = tid; idx < nt * 128; idx += nthreads) {
             const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, f = (ta + T) * 8 + i;
             if (t < g.m && i < 8 && f * 2 < g.N) {
                 const float gate = L.scale[t] * L.red[idx], up = L.scale[t] * L.red[idx + 8];
-                store_act_io<Io, F16>((uint16_t *)g.Bnext, g.Bnext_KT, f, t, gate / (1.0f + __expf(-gate)) * up);
+                store_act_agent((uint16_t *)g.Bnext, g.Bnext_KT, f, t, gate / (1.0f + __expf(-gate)) * up);
             }
         }
     }
@@ -147,30 +114,27 @@ __device__ __forceinline__ bf16x8 load_tile(const bf16x8 *W, unsigned unit) {
     return __builtin_nontemporal_load((const bf16x8 *)((const char *)W + (unit << 4)));
 }
 
-template <int NPL, int CH>
-__device__ __forceinline__ void load_chunk(bf16x8 (&a)[CH][NPL], const bf16x8 *W, unsigned p, int n) {
+template <int CH>
+__device__ __forceinline__ void load_chunk(bf16x8 (&a)[CH], const bf16x8 *W, unsigned p, int n) {
     if (n == CH) {   // the common case: straight-line loads
 #pragma unroll
-        for (int j = 0; j < CH; ++j)
-#pragma unroll
-            for (int q = 0; q < NPL; ++q) a[j][q] = load_tile(W, p + (unsigned)(j * NPL + q) * 64u);
+        for (int j = 0; j < CH; ++j) a[j] = load_tile(W, p + (unsigned)j * 64u);
     } else {
         // a short chunk: entries past the end repeat its last k-step (same cache lines; their products are skipped),
         // so that the buffer is still filled by straight-line loads into fixed registers
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
             const int jj = j < n ? j : n - 1;
-#pragma unroll
-            for (int q = 0; q < NPL; ++q) a[j][q] = load_tile(W, p + (unsigned)(jj * NPL + q) * 64u);
+            a[j] = load_tile(W, p + (unsigned)jj * 64u);
         }
     }
 }
 
 // This wavefront's share of workgroup wg's weights (row tiles [t0, t1), k-steps [ks0, ks0 + nks)) and its two
 // chunk buffers.
-template <int NPL, int CH>
+template <int CH>
 struct StatStream {
-    bf16x8 a0[CH][NPL], a1[CH][NPL];
+    bf16x8 a0[CH], a1[CH];
     const bf16x8 *W;
     unsigned wbase, tstride;       // 16-byte units
     int t0, t1, ks0, nks, nch, total;
@@ -185,10 +149,10 @@ struct StatStream {
         nch = (nks + CH - 1) / CH;                 // chunks per tile (0 if this wavefront has no K slice)
         total = (t1 - t0) * nch;                   // chunks in this wavefront's stream
         W = (const bf16x8 *)((const char *)g.W + w_off);
-        wbase = (unsigned)(((size_t)t0 * g.KT + ks0) * NPL * 64 + lane);
-        tstride = (unsigned)g.KT * NPL * 64u;
+        wbase = (unsigned)(((size_t)t0 * g.KT + ks0) * 64 + lane);
+        tstride = (unsigned)g.KT * 64u;
     }
-    __device__ __forceinline__ unsigned chunk_ptr(int c) const { return wbase + (unsigned)(c / nch) * tstride + (unsigned)(c % nch) * (CH * NPL * 64u); }
+    __device__ __forceinline__ unsigned chunk_ptr(int c) const { return wbase + (unsigned)(c / nch) * tstride + (unsigned)(c % nch) * (CH * 64u); }
     __device__ __forceinline__ int chunk_len(int c) const { const int r = nks - (c % nch) * CH; return r < CH ? r : CH; }
     // The first two weight chunks go in flight.  The loads are unconditional (a wavefront with fewer chunks reads
     // the start of the matrix instead, and nothing is done with it): code after this call then knows how many loads
@@ -203,17 +167,15 @@ struct StatStream {
         load_chunk_clamped(a0, p0, n0);
         load_chunk_clamped(a1, p1, n1);
     }
-    __device__ __forceinline__ void load_chunk_clamped(bf16x8 (&a)[CH][NPL], unsigned p, int n) {
+    __device__ __forceinline__ void load_chunk_clamped(bf16x8 (&a)[CH], unsigned p, int n) {
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
             const int jj = j < n ? j : n - 1;
-#pragma unroll
-            for (int q = 0; q < NPL; ++q) a[j][q] = load_tile(W, p + (unsigned)(jj * NPL + q) * 64u);
+            a[j] = load_tile(W, p + (unsigned)jj * 64u);
         }
     }
 };
 
-// `tail` runs once, after the workgroup's last MFMA and before its last reduction and epilogue.
 // PREFETCHED: S.prefetch() has been called already (a phase whose weights went in flight while the workgroup
 // waited for its inputs).  Otherwise the function calls it itself, right after it has issued the loads of its
 // activations: a wavefront's loads return in order, so activations requested behind 16 KiB of weights would arrive
@@ -222,11 +184,10 @@ struct StatStream {
 // one, which costs no extra cache lines, and masked afterwards), so that their number is known at compile time and
 // the waits for the activations do not also wait for the weights behind them.
 // NCHMAX: most chunks per tile and wavefront this instance covers (the B slice takes NCHMAX * CH registers x 4).
-// F16: the weights and the 16-bit halves of the activations are fp16 (else bf16).
-template <int NPL, int CH, int NCHMAX, class Io, int EPI, bool F16, bool PREFETCHED, class Tail>
-__device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NPL, CH> &S, GemmLds &L, Tail tail, long long w_off = 0) {
+template <int CH, int NCHMAX, int EPI, bool PREFETCHED>
+__device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<CH> &S, GemmLds &L, long long w_off = 0) {
     constexpr int KSB = NCHMAX * CH;   // B registers cover whole chunks
-    constexpr int kWaves = kStatWaves, kThreads = kStatThreads;         // this mode's workgroup shape
+    constexpr int kWaves = kStatWaves, kThreads = kStatThreads;
     const int tid = thread_index(), lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, gq = lane >> 4, t_lane = n & 7;
     const int t0 = S.t0, t1 = S.t1, ks0 = S.ks0, nks = S.nks, nch = S.nch, total = S.total;
@@ -249,26 +210,19 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
         // two passes' worth of loads are in flight: those of pass p + 1 are issued before pass p is converted
         f32x4 xr[2][8];
         u32x4 wraw[2];
-        const bool w16 = g.norm_elem != ELEM_F32;
-        const char *wsrc = g.norm_w ? (const char *)g.norm_w + w_off : (const char *)g.x;     // without a norm vector: any valid address
+        const char *wsrc = (const char *)g.norm_w + w_off;
         auto load_pass = [&](f32x4 (&xp)[8], u32x4 &wp, int p) {
             const int k = (ks0 + p * 8) * 32 + lane * 4;
             const int kc = (k > g.K - 4) ? g.K - 4 : k;              // clamped address, masked result
-            // the lane's four norm weights: 16-bit kinds load the aligned group of eight that holds them
-            wp = *(const u32x4 *)(wsrc + (w16 ? (size_t)(kc & ~7) * 2 : (size_t)kc * 4));
+            wp = *(const u32x4 *)(wsrc + (size_t)(kc & ~7) * 2);     // the aligned group of eight that holds the lane's four norm weights
 #pragma unroll
-            for (int t = 0; t < 8; ++t) xp[t] = Io::ld4(g.x + (size_t)(t < g.m ? t : g.m - 1) * g.ldx + kc);
+            for (int t = 0; t < 8; ++t) xp[t] = IoAcquired::ld4(g.x + (size_t)(t < g.m ? t : g.m - 1) * g.ldx + kc);
         };
         auto norm4 = [&](const u32x4 &raw, int p) -> f32x4 {
-            if (!g.norm_w) return (f32x4){1.f, 1.f, 1.f, 1.f};
-            if (g.norm_elem == ELEM_F32) return (f32x4){__uint_as_float(raw[0]), __uint_as_float(raw[1]), __uint_as_float(raw[2]), __uint_as_float(raw[3])};
             const int k = (ks0 + p * 8) * 32 + lane * 4;
             const int kc = (k > g.K - 4) ? g.K - 4 : k;
             const unsigned lo = (kc & 4) ? raw[2] : raw[0], hi = (kc & 4) ? raw[3] : raw[1];
-            if (g.norm_elem == ELEM_BF16)
-                return (f32x4){__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
-            return (f32x4){f16_bits_to_f32((uint16_t)(lo & 0xffffu)), f16_bits_to_f32((uint16_t)(lo >> 16)),
-                           f16_bits_to_f32((uint16_t)(hi & 0xffffu)), f16_bits_to_f32((uint16_t)(hi >> 16))};
+            return (f32x4){__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
         };
         load_pass(xr[0], wraw[0], 0);
         if (NPASS > 1) load_pass(xr[1], wraw[1], 1);
@@ -293,7 +247,7 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
                         for (int e = 0; e < 4; ++e) {
                             const float xv = k_on ? xp[t][e] : 0.f;
                             ssq[t] += xv * xv;
-                            split_hi_lo<F16>(xv * wp[e], hi.u[e], lo.u[e]);
+                            split_hi_lo(xv * wp[e], hi.u[e], lo.u[e]);
                         }
                         *(uint64_t *)(strip16 + sw(u0 + t) * 8 + (lane & 1) * 4) = hi.v;
                         *(uint64_t *)(strip16 + sw(u0 + 8 + t) * 8 + (lane & 1) * 4) = lo.v;
@@ -326,7 +280,7 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
         const int src_lane = lane_on ? lane : (lane & ~7);
         const int ks_last = nks > 0 ? ks0 + nks - 1 : (ks0 < g.KT ? ks0 : g.KT - 1);
 #pragma unroll
-        for (int j = 0; j < KSB; ++j) b[j] = Io::ldb((const bf16x8 *)g.B + act_operand_index(j < nks ? ks0 + j : ks_last, src_lane, g.KT));
+        for (int j = 0; j < KSB; ++j) b[j] = IoAcquired::ldb((const bf16x8 *)g.B + act_operand_index(j < nks ? ks0 + j : ks_last, src_lane, g.KT));
         // the producer left per-tile sums of squares: wavefront t adds up token t's, in tile order per lane and
         // then across the lanes (fixed order).  The first 512 tiles' loads are issued before the weights'.
         const int t = wave;
@@ -336,7 +290,7 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int tile = lane + 64 * i;
-            sq[i] = Io::ld(sq_src + (size_t)(tile < sq_last ? tile : sq_last) * 8 + t);
+            sq[i] = IoAcquired::ld(sq_src + (size_t)(tile < sq_last ? tile : sq_last) * 8 + t);
         }
         if (!PREFETCHED) S.prefetch();
 #pragma unroll
@@ -348,7 +302,7 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
             for (int i = 0; i < 8; ++i)
                 if (t < g.m && lane + 64 * i < g.ssq_tiles) v += sq[i];
             if (t < g.m)
-                for (int i = lane + 512; i < g.ssq_tiles; i += 64) v += Io::ld(g.ssq_in + (size_t)i * 8 + t);
+                for (int i = lane + 512; i < g.ssq_tiles; i += 64) v += IoAcquired::ld(g.ssq_in + (size_t)i * 8 + t);
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
             if (lane == 0) L.ssq_part[t] = v;
         }
@@ -367,11 +321,11 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
             scale_set = true;
             if (tid < 8) {
                 float s = 1.0f;
-                if (g.x && g.norm_w) {
+                if (g.x) {
                     s = 0.f;
                     for (int w = 0; w < kWaves; ++w) s += L.ssq_part[w * 8 + tid];
                     s = 1.0f / sqrtf(s * g.inv_dim + g.eps);
-                } else if (!g.x && g.ssq_in) {
+                } else if (g.ssq_in) {
                     s = 1.0f / sqrtf(L.ssq_part[tid] * g.inv_dim + g.eps);
                 }
                 L.scale[tid] = s;
@@ -388,23 +342,20 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
             L.red[idx] = v;
         }
         __syncthreads();
-        epilogue<Io, EPI, F16>(g, L, ta, nt, tid, kThreads);
+        epilogue<EPI>(g, L, ta, nt, tid, kThreads);
         __syncthreads();
     };
 
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // multiply chunk c (held in `a`) into the tile accumulator; at the end of a tile publish it to the slots
-    auto mma_chunk = [&](const bf16x8 (&a)[CH][NPL], int c) {
+    auto mma_chunk = [&](const bf16x8 (&a)[CH], int c) {
         const int cc = c % nch, len = S.chunk_len(c);
 #pragma unroll
         for (int q = 0; q < NCHMAX; ++q) {      // q == cc selects the B registers of this chunk statically
             if (q == cc) {
 #pragma unroll
                 for (int j = 0; j < CH; ++j)
-                    if (j < len) {
-#pragma unroll
-                        for (int pl = 0; pl < NPL; ++pl) acc = mma16<F16>(a[j][pl], b[q * CH + j], acc);
-                    }
+                    if (j < len) acc = mma16<false>(a[j], b[q * CH + j], acc);
             }
         }
         if (cc == nch - 1) {
@@ -440,98 +391,88 @@ __device__ __forceinline__ void gemm_stationary(const GemmArgs &g, StatStream<NP
 #pragma nounroll
         for (; c + 4 <= total; c += 2) {
             mma_chunk(S.a0, c);
-            load_chunk<NPL, CH>(S.a0, S.W, S.chunk_ptr(c + 2), S.chunk_len(c + 2));
+            load_chunk<CH>(S.a0, S.W, S.chunk_ptr(c + 2), S.chunk_len(c + 2));
             tile_done(c);
             mma_chunk(S.a1, c + 1);
-            load_chunk<NPL, CH>(S.a1, S.W, S.chunk_ptr(c + 3), S.chunk_len(c + 3));
+            load_chunk<CH>(S.a1, S.W, S.chunk_ptr(c + 3), S.chunk_len(c + 3));
             tile_done(c + 1);
         }
 #pragma nounroll
         for (; c < total; c += 2) {
             mma_chunk(S.a0, c);
-            if (c + 2 < total) load_chunk<NPL, CH>(S.a0, S.W, S.chunk_ptr(c + 2), S.chunk_len(c + 2));
+            if (c + 2 < total) load_chunk<CH>(S.a0, S.W, S.chunk_ptr(c + 2), S.chunk_len(c + 2));
             tile_done(c);
             if (c + 1 < total) {
                 mma_chunk(S.a1, c + 1);
-                if (c + 3 < total) load_chunk<NPL, CH>(S.a1, S.W, S.chunk_ptr(c + 3), S.chunk_len(c + 3));
+                if (c + 3 < total) load_chunk<CH>(S.a1, S.W, S.chunk_ptr(c + 3), S.chunk_len(c + 3));
                 tile_done(c + 1);
             }
         }
     }
-    // the weight stream has ended: the tail runs here, with the chunk buffers and the B slice dead
-    __builtin_amdgcn_sched_barrier(0);      // keep the tail's loads out of the stream's register live ranges
-    tail();
-    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);      // the weight stream has ended
     if (t1 > t0) finish_round(t1);
 }
 
 // ---- streamed mode -----------------------------------------------------------------------------------------
-// NW wavefronts; the workgroup's tiles are taken in rounds of up to 8, and inside a round wavefront w streams
-// the contiguous range [xa, xb) of the round's (tile, k-step) pairs, U pairs per batch, two batches in flight.
-template <int NPL, int U, int NW>
+// NW wavefronts; a workgroup has at most 8 tiles, and wavefront w streams the contiguous range [xa, xb) of their (tile, k-step)
+// pairs, U pairs per batch, two batches in flight.
+template <int U, int NW>
 struct StreamStream {
-    bf16x8 a0[U][NPL], a1[U][NPL];
+    bf16x8 a0[U], a1[U];
     int t0, t1;
-    bool primed;
 
     __device__ __forceinline__ void init(const GemmArgs &g, int wg, int nwg) {
         t0 = wg * g.tq + (wg < g.tr ? wg : g.tr);
         t1 = t0 + g.tq + (wg < g.tr ? 1 : 0);
         if (wg >= nwg) t0 = t1 = 0;                // not one of this GEMM's workgroups
-        primed = false;
     }
-    // Batch [x, x + U) of (tile, k-step) pairs of a round whose first pair sits at unit offset `base`: entries past
-    // `x_ok` (the wavefront's last pair, or any valid pair of the round if it has none) repeat that pair -- the same
-    // cache lines, products skipped -- so that every call issues exactly U * NPL loads into fixed registers and the
+    // Batch [x, x + U) of (tile, k-step) pairs of which the first sits at unit offset `base`: entries past
+    // `x_ok` (the wavefront's last pair, or any valid pair if it has none) repeat that pair -- the same
+    // cache lines, products skipped -- so that every call issues exactly U loads into fixed registers and the
     // code around it can wait for an earlier batch without waiting for this one.
-    static __device__ __forceinline__ void load_a(bf16x8 (&a)[U][NPL], const bf16x8 *W, unsigned base, int x, int x_ok) {
+    static __device__ __forceinline__ void load_a(bf16x8 (&a)[U], const bf16x8 *W, unsigned base, int x, int x_ok) {
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const int xx = x + j < x_ok ? x + j : x_ok;
-#pragma unroll
-            for (int q = 0; q < NPL; ++q) a[j][q] = load_tile(W, base + (unsigned)(xx * NPL + q) * 64u);
+            a[j] = load_tile(W, base + (unsigned)xx * 64u);
         }
     }
     static __device__ __forceinline__ int valid_pair(int xa, int xb, int tot) { return xb > xa ? xb - 1 : (xa < tot ? xa : tot - 1); }
-    // the A tiles of the first two batches of the first round go in flight
+    // the A tiles of the first two batches go in flight
     __device__ __forceinline__ void prefetch(const GemmArgs &g, long long w_off = 0) {
         const int tid_ = thread_index(), lane = tid_ & 63, wave = tid_ >> 6;
         if (t0 < t1) {
-            const int tb = (t1 < t0 + 8) ? t1 : t0 + 8, tot = (tb - t0) * g.KT;
+            const int tot = (t1 - t0) * g.KT;
             const int xa = part_start(tot, wave, NW), xb = part_start(tot, wave + 1, NW);
-            unsigned base = (unsigned)((size_t)t0 * g.KT * NPL * 64 + lane);
+            unsigned base = (unsigned)((size_t)t0 * g.KT * 64 + lane);
             asm volatile("" : "+v"(base));     // keep the address arithmetic of these loads here (see StatStream)
             const int x_ok = valid_pair(xa, xb, tot);
             const bf16x8 *W = (const bf16x8 *)((const char *)g.W + w_off);
             load_a(a0, W, base, xa, x_ok);
             load_a(a1, W, base, xa + U, x_ok);
         }
-        primed = true;
     }
 };
 
-// ONE_ROUND: the caller guarantees at most 8 row tiles per workgroup (then there is no loop over rounds, and the
-// tail runs with the stream's buffers dead).
-template <int NPL, int U, int NW, class Io, int EPI, bool ONE_ROUND, bool F16, class Tail>
-__device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NPL, U, NW> &S, GemmLds &L, Tail tail, long long w_off = 0) {
+// out = resid + W B.  The stream's first two batches are in flight (prefetch()).
+template <int U, int NW>
+__device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<U, NW> &S, GemmLds &L, long long w_off = 0) {
     constexpr int NTHREADS = NW * 64;
-    constexpr int RP = (kTilesPerRound * 128 + NTHREADS - 1) / NTHREADS;   // residual entries per thread and round
+    constexpr int RP = (kTilesPerRound * 128 + NTHREADS - 1) / NTHREADS;   // residual entries per thread
     const int tid = thread_index(), lane = tid & 63, wave = tid >> 6;
     const int t0 = S.t0, t1 = S.t1;
-    if (tid < 8) L.scale[tid] = 1.0f;
     const bool bact = (lane & 7) < g.m;
     const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
     const bf16x8 *B = (const bf16x8 *)g.B;
     const int KT = g.KT;
-    for (int ta = t0; ta < t1; ta += (ONE_ROUND ? (1 << 30) : 8)) {
-        const int tb = (t1 < ta + 8) ? t1 : ta + 8, nt = tb - ta;
-        const int tot = nt * KT;
+    if (t0 < t1) {
+        const int ta = t0, nt = t1 - t0, tot = nt * KT;
         const int xa = part_start(tot, wave, NW), xb = part_start(tot, wave + 1, NW);
         int tile = xa / KT, ks = xa % KT;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         const bf16x8 *W = (const bf16x8 *)((const char *)g.W + w_off);
-        const unsigned base = (unsigned)((size_t)ta * KT * NPL * 64 + lane);
-        const int x_ok = StreamStream<NPL, U, NW>::valid_pair(xa, xb, tot);
+        const unsigned base = (unsigned)((size_t)ta * KT * 64 + lane);
+        const int x_ok = StreamStream<U, NW>::valid_pair(xa, xb, tot);
         bf16x8 b0[U], b1[U];
         // the B operands of batch [x, x + U), whose first pair is k-step ks_at of its tile: every call issues exactly U
         // loads (entries past the range read unit 0 of the block and are never multiplied; lanes of tokens past the
@@ -545,16 +486,14 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
                 if (KT >= U) kk -= (kk >= KT) ? KT : 0;
                 else kk %= KT;
                 const bool on = x + j < xb;
-                b[j] = Io::ldb(B + (on ? act_operand_index(kk, src_lane, KT) : 0));
+                b[j] = IoAcquired::ldb(B + (on ? act_operand_index(kk, src_lane, KT) : 0));
             }
         };
-        auto mma = [&](const bf16x8 (&a)[U][NPL], const bf16x8 (&b)[U], int x) {
+        auto mma = [&](const bf16x8 (&a)[U], const bf16x8 (&b)[U], int x) {
 #pragma unroll
             for (int j = 0; j < U; ++j)
                 if (x + j < xb) {
-                    const bf16x8 bb = bact ? b[j] : zero;
-#pragma unroll
-                    for (int q = 0; q < NPL; ++q) acc = mma16<F16>(a[j][q], bb, acc);
+                    acc = mma16<false>(a[j], bact ? b[j] : zero, acc);
                     if (++ks == KT) {
                         *(f32x4 *)(L.slots + (wave + tile) * 256 + (lane & 15) * 16 + (lane >> 4) * 4) = acc;
                         acc = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -565,25 +504,18 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
         };
         // residual values of this thread's output entries (and the next GEMM's norm weights for them), ahead of the stream
         float rpre[RP], npre[RP];
-        if (EPI == EPI_RESID) {
 #pragma unroll
-            for (int j = 0; j < RP; ++j) {
-                const int idx = tid + j * NTHREADS, T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-                const bool on = idx < nt * 128 && t < g.m && n < g.N;
-                rpre[j] = on ? Io::ld(g.resid + (size_t)t * g.ld + n) : 0.f;
-                npre[j] = (on && g.Bnext) ? load_w((const char *)g.next_norm_w + w_off, g.next_norm_elem, (size_t)n) : 0.f;
-            }
+        for (int j = 0; j < RP; ++j) {
+            const int idx = tid + j * NTHREADS, T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
+            const bool on = idx < nt * 128 && t < g.m && n < g.N;
+            rpre[j] = on ? IoAcquired::ld(g.resid + (size_t)t * g.ld + n) : 0.f;
+            npre[j] = (on && g.Bnext) ? bf16_bits_to_f32(*(const uint16_t *)((const char *)g.next_norm_w + w_off + (size_t)n * 2)) : 0.f;
         }
         // Two batches are in flight while a third is multiplied: a0/b0 hold batch x, a1/b1 batch x + U.  While four
         // whole batches remain, every load of the loop is in range and unconditional, so each multiplication waits for
         // its own operands only; the last batches take their loads under conditions (no duplicate traffic at the end).
-        const bool primed = S.primed && ta == t0;     // the A tiles of batches 0 and 1 are in flight already
         auto wrap = [&](int k) { if (KT >= U) return k - (k >= KT ? KT : 0); return k % KT; };
         int ks_b = ks;                                  // k-step of the first pair of the batch whose B operands load next
-        if (!primed) {
-            S.load_a(S.a0, W, base, xa, x_ok);
-            S.load_a(S.a1, W, base, xa + U, x_ok);
-        }
         load_b(b0, xa, ks_b);
         ks_b = wrap(ks_b + U);
         load_b(b1, xa + U, ks_b);
@@ -616,9 +548,7 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
             }
         }
         if (ks != 0) *(f32x4 *)(L.slots + (wave + tile) * 256 + (lane & 15) * 16 + (lane >> 4) * 4) = acc;
-        __builtin_amdgcn_sched_barrier(0);  // keep the tail's loads out of the stream's register live ranges
-        if (tb == t1) tail();
-        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);  // the weight stream has ended
         __syncthreads();
         // The sum of a tile's slots, in wavefront order: wavefronts w0 .. w1 hold pairs of tile T (pairs [T * KT, T * KT + KT)
         // of the round; wavefront w holds pairs [tot * w / NW, tot * (w + 1) / NW)), those without pairs are skipped.
@@ -635,38 +565,27 @@ __device__ __forceinline__ void gemm_streamed(const GemmArgs &g, StreamStream<NP
             }
             return v;
         };
-        if (EPI == EPI_RESID) {
-            // each thread sums its own output entries and finishes them
+        // each thread sums its own output entries and finishes them
 #pragma unroll
-            for (int j = 0; j < RP; ++j) {
-                const int idx = tid + j * NTHREADS, T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
-                const bool on = idx < nt * 128 && t < g.m && n < g.N;
-                const float y = on ? rpre[j] + tile_sum(T, t, i) : 0.f;
-                if (on) Io::st(g.out + (size_t)t * g.ld + n, y);
-                if (g.Bnext) {
-                    // input of the next GEMM: y * norm weight, packed; and this tile's share of sum(y^2) per token
-                    // (the 16 outputs of a (tile, token) pair sit in 16 neighbouring lanes)
-                    if (on) store_act_io<Io, F16>((uint16_t *)g.Bnext, g.Bnext_KT, n, t, y * npre[j]);
-                    float q = y * y;
-                    q += __shfl_xor(q, 8);
-                    q += __shfl_xor(q, 4);
-                    q += __shfl_xor(q, 2);
-                    q += __shfl_xor(q, 1);
-                    if (i == 0 && idx < nt * 128 && t < g.m) Io::st(g.ssq_out + (size_t)(ta + T) * 8 + t, q);
-                }
+        for (int j = 0; j < RP; ++j) {
+            const int idx = tid + j * NTHREADS, T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15, n = (ta + T) * 16 + i;
+            const bool on = idx < nt * 128 && t < g.m && n < g.N;
+            const float y = on ? rpre[j] + tile_sum(T, t, i) : 0.f;
+            if (on) IoAgent::st(g.out + (size_t)t * g.ld + n, y);
+            if (g.Bnext) {
+                // input of the next GEMM: y * norm weight, packed; and this tile's share of sum(y^2) per token
+                // (the 16 outputs of a (tile, token) pair sit in 16 neighbouring lanes)
+                if (on) store_act_agent((uint16_t *)g.Bnext, g.Bnext_KT, n, t, y * npre[j]);
+                float q = y * y;
+                q += __shfl_xor(q, 8);
+                q += __shfl_xor(q, 4);
+                q += __shfl_xor(q, 2);
+                q += __shfl_xor(q, 1);
+                if (i == 0 && idx < nt * 128 && t < g.m) IoAgent::st(g.ssq_out + (size_t)(ta + T) * 8 + t, q);
             }
-        } else {
-            for (int idx = tid; idx < nt * 128; idx += NTHREADS) {
-                const int T = idx >> 7, t = (idx >> 4) & 7, i = idx & 15;
-                L.red[idx] = t < g.m ? tile_sum(T, t, i) : 0.f;
-            }
-            __syncthreads();
-            epilogue<Io, EPI, F16>(g, L, ta, nt, tid, NTHREADS);
         }
         __syncthreads();
-        if (ONE_ROUND) break;     // (said here as well, so that the body is not compiled as a loop)
     }
-    if (t1 == t0) tail();
 }
 
 }  // namespace ad

@@ -527,7 +527,7 @@ static void qkv_args(const ad_model *m, int32_t ly, const void *hidden, int32_t 
     gq.W = lp.wqkv; gq.NT = L.nqkv / 16; gq.KT = L.kt_d; gq.N = L.nqkv; gq.K = L.d; gq.m = n; gq.mode = GEMM_STATIONARY;
     gq.inv_dim = 1.0f / (float)L.d; gq.eps = c.rms_eps;
     if (from_prev) { gq.B = m->Bq; gq.ssq_in = m->ssq_q; gq.ssq_tiles = m->layer_mode == AD_LAYER_FUSED ? L.d / 16 : L.d / 8; }
-    else { gq.x = (const float *)hidden; gq.ldx = L.d; gq.norm_w = lp.attn_norm; gq.norm_elem = ek; }
+    else { gq.x = (const float *)hidden; gq.ldx = L.d; gq.norm_w = lp.attn_norm; }
     gq.epi = EPI_STORE; gq.out = m->qkv; gq.ld = L.nqkv;
 }
 
@@ -585,7 +585,7 @@ static int layer_steps(const ad_model *m, ad_kv *kv, int32_t layer, int32_t coun
         go.W = lp.wo; go.B = m->Bo; go.NT = L.d / 16; go.KT = L.kt_q; go.N = L.d; go.K = L.dq; go.m = n; go.mode = GEMM_STREAMED;
         go.epi = EPI_RESID; go.resid = (const float *)hidden; go.out = m->x1; go.ld = L.d;
         // ... and the Wo epilogue already prepares the gate/up GEMM's input: x' * ffn norm weight packed, sum(x'^2) per tile
-        go.Bnext = m->Bx; go.Bnext_KT = L.kt_d; go.next_norm_w = lp.ffn_norm; go.next_norm_elem = ek; go.ssq_out = m->ssq;
+        go.Bnext = m->Bx; go.Bnext_KT = L.kt_d; go.next_norm_w = lp.ffn_norm; go.ssq_out = m->ssq;
         // 4. g = silu(Wg b) * (Wu b), b = RMSNorm(x') fused as in step 1
         memset(&gg, 0, sizeof gg);
         gg.elem = ek;
@@ -599,7 +599,7 @@ static int layer_steps(const ad_model *m, ad_kv *kv, int32_t layer, int32_t coun
         gd.epi = EPI_RESID; gd.resid = m->x1; gd.out = (float *)hidden; gd.ld = L.d;
         // ... and, like step 3 for step 4, prepares the next layer's QKV input: y * its attention norm weight packed, sum(y^2) per tile
         if (feeds_next) {
-            gd.Bnext = m->Bq; gd.Bnext_KT = L.kt_d; gd.next_norm_w = m->layers[ly].attn_norm; gd.next_norm_elem = ek; gd.ssq_out = m->ssq_q;
+            gd.Bnext = m->Bq; gd.Bnext_KT = L.kt_d; gd.next_norm_w = m->layers[ly].attn_norm; gd.ssq_out = m->ssq_q;
         }
     };
 
@@ -748,12 +748,12 @@ static int run_head(const ad_model *m, int32_t layer, const void *hidden, int32_
         memset(&t, 0, sizeof t);
         t.elem = ek;
         t.W = m->T[slot]; t.NT = L.d / 16; t.KT = L.kt_d; t.N = L.d; t.K = L.d; t.m = n; t.mode = GEMM_STATIONARY;
-        t.x = (const float *)hidden; t.ldx = L.d; t.norm_w = m->final_norm; t.norm_elem = ek; t.inv_dim = 1.0f / (float)L.d; t.eps = c.rms_eps;
+        t.x = (const float *)hidden; t.ldx = L.d; t.norm_w = m->final_norm; t.inv_dim = 1.0f / (float)L.d; t.eps = c.rms_eps;
         t.epi = EPI_PACK; t.Bnext = m->B1; t.Bnext_KT = L.kt_d;
         if ((rc = gemm(m, t, L.d, L.d, ctx))) return hip_fail(rc, who);
         g.B = m->B1;
     } else {
-        g.x = (const float *)hidden; g.ldx = L.d; g.norm_w = m->final_norm; g.norm_elem = ek; g.inv_dim = 1.0f / (float)L.d; g.eps = c.rms_eps;
+        g.x = (const float *)hidden; g.ldx = L.d; g.norm_w = m->final_norm; g.inv_dim = 1.0f / (float)L.d; g.eps = c.rms_eps;
     }
     if ((rc = gemm(m, g, L.V, L.d, ctx))) return hip_fail(rc, who);
     return AD_OK;

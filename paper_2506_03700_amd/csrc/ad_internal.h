@@ -24,8 +24,6 @@ enum : int { kElemF32 = 0, kElemBF16 = 1, kElemF16 = 2 };   // host-side names o
 // cache line, and a call with m tokens touches m lines per k-step (KT * 1 KiB for a full block).
 constexpr int kTileRows = 16;
 constexpr int kTileK = 32;
-constexpr int kThreads = 1024;   // LDS slots are laid out for up to 16 wavefronts
-constexpr int kWaves = kThreads / 64;
 
 inline size_t packed_bytes(int64_t N, int64_t K, int planes) {
     const int64_t nt = (N + kTileRows - 1) / kTileRows, kt = (K + kTileK - 1) / kTileK;
@@ -43,7 +41,7 @@ struct GemmArgs {
     // rsqrt(mean(x^2) + eps) when norm_w is given), or a packed block B
     const float *x;
     const void *B;
-    const void *norm_w;
+    const void *norm_w;   // of the weights' type, as next_norm_w is
     int NT, KT;           // row tiles, k-steps
     int K;                // valid inputs
     int m;                // tokens
@@ -54,7 +52,6 @@ struct GemmArgs {
     // ---- end of the first line ----
     int mode;             // GemmMode
     int elem;             // ElemKind of the weights: fp32 (three bf16 planes), bf16, or fp16 (fp16 MFMA, fp16 hi/lo activations)
-    int norm_elem;        // ElemKind of norm_w
     float inv_dim, eps;
     int epi;
     // EPI_STORE: out[t*ld + n] = scale_t * acc
@@ -73,7 +70,6 @@ struct GemmArgs {
     // B = that block, ssq_in = those partials, ssq_tiles of them) only has to load its operand registers and add the
     // partials up for the 1/rms factor.
     const void *next_norm_w;
-    int next_norm_elem;
     float *ssq_out;
     const float *ssq_in;
     int ssq_tiles;

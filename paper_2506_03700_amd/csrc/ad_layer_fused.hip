@@ -105,7 +105,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         ++n_stamp;
     };
 
-    StatStream<1, CH> s_qkv;   // the only weight stream that is in flight from one layer to the next
+    StatStream<CH> s_qkv;   // the only weight stream that is in flight from one layer to the next
     // the layer's weights, norm weights and cache: those of the first layer moved on by these many bytes
     long long w_off = 0, kv_off = 0;
     s_qkv.init(f0.qkv, wg, f0.nwg_qkv);
@@ -118,8 +118,8 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
     for (int l = 0;; ++l) {
         asm volatile("" : "+s"(fp));
         const FusedArgs &f = *(const FusedArgs *)fp;
-        StatStream<1, CH> s_gu;
-        StreamStream<1, U, NW> s_wo, s_down;
+        StatStream<CH> s_gu;
+        StreamStream<U, NW> s_wo, s_down;
         n_stamp = 0;
         stamp();
         // ---- 1. q, k, v = W (RMSNorm(x)) -----------------------------------------------------------------
@@ -128,8 +128,8 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         if (wg < f.nwg_qkv) {
             // first layer: x was written before the launch and is requested ahead of the weights; later layers: the
             // weights went in flight at the barrier that made x visible
-            if (l == 0) gemm_stationary<1, CH, NCHMAX, IoAcquired, EPI_STORE, false, false>(f.qkv, s_qkv, L.gemm, NoTail(), w_off);
-            else gemm_stationary<1, CH, NCHMAX, IoAcquired, EPI_STORE, false, true>(f.qkv_next, s_qkv, L.gemm, NoTail(), w_off);
+            if (l == 0) gemm_stationary<CH, NCHMAX, EPI_STORE, false>(f.qkv, s_qkv, L.gemm, w_off);
+            else gemm_stationary<CH, NCHMAX, EPI_STORE, true>(f.qkv_next, s_qkv, L.gemm, w_off);
         }
         stamp();
         forget(kv.k);
@@ -138,13 +138,13 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         stamp();
 
         // ---- 2. rotary embedding, KV append, attention partials ----------------------------------------------
-        attn_mfma_items<DH, IoAgent>(f.attn, L.attn, wg, nwg, kv, true, kv_off);
+        attn_mfma_items<DH>(f.attn, L.attn, wg, nwg, kv, true, kv_off);
         stamp();
-        if (!bar.sync(false, NoTail())) return;
+        if (!bar.sync(false, []() {})) return;
         stamp();
 
         // ---- 3. fold the splits of each query row (one wavefront per row), packed for Wo -----------------------
-        for (int row = (thread_index() >> 6) * nwg + wg; row < f.attn.Hq * f.attn.m; row += NW * nwg) attn_combine_row<IoAgent, false>(f.attn, row);
+        for (int row = (thread_index() >> 6) * nwg + wg; row < f.attn.Hq * f.attn.m; row += NW * nwg) attn_combine_row(f.attn, row);
         s_wo.init(f.wo, wg, f.nwg_wo);
         auto pre_wo = [&]() { s_wo.prefetch(f.wo, w_off); };
         stamp();
@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         // ---- 4. x' = x + Wo o ----------------------------------------------------------------------------------
         s_gu.init(f.gu, wg, f.nwg_gu, w_off);
         auto pre_gu = [&]() { s_gu.prefetch(); };
-        if (wg < f.nwg_wo) gemm_streamed<1, U, NW, IoAcquired, EPI_RESID, true, false>(f.wo, s_wo, L.gemm, NoTail(), w_off);
+        if (wg < f.nwg_wo) gemm_streamed<U, NW>(f.wo, s_wo, L.gemm, w_off);
         stamp();
         forget(s_gu.a0);
         forget(s_gu.a1);
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         // ---- 5. g = silu(Wg b) * (Wu b), b = RMSNorm(x') ---------------------------------------------------------
         s_down.init(f.down_last, wg, f.nwg_down);
         auto pre_down = [&]() { s_down.prefetch(f.down_last, w_off); };
-        if (wg < f.nwg_gu) gemm_stationary<1, CH, NCHMAX, IoAcquired, EPI_SWIGLU, false, true>(f.gu, s_gu, L.gemm, NoTail(), w_off);
+        if (wg < f.nwg_gu) gemm_stationary<CH, NCHMAX, EPI_SWIGLU, true>(f.gu, s_gu, L.gemm, w_off);
         stamp();
         forget(s_down.a0);
         forget(s_down.a1);
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         // ---- 6. y = x' + Wd g --------------------------------------------------------------------------------------
         // (a layer that is followed by another also leaves that layer's QKV input behind, packed)
         const bool more = l + 1 < f.n_layers;
-        if (wg < f.nwg_down) gemm_streamed<1, U, NW, IoAcquired, EPI_RESID, true, false>(more ? f.down : f.down_last, s_down, L.gemm, NoTail(), w_off);
+        if (wg < f.nwg_down) gemm_streamed<U, NW>(more ? f.down : f.down_last, s_down, L.gemm, w_off);
         stamp();
         if (!more) break;
 
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_layer_fused(FusedArgs f0) {
         kv_off += f.kv_stride;
         // (a stream object of its own: filled under conditions, s_qkv itself would have to keep its old registers
         // alive through all phases)
-        StatStream<1, CH> s_next;
+        StatStream<CH> s_next;
         s_next.init(f.qkv, wg, f.nwg_qkv, w_off);
         auto pre_qkv = [&]() { s_next.prefetch(); };
         forget(s_next.a0);
@@ -224,7 +224,7 @@ int launch_layer_fused(const FusedArgs &f_in, const LaunchCtx &c) {
     if (f.qkv.mode != GEMM_STATIONARY || f.gu.mode != GEMM_STATIONARY) return (int)hipErrorInvalidValue;
     // the streamed phases run a single round of at most 8 row tiles per workgroup
     if (f.wo.NT > 8 * f.nwg_wo || f.down.NT > 8 * f.nwg_down) return (int)hipErrorInvalidValue;
-    if ((f.qkv.KT + kStatWaves - 1) / kStatWaves > kKsMax || f.qkv.K < 8) return (int)hipErrorInvalidValue;
+    if ((f.qkv.KT + kStatWaves - 1) / kStatWaves > kKsMax || f.qkv.K < 8 || !f.qkv.norm_w) return (int)hipErrorInvalidValue;
     if (f.attn.kv_elem != kElemBF16 || f.qkv.elem != kElemBF16 || c.n_wg < 1 || f.n_layers < 1) return (int)hipErrorInvalidValue;
     const bool small = (f.qkv.KT + kStatWaves - 1) / kStatWaves <= 16;
     if (f.attn.dh == 128) return small ? launch_fused_dh<128, 2>(f, c) : launch_fused_dh<128, 3>(f, c);

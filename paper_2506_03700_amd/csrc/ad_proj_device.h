@@ -108,13 +108,4 @@ __device__ __forceinline__ void sum_ssq(const GemmArgs &g, int wave, int lane, f
     if (lane == 0) ssq_part[wave] = v;
 }
 
-// v as input k of token t in a packed activation block of KT k-steps
-template <bool F16>
-__device__ __forceinline__ void store_act(void *B, int KT, int k, int t, float v) {
-    uint16_t hi, lo;
-    split16<F16>(v, hi, lo);
-    ((uint16_t *)B)[act_index(k, t, KT)] = hi;
-    ((uint16_t *)B)[act_index(k, 8 + t, KT)] = lo;
-}
-
 }  // namespace ad
