@@ -220,11 +220,13 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     // columns n and n + 8 hold the hi and lo products of token n; the wavefront's slots: [slot][token][16 rows]
     float *slot = (float *)(lds_raw + wave * WB);
     if (HALF) {
-        // rows 0..7 of the first product and 8..15 of the second are the half tile's, each over its own k-steps
+        // rows 0..7 of the first product and 8..15 of the second are the half tile's, each over its own k-steps: added up in the order of
+        // a whole tile's sums, so that equal rows of a head have equal logits wherever they lie
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float v = add_lane_xor8(gq < 2 ? acch[0][e] : acch[1][e]);
-            acch[0][e] = v;
+            const unsigned u = __float_as_uint(gq < 2 ? acch[0][e] : acch[1][e]);
+            const auto v = __builtin_amdgcn_permlane32_swap(u, u, false, false);       // the lower and the upper lanes' values, everywhere
+            acch[0][e] = add_lane_xor8(__uint_as_float(v[0]) + __uint_as_float(v[1]));
         }
     }
 #pragma unroll
@@ -234,7 +236,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     if (n < g.m) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) *(f32x4 *)(slot + f * 128 + n * 16 + gq * 4) = acc[f][0];
-        if (HALF) *(f32x4 *)(slot + NF * 128 + n * 16 + gq * 4) = acch[0];
+        if (HALF && gq < 2) *(f32x4 *)(slot + NF * 128 + n * 16 + gq * 4) = acch[0];
     }
     __syncthreads();
     if (wave >= H) return;
@@ -260,8 +262,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     if (g.epi != EPI_HEAD && !on) return;
     float v;
     if (HALF && (upper ? wave == 0 : wave == H - 1)) {
-        const float *p = base + NF * 128;
-        v = sum_rows(p) + sum_rows(p + 8);
+        v = sum_rows(base + NF * 128);
     } else {
         const int r = wave - (HALF ? upper : 0);                // half r of the whole tiles
         v = sum_rows(base + (r >> 1) * 128 + (r & 1) * 8);

@@ -58,6 +58,35 @@ def test_logits_that_are_no_numbers_are_passed_by(ad, V, dtype):
     g.close()
 
 
+@pytest.mark.parametrize("V,dtype", [(V, t) for V in (4096, 4097, 5003, 6144, 6145, 8192, 8193) for t in (F32, BF16, F16)], ids=str)
+def test_logits_and_tokens_at_the_edges_of_the_split(ad, V, dtype):
+    """2 (4096 ids), 3 (4097 to 6144), 4 halves of a tile per workgroup, beyond 8192 whole tiles: every logit in its place, and among equal
+    ones the lowest id, whether they share 8 rows, a tile, a workgroup (24 ids with 3 halves) or none of these."""
+    s = shape(V, dtype)
+    w = synth.make_weights(s, seed=11, norm_jitter=0.2)
+    w["lm_head"] = w["lm_head"].copy()
+    best = np.array([2, 17, 33, 1203, 2407, V - 22, V - 2, 41])
+    also = np.array([5, 25, 49, 1212, V - 40, V - 5, V - 1, V // 2 + 3])
+    w["lm_head"][also] = w["lm_head"][best]
+    hidden = pointing_at(w, best)
+    g, o = ad.Model(s, w, max_pos=8), orc.Oracle(s, w, max_pos=8)
+    h = hidden.cpu().numpy()
+    z = g.ad_head_logits(2, hidden).cpu().numpy()
+    for r, b in enumerate(best):
+        print(f"case V {V} dtype {dtype} id {b}", flush=True)
+        check_rows(dtype, z[r], o.head(-1, h[r], want_logits=True)[3], "logits")
+        assert z[r, b] == z[r, also[r]] == z[r].max()
+        tok, conf = g.ad_exit_head(1, hidden[r])
+        e = np.exp(z[r].astype(np.float64) - z[r].max())
+        assert tok == b and abs(conf - e.max() / e.sum()) <= 1e-5
+    for static in (False, True):
+        n, nxt, arg = g.ad_verify(hidden, best[:-1], static=static)
+        assert n == 7 and nxt == best[7] and np.array_equal(arg, best)
+        n, nxt, arg = g.ad_verify(hidden, also[:-1], static=static)
+        assert n == 0 and nxt == best[0] and np.array_equal(arg, best)
+    g.close()
+
+
 @pytest.mark.parametrize("d,dtype", [(d, F32) for d in (512, 528, 1024, 1040, 2048, 2064, 3072, 3088, 4096, 4112, 5120)] +
                          [(d, t) for d in (64, 512, 528, 1024, 1040) for t in (BF16, F16)], ids=str)
 def test_large_vocabularies(ad, d, dtype):
