@@ -84,26 +84,46 @@ def test_storage_without_the_scratch_is_a_cache_too(ad):
     g.close()
 
 
-@pytest.mark.parametrize("shape", [ODD, ODD.with_(name="odd-f16", dtype=synth.F16), DH128, MHA], ids=lambda s: s.name)
-def test_nothing_is_read_that_was_not_written(ad, shape):
-    """A cache in storage full of NaN gives the same bits as one in zeros, prompt after prompt."""
+# The pieces of q/k/v (N 1536) and Wo (N 2048) of some 100 tokens, four of each, take 2.4 and 3.2 MB: more than the 2 MB set aside for
+# them in a cache of 128 rows, so that they run on into the SwiGLU activations; those of down lie over queries and attention output.
+SHARED = ODD.with_(name="shared-bf16", n_q_heads=16, n_kv_heads=4, d_model=2048, d_ffn=2752)
+
+
+def same_bits_in_poisoned_storage(ad, shape, max_pos, lengths):
     import torch
     w = synth.make_weights(shape, seed=8, norm_jitter=0.2)
-    g = ad.Model(shape, w, max_pos=320)
+    g = ad.Model(shape, w, max_pos=max_pos)
     want = []
     for fill in (0, 255):
         g.L.ad_kv_destroy(g.kv)
         g.kv_storage.fill_(fill)
         kv = C.c_void_p()
-        assert g.L.ad_kv_create(g.model, C.c_void_p(g.kv_storage.data_ptr()), g.kv_storage.numel(), 320,
+        assert g.L.ad_kv_create(g.model, C.c_void_p(g.kv_storage.data_ptr()), g.kv_storage.numel(), max_pos,
                                 C.c_void_p(torch.cuda.current_stream().cuda_stream), C.byref(kv)) == ad.AD_OK
         g.kv = kv
-        for i, n in enumerate((17, 10, 140, 70, 300)):
+        for i, n in enumerate(lengths):
             g.ad_generate(synth.make_prompt(shape, n, n), 3, 2.0, 0)
             got = [a for l in range(1, shape.n_layers + 1) for a in g.kv_read(l, n)]
             if fill == 0:
                 want.append(got)
             assert all(np.array_equal(a, b) and np.all(np.isfinite(a)) for a, b in zip(got, want[i])), (fill, n)
+    g.close()
+
+
+@pytest.mark.parametrize("shape", [ODD, ODD.with_(name="odd-f16", dtype=synth.F16), DH128, MHA], ids=lambda s: s.name)
+def test_nothing_is_read_that_was_not_written(ad, shape):
+    """A cache in storage full of NaN gives the same bits as one in zeros, prompt after prompt."""
+    same_bits_in_poisoned_storage(ad, shape, 320, (17, 10, 140, 70, 300))
+
+
+@pytest.mark.parametrize("shape", [SHARED, SHARED.with_(name="shared-f16", dtype=synth.F16)], ids=lambda s: s.name)
+def test_pieces_in_scratch_of_other_steps(ad, shape):
+    same_bits_in_poisoned_storage(ad, shape, 120, (100, 10, 65, 110))
+    w = synth.make_weights(shape, seed=9, norm_jitter=0.2)
+    g, o = ad.Model(shape, w, max_pos=120), orc.Oracle(shape, w, max_pos=120)
+    for n in (34, 100, 117):
+        print(f"case {shape.name} {n} tokens", flush=True)
+        follow_up(shape, g, o, synth.make_prompt(shape, n, n + 1))
     g.close()
 
 
