@@ -495,10 +495,9 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
     constexpr int PR = DH + 2, TG = DH / 2, NG = 256 / TG, KB = 8;
     __shared__ float st[NG][2];
     __shared__ f32x2 part[NG][TG];
-    const int tid = threadIdx.x, grp = tid / TG, e = 2 * (tid % TG), S = a.S;
+    const int tid = threadIdx.x, grp = TG == 64 ? __builtin_amdgcn_readfirstlane(tid / TG) : tid / TG, e = 2 * (tid % TG), S = a.S;
     const int row = blockIdx.x, g = div_small(row, a.mul_R), r = row - g * a.R, t = div_small(r, a.mul_G), hq = g * a.G + (r - t * a.G);
     const float *base = a.part + ((size_t)g * S * a.R + r) * PR;
-    const size_t sstride = (size_t)a.R * PR;                   // (an fp32 cache's splits grow with the context: beyond 32 bits in all)
     float M = -INFINITY, den = 0.f;
     f32x2 o = {0.f, 0.f};
     for (int s0 = grp; s0 < S; s0 += NG * KB) {
@@ -506,7 +505,8 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 #pragma unroll
         for (int k = 0; k < KB; ++k) {                          // splits past the end repeat the group's first (weight 0)
             const int s = s0 + k * NG;
-            const float *p = base + (size_t)(s < S ? s : s0) * sstride;
+            // (32 bits count rows of partials, not their floats: an fp32 cache's splits grow with the context)
+            const float *p = base + (size_t)((unsigned)(s < S ? s : s0) * (unsigned)a.R) * PR;
             ms[k] = *(const f32x2 *)(p + DH);
             v[k] = *(const f32x2 *)(p + e);
         }
