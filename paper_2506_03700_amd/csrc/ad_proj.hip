@@ -273,9 +273,9 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
         if (g.head_stats) {
             // (max, sum of exp, argmax) of these 8 rows, a partial of each wavefront (a maximum that started as a value that is
             // no number would keep its index and take the others' values)
-            float M = -INFINITY, S = 0.f;
-            int I = 0x7fffffff;
-            if (on) max_merge(M, S, I, v, 1.0f, row);
+            const bool num = on && v == v;
+            float M = num ? v : -INFINITY, S = num ? 1.0f : on ? v : 0.f;
+            int I = num ? row : 0x7fffffff;
 #pragma unroll
             for (int off = 4; off > 0; off >>= 1) max_merge(M, S, I, __shfl_xor(M, off), __shfl_xor(S, off), __shfl_xor(I, off));
             if (ei == 0 && et < g.m) {
