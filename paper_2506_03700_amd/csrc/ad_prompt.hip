@@ -31,7 +31,8 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // WR x WT accumulators.  Both operands lie in memory in MFMA operand order, so tiles are copied as they are and every LDS
 // access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.
 //
-// The accumulators are emptied into a second set every kFlush k-steps: one long chain of fp32 additions is off by 5.7e-7 of
+// The accumulators are emptied into a second set every kFlush k-steps, each at its own turn (at the end of a piece whose length is no
+// multiple of kFlush up to 2 * kFlush - 1 k-steps are in one chain): one long chain of fp32 additions is off by 5.7e-7 of
 // the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
 // 512 inputs each and then each other, is as good).
 constexpr int kFlush = 8;
