@@ -34,8 +34,9 @@ struct PromptGemm {
     void *Bnext;              // swiglu: activation tiles of the next projection, Bnext_KT k-steps
     int Bnext_KT;
     int f16;                  // fp16 operands (else bf16)
-    // set by the launcher: workgroups along the rows and along the tokens, pieces along K and k-steps per piece
-    int n_rb, n_tb, n_split, k_per;
+    // set by the launcher: tiles along the rows and along the tokens, pieces along K and k-steps per piece; tiles that are a workgroup each
+    // (the rest are two)
+    int n_rb, n_tb, n_split, k_per, n_full;
 };
 
 // x[t] (+)= sum of the pieces; activation tiles of x[t] * w, and the factor 1 / rms(x[t]) that makes RMSNorm of it, which

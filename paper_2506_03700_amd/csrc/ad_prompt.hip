@@ -9,7 +9,10 @@
 // k_prompt_gemm (Wo) -> k_prompt_rows (residual, RMSNorm, tiles) -> k_prompt_gemm (gate/up, SwiGLU) ->
 // k_prompt_gemm (down) -> k_prompt_rows.  The last layer is its K and V alone.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "ad_device.h"
 #include "ad_internal.h"
@@ -33,25 +36,28 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 //
 // The accumulators are emptied into a second set every kFlush k-steps, each at its own turn (at the end of a piece whose length is no
 // multiple of kFlush up to 2 * kFlush - 1 k-steps are in one chain): one long chain of fp32 additions is off by 5.7e-7 of
-// the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.7e-7 (the layer step, whose wavefronts add up
+// the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.8e-7 (the layer step, whose wavefronts add up
 // 512 inputs each and then each other, is as good).
 constexpr int kFlush = 8;
 enum { PG_PART = 0, PG_SWIGLU = 1 };
 
-// Which tiles and k-steps this workgroup has.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets a contiguous run
-// of (piece, row block, token block), so that the workgroups that share weights share an L2.
-struct PromptTile { int rb, tb, piece, k0, k1; };
+// Which tile and piece this workgroup has.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets a contiguous run
+// of (piece, row block, token block), so that the workgroups that share weights share an L2.  Tiles from g.n_full on are dealt as
+// two halves of their rows (half 0 or 1; else -1), a workgroup each.
+struct PromptTile { int rb, tb, piece, half; };
 __device__ __forceinline__ PromptTile prompt_tile(const PromptGemm &g) {
-    const int total = g.n_rb * g.n_tb * g.n_split, q8 = total >> 3, r8 = total & 7;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+    const int tiles = g.n_rb * g.n_tb * g.n_split;
+    const bool halves = (int)blockIdx.x >= g.n_full;
+    const int n = halves ? 2 * (tiles - g.n_full) : g.n_full, b = (int)blockIdx.x - (halves ? g.n_full : 0);
+    const int q8 = n >> 3, r8 = n & 7, xcd = b & 7;
+    const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + (b >> 3);
+    const int tile = halves ? g.n_full + (id >> 1) : id;
     PromptTile t;
-    t.tb = id % g.n_tb;
-    const int rest = id / g.n_tb;
+    t.half = halves ? id & 1 : -1;
+    t.tb = tile % g.n_tb;
+    const int rest = tile / g.n_tb;
     t.rb = rest % g.n_rb;
     t.piece = rest / g.n_rb;
-    t.k0 = t.piece * g.k_per;
-    t.k1 = (t.k0 + g.k_per < g.KT) ? t.k0 + g.k_per : g.KT;
     return t;
 }
 
@@ -128,106 +134,173 @@ __device__ __forceinline__ void copy_to_lds(const void *src, bf16x8 *dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
-// From about 128 tokens on bound by the matrix cores and, with them, by the power that operands on the move take (with operands of
-// zeros the same launches run 20 to 45 % faster); below by the weights' way from memory.  Weights and activations are copied from
-// memory into LDS without a way through registers, NST - 1 k-steps ahead; a step waits for its own stage, and for everyone to be
-// done with the one before it, whose place the newest copies take.  Stages: as many as leave room for two workgroups per compute unit
-// (5 and 4 of 12 and 16 KiB, 3 of 24).  Measured with weights that no cache holds, us for 6144 x 4096, 4096 x 4096, 4096 x 14336,
-// 28672 x 4096, against weights straight into registers a k-step ahead (up to 64 tokens: both through registers into LDS):
-//     32 tokens   13.6    9.0   22.4   44.6     13.0   10.4   25.9   51.4
-//     64          16.7   10.5   24.9   48.3     17.6   12.5   30.4   61.6
-//    128          24.3   16.0   37.2   72.3     26.2   19.7   51.4  106.6
-//    256          36.6   24.1   59.5  125       37.0   24.3   67.5  128.6
-//   1024         102.8   64.5  207    425      105.1   64.2  198.6  435.8
-// (executed rate at 1024 tokens, hi and lo products both counted: 1.0 to 1.16 PFLOP/s).  4 x 4 tiles by 4 x 2 wavefronts and 4 stages, one
-// workgroup per compute unit: 1024 tokens 105.7, 65.3, 194, 435, 96 tokens 98 us for 28672 x 4096 (69.9 with 2 x 4).
-template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI>
-__global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
+// One workgroup's tile: row tiles rt0 .., token block tb, k-steps of a piece.
+//
+// Weights and activations are copied from memory into LDS without a way through registers, up to NST k-steps ahead.  A k-step is two
+// phases, the products with the hi plane and those with the lo plane; in each the operands of the next phase are read from LDS, one read
+// between two products, so that no product waits for LDS.  Between the phases is the step's only barrier: behind it the next stage is
+// there and nobody reads this one any more, whose place the copies of k-step s + NST then take, half of them in this lo phase and half in the
+// next hi phase, spread between the products (all at once they hold up the products behind them).  ONE: a single phase, for tiles of so few
+// products that the reads take longer than a phase of them.
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, bool ONE>
+__device__ __forceinline__ void prompt_gemm_tile(const PromptGemm &g, int rt0, int tb, int piece, bf16x8 *lds) {
     constexpr int NW = NWR * NWT, BR = WR * NWR, BT = WT * NWT;
-    constexpr int SU = prompt_stage_units(BR, BT), NC = (BR + BT * 2) / NW;     // 16-byte units per stage, copies per wavefront
-    // Copies of a wavefront that may be in flight when a step begins.  The step's wait counts them, so that copies have to be issued in the
-    // order of their stages: no copy moves past the scheduling barriers between stages.
-    constexpr int FLY = NC * (NST - 2);
-    static_assert((BR + BT * 2) % NW == 0 && FLY < 64 && NST >= 3, "a stage is a whole number of copies per wavefront");
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    bf16x8 *lds = (bf16x8 *)lds_raw;                            // [NST][weight tiles, activation tiles]
+    constexpr int SU = prompt_stage_units(BR, BT), UNITS = BR + BT * 2;         // 16-byte units, and KiB, per stage
+    constexpr int NC = (UNITS + NW - 1) / NW, NH = ONE ? NC : NC / 2;      // copies of a wavefront per stage, of them in the lo phase
+    // Copies of a wavefront that may be in flight at a step's barrier.  The wait counts them, so that copies have to be issued in the
+    // order of their stages: no copy moves past the scheduling barriers between phases.
+    constexpr int FLY = NC * (NST - 2), FLY0 = NC * (NST - 2) + NH;
+    static_assert(FLY0 < 64 && NST >= 3, "the counter of loads in flight has six bits");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % NWR, wt = wave / NWR;
-    const PromptTile T = prompt_tile(g);
+    const int k0 = piece * g.k_per, k1 = k0 + g.k_per < g.KT ? k0 + g.k_per : g.KT;
 
     const char *src[NC];
     unsigned off[NC];
-    int shift[NC];                                              // log2 of the bytes from one k-step to the next
+    int shift[NC], dst[NC];                                     // log2 of the bytes from one k-step to the next; place in a stage
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-        const int u = wave * NC + i;                            // 1 KiB of a stage: a weight tile, or a token tile's plane
+        int u = wave * NC + i;                                  // 1 KiB of a stage: a weight tile, or a token tile's plane
+        if (u > UNITS - 1) u = UNITS - 1;                       // (no more of them: the last one again, to the same place)
+        dst[i] = u * 64;
         if (u < BR) {
-            int rt = T.rb * BR + u;
+            int rt = rt0 + u;
             if (rt > g.NT - 1) rt = g.NT - 1;                   // past the last row tile: its products are not stored
             src[i] = (const char *)g.W;
             off[i] = ((unsigned)rt * (unsigned)g.KT * 64u + (unsigned)lane) << 4;
             shift[i] = 10;
         } else {
-            const int v = u - BR;
+            const int v = u - BR, last = (g.M + 15) / 16 - 1;
+            int tt = tb * BT + (v >> 1);
+            if (tt > last) tt = last;                           // past the last token tile: likewise
             src[i] = (const char *)g.B;
-            off[i] = ((unsigned)(T.tb * BT + (v >> 1)) * (unsigned)g.KT * 128u + (unsigned)((v & 1) * 64 + lane)) << 4;
+            off[i] = ((unsigned)tt * (unsigned)g.KT * 128u + (unsigned)((v & 1) * 64 + lane)) << 4;
             shift[i] = 11;
         }
     }
-    const int k_last = T.k1 - 1;                                // copies past the piece repeat its last k-step
-    auto copy = [&](int stage, int k) {
+    const int k_last = k1 - 1;                                  // copies past the piece repeat its last k-step
+    auto copy = [&](int stage, int k, int i0, int i1) {
         const int kk = k < k_last ? k : k_last;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) copy_to_lds(src[i] + (size_t)(off[i] + ((unsigned)kk << shift[i])), lds + stage * SU + (wave * NC + i) * 64);
+        for (int i = 0; i < NC; ++i)
+            if (i >= i0 && i < i1) copy_to_lds(src[i] + (size_t)(off[i] + ((unsigned)kk << shift[i])), lds + stage * SU + dst[i]);
+    };
+    // waits until no more than n copies are in flight and every read of LDS is done (bits of the immediate: vmcnt 0-3 and 14-15, lgkmcnt
+    // 8-11, expcnt 4-6, all ones, is not waited for), then for everyone else
+    auto meet = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | (N >> 4 << 14));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     };
     PromptAcc<WR, WT> C;
     C.clear();
-    const int n_step = T.k1 - T.k0;
-    int cur = 0, put = NST - 1;
-    // turn: which accumulators the step empties (-1: none)
-    auto step = [&](int s, int turn) {
-        __builtin_amdgcn_sched_barrier(0);
-        // All but the newest FLY copies have landed.  (Bits of the immediate: vmcnt 0-3 and 14-15; expcnt 4-6 and lgkmcnt 8-11, all
-        // ones, are not waited for: a wavefront's reads of the stage before were over when it formed their products.)
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (FLY & 15) | (FLY >> 4 << 14));
-        __builtin_amdgcn_s_barrier();
-        copy(put, T.k0 + s + NST - 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (turn >= 0) C.flush_some(turn);
-        const bf16x8 *w = lds + cur * SU + wr * WR * 64 + lane, *p = lds + cur * SU + BR * 64 + wt * WT * 128 + lane;
-        bf16x8 a[WR], bh[WT], bl[WT];
+    struct Operands { bf16x8 a[WR], hi[WT], lo[WT]; } x, y;
+    const int la = wr * WR * 64 + lane, lb = BR * 64 + wt * WT * 128 + lane;
+    auto fetch_hi = [&](Operands &o, int stage) {
+        const bf16x8 *p = lds + stage * SU;
 #pragma unroll
-        for (int r = 0; r < WR; ++r) a[r] = w[r * 64];
+        for (int r = 0; r < WR; ++r) o.a[r] = p[la + r * 64];
 #pragma unroll
-        for (int t = 0; t < WT; ++t) {
-            bh[t] = p[t * 128];
-            bl[t] = p[t * 128 + 64];
+        for (int t = 0; t < WT; ++t) o.hi[t] = p[lb + t * 128];
+    };
+    auto fetch_lo = [&](Operands &o, int stage) {
+        const bf16x8 *p = lds + stage * SU;
+#pragma unroll
+        for (int t = 0; t < WT; ++t) o.lo[t] = p[lb + t * 128 + 64];
+    };
+    auto mma = [&](const bf16x8 (&w)[WR], const bf16x8 (&b)[WT]) {
+#pragma unroll
+        for (int r = 0; r < WR; ++r)
+#pragma unroll
+            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(w[r], b[t], C.acc[r][t]);
+    };
+    // a product, a read of LDS, in turn; then the copies, behind a few products each; then the rest of the products
+    auto interleave = [](auto reads, auto copies) {
+        constexpr int R = decltype(reads)::value, CP = decltype(copies)::value;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
 #pragma unroll
-        for (int r = 0; r < WR; ++r)
-#pragma unroll
-            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a[r], bh[t], C.acc[r][t]);
-#pragma unroll
-        for (int r = 0; r < WR; ++r)
-#pragma unroll
-            for (int t = 0; t < WT; ++t) C.acc[r][t] = mma16<F16>(a[r], bl[t], C.acc[r][t]);
-        put = cur;
-        cur = cur == NST - 1 ? 0 : cur + 1;
+        for (int i = 0; i < CP; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, WR * WT, 0);
+    };
+    const int n_step = k1 - k0;
+    int cur = 0, prev = NST - 1;
+    // turn: which accumulators the step empties (-1: none)
+    auto step = [&](int s, int turn, Operands &now, Operands &next) {
+        const int nxt = cur == NST - 1 ? 0 : cur + 1;
+        if constexpr (ONE) {
+            meet(std::integral_constant<int, FLY>{});
+            fetch_hi(next, nxt);
+            fetch_lo(next, nxt);
+            copy(cur, k0 + s + NST, 0, NC);
+            if (turn >= 0) C.flush_some(turn);
+            mma(now.a, now.hi);
+            mma(now.a, now.lo);
+        } else {
+            fetch_lo(now, cur);
+            copy(prev, k0 + s + NST - 1, NH, NC);
+            if (turn >= 0) C.flush_some(turn);
+            mma(now.a, now.hi);
+            interleave(std::integral_constant<int, WT>{}, std::integral_constant<int, NC - NH>{});
+            meet(std::integral_constant<int, FLY>{});
+            fetch_hi(next, nxt);
+            copy(cur, k0 + s + NST, 0, NH);
+            mma(now.a, now.lo);
+            interleave(std::integral_constant<int, WR + WT>{}, std::integral_constant<int, NH>{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        prev = cur;
+        cur = nxt;
     };
 #pragma unroll
-    for (int j = 0; j < NST - 1; ++j) {
-        copy(j, T.k0 + j);
+    for (int j = 0; j < NST; ++j) {
+        copy(j, k0 + j, 0, j < NST - 1 ? NC : NH);
         __builtin_amdgcn_sched_barrier(0);
     }
+    meet(std::integral_constant<int, FLY0>{});
+    fetch_hi(x, 0);
+    if constexpr (ONE) fetch_lo(x, 0);
     int s = 0;
     for (; s + kFlush <= n_step; s += kFlush) {
 #pragma unroll
-        for (int j = 0; j < kFlush; ++j) step(s + j, j);
+        for (int j = 0; j < kFlush; j += 2) {
+            step(s + j, j, x, y);
+            step(s + j + 1, j + 1, y, x);
+        }
     }
-    for (; s < n_step; ++s) step(s, -1);
-    __builtin_amdgcn_s_waitcnt(0x0F70);                         // the copies past the end land before the workgroup's LDS is another's
+    for (; s < n_step; ++s) {
+        step(s, -1, x, y);
+        x = y;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);                         // the copies past the end land before the workgroup's LDS is another's
     C.flush();
-    C.template store<F16, EPI>(g, T.rb * BR + wr * WR, T.tb * BT + wt * WT, T.piece, lane);
+    C.template store<F16, EPI>(g, rt0 + wr * WR, tb * BT + wt * WT, piece, lane);
+}
+
+// HALVES: tiles from g.n_full on are workgroups of half the rows.
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, bool ONE, bool HALVES>
+__global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    bf16x8 *lds = (bf16x8 *)lds_raw;                            // [NST][weight tiles, activation tiles]
+    const PromptTile T = prompt_tile(g);
+    if constexpr (HALVES) {
+        if (T.half >= 0) {
+            const int rt0 = (T.rb * WR + T.half * (WR / 2)) * NWR;
+            if (rt0 < g.NT) prompt_gemm_tile<WR / 2, WT, NWR, NWT, NST, F16, EPI, ONE>(g, rt0, T.tb, T.piece, lds);
+            return;
+        }
+    }
+    prompt_gemm_tile<WR, WT, NWR, NWT, NST, F16, EPI, ONE>(g, T.rb * WR * NWR, T.tb, T.piece, lds);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -560,46 +633,102 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-// Workgroups of BR row tiles x BT token tiles; with PG_PART also the pieces along K: up to two workgroups per compute unit,
-// within the room for partial rows.  Returns a hipError_t.
-template <int EPI>
-int plan_gemm(PromptGemm &g, int BR, int BT, int n_wg, int *n_split) {
-    g.n_rb = (g.NT + BR - 1) / BR;
-    g.n_tb = ((g.M + 15) / 16 + BT - 1) / BT;
-    int split = 1;
-    if (EPI == PG_PART) {
-        const int blocks = g.n_rb * g.n_tb;
-        while (split < kPromptMaxSplit && blocks * split * 2 <= 2 * n_wg && g.KT / (split * 2) >= 8 &&
-               (size_t)(split * 2) * g.M * g.N <= g.part_floats)
-            split *= 2;
-        if ((size_t)g.M * g.N > g.part_floats) return (int)hipErrorInvalidValue;
-    }
-    g.k_per = (g.KT + split - 1) / split;
-    g.n_split = (g.KT + g.k_per - 1) / g.k_per;
-    if (n_split) *n_split = g.n_split;
-    return 0;
-}
-
-template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI>
-int launch_gemm_as(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
-    constexpr int BR = WR * NWR, BT = WT * NWT, lds = NST * prompt_stage_units(BR, BT) * 16;
-    if (int rc = plan_gemm<EPI>(g, BR, BT, n_wg, n_split)) return rc;
+template <int WR, int WT, int NWR, int NWT, int NST, bool ONE, bool F16, int EPI>
+int launch_gemm_as(const PromptGemm &g, hipStream_t s) {
+    constexpr bool HALVES = WR == 4;
+    constexpr int lds = NST * prompt_stage_units(WR * NWR, WT * NWT) * 16;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, ONE, HALVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI>), dim3(g.n_rb * g.n_tb * g.n_split), dim3(64 * NWR * NWT), lds, s, g);
+    const int tiles = g.n_rb * g.n_tb * g.n_split, grid = g.n_full + 2 * (tiles - g.n_full);
+    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, ONE, HALVES>), dim3(grid), dim3(64 * NWR * NWT), lds, s, g);
     return (int)hipGetLastError();
 }
 
-// 128 rows by as many tokens as a prompt has, up to 128 (the others are products for nothing)
+// A kind of tile: 4 * wr row tiles by bt token tiles.  About `step` us go by per k-step, `round` more per round of a workgroup per compute
+// unit, `piece` us and 1 / rate per byte for a piece after the first.  pair: two workgroups share a compute unit, so that 1.5 rounds take 1.5 times one's
+// time and not two.  halves: tiles that would fill less than half of a last round are dealt as two of half the rows, whose k-step takes half_step.
+struct PromptTileKind { int wr, bt; double step, half_step, round, piece, rate; bool pair, halves; };
+
+// Lays the product out in such tiles and, with `pieces`, in the number of pieces along K that takes the least time; returns about how many microseconds.
+double lay_out(PromptGemm &g, const PromptTileKind &t, bool pieces, int n_wg) {
+    g.n_rb = (g.NT + 4 * t.wr - 1) / (4 * t.wr);
+    g.n_tb = ((g.M + 15) / 16 + t.bt - 1) / t.bt;
+    PromptGemm best = g;
+    double least = INFINITY;
+    for (int split = 1; split <= (pieces ? kPromptMaxSplit : 1); ++split) {
+        if (split > 1 && (g.KT / split < kFlush || (size_t)split * g.M * g.N > g.part_floats)) break;
+        PromptGemm h = g;
+        h.k_per = (g.KT + split - 1) / split;
+        h.n_split = (g.KT + h.k_per - 1) / h.k_per;
+        const int tiles = h.n_rb * h.n_tb * h.n_split, rest = tiles % n_wg;
+        const bool halves = t.halves && rest && 2 * rest <= n_wg;
+        h.n_full = halves ? tiles - rest : tiles;
+        const double round = t.round + h.k_per * t.step;
+        double us = (double)(h.n_split - 1) * ((double)g.M * g.N * 4 / t.rate + t.piece);
+        if (t.pair) us += round * (tiles <= n_wg ? 1.0 : (double)tiles / n_wg);
+        else us += round * (tiles / n_wg) + (!rest ? 0.0 : halves ? t.round + h.k_per * t.half_step : round);
+        if (us < least) {
+            least = us;
+            best = h;
+        }
+    }
+    g = best;
+    return least;
+}
+
+// The tile whose time is least.  Up to 64 tokens bound by the weights' way from memory, or, where a product has less than the chip's
+// workgroups, by the chain through a workgroup's k-steps: 64 or 128 rows by 32 tokens, 128 by 64.  More: 8 wavefronts, 128, 192 or
+// 256 rows by 96 or 128 tokens, so that the least of the last round and of the last token block is empty.  The times are fitted to the products of the
+// 8B and 13B shapes and of models of 1024 and 2048 inputs at 16 to 1023 tokens, where the rule's choice takes 1.5 % (up to 64 tokens) and 2.6 %
+// longer in the mean than the best of all tiles and pieces.
+//
+// Large products are bound by the matrix cores and, with them, by the power that operands on the move take: a loop of 16x16x32 products on registers alone reaches
+// 1.92 PFLOP/s here with random operands (2.38 with zeros; 32x32x16 ones 1.78, their accumulators move twice as often), with operands from
+// LDS as 4 x 4 tiles need them 1.75.  Larger wavefront tiles take fewer reads of LDS per product (12 for 32 with 4 x 4, 10 for 16 with 2 x 4).  One
+// wavefront per SIMD with 8 x 4 tiles, and 32x32x16 products, were slower.  Measured with weights that no cache holds, us for 6144 x 4096, 4096 x
+// 4096, 4096 x 14336, 28672 x 4096, against 2 x 4 tiles for every product, all operands read at the start of a step, power-of-two pieces:
+//     16 tokens   11.8    8.3   21.8   43.2     13.8    9.9   23.8   45.9
+//     64          15.5   11.9   27.2   47.3     20.5   14.0   29.6   53.3
+//    160          26.4   20.8   48.3   76.9     36.3   29.4   62.7  127
+//    256          32.8   24.0   57    102       39.7   33.0   66.5  127
+//    640          56.6   43.1  138    301       66.5   58.8  207    337
+//   1023          81.6   58    178    377      113     68    205    412    (within a prompt of 8 layers; 1.18 to 1.35 PFLOP/s, hi and lo products both counted)
 template <bool F16, int EPI>
 int launch_gemm_sized(PromptGemm g, int n_wg, int *n_split, hipStream_t s) {
-    if (g.M <= 32) return launch_gemm_as<2, 2, 4, 1, 5, F16, EPI>(g, n_wg, n_split, s);
-    if (g.M <= 64) return launch_gemm_as<2, 2, 4, 2, 4, F16, EPI>(g, n_wg, n_split, s);
-    return launch_gemm_as<2, 4, 4, 2, 3, F16, EPI>(g, n_wg, n_split, s);
+    constexpr bool P = EPI == PG_PART;
+    if (P && (size_t)g.M * g.N > g.part_floats) return (int)hipErrorInvalidValue;
+    auto step8 = [](int n) { return 0.093 + 0.0356 * n; };      // 8 wavefronts of n accumulators
+    auto large = [&](int wr, int wt) { return PromptTileKind{wr, 2 * wt, step8(wr * wt), step8(wr * wt / 2), 2, 0.5, 1.5e6, false, wr == 4}; };
+    const PromptTileKind kinds[9] = {{1, 2, 0.12, 0, 0, 0.1, 2e6, true, false}, {2, 2, 0.19, 0, 0, 0.1, 2e6, false, false}, {2, 4, 0.24, 0, 0, 0.1, 2e6, false, false},
+                                     large(2, 3), large(2, 4), large(3, 3), large(3, 4), large(4, 3), large(4, 4)};
+    const PromptGemm plain = g;
+    double least = INFINITY;
+    int kind = 0;
+    for (int i = g.M <= 64 ? 0 : 3; i < (g.M <= 64 ? 3 : 9); ++i) {
+        PromptGemm h = plain;
+        const double us = lay_out(h, kinds[i], P, n_wg);
+        if (us < least) {
+            least = us;
+            g = h;
+            kind = i;
+        }
+    }
+    if (n_split) *n_split = g.n_split;
+    switch (kind) {
+        case 0: return launch_gemm_as<1, 2, 4, 1, 8, true, F16, EPI>(g, s);
+        case 1: return launch_gemm_as<2, 2, 4, 1, 5, true, F16, EPI>(g, s);
+        case 2: return launch_gemm_as<2, 2, 4, 2, 5, true, F16, EPI>(g, s);
+        case 3: return launch_gemm_as<2, 3, 4, 2, 4, false, F16, EPI>(g, s);
+        case 4: return launch_gemm_as<2, 4, 4, 2, 4, false, F16, EPI>(g, s);
+        case 5: return launch_gemm_as<3, 3, 4, 2, 4, false, F16, EPI>(g, s);
+        case 6: return launch_gemm_as<3, 4, 4, 2, 4, false, F16, EPI>(g, s);
+        case 7: return launch_gemm_as<4, 3, 4, 2, 4, false, F16, EPI>(g, s);
+        default: return launch_gemm_as<4, 4, 4, 2, 4, false, F16, EPI>(g, s);
+    }
 }
 
 }  // namespace

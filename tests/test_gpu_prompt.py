@@ -59,6 +59,24 @@ def test_prompt_lengths_at_tile_edges(ad, shape):
     g.close()
 
 
+# Every tile of the projections (128, 192 or 256 rows by 96 or 128 tokens) with rows and tokens left over in the last ones.  Gate and up:
+# 2 x 3 tiles a wavefront at 70 tokens, 4 x 3 at 180, 4 x 4 at 200, 3 x 4 at 300, 4 x 4 and a last round of halves at 750 (and 1000 rows further on, 2 x 4 at
+# 200, 3 x 3 at 300); Wo and down of the widest model: 2 x 3 at 300, 2 x 4 at 400, 3 x 4 at 600, 4 x 3 at 750, 4 x 4 at 1000; q/k/v of
+# 130 heads: 3 x 3 at 400.
+@pytest.mark.parametrize("shape,lengths", [
+    (ODD.with_(name="ffn-12312", d_model=96, d_ffn=12312, n_layers=2), (70, 180, 200, 300, 750)),
+    (ODD.with_(name="ffn-6008-f16", dtype=synth.F16, d_model=64, d_ffn=6008, n_layers=2), (200, 300)),
+    (ODD.with_(name="wide", d_model=8192, d_ffn=64, n_q_heads=1, n_kv_heads=1, n_layers=2), (300, 400, 600, 750, 1000)),
+    (ODD.with_(name="heads-130", d_model=64, n_q_heads=130, n_kv_heads=1, n_layers=2), (400,))], ids=lambda x: getattr(x, "name", ""))
+def test_every_tile_of_the_projections(ad, shape, lengths):
+    w = synth.make_weights(shape, seed=4, norm_jitter=0.2)
+    g, o = ad.Model(shape, w, max_pos=1024), orc.Oracle(shape, w, max_pos=1024)
+    for n in lengths:
+        print(f"case {shape.name} {n} tokens", flush=True)
+        follow_up(shape, g, o, synth.make_prompt(shape, n, n + 1))
+    g.close()
+
+
 # beyond 1024 tokens: a second pass at position 1024, of more and of fewer tokens than a layer step takes
 @pytest.mark.parametrize("shape,n", [(DH128, 1024), (DH128, 1031), (ODD, 1100)], ids=["one-pass", "pass-and-step", "two-passes"])
 def test_prompts_longer_than_a_pass(ad, shape, n):
