@@ -191,6 +191,19 @@ ad_status ad_verify_sampled(const ad_model *, const void *final_logits, const vo
                             int32_t m, float temperature, const float *u_accept, const float *u_resample, float u_final,
                             int32_t *n_accept, int32_t *next_token, float *ratio, void *stream);
 
+/* ad_exit_head, ad_verify, ad_sample_logits and ad_verify_sampled that return with their results, in the caller's host memory
+ * (any, n_accept and next_token of one element, row_argmax and ratio as there or NULL).  They wait for the evaluation, and with it for
+ * everything before it on the stream, by watching a word that the last kernel writes behind its results, which takes some microseconds less than
+ * waiting until the stream has drained; errors of the device may surface in a later call.  Not under stream capture. */
+ad_status ad_exit_head_wait(const ad_model *, int32_t layer, const void *hidden_row, int32_t *token, float *conf, void *stream);
+ad_status ad_verify_wait(const ad_model *, const void *hidden, const int32_t *draft, int32_t m, int32_t *n_accept,
+                         int32_t *next_token, int32_t *row_argmax, void *stream);
+ad_status ad_sample_logits_wait(const ad_model *, const void *logits, float temperature, float u, int32_t *token, float *prob,
+                                void *stream);
+ad_status ad_verify_sampled_wait(const ad_model *, const void *final_logits, const void *draft_logits, const int32_t *draft,
+                                 int32_t m, float temperature, const float *u_accept, const float *u_resample, float u_final,
+                                 int32_t *n_accept, int32_t *next_token, float *ratio, void *stream);
+
 /* ---- Algorithm 1 --------------------------------------------------------------------------------- */
 typedef struct {
     float   gamma;               /* early-prediction threshold of Eq. 1 (strict >) */

@@ -26,7 +26,7 @@ AD_PROBE_ONE_KERNEL, AD_PROBE_PER_PHASE = 0, 1
 
 EXPORTS = ["ad_workspace_bytes", "ad_model_create", "ad_model_destroy", "ad_kv_bytes", "ad_kv_create", "ad_kv_destroy",
            "ad_kv_len", "ad_kv_set_len", "ad_kv_truncate", "ad_embed", "ad_layer_step", "ad_layer_steps", "ad_set_layer_mode", "ad_exit_head", "ad_verify",
-           "ad_verify_static",
+           "ad_verify_static", "ad_exit_head_wait", "ad_verify_wait", "ad_sample_logits_wait", "ad_verify_sampled_wait",
            "ad_head_logits", "ad_sample_logits", "ad_verify_sampled", "ad_generate", "ad_layer_trace", "ad_profile_start", "ad_profile_stop", "ad_probe_stream",
            "ad_last_error", "ad_version"]
 
@@ -105,6 +105,8 @@ def lib() -> C.CDLL:
         L.ad_head_logits.argtypes = [P, i32, P, i32, P, P]
         L.ad_sample_logits.argtypes = [P, P, C.c_float, C.c_float, P, P, P]
         L.ad_verify_sampled.argtypes = [P, P, P, P, i32, C.c_float, P, P, C.c_float, P, P, P, P]
+        for n in ("exit_head", "verify", "sample_logits", "verify_sampled"):
+            getattr(L, f"ad_{n}_wait").argtypes = getattr(L, "ad_" + n).argtypes
         L.ad_generate.argtypes = [P, P, P, i32, C.POINTER(GenParams), P, P, C.POINTER(Stats), P, C.c_int64, P, P]
         L.ad_profile_start.argtypes = [P, i32, i32, i32]
         L.ad_set_layer_mode.argtypes = [P, i32]
@@ -304,11 +306,11 @@ class Model:
         torch = self.torch
         assert hidden_row.dtype == torch.float32 and hidden_row.is_contiguous() and hidden_row.numel() == self.shape.d_model
         out = self._pinned
-        _check(self.L.ad_exit_head(self.model, layer, C.c_void_p(hidden_row.data_ptr()), C.c_void_p(out.data_ptr()),
-                                   C.c_void_p(out.data_ptr() + 4), _stream_ptr(torch)))
+        fn = self.L.ad_exit_head_wait if sync else self.L.ad_exit_head
+        _check(fn(self.model, layer, C.c_void_p(hidden_row.data_ptr()), C.c_void_p(out.data_ptr()), C.c_void_p(out.data_ptr() + 4),
+                  _stream_ptr(torch)))
         if not sync:
             return None
-        self._synchronize()
         res = out.numpy()
         return int(res[0]), float(res[1:2].view(np.float32)[0])
 
@@ -321,10 +323,11 @@ class Model:
         assert d.size == m - 1
         dptr = d.ctypes.data if m > 1 else None
         out = self._pinned
-        fn = self.L.ad_verify_static if static else self.L.ad_verify
+        fn = self.L.ad_verify_static if static else self.L.ad_verify_wait
         _check(fn(self.model, C.c_void_p(hidden.data_ptr()), dptr, m, C.c_void_p(out.data_ptr() + 32),
                   C.c_void_p(out.data_ptr() + 36), C.c_void_p(out.data_ptr() + 64), _stream_ptr(torch)))
-        self._synchronize()
+        if static:
+            self._synchronize()
         res = out.numpy()
         return int(res[8]), int(res[9]), res[16:16 + m].copy()
 
@@ -340,9 +343,8 @@ class Model:
         torch = self.torch
         assert logits.dtype == torch.float32 and logits.is_contiguous() and logits.numel() == self.shape.vocab
         out = self._pinned
-        _check(self.L.ad_sample_logits(self.model, C.c_void_p(logits.data_ptr()), temperature, u, C.c_void_p(out.data_ptr()),
-                                       C.c_void_p(out.data_ptr() + 4), _stream_ptr(torch)))
-        self._synchronize()
+        _check(self.L.ad_sample_logits_wait(self.model, C.c_void_p(logits.data_ptr()), temperature, u, C.c_void_p(out.data_ptr()),
+                                            C.c_void_p(out.data_ptr() + 4), _stream_ptr(torch)))
         res = out.numpy()
         return int(res[0]), float(res[1:2].view(np.float32)[0])
 
@@ -360,13 +362,12 @@ class Model:
         if m > 1:
             assert draft_logits.dtype == torch.float32 and draft_logits.is_contiguous() and tuple(draft_logits.shape) == (m - 1, V)
         out = self._pinned
-        _check(self.L.ad_verify_sampled(self.model, C.c_void_p(final_logits.data_ptr()),
-                                        C.c_void_p(draft_logits.data_ptr()) if m > 1 else None,
-                                        d.ctypes.data if m > 1 else None, m, temperature,
-                                        ua.ctypes.data if m > 1 else None, ur.ctypes.data if m > 1 else None, u_final,
-                                        C.c_void_p(out.data_ptr() + 32), C.c_void_p(out.data_ptr() + 36),
-                                        C.c_void_p(out.data_ptr() + 64), _stream_ptr(torch)))
-        self._synchronize()
+        _check(self.L.ad_verify_sampled_wait(self.model, C.c_void_p(final_logits.data_ptr()),
+                                             C.c_void_p(draft_logits.data_ptr()) if m > 1 else None,
+                                             d.ctypes.data if m > 1 else None, m, temperature,
+                                             ua.ctypes.data if m > 1 else None, ur.ctypes.data if m > 1 else None, u_final,
+                                             C.c_void_p(out.data_ptr() + 32), C.c_void_p(out.data_ptr() + 36),
+                                             C.c_void_p(out.data_ptr() + 64), _stream_ptr(torch)))
         res = out.numpy()
         return int(res[8]), int(res[9]), res[16:16 + m - 1].view(np.float32).copy()
 

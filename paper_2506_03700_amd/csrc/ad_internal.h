@@ -83,7 +83,7 @@ struct GemmArgs {
     int32_t *n_accept_out, *next_out;   // verify outputs or null
     int32_t draft[8];
     int verify;
-    // optional: host-visible word that the head's second kernel sets to done_seq, at system scope, after its results
+    // optional: host-visible word that the last kernel sets to done_seq, at system scope, after its results
     // are written; a host thread that polls it learns the outcome without waiting for the stream to drain
     int32_t *done_flag;
     int32_t done_seq;
@@ -169,6 +169,8 @@ struct SampleArgs {
     int32_t *tok_out;       // pinned host or dev
     float *prob_out;        // pinned host or dev: probability of the drawn token
     void *scratch;          // dev, kSampleScratchBytes
+    int32_t *done_flag;     // null, or as in GemmArgs
+    int32_t done_seq;
 };
 struct VerifySampledArgs {
     const float *zf;        // dev [m][V]: final-layer logits of the m rows
@@ -180,6 +182,8 @@ struct VerifySampledArgs {
     void *scratch;          // dev, kSampleScratchBytes
     int32_t *n_accept_out, *next_out;   // pinned host or dev
     float *ratio_out;       // null, or pinned host or dev [m - 1]: p*(t) / p_draft(t) of the drafts that were checked, else 0
+    int32_t *done_flag;     // null, or as in GemmArgs
+    int32_t done_seq;
 };
 
 struct LaunchCtx { void *stream; int n_wg; };

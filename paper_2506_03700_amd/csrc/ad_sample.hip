@@ -307,6 +307,7 @@ __global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, con
     if (d.owner) {
         *a.tok_out = d.tok;
         *a.prob_out = d.w / d.total;
+        if (a.done_flag) __hip_atomic_store(a.done_flag, a.done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -334,8 +335,9 @@ struct Decision { int n_acc, rejected; SegStat f, q; };      // of row n_acc: st
 // segment, took 37.9 us a call for 5 and 8 rows of 2048 logits when three kernels took 36.1 (31.7 now).
 enum RowSource { ROWS_LOGITS, ROWS_SEGMENT, ROWS_SEGMENTS };     // the logits, one segment per row, several
 
+// *ratio: of draft `lane` (0 if it was not checked), the same in every wavefront
 template <RowSource SRC>
-__device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const SegStat *seg, int n_seg, bool write_ratio) {
+__device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const SegStat *seg, int n_seg, float *ratio_out) {
     __shared__ SegStat row[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_draft = a.m - 1, n_rows = 2 * a.m - 1;
     // a lane per draft, in every wavefront
@@ -374,7 +376,7 @@ __device__ __forceinline__ Decision decide(const VerifySampledArgs &a, const Seg
     Decision d;
     d.n_acc = mask ? __ffsll(mask) - 1 : n_draft;    // the first rejected draft, n_draft if none is
     d.rejected = d.n_acc < n_draft;
-    if (write_ratio && wave == 0 && a.ratio_out && k < n_draft) a.ratio_out[k] = k <= d.n_acc ? ratio : 0.f;
+    *ratio_out = k <= d.n_acc ? ratio : 0.f;
     d.f = row[d.n_acc];
     d.q = d.rejected ? row[a.m + d.n_acc] : SegStat{0.f, 0.f};
     return d;
@@ -417,7 +419,9 @@ __device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j
 __global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out, Decision *dec) {
     __shared__ SampleLds L;
     const bool first = blockIdx.x == 0;
-    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, first);
+    float ratio;
+    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, &ratio);
+    if (first && a.ratio_out && (int)threadIdx.x < a.m - 1) a.ratio_out[threadIdx.x] = ratio;
     if (first && threadIdx.x == 0) *dec = d;
     if (!d.rejected) return;
     const int j0 = blockIdx.x * seg_ids;
@@ -432,11 +436,13 @@ __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampled
     __shared__ SampleLds L;
     RowSegs segs;
     Decision d;
-    if (SRC == ROWS_SEGMENTS && dec) {
+    float ratio = 0.f;
+    const bool here = !(SRC == ROWS_SEGMENTS && dec);    // the decision and the ratios are this kernel's
+    if (!here) {
         segs.load(res_seg, n_seg);                   // (whatever the decision: not used if no draft was rejected)
         d = *dec;
     } else {
-        d = decide<SRC>(a, seg, n_seg, true);
+        d = decide<SRC>(a, seg, n_seg, &ratio);
     }
     const int r = d.n_acc;
     Draw dr{-1, 0.f, 0.f, false};
@@ -455,9 +461,12 @@ __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampled
         const float mine = segs.rescale(d.f.mx, a.inv_t);
         dr = draw_from(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, segs, mine, a.V, seg_ids, d.rejected ? a.u_resample[r] : a.u_final, L);
     }
+    // the wavefront that has the token reports everything: its store of the done word is ordered behind its own
+    if (here && a.ratio_out && __any(dr.owner) && (int)(threadIdx.x & 63) < a.m - 1) a.ratio_out[threadIdx.x & 63] = ratio;
     if (dr.owner) {
         *a.n_accept_out = r;
         *a.next_out = dr.tok;
+        if (a.done_flag) __hip_atomic_store(a.done_flag, a.done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

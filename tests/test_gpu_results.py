@@ -1,0 +1,48 @@
+"""The calls that return with their results against the ones that only enqueue, through the C ABI: same results, in host memory that is not
+pinned, call after call (also past the number after which the stream is waited for all the same) and on another stream."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2506_03700_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [301, 5000])
+def test_results_are_there_when_the_call_returns(vocab):
+    import torch
+    from paper_2506_03700_amd import binding as ad
+    shape = synth.TINY.with_(name="tiny-untied", tied_head=False, vocab=vocab, dtype=synth.BF16)
+    g = ad.Model(shape, synth.make_weights(shape, seed=1), max_pos=16)
+    L, m = g.L, 4
+    pin = torch.zeros(64, dtype=torch.int32).pin_memory()
+    rng = np.random.default_rng(0)
+    P = lambda a: C.c_void_p(a.ctypes.data)
+    D = lambda t: C.c_void_p(t.data_ptr())
+    at = lambda i: C.c_void_p(pin.data_ptr() + 4 * i)
+    for turn in range(300):
+        stream = torch.cuda.Stream() if turn % 64 == 63 else torch.cuda.current_stream()
+        with torch.cuda.stream(stream):
+            s = C.c_void_p(stream.cuda_stream)
+            h = torch.randn(m, shape.d_model, device="cuda:0")
+            z, zq = (3 * torch.randn(m, vocab, device="cuda:0") for _ in range(2))
+            draft = rng.integers(0, vocab, m - 1, dtype=np.int32)
+            u = rng.random(2 * m, dtype=np.float32) * np.float32(0.999)
+            got = np.full(16, -7, np.int32)
+            calls = [
+                (lambda f, a, st: f(g.model, 2, D(h), a(0), a(1), st), L.ad_exit_head, L.ad_exit_head_wait, 2),
+                (lambda f, a, st: f(g.model, D(h), P(draft), m, a(0), a(1), a(2), st), L.ad_verify, L.ad_verify_wait, 2 + m),
+                (lambda f, a, st: f(g.model, D(z), 0.9, float(u[0]), a(0), a(1), st), L.ad_sample_logits, L.ad_sample_logits_wait, 2),
+                (lambda f, a, st: f(g.model, D(z), D(zq), P(draft), m, 0.9, P(u[1:m]), P(u[m:2 * m - 1]), float(u[0]), a(0), a(1), a(2), st),
+                 L.ad_verify_sampled, L.ad_verify_sampled_wait, 2 + m - 1)]
+            for call, enqueue, wait, n in calls:
+                got[:] = -7
+                assert call(wait, lambda i: C.c_void_p(got.ctypes.data + 4 * i), s) == ad.AD_OK
+                have = got.copy()
+                pin.fill_(-7)
+                assert call(enqueue, at, s) == ad.AD_OK
+                stream.synchronize()
+                assert np.array_equal(have[:n], pin.numpy()[:n]) and np.all(have[n:] == -7), (turn, enqueue, have, pin[:n])
+    g.close()
