@@ -179,6 +179,40 @@ __device__ __forceinline__ void max_merge(float &M, float &S, int &I, float m2, 
     M = nm;
 }
 
+// ---- what the workgroups of a launch leave for the last of them ----
+// Relaxed agent-scope accesses: stores go through to memory and loads do not use a stale copy in another XCD's L2.
+__device__ __forceinline__ void publish(float *p, f32x2 v) {
+    __hip_atomic_store((uint64_t *)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 published(const float *p) {
+    return __builtin_bit_cast(f32x2, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// Called by every thread of each of n workgroups (n the same for all launches on this counter) when its wavefront 0 has published what
+// the workgroup leaves: true in the workgroup that is the last to call, where all of it can be read.  Nobody waits for another workgroup.
+// The counter counts modulo n, so that it is back at 0 when the launch ends (and also after launches that ran at the same time, whose outcomes are
+// then anybody's).  In place of a second kernel it saves 1.5 to 2 us behind 63 workgroups (a draw from 128256 logits, a sampled verification), and
+// nothing behind the 256 of a vocabulary pass, whose arrivals take as long as the launch did.
+__device__ __forceinline__ bool last_to_arrive(unsigned *counter, unsigned n, int *shared) {
+    if (threadIdx.x < 64) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // what this wavefront has published is in memory
+        if (threadIdx.x == 0) *shared = atomicInc(counter, n - 1) == n - 1;
+    }
+    __syncthreads();
+    return *shared;
+}
+
+// A result for the host: written through to (pinned, uncached) memory.  done: the word that the host watches, behind the results that this wavefront
+// has reported (those of others have to be in memory before: reported, and then a barrier).  A release store would write the L2's dirty
+// lines back first, which nothing here needs.
+__device__ __forceinline__ void report(int32_t *p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ __forceinline__ void report(float *p, float v) { report((int32_t *)p, __float_as_int(v)); }
+__device__ __forceinline__ void reported() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void report_done(int32_t *flag, int32_t seq) {
+    if (!flag) return;
+    reported();
+    report(flag, seq);
+}
+
 // D += A (16 rows x 32) * B (32 x 16 columns), 16-bit operands of the model's type, fp32 accumulation
 template <bool F16>
 __device__ __forceinline__ f32x4 mma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {

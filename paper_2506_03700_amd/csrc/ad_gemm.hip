@@ -48,10 +48,11 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
         I = min64(M == m ? I : 0x7fffffff);
         if (lane == 0) {
             idx_sh[t] = I;
-            if (g.tok_out) g.tok_out[t] = I;
-            if (g.conf_out) g.conf_out[t] = 1.0f / S;   // exp(max - logsumexp)
+            if (g.tok_out) report(g.tok_out + t, I);
+            if (g.conf_out) report(g.conf_out + t, 1.0f / S);   // exp(max - logsumexp)
         }
     }
+    if (g.done_flag) reported();
     __syncthreads();
     if (g.verify && threadIdx.x == 0) {
         // the first row whose final-layer token differs from the token drafted after it ends the accepted
@@ -59,13 +60,10 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
         int acc = g.m - 1;
         for (int j = 0; j < g.m - 1; ++j)
             if (idx_sh[j] != g.draft[j]) { acc = j; break; }
-        *g.n_accept_out = acc;
-        *g.next_out = idx_sh[acc];
+        report(g.n_accept_out, acc);
+        report(g.next_out, idx_sh[acc]);
     }
-    if (g.done_flag && threadIdx.x == 0) {
-        // the other wavefronts' results were written before the barrier above: this release covers them too
-        __hip_atomic_store(g.done_flag, g.done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (threadIdx.x == 0) report_done(g.done_flag, g.done_seq);
 }
 
 int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {

@@ -127,6 +127,7 @@ void make_layout(const ad_config &c, Layout &L) {
     s += 2 * align_up((size_t)8 * L.d * 4);                    // x1, rows
     s += align_up((size_t)4096 * 8 * 4 * 4);                   // head partials (up to 4096 workgroups)
     s += align_up((size_t)kBarrierWords * 4);                  // grid-barrier counters of the fused layer step
+    s += align_up((size_t)kArrivalWords * 4);                  // the sampling kernels' counter of workgroups
     s += 2 * align_up((size_t)AD_M_MAX * L.V * 4);             // sampled decoding: draft and final logits of the open rows
     L.scratch_bytes = s;
     L.total = off + s;
@@ -164,6 +165,7 @@ struct ad_model {
     // fused layer step: mode, barrier counters (device), barriers completed so far, abort word (pinned host)
     int32_t layer_mode;
     unsigned *bar_ctr;
+    unsigned *arrivals;       // device: the sampling kernels' counter of workgroups
     mutable unsigned bar_round;
     unsigned *bar_abort;
     long long *layer_trace;   // device buffer for the fused kernel's phase timestamps, or null
@@ -278,6 +280,7 @@ ad_status ad_model_create(const ad_config *cfg, const ad_layer_weights *layers, 
     m->head_part = (float *)take((size_t)4096 * 8 * 4 * 4);
     m->bar_ctr = (unsigned *)take((size_t)kBarrierWords * 4);     // zeroed with the rest of the scratch above
     m->bar_round = 0;
+    m->arrivals = (unsigned *)take((size_t)kArrivalWords * 4);    // likewise
     m->draft_logits = (float *)take((size_t)AD_M_MAX * L.V * 4);
     m->final_logits = (float *)take((size_t)AD_M_MAX * L.V * 4);
     m->pin = (int32_t *)pinned_alloc(4096);
@@ -825,7 +828,8 @@ static int sample_logits(const ad_model *m, const void *logits, float temperatur
     if (!m || !logits || !token || !prob) return fail(AD_EINVAL, "ad_sample_logits: null argument");
     if (!(temperature > 0.f) || !(u >= 0.f && u < 1.f)) return fail(AD_ERANGE, "ad_sample_logits: temperature must be > 0 and u in [0, 1)");
     SampleArgs a;
-    a.z = (const float *)logits; a.V = m->cfg.vocab; a.inv_t = 1.0f / temperature; a.u = u; a.tok_out = token; a.prob_out = prob; a.scratch = m->head_part;
+    memset(&a, 0, sizeof a);
+    a.z = (const float *)logits; a.V = m->cfg.vocab; a.inv_t = 1.0f / temperature; a.u = u; a.tok_out = token; a.prob_out = prob; a.scratch = m->head_part; a.arrivals = m->arrivals;
     a.done_flag = done_flag; a.done_seq = done_seq;
     const int rc = launch_sample_row(a, stream);
     return rc ? hip_fail(rc, "ad_sample_logits") : AD_OK;
@@ -851,7 +855,7 @@ static int verify_sampled(const ad_model *m, const void *final_logits, const voi
             return fail(AD_ERANGE, "ad_verify_sampled: draws must be in [0, 1)");
         a.draft[i] = draft[i]; a.u_accept[i] = u_accept[i]; a.u_resample[i] = u_resample[i];
     }
-    a.u_final = u_final; a.scratch = m->head_part; a.n_accept_out = n_accept; a.next_out = next_token; a.ratio_out = ratio;
+    a.u_final = u_final; a.scratch = m->head_part; a.arrivals = m->arrivals; a.n_accept_out = n_accept; a.next_out = next_token; a.ratio_out = ratio;
     a.done_flag = done_flag; a.done_seq = done_seq;
     const int rc = launch_verify_sampled(a, stream);
     return rc ? hip_fail(rc, "ad_verify_sampled") : AD_OK;

@@ -148,6 +148,7 @@ struct FusedArgs {
 };
 constexpr int kFusedTraceStamps = 12;      // of the launch's last layer: start, before and after each of its 5 barriers, end
 constexpr int kBarrierWords = 32 * 9;      // one 128-byte line for the global counter and for each of 8 groups
+constexpr int kArrivalWords = 32;          // a line for the workgroups of a sampling kernel (see last_to_arrive)
 inline unsigned fused_barriers(int n_layers) { return 6u * (unsigned)n_layers - 1u; }   // barriers per launch
 
 struct EmbedArgs {
@@ -167,8 +168,10 @@ struct SampleArgs {
     int V;
     float inv_t, u;
     int32_t *tok_out;       // pinned host or dev
-    float *prob_out;        // pinned host or dev: probability of the drawn token
+    float *prob_out;        // null, or pinned host or dev: probability of the drawn token
+    int32_t *n_accept_out;  // null, or pinned host or dev: set to 0 (the verification of one row)
     void *scratch;          // dev, kSampleScratchBytes
+    unsigned *arrivals;     // dev, a counter of this model's sampling kernels (see last_to_arrive)
     int32_t *done_flag;     // null, or as in GemmArgs
     int32_t done_seq;
 };
@@ -180,6 +183,7 @@ struct VerifySampledArgs {
     int32_t draft[8];
     float u_accept[8], u_resample[8], u_final;
     void *scratch;          // dev, kSampleScratchBytes
+    unsigned *arrivals;     // as in SampleArgs
     int32_t *n_accept_out, *next_out;   // pinned host or dev
     float *ratio_out;       // null, or pinned host or dev [m - 1]: p*(t) / p_draft(t) of the drafts that were checked, else 0
     int32_t *done_flag;     // null, or as in GemmArgs

@@ -5,13 +5,13 @@
 //
 // Every draw is a uniform number u in [0, 1) handed in by the caller and turned into a token by inversion of
 // the cumulative distribution in token-id order: the first id whose cumulative weight exceeds u * (total
-// weight).  A row is cut into segments of consecutive ids, one workgroup each: a first kernel leaves each segment's maximum
-// and sum of weights, a second one (one workgroup) finds the segment that holds the target from those (in every wavefront at once)
+// weight).  A row is cut into segments of consecutive ids, one workgroup each, which leaves its segment's maximum
+// and sum of weights; the last workgroup to arrive finds the segment that holds the target from those (in every wavefront at once)
 // and walks that segment alone.  What bounds these calls is not the row (0.5 MB) but the chain of dependent loads, reductions and kernel
 // boundaries: with one workgroup that passed over the whole row three times a draw from 128256 logits took 97 us on the
 // GPU, with segments and every reduction and scan through LDS 12.5, now that they move between registers and the wavefronts repeat
 // what is small instead of waiting for one of them 6.4 (a call 31.8 -> 26.2; verification of 6 rows 21.3 -> 15.1, a call 46.9 ->
-// 37.4); the sums are added up in a fixed order (no float atomics), so everything is deterministic.
+// 37.4); the last workgroup in place of a kernel behind it: a call 16.6 -> 14.8 us, of verification 27.5 -> 25.8; the sums are added up in a fixed order (no float atomics), so everything is deterministic.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,6 +31,7 @@ struct SampleLds {
     float wave_val[2][kSampleWaves];
     int wave_id[2][kSampleWaves];
     int last_pos;
+    int last_wg;
 };
 
 // (largest value, sum of the weights relative to it) of a segment
@@ -69,13 +70,22 @@ constexpr int kLaneSegs = kSampleThreads / 64;           // most segments per la
 struct RowSegs {
     SegStat v[kLaneSegs];
     int per, lane;
+    // PUBLISHED: by other workgroups of this launch
+    template <bool PUBLISHED = false>
     __device__ __forceinline__ void load(const SegStat *seg, int n_seg) {
         lane = threadIdx.x & 63;
         per = (n_seg + 63) >> 6;
 #pragma unroll
         for (int i = 0; i < kLaneSegs; ++i) {
             v[i] = SegStat{-INFINITY, 0.f};
-            if (i < per && lane * per + i < n_seg) v[i] = seg[lane * per + i];
+            if (i < per && lane * per + i < n_seg) {
+                if constexpr (PUBLISHED) {
+                    const f32x2 p = published((const float *)(seg + lane * per + i));
+                    v[i] = SegStat{p[0], p[1]};
+                } else {
+                    v[i] = seg[lane * per + i];
+                }
+            }
         }
     }
     __device__ __forceinline__ void one(SegStat s) {     // a row of one segment
@@ -291,23 +301,28 @@ __device__ __forceinline__ SegStat row_from_segments(RowSegs &segs, float inv_t)
     return SegStat{m, sum64(segs.rescale(m, inv_t))};
 }
 
-// seg: the segments' statistics, or null for a row of one segment, whose statistics are formed here (one kernel less)
-__global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, const SegStat *seg, int n_seg, int seg_ids) {
+// A workgroup per segment; the last one to arrive draws.
+__global__ void __launch_bounds__(kSampleThreads) k_sample_row(SampleArgs a, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
+    const int j0 = blockIdx.x * seg_ids;
+    const SegStat st = segment_stat(a.z, j0, min(a.V, j0 + seg_ids), a.inv_t, L);
     RowSegs segs;
-    if (seg) {
-        segs.load(seg, n_seg);
-    } else {
-        const SegStat st = segment_stat(a.z, 0, a.V, a.inv_t, L);
+    if (n_seg == 1) {
         segs.one(st);
         __syncthreads();
+    } else {
+        SegStat *seg = (SegStat *)a.scratch;
+        if (threadIdx.x == 0) publish((float *)(seg + blockIdx.x), (f32x2){st.mx, st.sum});
+        if (!last_to_arrive(a.arrivals, n_seg, &L.last_wg)) return;
+        segs.load<true>(seg, n_seg);
     }
     const float mx = segs.max(), mine = segs.rescale(mx, a.inv_t);
     const Draw d = draw_from(SoftmaxWeight{a.z, mx, a.inv_t}, segs, mine, a.V, seg_ids, a.u, L);
     if (d.owner) {
-        *a.tok_out = d.tok;
-        *a.prob_out = d.w / d.total;
-        if (a.done_flag) __hip_atomic_store(a.done_flag, a.done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        report(a.tok_out, d.tok);
+        if (a.prob_out) report(a.prob_out, d.w / d.total);
+        if (a.n_accept_out) report(a.n_accept_out, 0);
+        report_done(a.done_flag, a.done_seq);
     }
 }
 
@@ -414,45 +429,33 @@ __device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j
     return SegStat{w.c, block_sum(s, L, 1)};
 }
 
-// The decision, and the residual's segments if a draft was rejected.  The first workgroup leaves the decision (and the ratios) for the
-// last kernel, which then needs neither the rows' statistics nor the drafts.
-__global__ void __launch_bounds__(kSampleThreads) k_residual_segments(VerifySampledArgs a, const SegStat *seg, int n_seg, int seg_ids, SegStat *out, Decision *dec) {
-    __shared__ SampleLds L;
-    const bool first = blockIdx.x == 0;
-    float ratio;
-    const Decision d = decide<ROWS_SEGMENTS>(a, seg, n_seg, &ratio);
-    if (first && a.ratio_out && (int)threadIdx.x < a.m - 1) a.ratio_out[threadIdx.x] = ratio;
-    if (first && threadIdx.x == 0) *dec = d;
-    if (!d.rejected) return;
-    const int j0 = blockIdx.x * seg_ids;
-    const SegStat st = residual_stat(residual_of(a, d), j0, min(a.V, j0 + seg_ids), L);
-    if (threadIdx.x == 0) out[blockIdx.x] = st;
-}
-
-// seg: null for ROWS_LOGITS; res_seg, dec: of the kernel before (several segments and more than one row), else null and the decision is
-// taken here (a residual of one segment is formed here)
+// Everything from the rows' statistics on.  ROWS_SEGMENTS: every workgroup takes the decision; if a draft was rejected, it reduces its segment of
+// the residual, and the last one to arrive draws, else the first one does.  Otherwise one workgroup does it all (seg: null for ROWS_LOGITS).
 template <RowSource SRC>
-__global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, const SegStat *res_seg, const Decision *dec, int n_seg, int seg_ids) {
+__global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, SegStat *res_seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
     RowSegs segs;
-    Decision d;
-    float ratio = 0.f;
-    const bool here = !(SRC == ROWS_SEGMENTS && dec);    // the decision and the ratios are this kernel's
-    if (!here) {
-        segs.load(res_seg, n_seg);                   // (whatever the decision: not used if no draft was rejected)
-        d = *dec;
-    } else {
-        d = decide<SRC>(a, seg, n_seg, &ratio);
-    }
+    float ratio;
+    const Decision d = decide<SRC>(a, seg, n_seg, &ratio);
     const int r = d.n_acc;
     Draw dr{-1, 0.f, 0.f, false};
     if (d.rejected) {
         ResidualWeight w = residual_of(a, d);
-        if (SRC != ROWS_SEGMENTS) segs.one(residual_stat(w, 0, a.V, L));
-        __syncthreads();
+        if (SRC == ROWS_SEGMENTS) {
+            const int j0 = blockIdx.x * seg_ids;
+            const SegStat st = residual_stat(w, j0, min(a.V, j0 + seg_ids), L);
+            if (threadIdx.x == 0) publish((float *)(res_seg + blockIdx.x), (f32x2){st.mx, st.sum});
+            if (!last_to_arrive(a.arrivals, n_seg, &L.last_wg)) return;
+            segs.load<true>(res_seg, n_seg);
+        } else {
+            segs.one(residual_stat(w, 0, a.V, L));
+            __syncthreads();
+        }
         w.c = segs.max();
         const float mine = segs.rescale(w.c, 1.0f);
         if (w.c != -INFINITY) dr = draw_from(w, segs, mine, a.V, seg_ids, a.u_resample[r], L);
+    } else if (SRC == ROWS_SEGMENTS && blockIdx.x) {
+        return;
     }
     if (dr.tok < 0) {  // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
         if (SRC == ROWS_SEGMENTS) segs.load(seg + (size_t)r * n_seg, n_seg);
@@ -462,11 +465,11 @@ __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampled
         dr = draw_from(SoftmaxWeight{a.zf + (size_t)r * a.V, d.f.mx, a.inv_t}, segs, mine, a.V, seg_ids, d.rejected ? a.u_resample[r] : a.u_final, L);
     }
     // the wavefront that has the token reports everything: its store of the done word is ordered behind its own
-    if (here && a.ratio_out && __any(dr.owner) && (int)(threadIdx.x & 63) < a.m - 1) a.ratio_out[threadIdx.x & 63] = ratio;
+    if (a.ratio_out && __any(dr.owner) && (int)(threadIdx.x & 63) < a.m - 1) report(a.ratio_out + (threadIdx.x & 63), ratio);
     if (dr.owner) {
-        *a.n_accept_out = r;
-        *a.next_out = dr.tok;
-        if (a.done_flag) __hip_atomic_store(a.done_flag, a.done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        report(a.n_accept_out, r);
+        report(a.next_out, dr.tok);
+        report_done(a.done_flag, a.done_seq);
     }
 }
 
@@ -479,48 +482,43 @@ void segments(int V, int *n_seg, int *seg_ids) {
 
 }  // namespace
 
-static_assert(sizeof(SegStat) * 16 * kSampleThreads + sizeof(Decision) <= kSampleScratchBytes, "the segments of 15 rows and of a residual, the decision");
+static_assert(sizeof(SegStat) * 16 * kSampleThreads <= kSampleScratchBytes, "the segments of 15 rows and of a residual");
 
 int launch_sample_row(const SampleArgs &a, void *stream) {
     if (a.V < 1 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    SegStat *seg = n_seg > 1 ? (SegStat *)a.scratch : nullptr;
-    if (seg) hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 1), dim3(kSampleThreads), 0, (hipStream_t)stream,
-                       SegArgs{a.z, nullptr, 1, a.V, n_seg, seg_ids, a.inv_t, seg});
-    const int rc = (int)hipGetLastError();
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_sample_row, dim3(1), dim3(kSampleThreads), 0, (hipStream_t)stream, a, seg, n_seg, seg_ids);
+    hipLaunchKernelGGL(k_sample_row, dim3(n_seg), dim3(kSampleThreads), 0, (hipStream_t)stream, a, n_seg, seg_ids);
     return (int)hipGetLastError();
 }
 
 int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     if (a.V < 1 || a.m < 1 || a.m > 8 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
+    if (a.m == 1) {                                  // no drafts: a draw from the row
+        SampleArgs s;
+        s.z = a.zf; s.V = a.V; s.inv_t = a.inv_t; s.u = a.u_final; s.tok_out = a.next_out; s.prob_out = nullptr; s.n_accept_out = a.n_accept_out;
+        s.scratch = a.scratch; s.arrivals = a.arrivals; s.done_flag = a.done_flag; s.done_seq = a.done_seq;
+        return launch_sample_row(s, stream);
+    }
     for (int k = 0; k + 1 < a.m; ++k)
         if (a.draft[k] < 0 || a.draft[k] >= a.V) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    SegStat *seg = nullptr, *res_seg = nullptr;
-    Decision *dec = nullptr;
+    SegStat *seg = nullptr;
     const dim3 wg(kSampleThreads);
-    int rc;
     // rows of one segment: up to as many as a workgroup has wavefronts are cheaper to reduce in the last kernel than in one of
     // their own (2048 logits, 3 rows: 28.5 against 29.3 us a call, 4 rows 31.2 / 31.9; more take a kernel of their own), and the
     // residual always is
     if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
         hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
-        if ((rc = (int)hipGetLastError())) return rc;
+        const int rc = (int)hipGetLastError();
+        if (rc) return rc;
     }
-    if (n_seg > 1 && a.m > 1) {
-        res_seg = seg + (size_t)(2 * a.m - 1) * n_seg;
-        dec = (Decision *)(seg + (size_t)16 * kSampleThreads);
-        hipLaunchKernelGGL(k_residual_segments, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, n_seg, seg_ids, res_seg, dec);
-        if ((rc = (int)hipGetLastError())) return rc;
-    }
-    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
-    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
-    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, res_seg, dec, n_seg, seg_ids);
+    SegStat *res_seg = n_seg > 1 ? seg + (size_t)(2 * a.m - 1) * n_seg : nullptr;
+    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
+    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, nullptr, n_seg, seg_ids);
+    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, nullptr, n_seg, seg_ids);
     return (int)hipGetLastError();
 }
 

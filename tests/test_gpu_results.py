@@ -46,3 +46,39 @@ def test_results_are_there_when_the_call_returns(vocab):
                 stream.synchronize()
                 assert np.array_equal(have[:n], pin.numpy()[:n]) and np.all(have[n:] == -7), (turn, enqueue, have, pin[:n])
     g.close()
+
+
+@pytest.mark.parametrize("vocab", [300, 2049, 32016])
+def test_sampling_in_a_graph(vocab):
+    """Captured draws and sampled verifications, replayed over other logits with eager calls in between: the results of the eager calls."""
+    import torch
+    from paper_2506_03700_amd import binding as ad
+    shape = synth.TINY.with_(name="small", tied_head=False, n_layers=1, exit_layers=(), d_model=16, n_q_heads=1, n_kv_heads=1, d_ffn=8,
+                             dtype=synth.BF16, vocab=vocab)
+    g = ad.Model(shape, synth.make_weights(shape, seed=0), max_pos=8)
+    m = 3
+    z, zq = torch.zeros(m, vocab, device="cuda:0"), torch.zeros(m - 1, vocab, device="cuda:0")
+    out = torch.zeros(16, dtype=torch.int32, device="cuda:0")
+    draft, ua, ur = np.array([1, 2], np.int32), np.array([0.5, 0.5], np.float32), np.array([0.3, 0.6], np.float32)
+    at = lambda i: C.c_void_p(out.data_ptr() + 4 * i)
+
+    def enqueue():
+        s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert g.L.ad_sample_logits(g.model, C.c_void_p(z.data_ptr()), 0.9, 0.4, at(0), at(1), s) == ad.AD_OK
+        assert g.L.ad_verify_sampled(g.model, C.c_void_p(z.data_ptr()), C.c_void_p(zq.data_ptr()), C.c_void_p(draft.ctypes.data), m, 0.9,
+                                     C.c_void_p(ua.ctypes.data), C.c_void_p(ur.ctypes.data), 0.7, at(2), at(3), at(4), s) == ad.AD_OK
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        enqueue()
+    for turn in range(4):
+        z.normal_(0, 2)
+        zq.copy_(z[:m - 1] if turn % 2 else torch.randn_like(zq))
+        out.zero_()
+        graph.replay()
+        have = out.cpu().numpy()
+        out.zero_()
+        enqueue()
+        assert np.array_equal(have, out.cpu().numpy()), turn
+        tok, _ = g.ad_sample_logits(z[0], 0.9, 0.4)
+        assert tok == have[0]
+    g.close()
