@@ -490,23 +490,47 @@ __global__ void __launch_bounds__(256) k_prompt_qkv(PromptQkv a) {
 // The products are those of the decode kernel (ad_attention_device.h): S^T = K q^T with the rows of the two score tiles
 // assigned to keys so that a lane ends up with 8 consecutive keys of its query row, which is the B operand layout of
 // O^T = V^T P^T; queries and probabilities are split hi/lo.  A wavefront holds 16 query rows; the workgroup's four
-// wavefronts share the K and V tiles of 32 positions, staged in LDS one block ahead, and run the softmax online.  Bound by
-// the chain through a block (scores, softmax, second product) more than by its arithmetic: 16 rows a wavefront and twice
-// the workgroups beat 32, 8B shape, 1024 tokens 45.1 against 55.7 us, 128 tokens 8.9 / 12.0, 1024 after 7168 313 / 354.
+// wavefronts share the K and V tiles of 64 positions, copied into LDS one block ahead without a way through registers, and run the softmax
+// online.  Bound by the chain through a block (scores, softmax, second product) more than by its arithmetic: 16 rows a wavefront and twice
+// the workgroups beat 32 (1024 tokens of the 8B shape 45.1 against 55.7 us), and blocks of 64 positions, whose two halves go through the chain side by
+// side, beat 32: 8B shape, 299 / 511 / 1023 tokens 15.3 / 23.2 / 48.2 -> 14.3 / 20.1 / 40.6 us, 13B 16.5 (299) / 47.3 (1023) -> 14.4 / 41.6.
 constexpr int kPromptAttnRows = 64;
 
 template <int DH, bool F16>
 __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
     constexpr int KS = DH / 32, DT = DH / 16;
-    constexpr int KU = 2 * KS * 64, VU = DT * 64, NL = (KU + VU) / 256;
-    __shared__ bf16x8 lds[2][KU + VU];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, gq = lane >> 4;
+    constexpr int KU = 2 * KS * 64, VU = DT * 64, HU = KU + VU;  // 16-byte units of 32 positions: K tiles, V tiles, both
+    constexpr int NC = 2 * HU / 64 / 4;                          // copies of 1 KiB per wavefront and block
+    __shared__ bf16x8 lds[2][2 * HU];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, gq = lane >> 4;
     const int kvh = blockIdx.x % a.Hkv, n_blk = (a.M * a.G + kPromptAttnRows - 1) / kPromptAttnRows;
     const int blk = n_blk - 1 - blockIdx.x / a.Hkv;              // the blocks with the most keys first
     const int R = a.M * a.G, r_blk = blk * kPromptAttnRows;
     const int r_last = (r_blk + kPromptAttnRows < R ? r_blk + kPromptAttnRows : R) - 1;
     const int n_key = a.pos0 + r_last / a.G + 1;                 // keys the block's last row sees
-    const int n_kb = (n_key + 31) / 32;
+    const int n_kb = (n_key + 63) / 64;
+
+    const uint16_t *Kg = (const uint16_t *)a.Kc + (size_t)kvh * a.stride * DH;
+    const uint16_t *Vg = (const uint16_t *)a.Vc + (size_t)kvh * DH * a.stride;
+    // A block of 64 positions in LDS: of each half its K tiles [aa][j][lane], then its V tiles [dt][lane].  A block lies inside the cache row
+    // (stride and pos0 are multiples of 64); positions at or past the row's end of keys are masked.
+    unsigned src[NC];                                            // byte offset of this lane's 16 bytes in the first block
+    bool is_k[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int t = wave * NC + i, h = t / (HU / 64), u = t % (HU / 64);      // half, tile of it
+        is_k[i] = u < 2 * KS;
+        if (is_k[i]) src[i] = ((unsigned)(h * 32 + 8 * (n >> 2) + 4 * (u / KS) + (n & 3)) * DH + (u % KS) * 32 + gq * 8) * 2u;
+        else src[i] = ((unsigned)((u - 2 * KS) * 16 + n) * (unsigned)a.stride + h * 32 + gq * 8) * 2u;
+    }
+    auto copy = [&](int kb, int buf) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const char *base = is_k[i] ? (const char *)Kg + (size_t)kb * 64 * DH * 2 : (const char *)Vg + (size_t)kb * 128;
+            copy_to_lds(base + src[i], &lds[buf][(wave * NC + i) * 64]);
+        }
+    };
+    copy(0, 0);
 
     const int row0 = r_blk + wave * 16, row = row0 + n;          // this wavefront's first row, this lane's row
     const bf16x8 *Q = (const bf16x8 *)a.Q + ((size_t)kvh * (a.q_rows / 16) + row0 / 16) * KS * 128;
@@ -520,58 +544,39 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
     const int w_key = row0 < R ? a.pos0 + w_last / a.G + 1 : 0;  // keys this wavefront's last row sees
     const int w_full = row0 < R ? a.pos0 + row0 / a.G + 1 : 0;   // keys all its rows see
 
-    const uint16_t *Kg = (const uint16_t *)a.Kc + (size_t)kvh * a.stride * DH;
-    const uint16_t *Vg = (const uint16_t *)a.Vc + (size_t)kvh * DH * a.stride;
-    bf16x8 st[NL];
-    // unit u of a block: K tiles [aa][j][lane], then V tiles [dt][lane].  A block lies inside the cache row (stride is a
-    // multiple of 64); positions at or past the row's end of keys are masked.
-    auto load = [&](int kb) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int u = tid + i * 256, l = u & 63, ln = l & 15, lg = l >> 4;
-            if (i * 256 < KU) {
-                const int aa = u / (KS * 64), j = (u >> 6) % KS;
-                const int key = kb * 32 + 8 * (ln >> 2) + 4 * aa + (ln & 3);
-                st[i] = *(const bf16x8 *)(Kg + (size_t)key * DH + j * 32 + lg * 8);
-            } else {
-                const int dt = (u - KU) >> 6;
-                st[i] = *(const bf16x8 *)(Vg + (size_t)(dt * 16 + ln) * a.stride + kb * 32 + lg * 8);
-            }
-        }
-    };
-    auto store = [&](bf16x8 *s) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) s[tid + i * 256] = st[i];
-    };
-
     constexpr float kPScale = F16 ? 1024.0f : 1.0f;              // keeps small probabilities out of fp16's subnormals
     f32x4 o[DT];
     float mx = -INFINITY, sum = 0.f;
 #pragma unroll
     for (int d = 0; d < DT; ++d) o[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    load(0);
-    store(lds[0]);
-    if (n_kb > 1) load(1);
-    __syncthreads();
     for (int kb = 0; kb < n_kb; ++kb) {
+        // this block's copies have landed, everyone's, and nobody reads the other buffer any more
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (kb + 1 < n_kb) copy(kb + 1, (kb + 1) & 1);
         const bf16x8 *cur = lds[kb & 1];
-        if (kb * 32 < w_key) {
-            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        if (kb * 64 < w_key) {
+            f32x4 s[2][2];
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                const bf16x8 k0 = cur[j * 64 + lane], k1 = cur[(KS + j) * 64 + lane];
+            for (int h = 0; h < 2; ++h) s[h][0] = s[h][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    s0 = mma16<F16>(k0, q[j][p], s0);
-                    s1 = mma16<F16>(k1, q[j][p], s1);
-                }
-            }
-            const bool masked = kb * 32 + 32 > w_full;           // some row of this wavefront does not see the whole block
-            float sc[8], bm = -INFINITY;
+            for (int j = 0; j < KS; ++j)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                sc[c] = c < 4 ? s0[c & 3] : s1[c & 3];
-                if (masked && kb * 32 + gq * 8 + c > see) sc[c] = -INFINITY;
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int aa = 0; aa < 2; ++aa) s[h][aa] = mma16<F16>(cur[h * HU + (aa * KS + j) * 64 + lane], q[j][p], s[h][aa]);
+            const bool masked = kb * 64 + 64 > w_full;           // some row of this wavefront does not see the whole block
+            float sc[16], bm = -INFINITY;
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                sc[c] = s[c >> 3][(c >> 2) & 1][c & 3];
+                if (masked && kb * 64 + (c >> 3) * 32 + gq * 8 + (c & 7) > see) sc[c] = -INFINITY;
                 bm = fmaxf(bm, sc[c]);
             }
             bm = max_rows(bm);
@@ -579,34 +584,31 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
             const float alpha = __expf(mx - ref);
             mx = nm;
             float add = 0.f;
-            u16x8 h8, l8;
+            u16x8 h8[2], l8[2];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
+            for (int c = 0; c < 16; ++c) {
                 const float p = __expf(sc[c] - ref);
                 add += p;
                 uint16_t hi, lo;
                 split16<F16>(p * kPScale, hi, lo);
-                h8[c] = hi;
-                l8[c] = lo;
+                h8[c >> 3][c & 7] = hi;
+                l8[c >> 3][c & 7] = lo;
             }
-            const bf16x8 ph = __builtin_bit_cast(bf16x8, h8), pl = __builtin_bit_cast(bf16x8, l8);
             sum = sum * alpha + add;
             if (!__all(alpha == 1.0f)) {
 #pragma unroll
                 for (int d = 0; d < DT; ++d) o[d] *= alpha;
             }
 #pragma unroll
-            for (int d = 0; d < DT; ++d) {
-                const bf16x8 v = cur[KU + d * 64 + lane];
-                o[d] = mma16<F16>(v, ph, o[d]);
-                o[d] = mma16<F16>(v, pl, o[d]);
+            for (int h = 0; h < 2; ++h) {
+                if (h && kb * 64 + 32 >= w_key) break;           // (none of its rows sees a key there: no weights of 0 for entries that may be infinite)
+                const bf16x8 ph = __builtin_bit_cast(bf16x8, h8[h]), pl = __builtin_bit_cast(bf16x8, l8[h]);
+#pragma unroll
+                for (int d = 0; d < DT; ++d) o[d] = mma16<F16>(cur[h * HU + KU + d * 64 + lane], ph, o[d]);
+#pragma unroll
+                for (int d = 0; d < DT; ++d) o[d] = mma16<F16>(cur[h * HU + KU + d * 64 + lane], pl, o[d]);
             }
         }
-        if (kb + 1 < n_kb) {
-            store(lds[(kb + 1) & 1]);
-            if (kb + 2 < n_kb) load(kb + 2);
-        }
-        __syncthreads();
     }
     // lane (n, gq): query row n of the tile, dims d*16 + gq*4 .. +3
     sum = sum_rows(sum);
