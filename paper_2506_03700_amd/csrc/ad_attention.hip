@@ -22,6 +22,7 @@
 
 #include "ad_device.h"
 #include "ad_internal.h"
+#include "ad_launch.h"
 
 namespace ad {
 
@@ -491,13 +492,15 @@ __global__ void __launch_bounds__(kValuThreads, 2) k_attn_valu(AttnArgs a) {
 // wavefront per row (and up to 32 splits in flight, the weights handed around by shuffles) the layer step of the 8B shape took
 // 92.4 us against 91.2 now (1 row, context 4096), 113.5 / 112.0 (8 rows, 9203), that of the 13B shape 129.8 / 128.3 (2 rows, 777).
 template <int DH, bool F16>
-__global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
+__global__ void __launch_bounds__(256) k_attn_combine(const float *partials, void *Bo, uint64_t s_r, uint64_t g_kt, uint64_t mul_r_g) {
+    AttnArgs a;
+    a.Bo = Bo; a.R = (int)(s_r >> 32); a.G = (int)g_kt; a.Bo_KT = (int)(g_kt >> 32); a.mul_R = (unsigned)mul_r_g; a.mul_G = (unsigned)(mul_r_g >> 32);
     constexpr int PR = DH + 2, TG = DH / 2, NG = 256 / TG, KB = 8;
     __shared__ float st[NG][2];
     __shared__ f32x2 part[NG][TG];
-    const int tid = threadIdx.x, grp = TG == 64 ? __builtin_amdgcn_readfirstlane(tid / TG) : tid / TG, e = 2 * (tid % TG), S = a.S;
+    const int tid = threadIdx.x, grp = TG == 64 ? __builtin_amdgcn_readfirstlane(tid / TG) : tid / TG, e = 2 * (tid % TG), S = (int)s_r;
     const int row = blockIdx.x, g = div_small(row, a.mul_R), r = row - g * a.R, t = div_small(r, a.mul_G), hq = g * a.G + (r - t * a.G);
-    const float *base = a.part + ((size_t)g * S * a.R + r) * PR;
+    const float *base = partials + ((size_t)g * S * a.R + r) * PR;
     float M = -INFINITY, den = 0.f;
     f32x2 o = {0.f, 0.f};
     for (int s0 = grp; s0 < S; s0 += NG * KB) {
@@ -562,8 +565,7 @@ static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
     const int spare = c.n_wg / (a.Hkv * a.S), most = (a.R + 1) / 2;
     const int nz = spare < 1 ? 1 : spare < most ? spare : most;
     b.rows_wg = (a.R + nz - 1) / nz;
-    hipLaunchKernelGGL((k_attn_valu<DH>), dim3(a.Hkv * a.S, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
-    return (int)hipGetLastError();
+    return launch<k_attn_valu<DH>>(dim3(a.Hkv * a.S, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
 }
 
 template <int DH, bool F16, int RT, int NRH>
@@ -575,8 +577,7 @@ static int launch_dec_as(const AttnArgs &a, const LaunchCtx &c) {
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_attn_dec<DH, F16, RT, NRH>), dim3(a.Hkv * a.S), dim3(256 * NRH), lds, (hipStream_t)c.stream, a);
-    return (int)hipGetLastError();
+    return launch<k_attn_dec<DH, F16, RT, NRH>>(dim3(a.Hkv * a.S), dim3(256 * NRH), lds, (hipStream_t)c.stream, a);
 }
 
 // More than 16 query rows: two wavefronts per block of keys, a row tile each, while an item is one block per wavefront (the chain
@@ -617,6 +618,11 @@ bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg) {
     return kv_elem != kElemF32 && S > 1 && (long)n_kv_heads * (S + 1) <= n_wg;
 }
 
+template <int DH, bool F16>
+static int launch_combine(const AttnArgs &a, dim3 rows, hipStream_t s) {
+    return launch<k_attn_combine<DH, F16>>(rows, dim3(256), 0, s, a.part, a.Bo, two(a.S, a.R), two(a.G, a.Bo_KT), two((int)a.mul_R, (int)a.mul_G));
+}
+
 int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
     int rc;
     if (a.kv_elem == kElemBF16) {
@@ -635,14 +641,8 @@ int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
     if (rc || a.S == 1) return rc;
     const dim3 rows(a.Hq * a.m);
     hipStream_t st = (hipStream_t)c.stream;
-    if (a.kv_elem == kElemF16) {
-        if (a.dh == 128) hipLaunchKernelGGL((k_attn_combine<128, true>), rows, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((k_attn_combine<64, true>), rows, dim3(256), 0, st, a);
-    } else {
-        if (a.dh == 128) hipLaunchKernelGGL((k_attn_combine<128, false>), rows, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((k_attn_combine<64, false>), rows, dim3(256), 0, st, a);
-    }
-    return (int)hipGetLastError();
+    if (a.kv_elem == kElemF16) return a.dh == 128 ? launch_combine<128, true>(a, rows, st) : launch_combine<64, true>(a, rows, st);
+    return a.dh == 128 ? launch_combine<128, false>(a, rows, st) : launch_combine<64, false>(a, rows, st);
 }
 
 }  // namespace ad

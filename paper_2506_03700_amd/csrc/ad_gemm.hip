@@ -7,6 +7,7 @@
 
 #include "ad_device.h"
 #include "ad_internal.h"
+#include "ad_launch.h"
 
 namespace ad {
 
@@ -78,8 +79,7 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     if (rc) return rc;
     if (h.head_stats) {
         h.n_parts = few ? proj_head_parts(g.NT, c.n_wg) : grid;
-        hipLaunchKernelGGL(k_head_combine, dim3(1), dim3(512), 0, s, h);
-        rc = (int)hipGetLastError();
+        rc = launch<k_head_combine>(dim3(1), dim3(512), 0, s, h);
     }
     return rc;
 }

@@ -90,6 +90,8 @@ struct GemmArgs {
 };
 
 static_assert(offsetof(GemmArgs, mode) == 64, "GemmArgs: the first line holds the fields needed first");
+// two values in one kernel parameter (a launch costs the host 10 ns per parameter)
+inline uint64_t two(int lo, int hi) { return (uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
 // the launchers' partition of a GEMM's NT row tiles over n workgroups
 inline void set_tile_partition(GemmArgs &g, int n) { g.tq = g.NT / n; g.tr = g.NT % n; }
 

@@ -6,6 +6,7 @@
 
 #include "ad_device.h"
 #include "ad_internal.h"
+#include "ad_launch.h"
 
 namespace ad {
 
@@ -145,8 +146,7 @@ int launch_zero(void *dst, size_t bytes, void *stream) {
 }
 
 int launch_embed(const EmbedArgs &a, void *stream) {
-    hipLaunchKernelGGL(k_embed, dim3(32), dim3(256), 0, S(stream), a);
-    return (int)hipGetLastError();
+    return launch<k_embed>(dim3(32), dim3(256), 0, S(stream), a);
 }
 
 int launch_rope_table(const RopeArgs &a, void *stream) {

@@ -21,6 +21,7 @@
 
 #include "ad_device.h"
 #include "ad_internal.h"
+#include "ad_launch.h"
 #include "ad_proj_device.h"
 
 namespace ad {
@@ -39,8 +40,10 @@ constexpr size_t proj_lds_bytes(int h, bool from_x) {
 // NPL: planes of a weight tile (fp32 models three).  H: halves of a row tile per workgroup.  U: k-steps per batch.  FROM_X: the activations are fp32 rows
 // (times a norm weight, with 1 / rms applied to the result), else a packed block, with or without sums of squares for 1 / rms.
 template <int NPL, int H, int U, bool F16, bool FROM_X>
-__global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
-    warm_kernel_args<sizeof(GemmArgs)>();
+__global__ void __launch_bounds__(kProjThreads, 2) k_proj(const void *W, const void *act, const void *norm_w, uint64_t nt_kt, uint64_t k_m, uint64_t ldx_n, GemmArgs g) {
+    g.W = W; g.x = (const float *)act; g.B = act; g.norm_w = norm_w;
+    g.NT = (int)nt_kt; g.KT = (int)(nt_kt >> 32); g.K = (int)k_m; g.m = (int)(k_m >> 32); g.ldx = (int)ldx_n; g.N = (int)(ldx_n >> 32);
+    const KernelArgLines<48 + sizeof(GemmArgs)> lines;
     constexpr int NF = H / 2, NS = proj_slots(H), TB = NPL * 1024;   // whole tiles, slots, bytes of a tile
     constexpr bool HALF = H & 1;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -67,7 +70,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
     const int k_ok = kb > ka ? kb - 1 : (ka < KT ? ka : KT - 1);
 
     // weights: uniform base, 32-bit byte offsets (a packed matrix has less than 4 GiB)
-    const char *W = (const char *)g.W;
+    const char *Wb = (const char *)g.W;
     unsigned wf[NF], wh = 0;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -85,14 +88,14 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
             const unsigned o = (unsigned)k * TB;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const char *p = W + (size_t)(wf[f] + o);
+                const char *p = Wb + (size_t)(wf[f] + o);
 #pragma unroll
                 for (int j = 0; j < U; ++j)
 #pragma unroll
                     for (int q = 0; q < NPL; ++q) a.f[f][j][q] = load_weights(p + j * TB + q * 1024);
             }
             if (HALF) {
-                const char *p = W + (size_t)(wh + o + (unsigned)hi_row * TB);
+                const char *p = Wb + (size_t)(wh + o + (unsigned)hi_row * TB);
 #pragma unroll
                 for (int j = 0; j < U / 2; ++j)
 #pragma unroll
@@ -105,7 +108,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
 #pragma unroll
                 for (int f = 0; f < NF; ++f)
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = load_weights(W + (size_t)(wf[f] + o) + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.f[f][j][q] = load_weights(Wb + (size_t)(wf[f] + o) + q * 1024);
             }
             if (HALF) {
 #pragma unroll
@@ -113,7 +116,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
                     const int kk = k + 2 * j + hi_row;
                     const unsigned o = wh + (unsigned)(kk < k_ok ? kk : k_ok) * TB;
 #pragma unroll
-                    for (int q = 0; q < NPL; ++q) a.h[j][q] = load_weights(W + (size_t)o + q * 1024);
+                    for (int q = 0; q < NPL; ++q) a.h[j][q] = load_weights(Wb + (size_t)o + q * 1024);
                 }
             }
         }
@@ -175,6 +178,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
             [&]() {
                 load_w(a0, ka);
                 if (ka + U < kb) load_w(a1, ka + U);
+                lines.use();
             },
             [&](int j, bf16x8 v) {
                 if (j < U) b0[j % U] = v;
@@ -189,6 +193,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(GemmArgs g) {
             load_b(b1, ka + U);
             load_w(a1, ka + U);
         }
+        lines.use();
         load_resid();
         if (g.ssq_in) sum_ssq(g, wave, lane, ssq_part);
         // While four whole batches remain, the loads of the loop are unconditional, so that each product waits for its own
@@ -310,8 +315,8 @@ int launch_as(const GemmArgs &g, hipStream_t s) {
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_proj<NPL, H, U, F16, FROM_X>), dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g);
-    return (int)hipGetLastError();
+    return launch<k_proj<NPL, H, U, F16, FROM_X>>(dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g.W, FROM_X ? (const void *)g.x : g.B, g.norm_w,
+                                                  two(g.NT, g.KT), two(g.K, g.m), two(g.ldx, g.N), g);
 }
 
 template <int NPL, int H, bool F16>

@@ -18,6 +18,7 @@
 
 #include "ad_device.h"
 #include "ad_internal.h"
+#include "ad_launch.h"
 
 namespace ad {
 
@@ -488,8 +489,7 @@ int launch_sample_row(const SampleArgs &a, void *stream) {
     if (a.V < 1 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    hipLaunchKernelGGL(k_sample_row, dim3(n_seg), dim3(kSampleThreads), 0, (hipStream_t)stream, a, n_seg, seg_ids);
-    return (int)hipGetLastError();
+    return launch<k_sample_row>(dim3(n_seg), dim3(kSampleThreads), 0, (hipStream_t)stream, a, n_seg, seg_ids);
 }
 
 int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
@@ -511,15 +511,14 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     // residual always is
     if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
-        hipLaunchKernelGGL(k_segment_stats, dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
-        const int rc = (int)hipGetLastError();
+        const int rc = launch<k_segment_stats>(dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
         if (rc) return rc;
     }
     SegStat *res_seg = n_seg > 1 ? seg + (size_t)(2 * a.m - 1) * n_seg : nullptr;
-    if (n_seg > 1) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENTS>, dim3(n_seg), wg, 0, (hipStream_t)stream, a, seg, res_seg, n_seg, seg_ids);
-    else if (seg) hipLaunchKernelGGL(k_verify_sampled<ROWS_SEGMENT>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, nullptr, n_seg, seg_ids);
-    else hipLaunchKernelGGL(k_verify_sampled<ROWS_LOGITS>, dim3(1), wg, 0, (hipStream_t)stream, a, seg, nullptr, n_seg, seg_ids);
-    return (int)hipGetLastError();
+    hipStream_t s = (hipStream_t)stream;
+    if (n_seg > 1) return launch<k_verify_sampled<ROWS_SEGMENTS>>(dim3(n_seg), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
+    if (seg) return launch<k_verify_sampled<ROWS_SEGMENT>>(dim3(1), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
+    return launch<k_verify_sampled<ROWS_LOGITS>>(dim3(1), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
 }
 
 }  // namespace ad
