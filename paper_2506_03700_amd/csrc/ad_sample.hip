@@ -430,8 +430,8 @@ __device__ __forceinline__ SegStat residual_stat(ResidualWeight w, int j0, int j
     return SegStat{w.c, block_sum(s, L, 1)};
 }
 
-// Everything from the rows' statistics on.  ROWS_SEGMENTS: every workgroup takes the decision; if a draft was rejected, it reduces its segment of
-// the residual, and the last one to arrive draws, else the first one does.  Otherwise one workgroup does it all (seg: null for ROWS_LOGITS).
+// Everything from the rows' statistics on.  ROWS_SEGMENTS: every workgroup takes the decision and, if a draft was rejected, reduces its segment of
+// the residual; the last one to arrive draws.  Otherwise one workgroup does it all (seg: null for ROWS_LOGITS).
 template <RowSource SRC>
 __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampledArgs a, const SegStat *seg, SegStat *res_seg, int n_seg, int seg_ids) {
     __shared__ SampleLds L;
@@ -455,8 +455,11 @@ __global__ void __launch_bounds__(kSampleThreads) k_verify_sampled(VerifySampled
         w.c = segs.max();
         const float mine = segs.rescale(w.c, 1.0f);
         if (w.c != -INFINITY) dr = draw_from(w, segs, mine, a.V, seg_ids, a.u_resample[r], L);
-    } else if (SRC == ROWS_SEGMENTS && blockIdx.x) {
-        return;
+    } else if (SRC == ROWS_SEGMENTS) {
+        // here too the last one goes on: once the done word is out, no workgroup that started late still reads rows or statistics that the caller
+        // may then be writing on another stream
+        __syncthreads();
+        if (!last_to_arrive(a.arrivals, n_seg, &L.last_wg)) return;
     }
     if (dr.tok < 0) {  // nothing rejected (or a residual that is identically zero): draw from the row's final distribution
         if (SRC == ROWS_SEGMENTS) segs.load(seg + (size_t)r * n_seg, n_seg);
