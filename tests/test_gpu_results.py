@@ -82,3 +82,36 @@ def test_sampling_in_a_graph(vocab):
         tok, _ = g.ad_sample_logits(z[0], 0.9, 0.4)
         assert tok == have[0]
     g.close()
+
+
+def test_sampled_results_from_two_streams_in_turn():
+    """Waited-for verifications that accept everything, others that reject, and draws, each on the other stream than the call before, whose rows
+    are overwritten there as soon as it returns: the results of the same calls with the device drained between them."""
+    import torch
+    from paper_2506_03700_amd import binding as ad
+    V, m, turns = 32016, 4, 48
+    shape = synth.TINY.with_(name="small", tied_head=False, n_layers=1, exit_layers=(), d_model=16, n_q_heads=1, n_kv_heads=1, d_ffn=8,
+                             dtype=synth.BF16, vocab=V)
+    g = ad.Model(shape, synth.make_weights(shape, seed=0), max_pos=8)
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    rows = 2 * torch.randn(turns, m, V, device="cuda:0", generator=gen)
+    others = 2 * torch.randn(turns, m - 1, V, device="cuda:0", generator=gen)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    z, zq = torch.empty(m, V, device="cuda:0"), torch.empty(m - 1, V, device="cuda:0")
+    torch.cuda.synchronize()
+
+    def results(drain):
+        out = []
+        for t in range(turns):
+            with torch.cuda.stream(streams[t % 2]):
+                z.copy_(rows[t])
+                zq.copy_(rows[t][:m - 1] if t % 3 else others[t])
+                n, tok, ratio = g.ad_verify_sampled(z, zq, [5, 6, 7], 0.9, [0.5] * 3, [0.3] * 3, 0.1 + 0.8 * t / turns)
+                assert t % 3 == 0 or n == m - 1
+                out.append((n, tok, tuple(ratio)) if t % 4 else (n, tok, tuple(ratio), g.ad_sample_logits(z[0], 0.9, 0.4)))
+            if drain:
+                torch.cuda.synchronize()
+        return out
+    assert results(False) == results(True)
+    torch.cuda.synchronize()
+    g.close()
