@@ -18,7 +18,8 @@
  *     library never allocates or frees device memory.  "host" pointers are ordinary host memory, read or
  *     written before the call returns.  "pinned host or dev" pointers are written by a kernel: valid
  *     after the stream has been synchronised.
- *   - stream is a hipStream_t passed as void* (NULL = the default stream).
+ *   - stream is a hipStream_t passed as void* (NULL = the calling thread's current device's default stream).  Kernels run on the stream's
+ *     device, whatever device the calling thread has current.
  *   - Every call returns an ad_status; nothing is thrown or aborted.  ad_last_error() gives the text of
  *     the last failure on the calling thread.  A call that fails leaves the cache lengths unchanged.
  *   - One call at a time per ad_model: calls share the model's scratch area, so calls on the same model

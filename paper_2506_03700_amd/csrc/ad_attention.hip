@@ -565,7 +565,7 @@ static int launch_valu(const AttnArgs &a, const LaunchCtx &c) {
     const int spare = c.n_wg / (a.Hkv * a.S), most = (a.R + 1) / 2;
     const int nz = spare < 1 ? 1 : spare < most ? spare : most;
     b.rows_wg = (a.R + nz - 1) / nz;
-    return launch<k_attn_valu<DH>>(dim3(a.Hkv * a.S, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, (hipStream_t)c.stream, b);
+    return launch<k_attn_valu<DH>>(c, dim3(a.Hkv * a.S, (a.R + b.rows_wg - 1) / b.rows_wg), dim3(kValuThreads), 0, b);
 }
 
 template <int DH, bool F16, int RT, int NRH>
@@ -577,7 +577,7 @@ static int launch_dec_as(const AttnArgs &a, const LaunchCtx &c) {
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    return launch<k_attn_dec<DH, F16, RT, NRH>>(dim3(a.Hkv * a.S), dim3(256 * NRH), lds, (hipStream_t)c.stream, a);
+    return launch<k_attn_dec<DH, F16, RT, NRH>>(c, dim3(a.Hkv * a.S), dim3(256 * NRH), lds, a);
 }
 
 // More than 16 query rows: two wavefronts per block of keys, a row tile each, while an item is one block per wavefront (the chain
@@ -619,8 +619,8 @@ bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg) {
 }
 
 template <int DH, bool F16>
-static int launch_combine(const AttnArgs &a, dim3 rows, hipStream_t s) {
-    return launch<k_attn_combine<DH, F16>>(rows, dim3(256), 0, s, a.part, a.Bo, two(a.S, a.R), two(a.G, a.Bo_KT), two((int)a.mul_R, (int)a.mul_G));
+static int launch_combine(const AttnArgs &a, dim3 rows, const LaunchCtx &c) {
+    return launch<k_attn_combine<DH, F16>>(c, rows, dim3(256), 0, a.part, a.Bo, two(a.S, a.R), two(a.G, a.Bo_KT), two((int)a.mul_R, (int)a.mul_G));
 }
 
 int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
@@ -640,9 +640,8 @@ int launch_attn(const AttnArgs &a, const LaunchCtx &c) {
     }
     if (rc || a.S == 1) return rc;
     const dim3 rows(a.Hq * a.m);
-    hipStream_t st = (hipStream_t)c.stream;
-    if (a.kv_elem == kElemF16) return a.dh == 128 ? launch_combine<128, true>(a, rows, st) : launch_combine<64, true>(a, rows, st);
-    return a.dh == 128 ? launch_combine<128, false>(a, rows, st) : launch_combine<64, false>(a, rows, st);
+    if (a.kv_elem == kElemF16) return a.dh == 128 ? launch_combine<128, true>(a, rows, c) : launch_combine<64, true>(a, rows, c);
+    return a.dh == 128 ? launch_combine<128, false>(a, rows, c) : launch_combine<64, false>(a, rows, c);
 }
 
 }  // namespace ad

@@ -70,7 +70,6 @@ __global__ void __launch_bounds__(512) k_head_combine(GemmArgs g) {
 int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     // equal numbers of row tiles per workgroup: with per = ceil(NT / n_wg) tiles each, ceil(NT / per) workgroups
     const int grid = head_grid(g.NT, c.n_wg);
-    hipStream_t s = (hipStream_t)c.stream;
     if ((planes == 1) != (g.elem != kElemF32)) return (int)hipErrorInvalidValue;     // fp32 weights are three bf16 planes
     GemmArgs h = g;
     h.head_stats = g.epi == EPI_HEAD && (g.tok_out || g.conf_out || g.verify || g.done_flag);       // (the logits alone need no reduction)
@@ -79,7 +78,7 @@ int launch_gemm(const GemmArgs &g, int planes, const LaunchCtx &c) {
     if (rc) return rc;
     if (h.head_stats) {
         h.n_parts = few ? proj_head_parts(g.NT, c.n_wg) : grid;
-        rc = launch<k_head_combine>(dim3(1), dim3(512), 0, s, h);
+        rc = launch<k_head_combine>(c, dim3(1), dim3(512), 0, h);
     }
     return rc;
 }

@@ -474,6 +474,8 @@ static int gemm(const ad_model *m, const GemmArgs &g, int64_t rows, int64_t cols
     return rc;
 }
 
+static LaunchCtx launch_ctx(const ad_model *m, void *stream) { return LaunchCtx{stream, m->n_wg, stream_device(stream)}; }
+
 ad_status ad_embed(const ad_model *m, const int32_t *tokens, int32_t n, void *hidden, void *stream) {
     if (!m || !tokens || !hidden) return (ad_status)fail(AD_EINVAL, "ad_embed: null argument");
     if (n < 1 || n > m->cfg.m_max) return (ad_status)fail(AD_ERANGE, "ad_embed: m = %d outside 1..%d", n, m->cfg.m_max);
@@ -484,7 +486,7 @@ ad_status ad_embed(const ad_model *m, const int32_t *tokens, int32_t n, void *hi
         if (tokens[i] < 0 || tokens[i] >= m->cfg.vocab) return (ad_status)fail(AD_ERANGE, "ad_embed: token %d outside the vocabulary", tokens[i]);
         a.tok[i] = tokens[i];
     }
-    int rc = launch_embed(a, stream);
+    int rc = launch_embed(a, launch_ctx(m, stream));
     return rc ? (ad_status)hip_fail(rc, "ad_embed") : AD_OK;
 }
 
@@ -494,7 +496,7 @@ static int embed_from(const ad_model *m, const int32_t *token_src, void *hidden,
     memset(&a, 0, sizeof a);
     a.table = m->embed; a.elem = elem_kind(m->cfg); a.d = m->cfg.d_model; a.m = 1; a.out = (float *)hidden;
     a.tok_src = token_src; a.vocab = m->cfg.vocab;
-    const int rc = launch_embed(a, stream);
+    const int rc = launch_embed(a, launch_ctx(m, stream));
     return rc ? hip_fail(rc, "embedding issued ahead") : AD_OK;
 }
 
@@ -540,7 +542,7 @@ static void qkv_args(const ad_model *m, int32_t ly, const void *hidden, int32_t 
 static int qkv_ahead(const ad_model *m, int32_t layer, const void *hidden, int32_t n, void *stream) {
     GemmArgs gq;
     qkv_args(m, layer, hidden, n, false, gq);
-    const int rc = gemm(m, gq, m->lay.nqkv, m->lay.d, LaunchCtx{stream, m->n_wg});
+    const int rc = gemm(m, gq, m->lay.nqkv, m->lay.d, launch_ctx(m, stream));
     return rc ? hip_fail(rc, "layer step: qkv issued ahead") : AD_OK;
 }
 
@@ -560,7 +562,7 @@ static int layer_steps(const ad_model *m, ad_kv *kv, int32_t layer, int32_t coun
         if (pos[0] != kv->len[l - 1]) return fail(AD_ESTATE, "%s: pos[0] = %d but layer %d's cache ends at %d", who, pos[0], l, kv->len[l - 1]);
     if (pos[0] < 0 || pos[n - 1] >= kv->max_pos) return fail(AD_ERANGE, "%s: position %d beyond max_pos %d", who, pos[n - 1], kv->max_pos);
     const Layout &L = m->lay;
-    const LaunchCtx ctx{stream, m->n_wg};
+    const LaunchCtx ctx = launch_ctx(m, stream);
     const int ek = elem_kind(c);
     const bool fused = m->layer_mode == AD_LAYER_FUSED;
     int rc;
@@ -737,7 +739,7 @@ static int run_head(const ad_model *m, int32_t layer, const void *hidden, int32_
         if (slot < 0) return fail(AD_ESTATE, "%s: layer %d has no exit head", who, layer);
     }
     const Layout &L = m->lay;
-    const LaunchCtx ctx{stream, m->n_wg};
+    const LaunchCtx ctx = launch_ctx(m, stream);
     const int ek = elem_kind(c);
     int rc;
     g.elem = ek;
@@ -831,7 +833,7 @@ static int sample_logits(const ad_model *m, const void *logits, float temperatur
     memset(&a, 0, sizeof a);
     a.z = (const float *)logits; a.V = m->cfg.vocab; a.inv_t = 1.0f / temperature; a.u = u; a.tok_out = token; a.prob_out = prob; a.scratch = m->head_part; a.arrivals = m->arrivals;
     a.done_flag = done_flag; a.done_seq = done_seq;
-    const int rc = launch_sample_row(a, stream);
+    const int rc = launch_sample_row(a, launch_ctx(m, stream));
     return rc ? hip_fail(rc, "ad_sample_logits") : AD_OK;
 }
 
@@ -857,7 +859,7 @@ static int verify_sampled(const ad_model *m, const void *final_logits, const voi
     }
     a.u_final = u_final; a.scratch = m->head_part; a.arrivals = m->arrivals; a.n_accept_out = n_accept; a.next_out = next_token; a.ratio_out = ratio;
     a.done_flag = done_flag; a.done_seq = done_seq;
-    const int rc = launch_verify_sampled(a, stream);
+    const int rc = launch_verify_sampled(a, launch_ctx(m, stream));
     return rc ? hip_fail(rc, "ad_verify_sampled") : AD_OK;
 }
 

@@ -192,7 +192,8 @@ struct VerifySampledArgs {
     int32_t done_seq;
 };
 
-struct LaunchCtx { void *stream; int n_wg; };
+// device: the stream's (stream_device), -1 if it is not known
+struct LaunchCtx { void *stream; int n_wg, device; };
 
 // All launchers return 0 or a hipError_t value.
 // mode 0: W [N, K] -> packed.  mode 1: gate (src) and up (src2), each [N, K], interleaved 8 rows at a time.
@@ -202,7 +203,7 @@ int launch_pack_weights(const void *src, const void *src2, int src_elem, int64_t
 int launch_probe_stream(const void *p0, size_t bytes0, const void *p1, size_t bytes1, unsigned *sink, int n_wg, void *stream);
 int launch_copy(const void *src, void *dst, size_t bytes, void *stream);
 int launch_zero(void *dst, size_t bytes, void *stream);
-int launch_embed(const EmbedArgs &, void *stream);
+int launch_embed(const EmbedArgs &, const LaunchCtx &);
 int launch_rope_table(const RopeArgs &, void *stream);
 int rows_max_k(int planes);                // largest d_model that the projections' kernels cover
 int launch_gemm(const GemmArgs &, int planes, const LaunchCtx &);   // EPI_HEAD: also launches the vocabulary combine
@@ -217,14 +218,15 @@ int head_parts(int n_tiles, int n_wg);                              // most part
 constexpr int kStaticHeadParts = 4096;
 int static_head_scratch(float **ptr);
 int launch_attn(const AttnArgs &, const LaunchCtx &);
-int launch_sample_row(const SampleArgs &, void *stream);
-int launch_verify_sampled(const VerifySampledArgs &, void *stream);
+int launch_sample_row(const SampleArgs &, const LaunchCtx &);
+int launch_verify_sampled(const VerifySampledArgs &, const LaunchCtx &);
 int launch_layer_fused(const FusedArgs &, const LaunchCtx &);   // n_wg must not exceed the number of compute units
 int fused_phase_workgroups(int n_tiles, int n_wg);               // workgroups that own row tiles of a GEMM phase
 int attn_chunk(int kv_elem, int dh);   // cached positions per attention work item (fused layer step), and the fewest
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg);   // the same for a stand-alone launch
 bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg);      // whether the call's own rows are an item of their own there
 int device_info(int *n_cu);
+int stream_device(void *stream);       // the device of a stream (null: the current one), -1 if the runtime does not say
 const char *hip_error_text(int code);
 int stream_sync(void *stream);
 void *event_create();

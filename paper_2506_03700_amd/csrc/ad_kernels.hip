@@ -145,8 +145,8 @@ int launch_zero(void *dst, size_t bytes, void *stream) {
     return (int)hipGetLastError();
 }
 
-int launch_embed(const EmbedArgs &a, void *stream) {
-    return launch<k_embed>(dim3(32), dim3(256), 0, S(stream), a);
+int launch_embed(const EmbedArgs &a, const LaunchCtx &c) {
+    return launch<k_embed>(c, dim3(32), dim3(256), 0, a);
 }
 
 int launch_rope_table(const RopeArgs &a, void *stream) {
@@ -163,6 +163,13 @@ int device_info(int *n_cu) {
     if (e != hipSuccess) return (int)e;
     *n_cu = p.multiProcessorCount;
     return 0;
+}
+
+int stream_device(void *stream) {
+    int dev = -1;
+    if ((stream ? hipStreamGetDevice(S(stream), &dev) : hipGetDevice(&dev)) == hipSuccess) return dev;
+    (void)hipGetLastError();
+    return -1;
 }
 
 const char *hip_error_text(int code) { return hipGetErrorString((hipError_t)code); }

@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_proj(const void *W, const v
 }
 
 template <int NPL, int H, int U, bool F16, bool FROM_X>
-int launch_as(const GemmArgs &g, hipStream_t s) {
+int launch_as(const GemmArgs &g, const LaunchCtx &c) {
     constexpr size_t lds = proj_lds_bytes(H, FROM_X);
     static bool attr_set = false;
     if (!attr_set) {
@@ -315,23 +315,23 @@ int launch_as(const GemmArgs &g, hipStream_t s) {
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
-    return launch<k_proj<NPL, H, U, F16, FROM_X>>(dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, s, g.W, FROM_X ? (const void *)g.x : g.B, g.norm_w,
+    return launch<k_proj<NPL, H, U, F16, FROM_X>>(c, dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, g.W, FROM_X ? (const void *)g.x : g.B, g.norm_w,
                                                   two(g.NT, g.KT), two(g.K, g.m), two(g.ldx, g.N), g);
 }
 
 template <int NPL, int H, bool F16>
-int launch_src(const GemmArgs &g, hipStream_t s) {
+int launch_src(const GemmArgs &g, const LaunchCtx &c) {
     constexpr int U = proj_batch(NPL);
     if (NPL == 1 && g.KT <= kProjWaves * 2 * kProjSmallBatch)
-        return g.x ? launch_as<NPL, H, kProjSmallBatch, F16, true>(g, s) : launch_as<NPL, H, kProjSmallBatch, F16, false>(g, s);
-    return g.x ? launch_as<NPL, H, U, F16, true>(g, s) : launch_as<NPL, H, U, F16, false>(g, s);
+        return g.x ? launch_as<NPL, H, kProjSmallBatch, F16, true>(g, c) : launch_as<NPL, H, kProjSmallBatch, F16, false>(g, c);
+    return g.x ? launch_as<NPL, H, U, F16, true>(g, c) : launch_as<NPL, H, U, F16, false>(g, c);
 }
 
 template <int NPL, bool F16>
-int launch_halves(const GemmArgs &g, int halves, hipStream_t s) {
-    if (halves == 2) return launch_src<NPL, 2, F16>(g, s);
-    if (halves == 3) return launch_src<NPL, 3, F16>(g, s);
-    return launch_src<NPL, 4, F16>(g, s);
+int launch_halves(const GemmArgs &g, int halves, const LaunchCtx &c) {
+    if (halves == 2) return launch_src<NPL, 2, F16>(g, c);
+    if (halves == 3) return launch_src<NPL, 3, F16>(g, c);
+    return launch_src<NPL, 4, F16>(g, c);
 }
 
 }  // namespace
@@ -360,9 +360,8 @@ int launch_proj(const GemmArgs &g, int planes, const LaunchCtx &c) {
     if (g.x && !rows_covered(g, planes)) return (int)hipErrorInvalidValue;
     int halves = proj_halves(g.NT, c.n_wg);
     if (halves == 3 && g.epi == EPI_SWIGLU) halves = 4;
-    hipStream_t s = (hipStream_t)c.stream;
-    if (planes != 1) return launch_halves<3, false>(g, halves, s);
-    return g.elem == kElemF16 ? launch_halves<1, true>(g, halves, s) : launch_halves<1, false>(g, halves, s);
+    if (planes != 1) return launch_halves<3, false>(g, halves, c);
+    return g.elem == kElemF16 ? launch_halves<1, true>(g, halves, c) : launch_halves<1, false>(g, halves, c);
 }
 
 }  // namespace ad

@@ -227,7 +227,7 @@ __global__ void __launch_bounds__(kProjThreads, 2) k_rows(const void *weights, c
 }
 
 template <int NPL, int KS, bool F16, bool FROM_X>
-int launch_as(const GemmArgs &g, int grid, hipStream_t s) {
+int launch_as(const GemmArgs &g, int grid, const LaunchCtx &c) {
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)k_rows<NPL, KS, F16, FROM_X>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowsLdsBytes);
@@ -236,13 +236,13 @@ int launch_as(const GemmArgs &g, int grid, hipStream_t s) {
     }
     GemmArgs ga = g;
     set_tile_partition(ga, grid);
-    return launch<k_rows<NPL, KS, F16, FROM_X>>(dim3(grid), dim3(kProjThreads), kRowsLdsBytes, s, ga.W, FROM_X ? (const void *)ga.x : ga.B, ga.norm_w,
+    return launch<k_rows<NPL, KS, F16, FROM_X>>(c, dim3(grid), dim3(kProjThreads), kRowsLdsBytes, ga.W, FROM_X ? (const void *)ga.x : ga.B, ga.norm_w,
                                                 two(ga.KT, ga.K), two(ga.m, ga.ldx), two(ga.tq, ga.tr), ga);
 }
 
 template <int NPL, int KS, bool F16>
-int launch_src(const GemmArgs &g, int grid, hipStream_t s) {
-    return g.x ? launch_as<NPL, KS, F16, true>(g, grid, s) : launch_as<NPL, KS, F16, false>(g, grid, s);
+int launch_src(const GemmArgs &g, int grid, const LaunchCtx &c) {
+    return g.x ? launch_as<NPL, KS, F16, true>(g, grid, c) : launch_as<NPL, KS, F16, false>(g, grid, c);
 }
 
 // The instance whose registers hold the activations of a wavefront: 16-bit models of d_model <= 512, 1024, 2048, 4096, 5120, 6144, 8192.  An
@@ -250,25 +250,25 @@ int launch_src(const GemmArgs &g, int grid, hipStream_t s) {
 // exit head of 128256 tokens took 56.9 us at d_model 512 and 55.6 at 1024, 27.6 and 42.4 with 2 and 4 (54.5 and 61.3 with the kernel before
 // this one).
 template <bool F16>
-int launch16(const GemmArgs &g, int nks, int grid, hipStream_t s) {
-    if (nks <= 2) return launch_src<1, 2, F16>(g, grid, s);
-    if (nks <= 4) return launch_src<1, 4, F16>(g, grid, s);
-    if (nks <= 8) return launch_src<1, 8, F16>(g, grid, s);
-    if (nks <= 16) return launch_src<1, 16, F16>(g, grid, s);
-    if (nks <= 20) return launch_src<1, 20, F16>(g, grid, s);
-    if (nks <= 24) return launch_src<1, 24, F16>(g, grid, s);
-    return launch_src<1, 32, F16>(g, grid, s);
+int launch16(const GemmArgs &g, int nks, int grid, const LaunchCtx &c) {
+    if (nks <= 2) return launch_src<1, 2, F16>(g, grid, c);
+    if (nks <= 4) return launch_src<1, 4, F16>(g, grid, c);
+    if (nks <= 8) return launch_src<1, 8, F16>(g, grid, c);
+    if (nks <= 16) return launch_src<1, 16, F16>(g, grid, c);
+    if (nks <= 20) return launch_src<1, 20, F16>(g, grid, c);
+    if (nks <= 24) return launch_src<1, 24, F16>(g, grid, c);
+    return launch_src<1, 32, F16>(g, grid, c);
 }
 
 // the same for fp32 models of d_model <= 512, 1024, 2048, 3072, 4096, 5120: with 2 and 20 k-steps alone the logits of 32016 tokens took
 // 68.6 us at d_model 1024 and 86.0 at 2048, 31.0 and 61.3 with these (and 35.0 and 66.5 with the kernel before this one)
-int launch32(const GemmArgs &g, int nks, int grid, hipStream_t s) {
-    if (nks <= 2) return launch_src<3, 2, false>(g, grid, s);
-    if (nks <= 4) return launch_src<3, 4, false>(g, grid, s);
-    if (nks <= 8) return launch_src<3, 8, false>(g, grid, s);
-    if (nks <= 12) return launch_src<3, 12, false>(g, grid, s);
-    if (nks <= 16) return launch_src<3, 16, false>(g, grid, s);
-    return launch_src<3, 20, false>(g, grid, s);
+int launch32(const GemmArgs &g, int nks, int grid, const LaunchCtx &c) {
+    if (nks <= 2) return launch_src<3, 2, false>(g, grid, c);
+    if (nks <= 4) return launch_src<3, 4, false>(g, grid, c);
+    if (nks <= 8) return launch_src<3, 8, false>(g, grid, c);
+    if (nks <= 12) return launch_src<3, 12, false>(g, grid, c);
+    if (nks <= 16) return launch_src<3, 16, false>(g, grid, c);
+    return launch_src<3, 20, false>(g, grid, c);
 }
 
 }  // namespace
@@ -276,11 +276,10 @@ int launch32(const GemmArgs &g, int nks, int grid, hipStream_t s) {
 int rows_max_k(int planes) { return (planes == 1 ? 32 : 20) * kProjWaves * 32; }
 
 int launch_rows(const GemmArgs &g, int planes, int grid, const LaunchCtx &c) {
-    hipStream_t s = (hipStream_t)c.stream;
     if (g.KT * 32 > rows_max_k(planes) || g.K < 8 || (g.x && !g.norm_w) || g.epi == EPI_RESID) return (int)hipErrorInvalidValue;
     const int nks = (g.KT + kProjWaves - 1) / kProjWaves;       // most k-steps of a wavefront
-    if (planes != 1) return launch32(g, nks, grid, s);
-    return g.elem == kElemF16 ? launch16<true>(g, nks, grid, s) : launch16<false>(g, nks, grid, s);
+    if (planes != 1) return launch32(g, nks, grid, c);
+    return g.elem == kElemF16 ? launch16<true>(g, nks, grid, c) : launch16<false>(g, nks, grid, c);
 }
 
 }  // namespace ad

@@ -488,20 +488,20 @@ void segments(int V, int *n_seg, int *seg_ids) {
 
 static_assert(sizeof(SegStat) * 16 * kSampleThreads <= kSampleScratchBytes, "the segments of 15 rows and of a residual");
 
-int launch_sample_row(const SampleArgs &a, void *stream) {
+int launch_sample_row(const SampleArgs &a, const LaunchCtx &c) {
     if (a.V < 1 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
     int n_seg, seg_ids;
     segments(a.V, &n_seg, &seg_ids);
-    return launch<k_sample_row>(dim3(n_seg), dim3(kSampleThreads), 0, (hipStream_t)stream, a, n_seg, seg_ids);
+    return launch<k_sample_row>(c, dim3(n_seg), dim3(kSampleThreads), 0, a, n_seg, seg_ids);
 }
 
-int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
+int launch_verify_sampled(const VerifySampledArgs &a, const LaunchCtx &c) {
     if (a.V < 1 || a.m < 1 || a.m > 8 || !(a.inv_t > 0.f)) return (int)hipErrorInvalidValue;
     if (a.m == 1) {                                  // no drafts: a draw from the row
         SampleArgs s;
         s.z = a.zf; s.V = a.V; s.inv_t = a.inv_t; s.u = a.u_final; s.tok_out = a.next_out; s.prob_out = nullptr; s.n_accept_out = a.n_accept_out;
         s.scratch = a.scratch; s.arrivals = a.arrivals; s.done_flag = a.done_flag; s.done_seq = a.done_seq;
-        return launch_sample_row(s, stream);
+        return launch_sample_row(s, c);
     }
     for (int k = 0; k + 1 < a.m; ++k)
         if (a.draft[k] < 0 || a.draft[k] >= a.V) return (int)hipErrorInvalidValue;
@@ -514,14 +514,13 @@ int launch_verify_sampled(const VerifySampledArgs &a, void *stream) {
     // residual always is
     if (n_seg > 1 || 2 * a.m - 1 > kSampleWaves) {
         seg = (SegStat *)a.scratch;
-        const int rc = launch<k_segment_stats>(dim3(n_seg, 2 * a.m - 1), wg, 0, (hipStream_t)stream, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
+        const int rc = launch<k_segment_stats>(c, dim3(n_seg, 2 * a.m - 1), wg, 0, SegArgs{a.zf, a.zq, a.m, a.V, n_seg, seg_ids, a.inv_t, seg});
         if (rc) return rc;
     }
     SegStat *res_seg = n_seg > 1 ? seg + (size_t)(2 * a.m - 1) * n_seg : nullptr;
-    hipStream_t s = (hipStream_t)stream;
-    if (n_seg > 1) return launch<k_verify_sampled<ROWS_SEGMENTS>>(dim3(n_seg), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
-    if (seg) return launch<k_verify_sampled<ROWS_SEGMENT>>(dim3(1), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
-    return launch<k_verify_sampled<ROWS_LOGITS>>(dim3(1), wg, 0, s, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
+    if (n_seg > 1) return launch<k_verify_sampled<ROWS_SEGMENTS>>(c, dim3(n_seg), wg, 0, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
+    if (seg) return launch<k_verify_sampled<ROWS_SEGMENT>>(c, dim3(1), wg, 0, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
+    return launch<k_verify_sampled<ROWS_LOGITS>>(c, dim3(1), wg, 0, a, (const SegStat *)seg, res_seg, n_seg, seg_ids);
 }
 
 }  // namespace ad
