@@ -34,11 +34,13 @@ __device__ __forceinline__ size_t act_unit(int t, int k, int KT, int plane) {
 // WR x WT accumulators.  Both operands lie in memory in MFMA operand order, so tiles are copied as they are and every LDS
 // access is 64 consecutive 16-byte units: no bank conflicts, no address arithmetic.
 //
-// The accumulators are emptied into a second set every kFlush k-steps, each at its own turn (at the end of a piece whose length is no
-// multiple of kFlush up to 2 * kFlush - 1 k-steps are in one chain): one long chain of fp32 additions is off by 5.7e-7 of
-// the result at K = 4096 and 1.1e-6 at 14336, the two sets by 1.6e-7 and 1.8e-7 (the layer step, whose wavefronts add up
-// 512 inputs each and then each other, is as good).
-constexpr int kFlush = 8;
+// The accumulators are emptied into a second set every few k-steps, each at its own turn: one long chain of fp32 additions is off by
+// 5.7e-7 of the result at K = 4096 and 1.1e-6 at 14336.  Squared, the error is 4.7e-15 * n (n + 1) / 2 for every chain of n k-steps (two products, each
+// rounded several times), 6.7e-16 times the k-steps in the sum for every addition to it, and 8e-16 times those in the pieces for
+// every piece added, over the k-steps of the product (fitted to 414 products of 1024 to 14336 inputs, within 3 %).  So short pieces are emptied every kFlush
+// k-steps, and those of more than kLongPiece, whose sums are longer, every kFlushLong; a tail that is no multiple of it lengthens the last chain.
+constexpr int kFlush = 4, kFlushLong = 8;
+constexpr int kLongPiece = 128, kShortestPiece = 8;
 enum { PG_PART = 0, PG_SWIGLU = 1 };
 
 // Which tile and piece this workgroup has.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets a contiguous run
@@ -80,13 +82,14 @@ struct PromptAcc {
                 acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
     }
-    // the same for those whose turn is k-step s of kFlush: a few at every k-step, so that the additions go by between products
+    // the same for those whose turn is k-step s of F: a few at every k-step, so that the additions go by between products
+    template <int F>
     __device__ __forceinline__ void flush_some(int s) {
 #pragma unroll
         for (int i = 0; i < WR; ++i)
 #pragma unroll
             for (int j = 0; j < WT; ++j)
-                if ((i * WT + j) * kFlush / (WR * WT) == s) {
+                if ((i * WT + j) * F / (WR * WT) == s) {
                     sum[i][j] += acc[i][j];
                     acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
                 }
@@ -142,7 +145,7 @@ __device__ __forceinline__ void copy_to_lds(const void *src, bf16x8 *dst) {
 // there and nobody reads this one any more, whose place the copies of k-step s + NST then take, half of them in this lo phase and half in the
 // next hi phase, spread between the products (all at once they hold up the products behind them).  ONE: a single phase, for tiles of so few
 // products that the reads take longer than a phase of them.
-template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, bool ONE>
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, int F, bool ONE>
 __device__ __forceinline__ void prompt_gemm_tile(const PromptGemm &g, int rt0, int tb, int piece, bf16x8 *lds) {
     constexpr int NW = NWR * NWT, BR = WR * NWR, BT = WT * NWT;
     constexpr int SU = prompt_stage_units(BR, BT), UNITS = BR + BT * 2;         // 16-byte units, and KiB, per stage
@@ -243,13 +246,13 @@ __device__ __forceinline__ void prompt_gemm_tile(const PromptGemm &g, int rt0, i
             fetch_hi(next, nxt);
             fetch_lo(next, nxt);
             copy(cur, k0 + s + NST, 0, NC);
-            if (turn >= 0) C.flush_some(turn);
+            if (turn >= 0) C.template flush_some<F>(turn);
             mma(now.a, now.hi);
             mma(now.a, now.lo);
         } else {
             fetch_lo(now, cur);
             copy(prev, k0 + s + NST - 1, NH, NC);
-            if (turn >= 0) C.flush_some(turn);
+            if (turn >= 0) C.template flush_some<F>(turn);
             mma(now.a, now.hi);
             interleave(std::integral_constant<int, WT>{}, std::integral_constant<int, NC - NH>{});
             meet(std::integral_constant<int, FLY>{});
@@ -271,9 +274,9 @@ __device__ __forceinline__ void prompt_gemm_tile(const PromptGemm &g, int rt0, i
     fetch_hi(x, 0);
     if constexpr (ONE) fetch_lo(x, 0);
     int s = 0;
-    for (; s + kFlush <= n_step; s += kFlush) {
+    for (; s + F <= n_step; s += F) {
 #pragma unroll
-        for (int j = 0; j < kFlush; j += 2) {
+        for (int j = 0; j < F; j += 2) {
             step(s + j, j, x, y);
             step(s + j + 1, j + 1, y, x);
         }
@@ -287,8 +290,8 @@ __device__ __forceinline__ void prompt_gemm_tile(const PromptGemm &g, int rt0, i
     C.template store<F16, EPI>(g, rt0 + wr * WR, tb * BT + wt * WT, piece, lane);
 }
 
-// HALVES: tiles from g.n_full on are workgroups of half the rows.
-template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, bool ONE, bool HALVES>
+// F: k-steps from one emptying of an accumulator to the next.  HALVES: tiles from g.n_full on are workgroups of half the rows.
+template <int WR, int WT, int NWR, int NWT, int NST, bool F16, int EPI, int F, bool ONE, bool HALVES>
 __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     bf16x8 *lds = (bf16x8 *)lds_raw;                            // [NST][weight tiles, activation tiles]
@@ -296,11 +299,11 @@ __global__ void __launch_bounds__(64 * NWR * NWT, 2) k_prompt_gemm(PromptGemm g)
     if constexpr (HALVES) {
         if (T.half >= 0) {
             const int rt0 = (T.rb * WR + T.half * (WR / 2)) * NWR;
-            if (rt0 < g.NT) prompt_gemm_tile<WR / 2, WT, NWR, NWT, NST, F16, EPI, ONE>(g, rt0, T.tb, T.piece, lds);
+            if (rt0 < g.NT) prompt_gemm_tile<WR / 2, WT, NWR, NWT, NST, F16, EPI, F, ONE>(g, rt0, T.tb, T.piece, lds);
             return;
         }
     }
-    prompt_gemm_tile<WR, WT, NWR, NWT, NST, F16, EPI, ONE>(g, T.rb * WR * NWR, T.tb, T.piece, lds);
+    prompt_gemm_tile<WR, WT, NWR, NWT, NST, F16, EPI, F, ONE>(g, T.rb * WR * NWR, T.tb, T.piece, lds);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -635,19 +638,24 @@ __global__ void __launch_bounds__(256, 2) k_prompt_attn(PromptAttn a) {
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-template <int WR, int WT, int NWR, int NWT, int NST, bool ONE, bool F16, int EPI>
-int launch_gemm_as(const PromptGemm &g, hipStream_t s) {
+template <int WR, int WT, int NWR, int NWT, int NST, bool ONE, bool F16, int EPI, int F>
+int launch_gemm_flush(const PromptGemm &g, hipStream_t s) {
     constexpr bool HALVES = WR == 4;
     constexpr int lds = NST * prompt_stage_units(WR * NWR, WT * NWT) * 16;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, ONE, HALVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, F, ONE, HALVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return (int)e;
         attr_set = true;
     }
     const int tiles = g.n_rb * g.n_tb * g.n_split, grid = g.n_full + 2 * (tiles - g.n_full);
-    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, ONE, HALVES>), dim3(grid), dim3(64 * NWR * NWT), lds, s, g);
+    hipLaunchKernelGGL((k_prompt_gemm<WR, WT, NWR, NWT, NST, F16, EPI, F, ONE, HALVES>), dim3(grid), dim3(64 * NWR * NWT), lds, s, g);
     return (int)hipGetLastError();
+}
+template <int WR, int WT, int NWR, int NWT, int NST, bool ONE, bool F16, int EPI>
+int launch_gemm_as(const PromptGemm &g, hipStream_t s) {
+    if (g.k_per > kLongPiece) return launch_gemm_flush<WR, WT, NWR, NWT, NST, ONE, F16, EPI, kFlushLong>(g, s);
+    return launch_gemm_flush<WR, WT, NWR, NWT, NST, ONE, F16, EPI, kFlush>(g, s);
 }
 
 // A kind of tile: 4 * wr row tiles by bt token tiles.  About `step` us go by per k-step, `round` more per round of a workgroup per compute
@@ -655,14 +663,24 @@ int launch_gemm_as(const PromptGemm &g, hipStream_t s) {
 // time and not two.  halves: tiles that would fill less than half of a last round are dealt as two of half the rows, whose k-step takes half_step.
 struct PromptTileKind { int wr, bt; double step, half_step, round, piece, rate; bool pair, halves; };
 
+// The fewest pieces along K: pieces of more than kLongPiece k-steps have long sums, and are taken only where more of them would leave the
+// chip no room for other work (8B shape, 512 tokens, 14336 inputs: two pieces off by 1.08 times as much as four).
+int fewest_pieces(const PromptGemm &g, int n_wg) {
+    const int tiles = (g.NT + 7) / 8 * ((g.M + 127) / 128);
+    int n = 1;
+    while (n < kPromptMaxSplit && n * kLongPiece < g.KT && tiles * (n + 1) <= 2 * n_wg && (size_t)(n + 1) * g.M * g.N <= g.part_floats) ++n;
+    return n;
+}
+
 // Lays the product out in such tiles and, with `pieces`, in the number of pieces along K that takes the least time; returns about how many microseconds.
 double lay_out(PromptGemm &g, const PromptTileKind &t, bool pieces, int n_wg) {
     g.n_rb = (g.NT + 4 * t.wr - 1) / (4 * t.wr);
     g.n_tb = ((g.M + 15) / 16 + t.bt - 1) / t.bt;
     PromptGemm best = g;
     double least = INFINITY;
-    for (int split = 1; split <= (pieces ? kPromptMaxSplit : 1); ++split) {
-        if (split > 1 && (g.KT / split < kFlush || (size_t)split * g.M * g.N > g.part_floats)) break;
+    const int fewest = pieces ? fewest_pieces(g, n_wg) : 1;
+    for (int split = fewest; split <= (pieces ? kPromptMaxSplit : 1); ++split) {
+        if (split > fewest && (g.KT / split < kShortestPiece || (size_t)split * g.M * g.N > g.part_floats)) break;
         PromptGemm h = g;
         h.k_per = (g.KT + split - 1) / split;
         h.n_split = (g.KT + h.k_per - 1) / h.k_per;
