@@ -1,5 +1,5 @@
 """Build the HIP library (gfx950) in-tree: paper_2506_03700_amd/libadadecode.so, plus the CPU-only
-scheduler test hook libad_sched_test.so (host code, g++)."""
+test hooks of the scheduler and of the prompt pass's layout, libad_sched_test.so (host code, g++)."""
 import os
 import subprocess
 import sys
@@ -49,7 +49,7 @@ def build_sched_test(force=True):
     if not force and not _stale(SCHED_LIB, _all_deps()):
         return SCHED_LIB
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-o", SCHED_LIB + ".tmp"] + \
-        _sources(["ad_sched.cpp", "ad_sched_testhook.cpp"])
+        _sources(["ad_sched.cpp", "ad_sched_testhook.cpp", "ad_prompt_testhook.cpp"])
     subprocess.run(cmd, check=True)
     os.replace(SCHED_LIB + ".tmp", SCHED_LIB)
     return SCHED_LIB

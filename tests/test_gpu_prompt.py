@@ -7,6 +7,7 @@ import pytest
 
 from oracle import oracle as orc
 from paper_2506_03700_amd import synth
+from prompt_gemm import layout
 from tolerances import check_kv, check_rows
 
 pytestmark = pytest.mark.gpu
@@ -46,20 +47,22 @@ def follow_up(shape, g, o, prompt):
     check_rows(shape.dtype, h.cpu().numpy(), ho, f"row after {n} tokens")
 
 
-# the prompt pass takes all but the last token of the prompt: 8 is the most that is left to a layer step; 16, 32, 64, 128
-# and 256 tokens are where tiles and workgroups of tokens end and the variants change
+# the prompt pass takes all but the last token of the prompt: 8 is the most that is left to a layer step; 16, 32, 64, 96, 192, 288 tokens are where
+# tiles and, in these shapes, workgroups of tokens of the projections end and the variants change, multiples of 64 rows (21 and a third, 16 and 64
+# tokens) those of the attention, 256 tokens those of the other kernels
 @pytest.mark.parametrize("shape", [ODD, ODD.with_(name="odd-f16", dtype=synth.F16), DH128, MHA], ids=lambda s: s.name)
 def test_prompt_lengths_at_tile_edges(ad, shape):
     w = synth.make_weights(shape, seed=4, norm_jitter=0.2)
     max_pos = 320
     g, o = ad.Model(shape, w, max_pos=max_pos), orc.Oracle(shape, w, max_pos=max_pos)
-    for n in (8, 9, 15, 17, 31, 32, 33, 64, 65, 127, 128, 129, 256, 257, 300):
+    for n in (8, 9, 15, 17, 31, 32, 33, 64, 65, 96, 97, 98, 127, 128, 129, 192, 193, 194, 256, 257, 289, 290, 300):
         print(f"case {shape.name} {n} tokens", flush=True)
         follow_up(shape, g, o, synth.make_prompt(shape, n, n + 1))
     g.close()
 
 
-# Every tile of the projections (128, 192 or 256 rows by 96 or 128 tokens) with rows and tokens left over in the last ones.  Gate and up:
+# Every tile of the projections (128, 192 or 256 rows by 96 or 128 tokens) with rows and tokens left over in the last ones, over two or three k-steps
+# (longer contractions: test_gpu_prompt_gemm.py; that the lengths take these tiles: test_prompt_layout.py).  Gate and up:
 # 2 x 3 tiles a wavefront at 70 tokens, 4 x 3 at 180, 4 x 4 at 200, 3 x 4 at 300, 4 x 4 and a last round of halves at 750 (and 1000 rows further on, 2 x 4 at
 # 200, 3 x 3 at 300); Wo and down of the widest model: 2 x 3 at 300, 2 x 4 at 400, 3 x 4 at 600, 4 x 3 at 750, 4 x 4 at 1000; q/k/v of
 # 130 heads: 3 x 3 at 400.
@@ -102,7 +105,7 @@ def test_storage_without_the_scratch_is_a_cache_too(ad):
     g.close()
 
 
-# The pieces of q/k/v (N 1536) and Wo (N 2048) of some 100 tokens, four of each, take 2.4 and 3.2 MB: more than the 2 MB set aside for
+# The pieces of q/k/v (N 1536) and Wo (N 2048) of some 100 tokens, five or four and three of them, take 2.4 to 3 MB: more than the 2 MB set aside for
 # them in a cache of 128 rows, so that they run on into the SwiGLU activations; those of down lie over queries and attention output.
 SHARED = ODD.with_(name="shared-bf16", n_q_heads=16, n_kv_heads=4, d_model=2048, d_ffn=2752)
 
@@ -136,6 +139,12 @@ def test_nothing_is_read_that_was_not_written(ad, shape):
 
 @pytest.mark.parametrize("shape", [SHARED, SHARED.with_(name="shared-f16", dtype=synth.F16)], ids=lambda s: s.name)
 def test_pieces_in_scratch_of_other_steps(ad, shape):
+    import torch
+    own, room = 128 * 2 * shape.d_model, 128 * (2 * shape.d_model + shape.d_ffn)        # floats
+    for N, K in ((shape.d_q + 2 * shape.d_kv, shape.d_model), (shape.d_model, shape.d_q)):
+        for m in (99, 109, 116):
+            pieces = layout(N, K, m, room, False, torch.cuda.get_device_properties(0).multi_processor_count)[1]
+            assert own < pieces * m * N <= room
     same_bits_in_poisoned_storage(ad, shape, 120, (100, 10, 65, 110))
     w = synth.make_weights(shape, seed=9, norm_jitter=0.2)
     g, o = ad.Model(shape, w, max_pos=120), orc.Oracle(shape, w, max_pos=120)

@@ -1,7 +1,7 @@
 """The prompt pass's projections on their own against the same products in 64 bits."""
 import pytest
 
-from prompt_gemm import project
+from prompt_gemm import CASES, project, project_swiglu
 
 pytestmark = pytest.mark.gpu
 
@@ -18,3 +18,22 @@ def test_short_chains(N, K, M, room, error):
     print(f"case {N} x {K}, {M} tokens", flush=True)
     got, pieces = project(N, K, M, torch.bfloat16, room)
     assert got < 1.01 * error, (got, pieces)
+
+
+# Sums: chains of up to 15 k-steps in the worst case (see the formula at the kernel): 2.5e-7.  SwiGLU's results are stored as hi and lo parts, of bf16 to
+# 2^-17 of a value; of fp16 to 2^-22, or 2^-25 where lo is subnormal, behind an exponential of some 2^-21.
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_every_tile(case, dtype):
+    import torch
+    swiglu, N, K, M, n_wg, _, pieces, _ = case
+    dt = getattr(torch, dtype)
+    print(f"case {case} {dtype}", flush=True)
+    if swiglu:
+        err = project_swiglu(N, K, M, dt, n_wg)
+        print(err)
+        assert err < (2 ** -17 if dt == torch.bfloat16 else 2 ** -20)
+    else:
+        err, n = project(N, K, M, dt, 8 * N * M, n_wg)
+        print(err)
+        assert n == pieces and err < 2.5e-7
