@@ -35,7 +35,8 @@ enum EpiKind : int { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3,
 enum GemmMode : int { GEMM_STREAMED = 0, GEMM_STATIONARY = 1 };
 
 struct GemmArgs {
-    // what a kernel needs before it can issue its first loads comes first (one line of the argument block)
+    // what a kernel needs before it can issue its first loads.  k_proj and k_rows take most of it as leading parameters of their own, which lie
+    // in registers when a wavefront starts, and do not read it from here.
     const void *W;        // packed weights
     // activations: either fp32 rows x [m][ldx] (stationary mode; multiplied by norm_w and, in the epilogue, by
     // rsqrt(mean(x^2) + eps) when norm_w is given), or a packed block B
@@ -49,7 +50,6 @@ struct GemmArgs {
                           // (set by the launchers for the grid they choose)
     int ldx;
     int N;                // valid output rows (EPI_SWIGLU: rows of the interleaved gate/up matrix = 2F)
-    // ---- end of the first line ----
     int mode;             // GemmMode
     int elem;             // ElemKind of the weights: fp32 (three bf16 planes), bf16, or fp16 (fp16 MFMA, fp16 hi/lo activations)
     float inv_dim, eps;
@@ -89,7 +89,6 @@ struct GemmArgs {
     int32_t done_seq;
 };
 
-static_assert(offsetof(GemmArgs, mode) == 64, "GemmArgs: the first line holds the fields needed first");
 // two values in one kernel parameter (a launch costs the host 10 ns per parameter)
 inline uint64_t two(int lo, int hi) { return (uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
 // the launchers' partition of a GEMM's NT row tiles over n workgroups
