@@ -34,9 +34,39 @@ inline size_t act_packed_bytes(int64_t K) { return (size_t)((K + kTileK - 1) / k
 enum EpiKind : int { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_PACK = 4 };
 enum GemmMode : int { GEMM_STREAMED = 0, GEMM_STATIONARY = 1 };
 
-struct GemmArgs {
-    // what a kernel needs before it can issue its first loads.  k_proj and k_rows take most of it as leading parameters of their own, which lie
-    // in registers when a wavefront starts, and do not read it from here.
+// What a projection's kernel needs from its epilogue on.
+struct GemmOut {
+    int epi;
+    int N;                // valid output rows (EPI_SWIGLU: rows of the interleaved gate/up matrix = 2F)
+    float inv_dim, eps;
+    // EPI_STORE: out[t*ld + n] = scale_t * acc
+    // EPI_RESID: out[t*ld + n] = resid[t*ld + n] + acc
+    // EPI_SWIGLU: tile rows 0..7 gate, 8..15 up of features tile*8 .. +8; packs silu(gate)*up into Bnext
+    // EPI_PACK: packs scale_t * acc into Bnext (used for the exit-head transform T)
+    // EPI_HEAD: per-token argmax / log-sum-exp over all rows; partials per workgroup, folded by a second kernel
+    float *out;
+    const float *resid;
+    int ld;
+    int Bnext_KT;         // k-steps of Bnext (the K of the GEMM that will read it, in units of 32)
+    void *Bnext;          // packed activations written by the epilogue
+    // EPI_RESID in streamed mode, optional (Bnext non-null): the epilogue also prepares the next GEMM's input, which is
+    // RMSNorm(out): it packs out * next_norm_w into Bnext and writes the sum of squares of its outputs per token to
+    // ssq_out[i][token], i a half tile of 8 rows (in the fused layer kernel a tile of 16).  The consumer (stationary mode,
+    // B = that block, ssq_in = those partials, ssq_tiles of them) only has to load its operand registers and add the
+    // partials up for the 1/rms factor.
+    const void *next_norm_w;
+    float *ssq_out;
+    const float *ssq_in;
+    int ssq_tiles;
+    // head
+    int head_stats;       // whether partials are wanted at all (set by the launcher)
+    float *head_part;     // [partial][8][4] (max, sumexp, argmax as int bits, unused), of a workgroup or one of its wavefronts
+    float *logits;        // null or [m][N]
+};
+
+// The same and what it needs before its first loads.  k_proj and k_rows take that as leading parameters, which lie in registers when a
+// wavefront starts, and a GemmOut behind them.
+struct ProjArgs : GemmOut {
     const void *W;        // packed weights
     // activations: either fp32 rows x [m][ldx] (stationary mode; multiplied by norm_w and, in the epilogue, by
     // rsqrt(mean(x^2) + eps) when norm_w is given), or a packed block B
@@ -49,35 +79,13 @@ struct GemmArgs {
     int tq, tr;           // row tiles per workgroup: workgroup w of the GEMM's n takes tq tiles, the first tr of them one more
                           // (set by the launchers for the grid they choose)
     int ldx;
-    int N;                // valid output rows (EPI_SWIGLU: rows of the interleaved gate/up matrix = 2F)
+};
+
+struct GemmArgs : ProjArgs {
     int mode;             // GemmMode
     int elem;             // ElemKind of the weights: fp32 (three bf16 planes), bf16, or fp16 (fp16 MFMA, fp16 hi/lo activations)
-    float inv_dim, eps;
-    int epi;
-    // EPI_STORE: out[t*ld + n] = scale_t * acc
-    // EPI_RESID: out[t*ld + n] = resid[t*ld + n] + acc
-    // EPI_SWIGLU: tile rows 0..7 gate, 8..15 up of features tile*8 .. +8; packs silu(gate)*up into Bnext
-    // EPI_PACK: packs scale_t * acc into Bnext (used for the exit-head transform T)
-    // EPI_HEAD: per-token argmax / log-sum-exp over all rows; partials per workgroup, folded by a second kernel
-    float *out;
-    const float *resid;
-    int ld;
-    void *Bnext;          // packed activations written by the epilogue
-    int Bnext_KT;         // k-steps of that block (the K of the GEMM that will read it, in units of 32)
-    // EPI_RESID in streamed mode, optional (Bnext non-null): the epilogue also prepares the next GEMM's input, which is
-    // RMSNorm(out): it packs out * next_norm_w into Bnext and writes the sum of squares of its outputs per token to
-    // ssq_out[i][token], i a half tile of 8 rows (in the fused layer kernel a tile of 16).  The consumer (stationary mode,
-    // B = that block, ssq_in = those partials, ssq_tiles of them) only has to load its operand registers and add the
-    // partials up for the 1/rms factor.
-    const void *next_norm_w;
-    float *ssq_out;
-    const float *ssq_in;
-    int ssq_tiles;
     // head
-    float *head_part;     // [partial][8][4] (max, sumexp, argmax as int bits, unused), of a workgroup or one of its wavefronts
     int n_parts;          // partials in head_part (set by the launcher)
-    int head_stats;       // whether partials are wanted at all (set by the launcher)
-    float *logits;        // null or [m][N]
     int32_t *tok_out;     // [m] (or null)
     float *conf_out;      // [m] (or null)
     int32_t *n_accept_out, *next_out;   // verify outputs or null
@@ -92,7 +100,7 @@ struct GemmArgs {
 // two values in one kernel parameter (a launch costs the host 10 ns per parameter)
 inline uint64_t two(int lo, int hi) { return (uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
 // the launchers' partition of a GEMM's NT row tiles over n workgroups
-inline void set_tile_partition(GemmArgs &g, int n) { g.tq = g.NT / n; g.tr = g.NT % n; }
+inline void set_tile_partition(ProjArgs &g, int n) { g.tq = g.NT / n; g.tr = g.NT % n; }
 
 struct RopeArgs {
     float *table;         // [n_pos][half][2] (cos, sin)

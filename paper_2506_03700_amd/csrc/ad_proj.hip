@@ -40,10 +40,12 @@ constexpr size_t proj_lds_bytes(int h, bool from_x) {
 // NPL: planes of a weight tile (fp32 models three).  H: halves of a row tile per workgroup.  U: k-steps per batch.  FROM_X: the activations are fp32 rows
 // (times a norm weight, with 1 / rms applied to the result), else a packed block, with or without sums of squares for 1 / rms.
 template <int NPL, int H, int U, bool F16, bool FROM_X>
-__global__ void __launch_bounds__(kProjThreads, 2) k_proj(const void *W, const void *act, const void *norm_w, uint64_t nt_kt, uint64_t k_m, uint64_t ldx_n, GemmArgs g) {
+__global__ void __launch_bounds__(kProjThreads, 2) k_proj(const void *W, const void *act, const void *norm_w, uint64_t nt_kt, uint64_t k_m, uint64_t ldx_n, GemmOut rest) {
+    ProjArgs g;
+    (GemmOut &)g = rest;
     g.W = W; g.x = (const float *)act; g.B = act; g.norm_w = norm_w;
     g.NT = (int)nt_kt; g.KT = (int)(nt_kt >> 32); g.K = (int)k_m; g.m = (int)(k_m >> 32); g.ldx = (int)ldx_n; g.N = (int)(ldx_n >> 32);
-    const KernelArgLines<48 + sizeof(GemmArgs)> lines;
+    const KernelArgLines<48 + sizeof(GemmOut)> lines;
     constexpr int NF = H / 2, NS = proj_slots(H), TB = NPL * 1024;   // whole tiles, slots, bytes of a tile
     constexpr bool HALF = H & 1;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -316,7 +318,7 @@ int launch_as(const GemmArgs &g, const LaunchCtx &c) {
         attr_set = true;
     }
     return launch<k_proj<NPL, H, U, F16, FROM_X>>(c, dim3((2 * g.NT + H - 1) / H), dim3(kProjThreads), lds, g.W, FROM_X ? (const void *)g.x : g.B, g.norm_w,
-                                                  two(g.NT, g.KT), two(g.K, g.m), two(g.ldx, g.N), g);
+                                                  two(g.NT, g.KT), two(g.K, g.m), two(g.ldx, g.N), (const GemmOut &)g);
 }
 
 template <int NPL, int H, bool F16>

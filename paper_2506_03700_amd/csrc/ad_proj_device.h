@@ -22,7 +22,7 @@ __device__ __forceinline__ bf16x8 load_weights(const char *p) { return __builtin
 // passes are requested first, then `weights` puts the first weights in flight.  ssq_part[t] receives the sum of squares of
 // token t's inputs here.
 template <int NPL, int KS, bool F16, class Weights, class Put>
-__device__ __forceinline__ void operand_from_rows(const GemmArgs &g, int ka, int kb, int lane, uint16_t *strip16, float *ssq_part, Weights weights, Put put) {
+__device__ __forceinline__ void operand_from_rows(const ProjArgs &g, int ka, int kb, int lane, uint16_t *strip16, float *ssq_part, Weights weights, Put put) {
     constexpr int NP = (KS + 7) / 8, NX = NP < 2 ? 1 : 2;
     f32x4 xr[NX][8], wn;
     u16x4 wr[NX];
@@ -88,7 +88,7 @@ __device__ __forceinline__ void operand_from_rows(const GemmArgs &g, int ka, int
 
 // 1 / rms of token t from its sums of squares: FROM_X the wavefronts' (ssq_part[wave * 8 + t]), else the producer's (ssq_part[t])
 template <bool FROM_X>
-__device__ __forceinline__ float inv_rms(const GemmArgs &g, const float *ssq_part, int t) {
+__device__ __forceinline__ float inv_rms(const ProjArgs &g, const float *ssq_part, int t) {
     float s = 0.f;
     if (FROM_X) {
 #pragma unroll
@@ -100,7 +100,7 @@ __device__ __forceinline__ float inv_rms(const GemmArgs &g, const float *ssq_par
 }
 
 // Wavefront t adds up the producer's partial sums of squares of token t, per lane and then over the lanes (fixed order).
-__device__ __forceinline__ void sum_ssq(const GemmArgs &g, int wave, int lane, float *ssq_part) {
+__device__ __forceinline__ void sum_ssq(const ProjArgs &g, int wave, int lane, float *ssq_part) {
     if (wave >= g.m) return;
     float v = 0.f;
     for (int i = lane; i < g.ssq_tiles; i += 64) v += g.ssq_in[(size_t)i * 8 + wave];

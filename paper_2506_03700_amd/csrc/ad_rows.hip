@@ -31,10 +31,12 @@ static_assert(kStripBytes <= 2 * kRoundBytes, "a wavefront's strip lies in the s
 constexpr int rows_batch(int npl, int ks) { return npl == 1 ? (ks == 32 ? 8 : ks / 2) : (ks == 2 ? 1 : 2); }
 
 template <int NPL, int KS, bool F16, bool FROM_X>
-__global__ void __launch_bounds__(kProjThreads, 2) k_rows(const void *weights, const void *act, const void *norm_w, uint64_t kt_k, uint64_t m_ldx, uint64_t tq_tr, GemmArgs g) {
+__global__ void __launch_bounds__(kProjThreads, 2) k_rows(const void *weights, const void *act, const void *norm_w, uint64_t kt_k, uint64_t m_ldx, uint64_t tq_tr, GemmOut rest) {
+    ProjArgs g;
+    (GemmOut &)g = rest;
     g.W = weights; g.x = (const float *)act; g.B = act; g.norm_w = norm_w;
     g.KT = (int)kt_k; g.K = (int)(kt_k >> 32); g.m = (int)m_ldx; g.ldx = (int)(m_ldx >> 32); g.tq = (int)tq_tr; g.tr = (int)(tq_tr >> 32);
-    const KernelArgLines<48 + sizeof(GemmArgs)> lines;
+    const KernelArgLines<48 + sizeof(GemmOut)> lines;
     constexpr int U = rows_batch(NPL, KS), NB = KS / U, TB = NPL * 1024;
     static_assert(NB % 2 == 0 && NB * U == KS, "batches of a tile");
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -237,7 +239,7 @@ int launch_as(const GemmArgs &g, int grid, const LaunchCtx &c) {
     GemmArgs ga = g;
     set_tile_partition(ga, grid);
     return launch<k_rows<NPL, KS, F16, FROM_X>>(c, dim3(grid), dim3(kProjThreads), kRowsLdsBytes, ga.W, FROM_X ? (const void *)ga.x : ga.B, ga.norm_w,
-                                                two(ga.KT, ga.K), two(ga.m, ga.ldx), two(ga.tq, ga.tr), ga);
+                                                two(ga.KT, ga.K), two(ga.m, ga.ldx), two(ga.tq, ga.tr), (const GemmOut &)ga);
 }
 
 template <int NPL, int KS, bool F16>
