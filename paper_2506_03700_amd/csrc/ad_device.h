@@ -68,8 +68,8 @@ __device__ __forceinline__ void warm_kernel_args() {
 
 // The same without the wait: `use` goes where the words are to have arrived.  For kernels whose first loads need nothing but leading scalar
 // parameters, of which the compiler has the first 14 words put into registers before a wavefront starts (-amdgpu-kernarg-preload-count):
-// the trip to memory for the others then passes beside those loads.  Layer step of the 8B shape, 1 / 5 rows 87.8 -> 86.8, 93.4 -> 92.0 us, four
-// fp16 layers 352 -> 348, the GPU's part of a tiny fp32 token 73.9 -> 68.5 (projections and the fold of the attention splits; the attention
+// the trip to memory for the others then passes beside those loads.  Layer step of the 8B shape, 1 / 5 rows 87.8 -> 86.4, 93.8 -> 92.0 us, four
+// fp16 layers 352 -> 346, the GPU's part of a tiny fp32 token 73.9 -> 67.4 (projections and the fold of the attention splits; the attention
 // kernels themselves gained nothing).
 template <int BYTES>
 struct KernelArgLines {

@@ -13,7 +13,7 @@ namespace ad {
 // projections cost beyond one block of arguments.  The handle is that of the stream's device (c.device), whatever device the calling
 // thread has current; that costs a question to the runtime, which is asked once per entry of the library and not per launch (a tiny model's
 // token, 22 launches: the host takes 71.3 us with one block of arguments and <<< >>>, 70.3 with the parameters and a question per
-// launch, 69.5 now).  hipGetFuncBySymbol answers for the current device: while that is another one, and for streams that have no answer, <<< >>>.
+// launch, 69.1 now).  hipGetFuncBySymbol answers for the current device: while that is another one, and for streams that have no answer, <<< >>>.
 template <class T>
 struct Param { using type = T; };
 template <auto Kernel, class... Params>

@@ -68,7 +68,7 @@ inline double lay_out(PromptGemm &g, const PromptTileKind &t, bool pieces, int n
 //    160          26.4   20.8   48.3   76.9     36.3   29.4   62.7  127
 //    256          32.8   24.0   57    102       39.7   33.0   66.5  127
 //    640          56.6   43.1  138    301       66.5   58.8  207    337
-//   1023          81.6   58    178    377      113     68    205    412    (within a prompt of 8 layers; 1.18 to 1.35 PFLOP/s, hi and lo products both counted)
+//   1023          84     59    173    368      113     68    205    412    (within a prompt of 8 layers; 1.16 to 1.39 PFLOP/s, hi and lo products both counted)
 constexpr int kPromptTileKinds = 9;
 inline int choose_prompt_tile(PromptGemm &g, bool pieces, int n_wg) {
     auto step8 = [](int n) { return 0.093 + 0.0356 * n; };      // 8 wavefronts of n accumulators
