@@ -233,7 +233,7 @@ int attn_chunk(int kv_elem, int dh);   // cached positions per attention work it
 int attn_chunk_for(int kv_elem, int dh, int n_kv_heads, int pos0, int n_wg);   // the same for a stand-alone launch
 bool attn_own_item(int kv_elem, int n_kv_heads, int S, int n_wg);      // whether the call's own rows are an item of their own there
 int device_info(int *n_cu);
-int stream_device(void *stream);       // the device of a stream (null: the current one), -1 if the runtime does not say
+int stream_device(void *stream);       // the device of a stream (null: the current one), -1 for the special handles and if the runtime does not say
 const char *hip_error_text(int code);
 int stream_sync(void *stream);
 void *event_create();

@@ -167,6 +167,8 @@ int device_info(int *n_cu) {
 
 int stream_device(void *stream) {
     int dev = -1;
+    // (hipStreamGetDevice takes hipStreamLegacy for an address)
+    if (S(stream) == hipStreamLegacy || S(stream) == hipStreamPerThread) return -1;
     if ((stream ? hipStreamGetDevice(S(stream), &dev) : hipGetDevice(&dev)) == hipSuccess) return dev;
     (void)hipGetLastError();
     return -1;

@@ -12,11 +12,15 @@
 static int current = 0, wrong = 0, by_handle = 0, by_address = 0;
 struct Stream { int device; };
 static Stream streams[2] = {{0}, {1}};
-static int device_of(hipStream_t s) { return s ? ((Stream *)s)->device : current; }
+static int device_of(hipStream_t s) { return s && s != hipStreamLegacy && s != hipStreamPerThread ? ((Stream *)s)->device : current; }
 
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = current; return hipSuccess; }
-hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d) { *d = device_of(s); return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d) {
+    if (s == hipStreamLegacy || s == hipStreamPerThread) abort();       // (the runtime takes the former for an address)
+    *d = device_of(s);
+    return hipSuccess;
+}
 hipError_t hipGetFuncBySymbol(hipFunction_t *f, const void *symbol) {
     *f = (hipFunction_t)((uintptr_t)symbol << 1 | (unsigned)current);
     return hipSuccess;
@@ -79,14 +83,15 @@ int main() {
         OK(ad_model_create(&c, lw, &top, w, ws, &streams[1], &m));
         OK(ad_kv_create(m, k, kb, 1000, &streams[1], &kv));
         // the model's device is 1; the first calls come from a thread with device 0 current, the others with either
-        const struct { int current; void *stream; } turns[] = {{0, &streams[1]}, {1, &streams[1]}, {0, &streams[1]}, {1, nullptr}, {0, nullptr}, {0, &streams[0]}, {1, &streams[0]}};
+        const struct { int current; void *stream; } turns[] = {{0, &streams[1]}, {1, &streams[1]}, {0, &streams[1]}, {1, nullptr}, {0, nullptr}, {0, &streams[0]}, {1, &streams[0]},
+                                                          {1, hipStreamLegacy}, {0, hipStreamPerThread}};
         for (const auto &t : turns) {
             current = t.current;
             wrong = by_handle = by_address = 0;
             if (calls(m, kv, p, t.stream)) return 1;
             printf("dtype %d, device %d current, stream of %d: %d launches by handle, %d by address, %d of another device\n", dtype, current,
                    device_of((hipStream_t)t.stream), by_handle, by_address, wrong);
-            if (wrong || by_handle + by_address != 21) return 1;
+            if (wrong || by_handle + by_address != 21 || ((t.stream == hipStreamLegacy || t.stream == hipStreamPerThread) && by_handle)) return 1;
         }
         ad_kv_destroy(kv);
         ad_model_destroy(m);
